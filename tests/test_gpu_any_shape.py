@@ -1,6 +1,7 @@
 """The any-shape kernels (fp32, and bf16 shapes outside the tuned kernels) where their tiles and lists have edges:
 16-row query tiles, 8 KB key tiles with blocks that straddle them, list sizes around the instantiated ones, odd page sizes."""
 import pytest
+import torch
 
 from paper_2406_09827_amd import synth
 from tests import gpu_util as U
@@ -29,3 +30,61 @@ def test_tile_and_list_edges(T, k, bq, bk, d, page, dtype, integer):
     n = w.n_query_blocks
     units = [(0, h, qb) for h in range(2) for qb in sorted({0, n // 3, n // 2, n - 2, n - 1})]
     U.run_case(w, U.hipattn.FORCE_GENERIC, units=units, rep_pos=(T // 100) % 3, n_sink=T % 7, n_window=T % 40, min_agreement=0.99)
+
+
+def _attention_by_rows(Q, K, V, idx, bq, bk, sm_scale, n_sink, n_window, finfo_max):
+    """Plain attention in 64 bits over the keys that count for each row, one sequence; a logit that overflows the type is infinite."""
+    hq, T, d = Q.shape
+    g = hq // K.shape[0]
+    out = torch.zeros(hq, T, d, dtype=torch.float64)
+    for h in range(hq):
+        for i in range(T):
+            w0 = max(i + 1 - n_window, 0)
+            keys = set(range(min(n_sink, w0))) | set(range(w0, i + 1))
+            for first in idx[h, i // bq].tolist():
+                keys |= {t for t in range(first, first + bk) if n_sink <= t < w0}
+            keys = sorted(keys)
+            if not keys:
+                continue
+            x = (K[h // g, keys] @ Q[h, i]) * sm_scale
+            x[x > finfo_max] = float("inf")
+            out[h, i] = torch.softmax(x, 0) @ V[h // g, keys]
+    return out
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("bq,bk,d,n_sink,n_window", [(16, 2, 64, 0, 0), (32, 5, 128, 3, 0), (64, 4, 128, 5, 20), (15, 1, 64, 0, 9)])
+@pytest.mark.parametrize("odd", ["value", "key", "logit"])
+def test_infinities_and_nan_reach_the_rows_that_attend_to_them_only(dtype, bq, bk, d, n_sink, n_window, odd):
+    # An infinite or NaN value, a NaN key and a logit that overflows: rows that attend to the key show it, as plain
+    # attention does; the rows of the same block before the key, and rows that re-read it as padding, do not.
+    T, kb, dev = 130, 6, "cuda"
+    gen = torch.Generator().manual_seed(17 * bk + bq)
+    dt = {"fp32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    Q, K, V = (torch.randn(1, n, T, d, generator=gen).to(dt) for n in (2, 1, 1))
+    nqb = -(-T // bq)
+    idx = torch.full((1, 2, nqb, kb), U.hipattn.SENTINEL, dtype=torch.int32)
+    for h in range(2):
+        for qb in range(nqb):
+            own = (min((qb + 1) * bq, T) - 1) // bk  # the block of the last row, and earlier ones (never block 0)
+            pick = torch.randperm(max(own - 1, 0), generator=gen)[:kb - 2] + 1
+            blocks = sorted({own, 23 // bk if qb % 2 else own, *pick.tolist()})
+            idx[0, h, qb, :len(blocks)] = torch.tensor(blocks, dtype=torch.int32) * bk
+    bad = ([] if n_sink else [0]) + [23, 40, T - 2]  # (as a sink key 0 would count for every row)
+    if odd == "value":
+        for t, x in zip(bad[::-1], (float("inf"), float("nan"), float("-inf"), float("inf"))):
+            V[0, 0, t, t % d] = x
+    elif odd == "key":
+        K[0, 0, bad] = float("nan")
+    else:
+        Q[0, :, 48:] = 1e25
+        for i, t in enumerate(bad):  # (no two alike: which of two equal logits of 1e26 is larger is up to the rounding)
+            K[0, 0, t] = 1e25 * (i + 1)
+    out = U.hipattn.hip_sparse_attn(Q.to(dev), K.to(dev), V.to(dev), idx.to(dev), kb * bk, bq, bk, n_sink=n_sink, n_window=n_window,
+                                    flags=U.hipattn.FORCE_GENERIC)[0].double().cpu()
+    ref = _attention_by_rows(Q[0].double(), K[0].double(), V[0].double(), idx[0], bq, bk, d ** -0.5, n_sink, n_window, 3.4e38)
+    fin = torch.isfinite(ref)
+    assert bool((~fin).any()) and bool(fin.any())
+    assert torch.equal(torch.isnan(out), torch.isnan(ref)) and torch.equal(out[~fin & ~torch.isnan(ref)], ref[~fin & ~torch.isnan(ref)])
+    # fp32: logits of up to 6e25 (the overflow case) decide by their order alone; the others are below 10, see gpu_util
+    assert float((out - ref)[fin].abs().max()) <= (1e-4 if dtype == "fp32" else 2e-2)
