@@ -38,82 +38,84 @@ __device__ __forceinline__ void store4(bf16_t *p, float4 v)
 }
 
 // e^x for x <= 0 within two units in the last place: 2^(x log2 e) with the rounding error of the product put back.
-// The correction alone is bounded (e^-120 is below the smallest float the unit returns; -inf has no rounding error to
-// put back), so a NaN - a NaN logit, or the difference of two infinite ones - comes out as NaN and not as probability 0.
+// The error alone is bounded (that of -inf and of what overflows is NaN or infinite, and the median takes the bound for
+// it), so a NaN - a NaN logit, or the difference of two infinite ones - comes out as NaN and not as probability 0.
 __device__ __forceinline__ float exp_neg(float x)
 {
-    const float c = fmaxf(x, -120.f), y = c * 1.44269504f, e = fmaf(c, 1.44269504f, -y) + c * 1.92596299e-8f;
-    const float v = __builtin_amdgcn_exp2f(x * 1.44269504f);
+    const float y = x * 1.44269504f, e = __builtin_amdgcn_fmed3f(fmaf(x, 1.44269504f, -y) + x * 1.92596299e-8f, -1.f, 1.f);
+    const float v = __builtin_amdgcn_exp2f(y);
     return fmaf(v, e * 0.693147181f, v);
 }
-// (by its bits: the compiler may assume that no float is a NaN)
-__device__ __forceinline__ bool not_finite(float x) { return (__float_as_uint(x) & 0x7f800000u) == 0x7f800000u; }
+// (by bits that the compiler knows nothing of: it may assume that no float is a NaN)
+__device__ __forceinline__ bool not_finite(float x)
+{
+    uint32_t u = __float_as_uint(x);
+    asm volatile("" : "+v"(u));
+    return (u & 0x7f800000u) == 0x7f800000u;
+}
 
 constexpr int kGenMaxKb = 1024;
 
-// The same rows one after the other, one key per lane and its value by all lanes: reads of K and V, and multiplies into a
-// row, only what counts for that row.  The matrix-core walk gives a key that does not count for a row (one in the row's
-// future, or of another of the three ranges) probability 0, and 0 * inf = NaN: a workgroup whose result is not finite
-// is done again here, so that an infinite or NaN value reaches the rows that attend to it and no others.
+// One query row by one wave, one key per lane and its value by all lanes: reads of K and V, and multiplies into the row,
+// only what counts for it.  The matrix-core walk gives a key that does not count for a row (one in the row's future, or of
+// another of the three ranges) probability 0, and 0 * inf = NaN: a row that is not finite is done again here, so that an
+// infinite or NaN value reaches the rows that attend to it and no others.
 template <typename T, int D>
-__device__ __forceinline__ void attend_row_by_row(const KParams &p, int b, int h, int hk, int kv_len, int row0, int n_rows, int pos0,
-                                                  const int32_t *idx, int wave, int lane)
+__device__ __forceinline__ void attend_row(const KParams &p, int b, int h, int hk, int kv_len, int row, const int32_t *idx, int lane)
 {
 #pragma clang fp contract(off)   // the largest logit minus itself is 0, whatever its size
     constexpr int CPL = D / 64;  // output channels per lane
-    for (int m = wave; m < n_rows; m += kThreads / 64) {
-        const T *q = (const T *)p.Q + (int64_t)b * p.qs_b + (int64_t)h * p.qs_h + (int64_t)(row0 + m) * p.qs_r;
-        // the selected blocks' keys in [n_sink, w0), then the sink [0, ns), then the window [w0, vis)
-        const int vis = min(pos0 + m + 1, kv_len), w0 = max(vis - p.n_window, 0), ns = min(p.n_sink, w0);
-        const int n_sel = p.kb * p.bk, n_keys = vis > 0 ? n_sel + ns + vis - w0 : 0;
-        float m_run = -INFINITY, l_run = 0.f, acc[CPL];
+    const T *q = (const T *)p.Q + (int64_t)b * p.qs_b + (int64_t)h * p.qs_h + (int64_t)row * p.qs_r;
+    // the selected blocks' keys in [n_sink, w0), then the sink [0, ns), then the window [w0, vis)
+    const int vis = min(kv_len - p.q_len + row + 1, kv_len), w0 = max(vis - p.n_window, 0), ns = min(p.n_sink, w0);
+    const int n_sel = p.kb * p.bk, n_keys = vis > 0 ? n_sel + ns + vis - w0 : 0;
+    float m_run = -INFINITY, l_run = 0.f, acc[CPL];
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
-        for (int base = 0; base < n_keys; base += 64) {
-            const int ki = base + lane;
-            int t = -1;  // this lane's key, -1: none
-            if (ki < n_sel) {
-                const int j = ki / p.bk, first = idx[j];
-                if (first >= 0 && first < kv_len) t = first + ki - j * p.bk;
-                if (t < p.n_sink || t >= w0) t = -1;
-            } else if (ki < n_keys) {
-                t = ki < n_sel + ns ? ki - n_sel : w0 + ki - n_sel - ns;
-            }
-            bool miss = false;
-            const int64_t off = t >= 0 ? kv_row_offset(p, b, hk, t, miss) : 0;
-            float x = -INFINITY;
-            if (t >= 0) {
-                const T *k = (const T *)(miss ? p.Kback : p.K) + off;
-                float dot = 0.f;
-#pragma unroll 4
-                for (int c = 0; c < D; ++c) dot = fmaf(ld_f32(q + c), ld_f32(k + c), dot);
-                x = dot * p.sm_scale;
-            }
-            float mx = x, sum;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-            const float m_new = fmaxf(m_run, mx), m_safe = m_new == -INFINITY ? 0.f : m_new, alpha = exp_neg(m_run - m_safe);
-            const float pr = sum = t >= 0 ? exp_neg(x - m_safe) : 0.f;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-            l_run = l_run * alpha + sum;
-            m_run = m_new;
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) acc[c] *= alpha;
-            const uint64_t live = __ballot(t >= 0);
-            for (int src = 0; src < 64; ++src) {
-                if (!((live >> src) & 1)) continue;
-                const float ps = __shfl(pr, src, 64);
-                const T *v = (const T *)(__shfl((int)miss, src, 64) ? p.Vback : p.V) + __shfl((long long)off, src, 64);
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) acc[c] = fmaf(ps, ld_f32(v + lane + 64 * c), acc[c]);
-            }
+    for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
+    for (int base = 0; base < n_keys; base += 64) {
+        const int ki = base + lane;
+        int t = -1;  // this lane's key, -1: none
+        if (ki < n_sel) {
+            const int j = ki / p.bk, first = idx[j];
+            if (first >= 0 && first < kv_len) t = first + ki - j * p.bk;
+            if (t < p.n_sink || t >= w0) t = -1;
+        } else if (ki < n_keys) {
+            t = ki < n_sel + ns ? ki - n_sel : w0 + ki - n_sel - ns;
         }
-        const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
-        T *o = (T *)p.O + (int64_t)b * p.os_b + (int64_t)h * p.os_h + (int64_t)(row0 + m) * p.os_r;
+        bool miss = false;
+        const int64_t off = t >= 0 ? kv_row_offset(p, b, hk, t, miss) : 0;
+        float x = -INFINITY;
+        if (t >= 0) {
+            const T *k = (const T *)(miss ? p.Kback : p.K) + off;
+            float dot = 0.f;
+#pragma unroll 4
+            for (int c = 0; c < D; ++c) dot = fmaf(ld_f32(q + c), ld_f32(k + c), dot);
+            x = dot * p.sm_scale;
+        }
+        float mx = x, sum;
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) st_f32(o + lane + 64 * c, acc[c] * inv);
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        const float m_new = fmaxf(m_run, mx), m_safe = m_new == -INFINITY ? 0.f : m_new, alpha = exp_neg(m_run - m_safe);
+        const float pr = sum = t >= 0 ? exp_neg(x - m_safe) : 0.f;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        l_run = l_run * alpha + sum;
+        m_run = m_new;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) acc[c] *= alpha;
+        const uint64_t live = __ballot(t >= 0);
+        for (int src = 0; src < 64; ++src) {
+            if (!((live >> src) & 1)) continue;
+            const float ps = __shfl(pr, src, 64);
+            const T *v = (const T *)(__shfl((int)miss, src, 64) ? p.Vback : p.V) + __shfl((long long)off, src, 64);
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) acc[c] = fmaf(ps, ld_f32(v + lane + 64 * c), acc[c]);
+        }
     }
+    const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
+    T *o = (T *)p.O + (int64_t)b * p.os_b + (int64_t)h * p.os_h + (int64_t)row * p.os_r;
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) st_f32(o + lane + 64 * c, acc[c] * inv);
 }
 
 template <typename T, int D, int MT>
@@ -127,7 +129,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     __shared__ __attribute__((aligned(16))) char lds[kLds];
     __shared__ float ml_s[4][2][MT * 16];
     __shared__ int n_blk_s;                      // list entries up to the last block
-    __shared__ int by_row_s;                     // 1: a result is not finite
     int64_t *blk_off = (int64_t *)lds;           // element offset of a selected block's first row, bit 0: in the backing pools
     int *blk_pos = (int *)(lds + kGenMaxKb * 8); // its position, -1: no block
 
@@ -148,7 +149,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     const int pos0 = kv_len - p.q_len + row0;
     const int32_t *idx = p.idx_in + (((int64_t)b * p.hq + h) * p.nqb + qb) * kb;
 
-    if (tid == 0) n_blk_s = by_row_s = 0;
+    if (tid == 0) n_blk_s = 0;
     __syncthreads();
     for (int j = tid; j < kb; j += kThreads) {
         const int first = idx[j];
@@ -327,6 +328,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     }
     __syncthreads();
     T *Ob = (T *)p.O + (int64_t)b * p.os_b + (int64_t)h * p.os_h + (int64_t)row0 * p.os_r;
+    bool odd = false;  // a result of this lane is not finite
     for (int i = tid; i < n_rows * (D / 4); i += kThreads) {
         const int row = i / (D / 4), c4 = (i % (D / 4)) * 4;
         float m = -INFINITY;
@@ -343,11 +345,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             sum.x = fmaf(x.x, a, sum.x); sum.y = fmaf(x.y, a, sum.y); sum.z = fmaf(x.z, a, sum.z); sum.w = fmaf(x.w, a, sum.w);
         }
         const float inv = l > 0.f ? 1.f / l : 0.f;
-        if (not_finite(sum.x) || not_finite(sum.y) || not_finite(sum.z) || not_finite(sum.w) || not_finite(l)) by_row_s = 1;
+        odd |= not_finite(fabsf(sum.x) + fabsf(sum.y) + fabsf(sum.z) + fabsf(sum.w) + l);
         store4(Ob + (int64_t)row * p.os_r + c4, make_float4(sum.x * inv, sum.y * inv, sum.z * inv, sum.w * inv));
     }
-    __syncthreads();
-    if (by_row_s) attend_row_by_row<T, D>(p, b, h, hk, kv_len, row0, n_rows, pos0, idx, wave, lane);
+    if (__ballot(odd) != 0) {  // the rows that this wave stored, again
+        __threadfence_block();
+        for (int i = tid - lane; i < n_rows * (D / 4); i += kThreads)
+            for (int row = i / (D / 4); row < min(i / (D / 4) + 256 / D, n_rows); ++row)
+                attend_row<T, D>(p, b, h, hk, kv_len, row0 + row, idx, lane);
+    }
 }
 
 template <typename T, int D>
