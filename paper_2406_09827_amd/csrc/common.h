@@ -177,21 +177,6 @@ __device__ __forceinline__ int chunk_bound(int j, int a, int r, int kb)
     return j * a + (2 * j * r + kb) / (2 * kb);
 }
 
-/*
- * Ordered top-kb selection among NB = 64*E keyed slots, run by one wave.
- *
- * Slot i*64 + lane is held by register i of `lane`.  Keeps the kb slots with the largest
- * keys (key 0 = empty slot, never kept); among equal keys the lower slot wins.  visit(i, kept, rank)
- * is called for every held slot, register by register, with its rank among the kept slots in slot
- * order, so survivors can be written out compacted and still sorted by position.
- *
- * The kb-th largest key is bracketed by [lo, hi] and the bracket is narrowed by counting the keys at or above a
- * candidate (a compare per register, a wave ballot and a scalar popcount; no sort, no barrier).  The candidate is the
- * linear interpolation of the scores at the bracket's ends by their counts: among the scores of one round it settles in
- * 6 to 8 counts (512 and 2048 slots), where a search over the key's 32 bits took 16 to 20.  After 8 of them, or from an
- * end that is -inf, the bracket's middle is taken, so 40 counts are the most whatever the keys.  It stops as soon as a
- * candidate has exactly kb keys at or above it.
- */
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
 {
     int v = (int)x;
@@ -207,51 +192,104 @@ __device__ __forceinline__ float key_score(uint32_t key)   // inverse of score_k
 {
     return __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key);
 }
-// The smallest key v with fewer than kb keys above it, or a v with exactly kb keys at or above it; 0 = keep every key
-template <int E>
+
+/*
+ * Ordered top-kb selection among NB = 64*E keyed slots, run by one wave (select_topk_visit, below).
+ *
+ * Slot i*64 + lane is held by register i of `lane`.  Keeps the kb slots with the largest
+ * keys (key 0 = empty slot, never kept); among equal keys the lower slot wins.  visit(i, kept, rank)
+ * is called for every held slot, register by register, with its rank among the kept slots in slot
+ * order, so survivors can be written out compacted and still sorted by position.
+ *
+ * The kb-th largest key is found by counting the keys at or above a candidate: a compare per register, a wave ballot and
+ * a scalar popcount, no sort, no barrier; a candidate with exactly kb keys at or above it ends the search.  Two ways:
+ *   BITS   the key's bits from the highest down, at most 32 counts.  Scores of one query row take 12 to 18.
+ *   else   [lo, hi] brackets the key and the candidate is the linear interpolation of the scores at its ends by their
+ *          counts: 6 to 8 counts for the scores of a round, where the bits take 16 to 20 for maxima over 32 or 64 query
+ *          rows, but a step costs about twice a step of the other way.  After 8 of them the bracket is halved, and for
+ *          E <= 8 its ends move to the nearest keys every 8th time, which settles equal keys (beyond, the registers that
+ *          takes would spill).  Modelled for kb = 256 and 1024: one score far out, heavy tails or two clusters take 8 steps
+ *          and 10 to 12 halvings; many equal scores 8 and 8 (E <= 8) or 8 and up to 30.  -inf is never inside the bracket.
+ * BITS holds for E <= 4, and in decode (one query row) for E <= 8.  Measured, mask estimation, 65536 tokens, former rule
+ * (interpolation everywhere, the bracket tested for -inf in every step) / now: decode, 32 heads in all, k/bk = 32 34.0 /
+ * 29.4 us, 128 40.3 / 35.7, 256 61.1 / 61.6, 512 109.8 / 106.6; 384 heads, k/bk = 128 83.6 / 81.8; prompts of 32 query
+ * heads over 8 kv heads, 3000 tokens 58.5 / 57.8, 16384 with 64 channels 151.1 / 148.3, of integers (equal scores) 3000
+ * tokens 65.5 / 60.9.
+ */
+// The smallest key v with fewer than kb keys above it, or a v with exactly kb keys at or above it; v = 0: keep every key
+template <int E, bool BITS>
 __device__ __forceinline__ uint32_t select_threshold(const uint32_t (&key)[E], int kb)
 {
-    uint32_t mx = 0, mn = 0;   // mn: the complement of the smallest key of a slot that is not empty
-#pragma unroll
-    for (int i = 0; i < E; ++i) {
-        mx = max(mx, key[i]);
-        mn = max(mn, key[i] != 0u ? ~key[i] : 0u);
-    }
-    uint32_t hi = wave_max_u32(mx), lo = ~wave_max_u32(mn);
     const auto count_ge = [&](uint32_t cand) __attribute__((always_inline)) {
         int c = 0;
 #pragma unroll
         for (int i = 0; i < E; ++i) c += __popcll(__ballot(key[i] >= cand));
         return c;
     };
-    int c_lo = hi != 0u ? count_ge(lo) : 0, c_hi = 0;   // keys >= lo, keys > hi
-    if (c_lo <= kb) return 0;
+    if constexpr (BITS) {
+        uint32_t v = 0;
 #pragma unroll 1
-    for (int it = 0; lo < hi; ++it) {
-        uint32_t cand;
-        if (it < 8 && lo > kKeyNegInf) {
-            const float a = key_score(lo), t = (float)(c_lo - kb) * __builtin_amdgcn_rcpf((float)(c_lo - c_hi));
-            cand = (uint32_t)__builtin_amdgcn_readfirstlane((int)score_key(fmaf(key_score(hi) - a, t, a)));
-            cand = min(max(cand, lo + 1), hi);   // (whatever the interpolation gave: always inside the bracket)
-        } else {
-            cand = lo + ((hi - lo + 1) >> 1);
+        for (int bit = 31; bit >= 0; --bit) {
+            const uint32_t cand = v | (1u << bit);
+            const int c = count_ge(cand);
+            if (c >= kb) v = cand;
+            if (c == kb) break;
         }
+        return v;
+    }
+    uint32_t mx = 0, mn = 0;   // mn: the complement of the smallest key above that of -inf
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+        mx = max(mx, key[i]);
+        mn = max(mn, key[i] > kKeyNegInf ? ~key[i] : 0u);
+    }
+    uint32_t hi = wave_max_u32(mx), lo = ~wave_max_u32(mn);
+    int c_lo = count_ge(lo), c_hi = 0;   // keys >= lo, keys > hi
+    if (c_lo <= kb) return kKeyNegInf;   // all of them, and the first ones of -inf
+#pragma unroll 1
+    for (int it = 0; it < 8 && lo < hi; ++it) {
+        const float a = key_score(lo), t = (float)(c_lo - kb) * __builtin_amdgcn_rcpf((float)(c_lo - c_hi));
+        uint32_t cand = (uint32_t)__builtin_amdgcn_readfirstlane((int)score_key(fmaf(key_score(hi) - a, t, a)));
+        cand = min(max(cand, lo + 1), hi);   // (whatever the interpolation gave: always inside the bracket)
         const int c = count_ge(cand);
         if (c >= kb) {
             lo = cand;
             c_lo = c;
-            if (c == kb) break;
+            if (c == kb) return lo;
         } else {
             hi = cand - 1;
             c_hi = c;
         }
     }
+#pragma unroll 1
+    for (int it = 1; lo < hi; ++it) {
+        if (E <= 8 && (it & 7) == 0) {
+            mx = mn = 0;
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                const bool in = key[i] >= lo && key[i] <= hi;
+                mx = max(mx, in ? key[i] : 0u);
+                mn = max(mn, in ? ~key[i] : 0u);
+            }
+            hi = wave_max_u32(mx);
+            lo = ~wave_max_u32(mn);
+            if (lo == hi) break;
+        }
+        const uint32_t cand = lo + ((hi - lo + 1) >> 1);
+        const int c = count_ge(cand);
+        if (c >= kb) {
+            lo = cand;
+            if (c == kb) break;
+        } else {
+            hi = cand - 1;
+        }
+    }
     return lo;
 }
-template <int E, typename Visit>
+template <int E, bool BITS = (E <= 4), typename Visit>
 __device__ __forceinline__ void select_topk_visit(const uint32_t (&key)[E], int kb, Visit visit)
 {
-    const uint32_t v = select_threshold<E>(key, kb);
+    const uint32_t v = select_threshold<E, BITS>(key, kb);
     int c_gt = 0;
 #pragma unroll
     for (int i = 0; i < E; ++i) c_gt += __popcll(__ballot(key[i] > v));
@@ -270,10 +308,10 @@ __device__ __forceinline__ void select_topk_visit(const uint32_t (&key)[E], int 
         base_keep += __popcll(bkp);
     }
 }
-template <int E>
+template <int E, bool BITS = (E <= 4)>
 __device__ __forceinline__ void select_topk_ordered(const uint32_t (&key)[E], int kb, bool (&keep)[E], int (&dest)[E])
 {
-    select_topk_visit<E>(key, kb, [&](int i, bool kp, int d) __attribute__((always_inline)) { keep[i] = kp; dest[i] = d; });
+    select_topk_visit<E, BITS>(key, kb, [&](int i, bool kp, int d) __attribute__((always_inline)) { keep[i] = kp; dest[i] = d; });
 }
 
 // ---- wave-local helpers -----------------------------------------------------------------

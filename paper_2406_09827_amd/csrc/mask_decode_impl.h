@@ -226,9 +226,9 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 ? 4 : E == 16 
                     ksel[i] = ens_key(key[i], ens_hash, rep_block((slot & 1) ? mid : s, (slot & 1) ? e : mid, p.rep_pos), p.ens_r);
                 }
             }
-            select_topk_ordered<E>(ksel, kb, keep, dest);
+            select_topk_ordered<E, E <= 8>(ksel, kb, keep, dest);
         } else {
-            select_topk_ordered<E>(key, kb, keep, dest);
+            select_topk_ordered<E, E <= 8>(key, kb, keep, dest);
         }
         int *ns2 = (int *)keys, *ne2 = ns2 + NB / 2;
 #pragma unroll
