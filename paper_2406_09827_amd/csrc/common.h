@@ -202,22 +202,25 @@ __device__ __forceinline__ float key_score(uint32_t key)   // inverse of score_k
  * order, so survivors can be written out compacted and still sorted by position.
  *
  * The kb-th largest key is found by counting the keys at or above a candidate: a compare per register, a wave ballot and
- * a scalar popcount, no sort, no barrier; a candidate with exactly kb keys at or above it ends the search.  Two ways:
- *   BITS   the key's bits from the highest down, at most 32 counts.  Scores of one query row take 12 to 18.
- *   else   [lo, hi] brackets the key and the candidate is the linear interpolation of the scores at its ends by their
- *          counts: 6 to 8 counts for the scores of a round, where the bits take 16 to 20 for maxima over 32 or 64 query
- *          rows, but a step costs about twice a step of the other way.  After 8 of them the bracket is halved, and for
- *          E <= 8 its ends move to the nearest keys every 8th time, which settles equal keys (beyond, the registers that
- *          takes would spill).  Modelled for kb = 256 and 1024: one score far out, heavy tails or two clusters take 8 steps
- *          and 10 to 12 halvings; many equal scores 8 and 8 (E <= 8) or 8 and up to 30.  -inf is never inside the bracket.
- * BITS holds for E <= 4, and in decode (one query row) for E <= 8.  Measured, mask estimation, 65536 tokens, former rule
- * (interpolation everywhere, the bracket tested for -inf in every step) / now: decode, 32 heads in all, k/bk = 32 34.0 /
- * 29.4 us, 128 40.3 / 35.7, 256 61.1 / 61.6, 512 109.8 / 106.6; 384 heads, k/bk = 128 83.6 / 81.8; prompts of 32 query
- * heads over 8 kv heads, 3000 tokens 58.5 / 57.8, 16384 with 64 channels 151.1 / 148.3, of integers (equal scores) 3000
- * tokens 65.5 / 60.9.
+ * a scalar popcount, no sort, no barrier; a candidate with exactly kb keys at or above it ends the search.  Three ways:
+ *   kBits             the key's bits from the highest down, at most 32 counts.  Scores of one query row take 12 to 18,
+ *                     maxima over 32 or 64 rows 16 to 20.
+ *   kInterpolate      [lo, hi] brackets the key and the candidate is the linear interpolation of the scores at its ends by
+ *                     their counts: 6 to 8 counts for the scores of a round, but a step costs about twice a step of the
+ *                     bits.  After 8 of them the bracket is halved.  Modelled for kb = 256 and 1024: one score far out,
+ *                     heavy tails or two clusters take 8 steps and 10 to 12 halvings, many equal scores 8 and up to 30.
+ *                     -inf is never inside the bracket.
+ *   kInterpolateTies  the same with the bracket's ends moved to the nearest keys before every 8th halving, which settles
+ *                     equal scores; takes 6 registers, or spills beyond E = 8.
+ * Measured, mask estimation, everything interpolated with -inf tested in every step / now: decode over 65536 tokens, 32
+ * heads in all, k/bk = 128 40.3 / 35.7 us (bits), 512 109.8 / 106.6; 384 heads, k/bk = 128 83.6 / 81.8 (bits); prompts of
+ * 32 query heads over 8 kv heads, 3000 tokens 58.5 / 57.8, 16384 with 64 channels 151.1 / 148.3, and of integers (equal
+ * scores) 3000 tokens 65.5 / 60.9.
  */
+enum { kBits, kInterpolate, kInterpolateTies };
+constexpr int default_search(int E) { return E <= 4 ? kBits : E <= 8 ? kInterpolateTies : kInterpolate; }
 // The smallest key v with fewer than kb keys above it, or a v with exactly kb keys at or above it; v = 0: keep every key
-template <int E, bool BITS>
+template <int E, int SEARCH>
 __device__ __forceinline__ uint32_t select_threshold(const uint32_t (&key)[E], int kb)
 {
     const auto count_ge = [&](uint32_t cand) __attribute__((always_inline)) {
@@ -226,7 +229,7 @@ __device__ __forceinline__ uint32_t select_threshold(const uint32_t (&key)[E], i
         for (int i = 0; i < E; ++i) c += __popcll(__ballot(key[i] >= cand));
         return c;
     };
-    if constexpr (BITS) {
+    if constexpr (SEARCH == kBits) {
         uint32_t v = 0;
 #pragma unroll 1
         for (int bit = 31; bit >= 0; --bit) {
@@ -263,7 +266,7 @@ __device__ __forceinline__ uint32_t select_threshold(const uint32_t (&key)[E], i
     }
 #pragma unroll 1
     for (int it = 1; lo < hi; ++it) {
-        if (E <= 8 && (it & 7) == 0) {
+        if (SEARCH == kInterpolateTies && (it & 7) == 0) {
             mx = mn = 0;
 #pragma unroll
             for (int i = 0; i < E; ++i) {
@@ -286,10 +289,10 @@ __device__ __forceinline__ uint32_t select_threshold(const uint32_t (&key)[E], i
     }
     return lo;
 }
-template <int E, bool BITS = (E <= 4), typename Visit>
+template <int E, int SEARCH = default_search(E), typename Visit>
 __device__ __forceinline__ void select_topk_visit(const uint32_t (&key)[E], int kb, Visit visit)
 {
-    const uint32_t v = select_threshold<E, BITS>(key, kb);
+    const uint32_t v = select_threshold<E, SEARCH>(key, kb);
     int c_gt = 0;
 #pragma unroll
     for (int i = 0; i < E; ++i) c_gt += __popcll(__ballot(key[i] > v));
@@ -308,10 +311,10 @@ __device__ __forceinline__ void select_topk_visit(const uint32_t (&key)[E], int 
         base_keep += __popcll(bkp);
     }
 }
-template <int E, bool BITS = (E <= 4)>
+template <int E, int SEARCH = default_search(E)>
 __device__ __forceinline__ void select_topk_ordered(const uint32_t (&key)[E], int kb, bool (&keep)[E], int (&dest)[E])
 {
-    select_topk_visit<E, BITS>(key, kb, [&](int i, bool kp, int d) __attribute__((always_inline)) { keep[i] = kp; dest[i] = d; });
+    select_topk_visit<E, SEARCH>(key, kb, [&](int i, bool kp, int d) __attribute__((always_inline)) { keep[i] = kp; dest[i] = d; });
 }
 
 // ---- wave-local helpers -----------------------------------------------------------------

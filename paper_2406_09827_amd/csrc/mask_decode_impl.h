@@ -211,6 +211,9 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 ? 4 : E == 16 
         // the survivors go where the keys were: every wave of the problem has to hold its copy of them first
         if (SPLIT) __syncthreads();
         if (selects) {
+        // four waves or one, E = 8: the registers that settling equal scores takes are the fourth wave of a SIMD (1024 paged
+        // problems of k/bk = 256: 302 us with them, 247 without, 252 with the bits)
+        constexpr int SEARCH = WS != 16 && E == 8 ? kInterpolate : default_search(E);
         bool keep[E];
         int dest[E];
         if (round == ens_round) {
@@ -226,9 +229,9 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 ? 4 : E == 16 
                     ksel[i] = ens_key(key[i], ens_hash, rep_block((slot & 1) ? mid : s, (slot & 1) ? e : mid, p.rep_pos), p.ens_r);
                 }
             }
-            select_topk_ordered<E, E <= 8>(ksel, kb, keep, dest);
+            select_topk_ordered<E, SEARCH>(ksel, kb, keep, dest);
         } else {
-            select_topk_ordered<E, E <= 8>(key, kb, keep, dest);
+            select_topk_ordered<E, SEARCH>(key, kb, keep, dest);
         }
         int *ns2 = (int *)keys, *ne2 = ns2 + NB / 2;
 #pragma unroll
