@@ -218,10 +218,14 @@ hipError_t launch_attn_decode(const KParams &p, hipStream_t st)
 {
     const int64_t waves = (int64_t)p.batch * p.hq;
     if (waves == 0) return hipSuccess;
-    // up to 256 problems (one per compute unit): sixteen waves share a problem's blocks (32 problems of 512 keys: 8.6 us
-    // against 12.7 us with four); up to 8192 a workgroup of four; beyond that a wave per problem (measured at 32 query
-    // heads, 512 keys, four waves against one: 3072 problems -11 %, 8192 -1 %, 16384 +3 %, 32768 +22 %)
-    const int ws = waves <= 256 ? 16 : waves <= 8192 ? 4 : 1;
+    // Up to 256 problems (one per compute unit) sixteen waves share a problem's blocks, unless the blocks are one stage or
+    // less for each of four waves; up to 8192 a workgroup of four; beyond that a wave per problem.  Measured, d = 128, bk = 2,
+    // four waves / sixteen: 32 problems of 64 keys 3.44 / 3.91 us, 128 4.28 / 4.24, 256 5.92 / 4.93, 512 9.3 / 6.5, 1024 17.0 /
+    // 10.6; 256 problems of 64 keys 3.60 / 4.11, 256 7.9 / 6.5, 512 14.7 / 14.0; 320 problems of 512 keys 18.0 / 19.8.  Four
+    // against one, 32 query heads, 512 keys: 3072 problems -11 %, 8192 -1 %, 16384 +3 %, 32768 +22 %.
+    const int piece = p.bk > 4 ? 4 : p.bk, stage = 512 / p.d * (4 / piece);  // keys per block read, blocks per wave and stage
+    const int64_t blocks = (int64_t)p.kb * (p.bk / piece) + ((int64_t)p.n_sink + piece - 1) / piece + ((int64_t)p.n_window + piece - 1) / piece;
+    const int ws = waves <= 256 && blocks > 4 * stage ? 16 : waves <= 8192 ? 4 : 1;
     dim3 grid((unsigned)(ws > 1 ? waves : (waves + 3) / 4)), block(ws == 16 ? 1024 : kThreads);
     const bool paged = p.page_table != nullptr;
     const int sub_shift = p.bk == 8 ? 1 : p.bk == 16 ? 2 : 0;  // blocks of 8 / 16 rows as pieces of 4

@@ -270,24 +270,42 @@ static hipError_t launch_r(const KParams &p, dim3 grid, int xcd_map, hipStream_t
     if (p.kb <= 64) HIPATTN_LAUNCH(2);
     else if (p.kb <= 128) HIPATTN_LAUNCH(4);
     else if (p.kb <= 256) HIPATTN_LAUNCH(8);
-    else if (WS == 16 || p.kb <= 512) HIPATTN_LAUNCH(16);   // (sixteen waves: k/bk <= 512, see launch_e)
+    else if (WS == 16 || p.kb <= 512) HIPATTN_LAUNCH(16);   // (sixteen waves: k/bk <= 512, 32 keys a lane do not fit their 128 registers)
     else if constexpr (WS != 16) HIPATTN_LAUNCH(32);
 #undef HIPATTN_LAUNCH
     return hipGetLastError();
 }
 
-// Up to 256 problems (one per compute unit) and k/bk <= 512: sixteen waves per (sequence, head).  Up to 8192 problems: a
-// workgroup of four waves per (sequence, head), so that enough loads are in flight per compute unit and the selection of
-// one problem overlaps with the loads of the others.  Beyond that a wave per problem (nothing computed twice, no
-// barriers) is faster.  Measured with 32 query heads over 8 kv heads, k/bk = 256, workgroup per problem against wave per
-// problem: 2048 problems -8 %, 4096 -4 %, 8192 -1 to -4 %, 16384 +6 %, 32768 +14 %.
+// Waves per (sequence, head), by the number of problems:
+//   up to 256 (one per compute unit) and k/bk <= 512: sixteen, unless the branches of a round are one stage or less for each
+//       of four waves.  Measured with d = 128, bk = 2, 65536 tokens, four waves / sixteen: 32 problems k/bk = 32 28.4 / 29.3 us
+//       (with stages of eight rows, see below), 48 39.8 / 31.2, 256 98.8 / 61.5, 512 159 / 107; 256 problems k/bk = 256 106 /
+//       80, 512 172 / 138; beyond a problem per compute unit 320 problems k/bk = 32 34 / 60, 256 127 / 150, 512 200 / 248.
+//   up to 8192: four, so that enough loads are in flight per compute unit and the selection of one problem overlaps with the
+//       loads of the others; beyond that one (nothing computed twice, no barriers).  Measured with 32 query heads over 8 kv
+//       heads, k/bk = 256, four against one: 2048 problems -8 %, 4096 -4 %, 8192 -1 to -4 %, 16384 +6 %, 32768 +14 %.
+// Sixteen waves take stages of four rows: a round has few stages for each wave, and at 128 registers a wave stages of eight
+// rows and k/bk > 256 spill.  Four rows against eight, 32 problems of 30000 tokens: d = 64, bk = 1, k/bk = 64 24.4 / 32.1 us,
+// 256 40.6 / 45.8; 256 problems, k/bk = 512 72.7 / 85.5 (four waves 83.6); d = 128, bk = 2, k/bk = 64 21.9 / 26.1.  With
+// d = 128, bk = 2 and k/bk from 129 to 256 eight rows make two stages, both in flight: 52.3 / 53.4 at 256.
 template <int BK, int D>
 static hipError_t launch_e(const KParams &p, hipStream_t st)
 {
     const int64_t problems = (int64_t)p.batch * p.hq;
     const int64_t groups = (int64_t)p.batch * p.hkv;
     const int xcd_map = groups % 8 == 0 ? 1 : 0;
-    if (problems <= 256 && p.kb <= 512) return launch_r<BK, D, 8, 16>(p, dim3((unsigned)problems), xcd_map, st);
+    if (problems <= 256 && p.kb <= 512) {
+        const dim3 grid((unsigned)problems);
+        if constexpr (D == 128 && BK == 2) {
+            if (p.kb > 128 && p.kb <= 256) {
+                if (p.page_table) hipLaunchKernelGGL((mask_decode_kernel<8, BK, D, 8, true, 16>), grid, dim3(1024), 0, st, p, xcd_map);
+                else hipLaunchKernelGGL((mask_decode_kernel<8, BK, D, 8, false, 16>), grid, dim3(1024), 0, st, p, xcd_map);
+                return hipGetLastError();
+            }
+        }
+        constexpr int ROWS = BK < 4 ? 4 : BK, STEP = 512 / D * (ROWS / BK);   // branches per stage of a wave
+        if (2 * p.kb > 4 * STEP) return launch_r<BK, D, ROWS, 16>(p, grid, xcd_map, st);
+    }
     if (problems <= 8192) return launch_r<BK, D, 8, 4>(p, dim3((unsigned)problems), xcd_map, st);
     return launch_r<BK, D, 8, 1>(p, dim3((unsigned)((problems + 3) / 4)), 0, st);
 }

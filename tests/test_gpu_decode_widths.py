@@ -25,3 +25,20 @@ def test_few_and_more_problems(batch, bk, d, k, T, page):
                            integer=integer, seed=811 + bk)
         units = [(b, h, 0) for b in (0, 1, 7, 18, batch - 1) for h in (0, 3, 7)]
         U.run_case(w, 0, units=units, n_sink=k % 5, n_window=T % 7)
+
+
+@pytest.mark.parametrize("bk,d,k", [
+    # the last block list that four waves take alone and the first of sixteen: mask estimation (2 k/bk branches against one
+    # stage each of four waves), then attention (k/bk blocks, or pieces of four rows, against one stage each)
+    (2, 128, 32), (2, 128, 34), (2, 128, 64), (2, 128, 66),
+    (1, 64, 64), (1, 64, 65), (1, 64, 128), (1, 64, 129),
+    (4, 128, 32), (4, 128, 36), (4, 128, 64), (4, 128, 68), (8, 128, 64), (8, 128, 72), (8, 64, 128), (8, 64, 136),
+    # stages of four and of eight rows
+    (2, 128, 256), (2, 128, 258), (2, 128, 514),
+])
+@pytest.mark.parametrize("page", [0, 16])
+def test_short_block_lists(bk, d, k, page):
+    for n_sink, n_window, b_sk in ((0, 0, 1), (1, 2, 1), (5, 30, 2 if bk > 1 else 1)):
+        T = 6 * k + 41
+        w = synth.Workload("decode_short", 9, 8, 2, d, 1, T, k, 1, bk, "bf16", rho=0.9, ragged=(k, T), page_size=page, integer=True, seed=821 + bk)
+        U.run_case(w, 0, n_sink=n_sink, n_window=n_window, b_sk=b_sk)
