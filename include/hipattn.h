@@ -171,7 +171,7 @@ int hip_mask_estimate(const hip_problem *p, const void *Q, const void *K, int32_
 /*
  * Block-sparse attention (Eq. 2-3 with the mask given by `indices`).
  *   indices  as written by hip_mask_estimate; any entry < 0 or >= kv_len means "no block";
- *            valid entries of a row must be distinct.
+ *            valid entries of a row must be distinct and multiples of bk.
  *   O        device, layout per o_strides, same dtype as Q.  Row i attends to the keys t of
  *            its query block's selected blocks (plus sink and window keys, see hip_problem) with
  *            t < kv_len and t <= pos(i); a row with no such key is written as zeros.  Softmax

@@ -59,7 +59,8 @@ constexpr int kGenMaxKb = 1024;
 // One query row by one wave, one key per lane and its value by all lanes: reads of K and V, and multiplies into the row,
 // only what counts for it.  The matrix-core walk gives a key that does not count for a row (one in the row's future, or of
 // another of the three ranges) probability 0, and 0 * inf = NaN: a row that is not finite is done again here, so that an
-// infinite or NaN value reaches the rows that attend to it and no others.
+// infinite or NaN value reaches the rows that attend to it and no others.  So are the rows of a query block with a block that
+// does not lie in one page; here every key's page is looked up.
 template <typename T, int D>
 __device__ __forceinline__ void attend_row(const KParams &p, int b, int h, int hk, int kv_len, int row, const int32_t *idx, int lane)
 {
@@ -128,7 +129,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     constexpr int kLds = (kGenMaxKb * 12 > 4 * MT * 16 * PITCH * 4) ? kGenMaxKb * 12 : 4 * MT * 16 * PITCH * 4;
     __shared__ __attribute__((aligned(16))) char lds[kLds];
     __shared__ float ml_s[4][2][MT * 16];
-    __shared__ int n_blk_s;                      // list entries up to the last block
+    __shared__ int n_blk_s;                      // list entries up to the last block; kCut: a block goes on in another page
+    constexpr int kCut = kGenMaxKb + 1;
     int64_t *blk_off = (int64_t *)lds;           // element offset of a selected block's first row, bit 0: in the backing pools
     int *blk_pos = (int *)(lds + kGenMaxKb * 8); // its position, -1: no block
 
@@ -153,7 +155,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     __syncthreads();
     for (int j = tid; j < kb; j += kThreads) {
         const int first = idx[j];
-        const bool ok = first >= 0 && first < kv_len;
+        bool ok = first >= 0 && first < kv_len;
+        if (ok && p.page_table && first - logical_page(p, first) * p.page_size + bk > p.page_size) {
+            atomicMax(&n_blk_s, kCut);   // (an entry that is no multiple of bk: no walk, the rows are done below)
+            ok = false;
+        }
         bool miss;
         const int64_t off = kv_row_offset(p, b, hk, ok ? first : 0, miss);
         blk_pos[j] = ok ? first : -1;
@@ -179,7 +185,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     // Key tiles: the selected blocks, then the sink keys [0, ns), then the window keys [wlo, vis_last).  For a row at
     // position q with vis = min(q + 1, kv_len) and w0 = max(vis - n_window, 0) a selected or sink key t counts iff
     // t < w0 (selected: also t >= n_sink), a window key iff w0 <= t < vis: every key counts once.
-    const int n_keys = n_blk_s * bk;
+    const int n_blk = __builtin_amdgcn_readfirstlane(n_blk_s), n_keys = n_blk < kCut ? n_blk * bk : 0;
     const int vis_last = min(pos0 + n_rows, kv_len);
     const int wlo = max(min(pos0 + 1, kv_len) - p.n_window, 0);
     const int ns = min(p.n_sink, max(vis_last - p.n_window, 0));
@@ -348,7 +354,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         odd |= not_finite(fabsf(sum.x) + fabsf(sum.y) + fabsf(sum.z) + fabsf(sum.w) + l);
         store4(Ob + (int64_t)row * p.os_r + c4, make_float4(sum.x * inv, sum.y * inv, sum.z * inv, sum.w * inv));
     }
-    if (__ballot(odd) != 0) {  // the rows that this wave stored, again
+    if (__ballot(odd) != 0 || n_blk == kCut) {  // the rows that this wave stored, again
         __threadfence_block();
         for (int i = tid - lane; i < n_rows * (D / 4); i += kThreads)
             for (int row = i / (D / 4); row < min(i / (D / 4) + 256 / D, n_rows); ++row)

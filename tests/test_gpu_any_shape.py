@@ -88,3 +88,33 @@ def test_infinities_and_nan_reach_the_rows_that_attend_to_them_only(dtype, bq, b
     assert torch.equal(torch.isnan(out), torch.isnan(ref)) and torch.equal(out[~fin & ~torch.isnan(ref)], ref[~fin & ~torch.isnan(ref)])
     # fp32: logits of up to 6e25 (the overflow case) decide by their order alone; the others are below 10, see gpu_util
     assert float((out - ref)[fin].abs().max()) <= (1e-4 if dtype == "fp32" else 2e-2)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("bq,bk,d,page", [(16, 4, 64, 8), (32, 5, 128, 15), (33, 16, 64, 48)])
+def test_blocks_across_pages(dtype, bq, bk, d, page):
+    # entries that are no multiples of bk: a block may go on in the next logical page, which lies anywhere in the pool
+    T, kb, dev = 200, 5, "cuda"
+    gen = torch.Generator().manual_seed(31 * bk + d)
+    dt = {"fp32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    Q, K, V = (torch.randn(1, n, T, d, generator=gen).to(dt) for n in (2, 1, 1))
+    nqb, n_pages = -(-T // bq), -(-T // page)
+    idx = torch.full((1, 2, nqb, kb), U.hipattn.SENTINEL, dtype=torch.int32)
+    for h in range(2):
+        for qb in range(nqb):
+            seen = min((qb + 1) * bq, T)
+            first = int(torch.randint(0, bk, (1,), generator=gen))
+            starts = torch.arange(first, seen, bk)[torch.randperm(len(torch.arange(first, seen, bk)), generator=gen)[:kb]].sort().values
+            idx[0, h, qb, :len(starts)] = starts.int()
+    table = torch.randperm(n_pages, generator=gen).int()
+    pools = []
+    for X in (K, V):
+        pool = torch.zeros(n_pages, 1, page, d, dtype=dt)
+        for i in range(n_pages):
+            n = min(page, T - i * page)
+            pool[table[i], 0, :n] = X[0, 0, i * page:i * page + n]
+        pools.append(pool.to(dev))
+    out = U.hipattn.hip_sparse_attn(Q.to(dev), *pools, idx.to(dev), kb * bk, bq, bk, page_table=table[None].to(dev), max_kv_len=T,
+                                    n_sink=2, n_window=3, flags=U.hipattn.FORCE_GENERIC)[0].double().cpu()
+    ref = _attention_by_rows(Q[0].double(), K[0].double(), V[0].double(), idx[0], bq, bk, d ** -0.5, 2, 3, 3.4e38)
+    assert float((out - ref).abs().max()) <= (1e-4 if dtype == "fp32" else 2e-2)
