@@ -6,7 +6,7 @@
 namespace hipattn {
 
 constexpr int kSentinel = 0x7fffffff;
-constexpr int kThreads = 256;  // every kernel here runs 4 waves of 64 lanes per workgroup
+constexpr int kThreads = 256;  // 4 waves of 64 lanes per workgroup (the decode kernels with few problems: 16)
 
 // Kernel-side view of one call; filled by the host entry points after validation.
 struct KParams {
