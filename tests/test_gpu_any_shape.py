@@ -2,6 +2,7 @@
 16-row query tiles, 8 KB key tiles with blocks that straddle them, list sizes around the instantiated ones, odd page sizes."""
 import pytest
 import torch
+import oracle
 
 from paper_2406_09827_amd import synth
 from tests import gpu_util as U
@@ -118,3 +119,23 @@ def test_blocks_across_pages(dtype, bq, bk, d, page):
                                     n_sink=2, n_window=3, flags=U.hipattn.FORCE_GENERIC)[0].double().cpu()
     ref = _attention_by_rows(Q[0].double(), K[0].double(), V[0].double(), idx[0], bq, bk, d ** -0.5, 2, 3, 3.4e38)
     assert float((out - ref).abs().max()) <= (1e-4 if dtype == "fp32" else 2e-2)
+
+
+@pytest.mark.parametrize("T,k,bq,bk,d", [(1024, 128, 16, 2, 64), (2500, 512, 32, 2, 128), (900, 128, 64, 4, 128), (700, 60, 15, 3, 64)])
+def test_fp32_attention_keeps_fp32_precision(T, k, bq, bk, d):
+    # On the kernel's own indices, against 64 bits: products and sums of 32 bits differ by a few 2^-24 of logits below 10,
+    # i.e. by less than 5e-6 in the norm; one of weights, probabilities or values in 16 bits would differ by 1e-3.
+    w = synth.Workload("prec", 1, 2, 1, d, T, T, k, bq, bk, "fp32", rho=0.9, seed=931)
+    x = synth.make_inputs(w, device="cuda", threads=4)
+    idx = U.gpu_mask(w, x)
+    out = U.gpu_attn(w, x, idx, n_sink=3, n_window=20).cpu().double()
+    p = U.oracle_problem(w, x, n_sink=3, n_window=20)
+    hx = U.host(x)
+    units = oracle.all_units(p)
+    ref = torch.from_numpy(oracle.sparse_attn_units(p, hx["Q"], hx["K"], hx["V"], units, idx.cpu().numpy().reshape(-1, w.kb), 0.0)).double()
+    got = torch.zeros_like(ref)
+    for u, (b, h, qb) in enumerate(units):
+        n = min(bq, T - qb * bq)
+        got[u, :n] = out[b, h, qb * bq:qb * bq + n]
+        ref[u, n:] = 0
+    assert float((got - ref).norm() / ref.norm()) <= 5e-6

@@ -519,7 +519,7 @@ def test_token_bank_decode(flags, resident_frac):
     U.run_bank_case(synth.scaled(w, page_size=2, head_dim=64), resident_frac, flags)
     U.run_bank_case(synth.scaled(w, bk=4, k=512, page_size=64, batch=2), resident_frac, flags, rep_pos=2, b_sk=2)
     U.run_bank_case(synth.scaled(w, batch=300, n_q_heads=2, n_kv_heads=1, kv_len=2000, ragged=(300, 2000), k=128),
-                    resident_frac, flags)   # wave-per-problem variants
+                    resident_frac, flags)   # four waves per problem
 
 
 @pytest.mark.parametrize("flags", FLAG_SETS)
@@ -600,7 +600,7 @@ def test_blocks_of_8_and_16_keys(integer):
                         integer=integer, seed=102)
     U.run_case(wd, 0, n_sink=5, n_window=21)
     U.run_case(synth.scaled(wd, bk=16, k=4096, page_size=64, head_dim=64), 0, b_sk=2, rep_pos=1, n_window=50)
-    U.run_case(synth.scaled(wd, batch=700, n_q_heads=2, n_kv_heads=1, kv_len=3000, ragged=(400, 3000), k=256), 0)   # wave-per-problem variants
+    U.run_case(synth.scaled(wd, batch=700, n_q_heads=2, n_kv_heads=1, kv_len=3000, ragged=(400, 3000), k=256), 0)   # four waves per problem
 
 
 @pytest.mark.parametrize("bk,b_sk,g,rep_pos,b_sq", [(1, 1, 4, 0, 1), (2, 2, 4, 0, 1), (2, 1, 4, 2, 2), (4, 1, 8, 0, 1), (8, 1, 4, 1, 1),
