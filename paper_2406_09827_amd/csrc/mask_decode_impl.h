@@ -265,8 +265,8 @@ static hipError_t launch_r(const KParams &p, dim3 grid, int xcd_map, hipStream_t
         else hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, false, WS>), grid, block, 0, st, p, xcd_map);       \
     } while (0)
     // E registers of 64 branch slots: every count of the selection is a compare and a ballot per register, whether the
-    // slots are in use or not (k/bk = 32, 940 paged problems of 1588 tokens, mask and attention: 76.6 us with four
-    // registers, 75.5 us with two)
+    // slots are in use or not (k/bk = 32, both with the bit search, four registers / two: 1024 problems of 65536 tokens
+    // 54.2 / 48.8 us, 4096 of 8192 144 / 133)
     if (p.kb <= 64) HIPATTN_LAUNCH(2);
     else if (p.kb <= 128) HIPATTN_LAUNCH(4);
     else if (p.kb <= 256) HIPATTN_LAUNCH(8);

@@ -16,8 +16,9 @@
 //     any number of rows per block.
 //   * Selection: the ordered threshold selection of common.h, run redundantly by the four waves.
 // Measured, fp32, 32 query heads over 8 kv heads, T = 4096, k = 512, bq = 32, bk = 2, d = 128: 11.77 ms with
-// vector-unit dot products and a shuffle per (row, key) before, 0.59 ms now = 98 TFLOP/s of the 152 a large fp32 matrix
-// product reaches; T = 1024, one head, k = 128, bq = 16, d = 64: 186 -> 18 us (64 workgroups: latency).
+// vector-unit dot products and a shuffle per (row, key) before, 0.58 ms now = 99 TFLOP/s of the 152 a large fp32 matrix
+// product reaches; T = 1024, one head, k = 128, bq = 16, d = 64: 187 -> 18 us (64 workgroups: latency; 20 us each with a
+// pause between launches).
 #pragma once
 #include "mfma_generic.h"
 #include "launch.h"
