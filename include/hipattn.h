@@ -21,7 +21,8 @@
  *     the arrays it points to (kv_lens, page_table) are DEVICE arrays read by the kernels.
  *   - Return value: HIP_ATTN_OK (0), a negative HIP_ATTN_E* argument error detected before
  *     any launch, or HIP_ATTN_ELAUNCH - (hipError_t) for a failed launch.  Nothing is
- *     printed; NaN/Inf inputs give unspecified indices.
+ *     printed; NaN/Inf inputs give unspecified indices.  In hip_sparse_attn they may show in any row of the
+ *     query blocks that read them; with HIP_ATTN_F32 only in the rows that attend to them.
  *   - Re-entrant; no mutable global state, except for hip_mask_estimate_noalloc (its static scratch, see there).
  *
  * Conventions (0-based):
