@@ -4,7 +4,7 @@
 //
 // One workgroup (4 waves) per (sequence, query head, query block, 16 or 32 query rows); the waves take every fourth
 // tile of 16 gathered keys, each with its own online softmax, and their states are merged through LDS at the end.
-// Both products run on the matrix cores (fp32: v_mfma_f32_16x16x4_f32, the unit that bounds the kernel):
+// Both products run on the matrix cores (fp32: v_mfma_f32_16x16x4_f32, the busiest unit: 58 % of the clocks by counter at 4096 tokens):
 //   * S^T = K Q^T: A = key rows (lane l: row l % 16, 16-byte chunk l / 16 of each 64 bytes), B = the query rows, which
 //     stay in registers.  A lane then holds 4 consecutive keys of one query, so the softmax runs along lanes l ^ 16 and
 //     l ^ 32 only and register r of the result IS the B operand (key 4 (l / 16) + r) of step r of the next product;
