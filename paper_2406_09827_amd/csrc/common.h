@@ -63,6 +63,13 @@ __device__ __forceinline__ uint32_t score_key(float f)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// The same from the float's bits, in whole numbers (all ones, no float that a score can be, give key 0)
+__device__ __forceinline__ uint32_t score_key_bits(uint32_t u)
+{
+    if ((u << 1) == 0u) u = 0u;
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
 // Element offset of logical key/value row t of sequence b, kv head h inside its pool; `miss` says that the
 // page-table entry is negative, i.e. that the row lives in the backing pool (entry e names page ~e of it).
 __device__ __forceinline__ int64_t kv_row_offset(const KParams &p, int b, int h, int t, bool &miss)
@@ -315,6 +322,51 @@ template <int E, int SEARCH = default_search(E)>
 __device__ __forceinline__ void select_topk_ordered(const uint32_t (&key)[E], int kb, bool (&keep)[E], int (&dest)[E])
 {
     select_topk_visit<E, SEARCH>(key, kb, [&](int i, bool kp, int d) __attribute__((always_inline)) { keep[i] = kp; dest[i] = d; });
+}
+
+/*
+ * The same for slots in pairs: lane `lane` holds slots 2 (i*64 + lane) and 2 (i*64 + lane) + 1 in registers l[i] and r[i], so a
+ * lane that holds a node holds its two branches.  visit(i, keep_l, rank_l, keep_r, rank_r).
+ */
+template <int H, int SEARCH = default_search(2 * H), typename Visit>
+__device__ __forceinline__ void select_topk_pairs(const uint32_t (&l)[H], const uint32_t (&r)[H], int kb, Visit visit)
+{
+    uint32_t key[2 * H];
+#pragma unroll
+    for (int i = 0; i < H; ++i) { key[2 * i] = l[i]; key[2 * i + 1] = r[i]; }
+    const uint32_t v = select_threshold<2 * H, SEARCH>(key, kb), at_least = max(v, 1u);   // (key 0 is never kept)
+    int c_ge = 0;
+#pragma unroll
+    for (int i = 0; i < 2 * H; ++i) c_ge += __popcll(__ballot(key[i] >= at_least));
+    int base = 0;
+    if (c_ge <= kb) {   // every key at the threshold is kept
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const bool kl = l[i] >= at_least, kr = r[i] >= at_least;
+            const uint64_t bl = __ballot(kl), br = __ballot(kr);
+            const int rank = base + lane_prefix_count(bl) + lane_prefix_count(br);
+            visit(i, kl, rank, kr, rank + (kl ? 1 : 0));
+            base += __popcll(bl) + __popcll(br);
+        }
+        return;
+    }
+    int c_gt = 0;
+#pragma unroll
+    for (int i = 0; i < 2 * H; ++i) c_gt += __popcll(__ballot(key[i] > v));
+    const int need = kb - c_gt;  // how many slots equal to the threshold are still wanted: the lowest
+    int base_tie = 0;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+        const bool el = l[i] == at_least, er = r[i] == at_least;
+        const uint64_t tl = __ballot(el), tr = __ballot(er);
+        const int tie = base_tie + lane_prefix_count(tl) + lane_prefix_count(tr);
+        const bool kl = l[i] > v || (el && tie < need), kr = r[i] > v || (er && tie + (el ? 1 : 0) < need);
+        const uint64_t bl = __ballot(kl), br = __ballot(kr);
+        const int rank = base + lane_prefix_count(bl) + lane_prefix_count(br);
+        visit(i, kl, rank, kr, rank + (kl ? 1 : 0));
+        base_tie += __popcll(tl) + __popcll(tr);
+        base += __popcll(bl) + __popcll(br);
+    }
 }
 
 // ---- wave-local helpers -----------------------------------------------------------------

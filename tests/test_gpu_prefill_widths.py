@@ -1,0 +1,43 @@
+"""Prefill mask estimation on either side of the lines between its kernels: table sizes (k/bk of 128, 256, 512), query tiles,
+head dims, a workgroup or a wave per work item, paged and contiguous keys, and the launch shapes for long contexts."""
+import pytest
+import torch
+
+import paper_2406_09827_amd as hipattn
+from paper_2406_09827_amd import synth
+from tests import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("heads", [(4, 1), (6, 2)], ids=["g4", "g3"])
+@pytest.mark.parametrize("k,bk,d,bq,rep_pos", [
+    (128, 1, 128, 32, 0), (258, 2, 128, 64, 1), (256, 1, 64, 64, 2), (1028, 4, 64, 32, 0), (1024, 2, 128, 32, 2),
+    (514, 1, 128, 64, 0), (64, 2, 64, 16, 0), (1032, 8, 128, 48, 1),
+])
+def test_table_sizes(k, bk, d, bq, rep_pos, heads, page):
+    hq, hkv = heads
+    for q_len in (3 * bq + 5, bq * (1540 // hq)):   # below and above the line between a workgroup and a wave per work item
+        T = max(q_len, 7 * k + 3)
+        w = synth.Workload("widths", 1, hq, hkv, d, q_len, T, k, bq, bk, "bf16", rho=0.9, page_size=page, integer=True, seed=300 + k)
+        nqb = w.n_query_blocks
+        units = [(0, h, qb) for h in (0, hq - 1) for qb in sorted({0, 1, nqb // 2, nqb - 1})]
+        U.run_case(w, 0, units=units, rep_pos=rep_pos, b_sk=2 if bk == 8 else 1)
+        U.run_case(synth.scaled(w, integer=False), 0, units=units[:3], rep_pos=rep_pos)
+
+
+@pytest.mark.parametrize("hq,bq,bk", [(4, 32, 2), (3, 32, 2), (4, 64, 4)])
+@pytest.mark.parametrize("pitch", [2048, 8192, 32768])
+def test_launch_shapes_of_long_contexts(pitch, hq, bq, bk):
+    # how many workgroups share a compute unit, and whether four heads stay in step, follows the bytes that a kv head's keys
+    # span: rows 4, 16 and 64 KB apart span 16, 67 and 268 MB.  Same indices as from the packed keys.
+    T = 4100
+    x = synth.make_inputs(synth.Workload("pitch", 1, hq, 1, 128, T, T, 256 * bk, bq // 4, bk, "bf16", rho=0.95, seed=311), device="cuda", threads=4)
+    wide = torch.empty(T * pitch, dtype=torch.bfloat16, device="cuda").as_strided((1, 1, T, 128), (T * pitch, T * pitch, pitch, 1))
+    wide.copy_(x["K"])
+    for b_sq, q_rows in ((1, bq), (1, bq // 4)):
+        a = hipattn.hip_mask_estimate(x["Q"], x["K"], 256 * bk, q_rows, bk, b_sq=b_sq)
+        b = hipattn.hip_mask_estimate(x["Q"], wide, 256 * bk, q_rows, bk, b_sq=b_sq)
+        torch.cuda.synchronize()
+        assert torch.equal(a, b)
