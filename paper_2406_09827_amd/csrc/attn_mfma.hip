@@ -1,25 +1,47 @@
-// Block-sparse attention for bf16 prefill on CDNA4 matrix cores (paper Eq. 2-3; the
-// "block sparse flash attention" of the appendix: online softmax over the gathered keys).
+// Block-sparse attention for bf16 prefill on CDNA4 matrix cores (paper Eq. 2-3; the "block sparse flash attention" of the
+// appendix: online softmax over the gathered keys).
 //
-// Work item = one wave = one (sequence, query head, query block, 32-row query tile); four
-// independent work items per workgroup, no workgroup barrier anywhere.
-// Per tile of 32 gathered keys:
-//   S^T = K_tile . Q^T     v_mfma_f32_32x32x16_bf16, A = key rows (loaded coalesced, staged in a
-//                          swizzled LDS tile, read back one row per lane), B = the query tile
-//                          held in registers.
-//                          The result has one query per lane and 16 keys in its registers,
-//                          so the softmax statistics of a query are lane-local (plus one
-//                          exchange with lane ^ 32) and P^T is already in B-operand layout.
-//   O^T += V_tile^T . P^T  (P as hi + lo bf16 terms) the value rows are loaded coalesced, staged
-//                          in this wave's LDS slice and read back channel-major with the LDS
-//                          transpose read ds_read_b64_tr_b16 (the contraction runs over keys, so
-//                          V has to be transposed on the way to the A operand).
-// The key positions of a tile and their row offsets are published through a small per-wave
-// LDS array so that every lane can mask by (key position, query position).
+// Work item = one wave = one (sequence, query head, query block, 32-row query tile), four per workgroup; with few work
+// items two or four waves share one (WPI).  Per tile of 32 gathered keys:
+//   S^T = K_tile . Q^T     v_mfma_f32_32x32x16_bf16, A = key rows (read back from LDS one row per lane), B = the query tile
+//                          held in registers.  The result has one query per lane and 16 keys in its registers, so the
+//                          softmax statistics of a query are lane-local (plus one exchange with lane ^ 32) and P^T is already
+//                          in B-operand layout.
+//   O^T += V_tile^T . P^T  the value rows are read back channel-major with the LDS transpose read ds_read_b64_tr_b16 (the
+//                          contraction runs over keys, so V has to be transposed on the way to the A operand).
+// P is a single bf16 term; the row sum is taken over the ROUNDED probabilities, so numerator and denominator of the output
+// carry the same weights: the rounding of P then perturbs the weights of a weighted mean by 2^-9 relative instead of adding
+// an error of that size to the output.
+// How a tile travels:
+//   * The keys of a work item - selected blocks, sink, window - are worked out before the loop, 16 tiles of them, into a list
+//     in LDS (position of every key; over a paged pool its page as well), with two bits per tile that say whether any key
+//     counts and whether any needs masking.  Longer lists are refilled 8 tiles at a time.  The loop itself then only reads
+//     its rows' positions.  (Any k in 72 KB of LDS: two workgroups to a compute unit where an index row of 1024 entries in LDS left one.)
+//   * global_load_lds_dwordx4 delivers lane l's 16 bytes at M0 + 16 l without passing through registers or the LDS
+//     instruction pipe.  Load j of a tile fills LDS rows RPI j .. RPI j + RPI - 1 (RPI = 4 rows of 256 bytes or 8 of 128); lane
+//     group lg supplies gathered key NLD lg + j (a lane's rows are consecutive keys: one or two 16-byte reads of the list tell
+//     it where they are), hence key x sits in LDS row RPI (x % NLD) + x / NLD.
+//   * XOR swizzles, applied to the global chunk a lane fetches, keep the operand reads free of bank conflicts.  Keys: 16-byte
+//     chunk c at place c ^ (x % 16), with 64 channels c ^ (x % 4 + 4 (x / 8 % 2)).  Values: 32-byte chunk pair p at place
+//     p ^ rotl3(x % 8), with 64 channels p ^ 2 (x % 2): the 16 consecutive channels a transpose read takes stay together and
+//     the eight 32-byte pieces that 32 lanes of it fetch fall into different banks.  With 64 channels two rows share the 256
+//     bytes of all banks, so the four keys that a lane takes per read have to be two of even and two of odd rows: row r of
+//     the score tile is gathered key r with bits 1 and 2 exchanged.
+//   * ONE key and ONE value buffer per wave: as soon as a tile's key operands are in registers the key buffer is refilled
+//     with the next tile's keys, which land while this tile is multiplied and its softmax runs; the same for the values
+//     after the transpose reads.  The direct loads are inline assembly with hand-placed waits (the compiler neither knows
+//     that they write LDS nor counts them) and, but for a refill of the list, the only vector memory instructions of the loop.
+// Measured, 32 query heads over 8 kv heads, d = 128, k = 512, bq = 32, against the form before (metadata in the loop, the whole
+// index row in LDS; 64 channels staged through registers at two waves a SIMD, now four): 3k tokens 59.2 -> 54.3 us, 32k 553 ->
+// 544, over pages 852 -> 763, d = 64 298 -> 265; k = 2048 2903 -> 1771.  At 32k two waves a SIMD, each a chain of about 4000
+// clocks per tile (a third of it waiting for loads), keep vector issue 44 %, the matrix pipe 23 %, the vector L1 53 % busy.
 #include "common.h"
 #include "launch.h"
+#include <type_traits>
 
 namespace hipattn {
+
+namespace {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
@@ -27,6 +49,8 @@ typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
 typedef __attribute__((address_space(3))) s16x4 *lds_s16x4_ptr;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) const u32x4 *lds_u32x4_ptr;
 
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {
@@ -34,31 +58,35 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
 }
 
-// MODE 0: contiguous K/V, a (sequence, kv head) slice below 4 GB: rows are addressed by a scalar slice base
-//         plus a 32-bit lane offset (one shift-add per row instead of 64-bit vector arithmetic);
-// MODE 1: paged pool; MODE 2: contiguous, any size (64-bit row addresses).
-// SPLIT: the workgroup takes ONE work item; wave w walks key tiles w, w + 4, ... with its own softmax state and the
-//        four states are merged through LDS at the end (for launches with too few work items to fill the GPU).
-template <int D, int MODE, bool SPLIT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void attn_mfma_kernel(KParams p, int log_bk, int mtn, int xcd_map)
+constexpr int kListTiles = 16;   // tiles whose keys are listed; refilled by halves
+
+}  // namespace
+
+// MODE 0: contiguous K/V, a (sequence, kv head) slice below 4 GB: rows are addressed by a scalar slice base plus a
+//         32-bit lane offset; MODE 1: paged pool; MODE 2: contiguous, any size (64-bit row addresses).
+// WPI: waves per work item.  With 2 or 4 the workgroup takes ONE work item; wave w walks key tiles w, w + WPI, ... with its own
+//      softmax state and the states are merged through LDS at the end.
+template <int D, int MODE, int WPI>
+__global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2))) void attn_mfma_kernel(KParams p, int log_bk, int mtn, int xcd_map)
 {
-    constexpr bool PAGED = MODE == 1, A32 = MODE == 0;
-    constexpr int KS = D / 16;     // k-steps of S^T = K Q^T
-    constexpr int CT = D / 32;     // 32-channel tiles of O^T
-    constexpr int PITCH = D + 32;  // value tile row pitch in bf16: 64 bytes of padding per row (4 keys x 2 channel halves fill the 64 banks)
-    constexpr int CPR = D / 8;     // 16-byte chunks per row
-    constexpr int RPI = 64 / CPR;  // rows covered by one wave-wide 16-byte load
-    constexpr int NLD = 32 / RPI;  // such loads per 32-row tile
-    constexpr int ROWB = D * 2;    // bytes per key row in the (swizzled, unpadded) key tile
-    typedef uint32_t stage_t __attribute__((ext_vector_type(4 * NLD)));
-    __shared__ __attribute__((aligned(16))) bf16_t vt_s[4][32 * PITCH];
-    __shared__ __attribute__((aligned(16))) uint4 kt_s[4][32 * ROWB / 16];
-    __shared__ __attribute__((aligned(16))) int tk_s[4][2][32];
-    __shared__ __attribute__((aligned(16))) uint32_t mo_s[4][32];
+    constexpr bool PAGED = MODE == 1, SPLIT = WPI > 1;
+    constexpr int W = SPLIT ? WPI : 4;   // waves of the workgroup
+    constexpr int KS = D / 16;           // k-steps of S^T = K Q^T
+    constexpr int CT = D / 32;           // 32-channel tiles of O^T
+    constexpr int CPR = D / 8;           // 16-byte chunks per row
+    constexpr int RPI = 64 / CPR;        // rows per wave-wide load
+    constexpr int NLD = 32 / RPI;        // such loads per 32-row tile
+    constexpr int ROWB = D * 2, TILEB = 32 * ROWB;
+    constexpr int LIST = kListTiles * 32;
+    // LDS: key and value buffer of every wave first (the targets of the direct loads, whose LDS address travels in M0), then
+    // the lists
+    constexpr int kOffList = W * 2 * TILEB, kOffPage = kOffList + W * LIST * 4;
+    static_assert(kOffList <= 65536, "direct-load targets must stay below 64 KB");
+    __shared__ __attribute__((aligned(1024))) char lds[kOffPage + (PAGED ? W * LIST * 4 : 0)];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, hh = lane >> 5;
-    const int lg = lane / CPR, lc = lane % CPR;  // loading role: rows lg*NLD .. +NLD-1, chunk lc
+    const int lg = lane / CPR, lc = lane % CPR;  // loading role: gathered keys lg*NLD .. +NLD-1, LDS chunk place lc
 
     // ---- which (sequence, head, query block, query tile) this wave owns
     const uint32_t groups = (uint32_t)p.batch * (uint32_t)p.hkv;
@@ -75,7 +103,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     const int n_rows = min(32, min(p.bq, p.q_len - qb * p.bq) - mt * 32);
     if (n_rows <= 0) return;
     const int pos0 = kv_len - p.q_len + row0;  // position of this tile's first query row
-    const int32_t *idx = p.idx_in + (((int64_t)b * p.hq + h) * p.nqb + qb) * p.kb;
     const int bk = 1 << log_bk;
     // Key tiles: first the selected blocks, then the sink keys [0, ns), then the window keys
     // [wlo, vis_last).  For a row at position q with vis = min(q+1, kv_len) and
@@ -103,15 +130,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         }
     }
 
+    auto uniform64 = [](int64_t v) __attribute__((always_inline)) {
+        return ((int64_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+    };
     const bf16_t *Kbase = (const bf16_t *)p.K, *Vbase = (const bf16_t *)p.V;
     const int64_t seq_off = (int64_t)b * p.ks_b + (int64_t)hk * p.ks_h;  // contiguous layout: row 0 of this slice
-    // the same in every lane: as a scalar (readfirstlane) it becomes the scalar base of the row loads
-    const int64_t slice_u = ((int64_t)__builtin_amdgcn_readfirstlane((int)((seq_off * 2) >> 32)) << 32) |
-                            (uint32_t)__builtin_amdgcn_readfirstlane((int)(seq_off * 2));
+    // the same in every lane: as a scalar it becomes the scalar base of the row loads
+    const int64_t slice_u = uniform64(seq_off * 2);
     const char *Kseq = (const char *)p.K + slice_u, *Vseq = (const char *)p.V + slice_u;
-    bf16_t *vt = vt_s[wave];
-    char *kt = (char *)kt_s[wave];
-    uint32_t *mo = mo_s[wave];
+    const uint32_t row_bytes = (uint32_t)p.ks_r * 2u;
+    const int32_t *idx = p.idx_in + (((int64_t)b * p.hq + h) * p.nqb + qb) * p.kb;
+
+    char *kt = lds + wave * 2 * TILEB, *vt = kt + TILEB;
+    int *list = (int *)(lds + kOffList) + wave * LIST;     // position of every listed key, or kNoKey
+    int *pages = (int *)(lds + kOffPage) + wave * LIST;    // paged pool: the page-table entry of its page
+    constexpr int kNoKey = (int)0xff000000;                // negative, and row 0 to a 24-bit multiply
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
+    const uint32_t kt_m0 = lds0 + wave * 2 * TILEB, vt_m0 = kt_m0 + TILEB;
 
     const float c = p.sm_scale * 1.44269504088896340736f;  // scores are kept in log2 units
     constexpr float kSlack = 8.f;
@@ -122,152 +157,196 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[ct][r] = 0.f;
 
-    // One tile of 32 gathered keys: lane `col` works out key row col (position or -1, row
-    // offset in 16-byte units), publishes both, then every lane loads its share of the key and
-    // value rows coalesced.  Rows that do not count load row 0 of the sequence (always mapped,
-    // finite) and get probability 0.  Returns flags: bit 0 = some key may count for some row,
-    // bit 1 = some (key, row) pair needs masking, bit 2 = window tile.
-    // The index entry lane `col` needs for a tile of selected blocks is loaded one tile before fetch()
-    // uses it, so that the row loads do not queue behind the latency of the index load.
-    auto index_entry = [&](int tile) __attribute__((always_inline)) {
-        const int ki = tile * 32 + col;
-        return (tile < tiles_sel && ki < n_keys) ? idx[ki >> log_bk] : -1;
+    // this wave's tiles: all of them, or every WPI-th one
+    int nt = SPLIT ? (n_tiles > wave ? (n_tiles - wave + WPI - 1) / WPI : 0) : n_tiles;
+
+    // Lists the keys of the wave's tiles i0 .. i0 + N - 1 (N = 8 or 16; i0 a multiple of 8).  Keys that do not count load
+    // row 0 of the sequence (always mapped, finite) and get probability 0.  Bit i % 16 of `any`: some key of tile i may count
+    // for some row; of `mask`: some (key, row) pair needs masking.
+    uint32_t any = 0, mask = 0;
+    const uint32_t plain = (uint32_t)max(w0_first - p.n_sink, 0);   // (w0_first <= kv_len)
+    auto list_tiles = [&](int i0, auto count) __attribute__((always_inline)) {
+        constexpr int N = decltype(count)::value;
+        const uint32_t at = (uint32_t)i0 % kListTiles, bits = ((1u << N) - 1u) << at;
+        any &= ~bits;
+        mask &= ~bits;
+        // all index entries first, then all page entries: two latencies, not one per tile
+        int t[N / 2];
+#pragma unroll
+        for (int u = 0; u < N / 2; ++u) {
+            const int tile = SPLIT ? wave + WPI * (i0 + 2 * u + hh) : i0 + 2 * u + hh;
+            t[u] = idx[min(tile * 32 + col, n_keys - 1) >> log_bk];
+        }
+#pragma unroll
+        for (int u = 0; u < N / 2; ++u) {
+            const int tile = SPLIT ? wave + WPI * (i0 + 2 * u + hh) : i0 + 2 * u + hh;
+            const int ki = tile * 32 + col, first = t[u], tk = first + (ki & (bk - 1));
+            // nearly always: 64 selected keys that all rows see
+            if (__ballot((uint32_t)(tk - p.n_sink) < plain && ki < n_keys) == ~0ull) {
+                t[u] = tk;
+                any |= 3u << (at + 2 * u);
+            } else {
+                bool counts, care = true;
+                if (tile < tiles_sel) {
+                    t[u] = ki < n_keys && first >= 0 && first < kv_len && tk < kv_len && tk >= p.n_sink ? tk : -1;
+                    counts = t[u] >= 0 && t[u] < w0_last;
+                    care = t[u] < 0 || t[u] >= w0_first;
+                } else {
+                    const bool sink = tile < tiles_sel + tiles_sink;
+                    const int te = ki - (sink ? tiles_sel * 32 : (tiles_sel + tiles_sink) * 32 - wlo);
+                    t[u] = te < (sink ? ns : vis_last) ? te : -1;
+                    counts = tile < n_tiles;
+                }
+                const uint64_t bc = __ballot(counts), bm = __ballot(care);
+                any |= (((uint32_t)bc != 0 ? 1u : 0u) | ((uint32_t)(bc >> 32) != 0 ? 2u : 0u)) << (at + 2 * u);
+                mask |= (((uint32_t)bm != 0 ? 1u : 0u) | ((uint32_t)(bm >> 32) != 0 ? 2u : 0u)) << (at + 2 * u);
+            }
+            list[(at + 2 * u) * 32 + lane] = t[u] >= 0 ? t[u] : kNoKey;
+        }
+        if constexpr (PAGED) {
+#pragma unroll
+            for (int u = 0; u < N / 2; ++u) t[u] = page_of_row<true>(p, b, max(t[u], 0));
+#pragma unroll
+            for (int u = 0; u < N / 2; ++u) pages[(at + 2 * u) * 32 + lane] = t[u];
+        }
+        any = (uint32_t)__builtin_amdgcn_readfirstlane((int)any);
+        mask = (uint32_t)__builtin_amdgcn_readfirstlane((int)mask);
     };
-    auto fetch = [&](int tile, int first, stage_t &RK, stage_t &RV, int *tk) __attribute__((always_inline)) {
-        int t_c = -1;
-        int flags;
-        if (tile < tiles_sel) {
-            const int ki = tile * 32 + col;
-            if (ki < n_keys) {
-                const int t = first + (ki & (bk - 1));
-                if (first >= 0 && first < kv_len && t < kv_len && t >= p.n_sink) t_c = t;
-            }
-            flags = (__ballot(t_c >= 0 && t_c < w0_last) != 0 ? 1 : 0) | (__ballot(t_c < 0 || t_c >= w0_first) != 0 ? 2 : 0);
-        } else if (tile < tiles_sel + tiles_sink) {
-            const int t = (tile - tiles_sel) * 32 + col;
-            if (t < ns) t_c = t;
-            flags = 1 | 2;
-        } else {
-            const int t = wlo + (tile - tiles_sel - tiles_sink) * 32 + col;
-            if (t < vis_last) t_c = t;
-            flags = 1 | 2 | 4;  // bit 2: window tile (keys count for the rows whose window holds them)
-        }
-        {
-            const int tr = t_c >= 0 ? t_c : 0;
-            // what a loading lane needs to find the row: the page (paged pool) or the row's offset
-            // from the start of this sequence / kv head slice in 16-byte units (contiguous)
-            const uint32_t m = PAGED ? (uint32_t)page_of_row<true>(p, b, tr)
-                                     : (uint32_t)(((int64_t)tr * p.ks_r) >> 3);
-            if (hh == 0) {
-                tk[col] = t_c;
-                mo[col] = m;
-            }
-        }
-        wave_lds_sync();
-        uint32_t off[NLD];
+    // Where this lane's rows of a listed tile are.
+    struct rows_t { uint32_t off[NLD]; int pg[PAGED ? NLD : 1]; };
+    auto read_rows = [&](int i, rows_t &R) __attribute__((always_inline)) {
+        const int x = (i % kListTiles) * 32 + lg * NLD;
 #pragma unroll
         for (int j = 0; j < NLD; j += 4) {
-            const uint4 m4 = *(const uint4 *)(mo + lg * NLD + j);
-            off[j] = m4.x; off[j + 1] = m4.y; off[j + 2] = m4.z; off[j + 3] = m4.w;
+            const int4 t4 = *(const int4 *)(list + x + j);
+            R.off[j] = (uint32_t)t4.x; R.off[j + 1] = (uint32_t)t4.y; R.off[j + 2] = (uint32_t)t4.z; R.off[j + 3] = (uint32_t)t4.w;
         }
-        int tkl[NLD];  // positions of this lane's rows (paged variant: the offset inside the page)
-        if (PAGED) {
+        if constexpr (PAGED) {
 #pragma unroll
             for (int j = 0; j < NLD; j += 4) {
-                const int4 t4 = *(const int4 *)(tk + lg * NLD + j);
-                tkl[j] = t4.x; tkl[j + 1] = t4.y; tkl[j + 2] = t4.z; tkl[j + 3] = t4.w;
+                const int4 p4 = *(const int4 *)(pages + x + j);
+                R.pg[j] = p4.x; R.pg[j + 1] = p4.y; R.pg[j + 2] = p4.z; R.pg[j + 3] = p4.w;
             }
         }
-        wave_lds_sync();
+        if constexpr (MODE == 0) {
 #pragma unroll
-        for (int j = 0; j < NLD; ++j) {
-            int64_t eo;
-            const bf16_t *Kp = Kbase, *Vp = Vbase;
-            if (PAGED) {
-                const int tr = max(tkl[j], 0);
-                // (a negative page-table entry names a page of the backing pools)
-                eo = row_offset_in<true>(p, b, hk, tr, page_in_pool((int)off[j])) + lc * 8;
-                Kp = (const bf16_t *)pool_of((int)off[j], Kbase, p.Kback);
-                Vp = (const bf16_t *)pool_of((int)off[j], Vbase, p.Vback);
-            } else {
-                eo = seq_off + ((int64_t)off[j] << 3) + lc * 8;
-            }
-            uint4 x, y;
-            if (A32) {
-                const uint32_t vo = (off[j] << 4) + (uint32_t)lc * 16u;
-                x = *(const uint4 *)(Kseq + vo);
-                y = *(const uint4 *)(Vseq + vo);
-            } else {
-                x = *(const uint4 *)(Kp + eo);
-                y = *(const uint4 *)(Vp + eo);
-            }
-            RK[4 * j] = x.x; RK[4 * j + 1] = x.y; RK[4 * j + 2] = x.z; RK[4 * j + 3] = x.w;
-            RV[4 * j] = y.x; RV[4 * j + 1] = y.y; RV[4 * j + 2] = y.z; RV[4 * j + 3] = y.w;
+            for (int j = 0; j < NLD; ++j) R.off[j] = __umul24(R.off[j], row_bytes);
         }
-        return flags;
     };
-
-    // this wave's tiles: all of them, or every fourth one (SPLIT)
-    const int nt = SPLIT ? (n_tiles > wave ? (n_tiles - wave + 3) >> 2 : 0) : n_tiles;
-    auto tile_of = [&](int i) __attribute__((always_inline)) { return SPLIT ? wave + 4 * i : i; };
-    stage_t RK, RV;
-    int flags_next = 0, first_next = -1;
-    if (nt > 0) {
-        flags_next = fetch(tile_of(0), index_entry(tile_of(0)), RK, RV, tk_s[wave][0]);
-        first_next = index_entry(tile_of(1));
-    }
-    for (int tile = 0; tile < nt; ++tile) {
-        const int flags = flags_next;
-        const int *tk = tk_s[wave][tile & 1];
-        // registers -> LDS: key tile swizzled (chunk lc of row r at slot lc ^ (r % CPR)), value tile padded
+    // The direct loads of a tile's keys (VAL = false) or values (VAL = true): load j brings gathered key x = NLD lg + j to LDS
+    // row RPI j + lg, this lane the 16-byte chunk that belongs at place lc of that row.  (M0 is a reserved register: the
+    // compiler warns that it does not track the clobber.  It is written and consumed inside one asm statement, and nothing else
+    // in this kernel uses M0.)
+    // An instruction offset moves both the global and the LDS address, so one M0 serves four loads; what it adds to the global
+    // address is taken off the lane's part (3072 bytes stand before it so that nothing gets negative).
+    const uint32_t kchunk = (uint32_t)((D == 128 ? lc ^ ((lg & 1) << 3) : lc ^ ((lg & 2) << 1)) << 4), vchunk = (uint32_t)(lc << 4);
+    auto issue_rows = [&](const rows_t &R, bool val) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < NLD; ++j) {
-            const int r = lg * NLD + j;
-            *(uint4 *)(kt + r * ROWB + ((lc ^ (r & (CPR - 1))) << 4)) = make_uint4(RK[4 * j], RK[4 * j + 1], RK[4 * j + 2], RK[4 * j + 3]);
-            *(uint4 *)(vt + r * PITCH + lc * 8) = make_uint4(RV[4 * j], RV[4 * j + 1], RV[4 * j + 2], RV[4 * j + 3]);
+            const int rot = D == 128 ? ((j & 3) << 1) | ((j >> 2) & 1) : (j & 1) << 1;   // value place = chunk pair ^ rot
+            uint32_t chunk = val ? vchunk : kchunk;
+            asm volatile("" : "+v"(chunk));   // (not a register per load)
+            chunk ^= (uint32_t)(val ? rot << 5 : j << 4);
+            const uint32_t dst = __builtin_amdgcn_readfirstlane((val ? vt_m0 : kt_m0) + (j & ~3) * 1024);
+            const int back = (j & 3) * 1024;
+            if constexpr (MODE == 0) {
+                const uint32_t vo = R.off[j] + chunk + (uint32_t)(3072 - back);
+                const char *base = (val ? Vseq : Kseq) - 3072;
+                if (j & 3) asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" :: "v"(vo), "s"(base), "i"(back) : "memory");
+                else asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                                  :: "v"(vo), "s"(base), "s"(dst) : "memory", "m0");
+            } else {
+                const char *src;
+                const int tr = max((int)R.off[j], 0);
+                if constexpr (PAGED) {
+                    // (a negative page-table entry names a page of the backing pools)
+                    const int e = R.pg[j];
+                    const bf16_t *pool = (const bf16_t *)(val ? pool_of(e, Vbase, p.Vback) : pool_of(e, Kbase, p.Kback));
+                    src = (const char *)(pool + row_offset_in<true>(p, b, hk, tr, page_in_pool(e))) + chunk;
+                } else {
+                    src = (const char *)((val ? Vbase : Kbase) + seq_off + (int64_t)tr * p.ks_r) + chunk;
+                }
+                src -= back;
+                if (j & 3) asm volatile("global_load_lds_dwordx4 %0, off offset:%1" :: "v"(src), "i"(back) : "memory");
+                else asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(src), "s"(dst) : "memory", "m0");
+            }
         }
-        if (tile + 1 < nt) {
-            flags_next = fetch(tile_of(tile + 1), first_next, RK, RV, tk_s[wave][(tile + 1) & 1]);
-            first_next = index_entry(tile_of(tile + 2));
-        }
-        wave_lds_sync();
+    };
+    // row r of the score tile is gathered key xkey(r)
+    auto xkey = [](int r) __attribute__((always_inline)) { return D == 128 ? r : (r & 25) | ((r & 2) << 1) | ((r & 4) >> 1); };
 
-        if (flags & 1) {
-            // ---- S^T = K Q^T: A = key rows from the LDS tile (lane: key row col), B = queries.  All operand reads
-            // are issued before the first multiply (one LDS latency per tile, not one per k-step); the wave
-            // raises its priority while it feeds the matrix pipe, so that of two waves on a SIMD one multiplies
-            // while the other runs its softmax arithmetic instead of both queueing on the same unit.
-            f32x16 sacc;
+    list_tiles(0, std::integral_constant<int, kListTiles>{});
+    // (the tail of a list that ends early: a prefix with fewer keys than k)
+    if (nt <= kListTiles) nt = any ? 32 - __builtin_clz(any) : 0;
+    // The query loads end here, where the compiler can see it: it does not count the loads that the loop issues from
+    // inline assembly, and a wait for a query fragment left inside that loop would wait for them.
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) asm volatile("" :: "v"(qf[kk]));
+    wave_lds_sync();
+    if (nt > 0) {
+        rows_t R0;
+        read_rows(0, R0);
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // nothing of the compiler's is in flight from here on
+        issue_rows(R0, false);
+        issue_rows(R0, true);
+    }
+    // Outstanding vector memory operations at the top of iteration i, oldest first: keys of tile i (NLD), values of
+    // tile i (NLD).
+    for (int i = 0; i < nt; ++i) {
+        const bool more = i + 1 < nt;
+        const uint32_t bit = 1u << (i % kListTiles);
+        const bool counts = any & bit;
+        if (more && i + 1 >= kListTiles && (i + 1) % (kListTiles / 2) == 0) {
+            // tiles i + 1 .. i + 8 go where tiles i - 15 .. i - 8 were (this tile's keys are in the other half)
+            list_tiles(i + 1, std::integral_constant<int, kListTiles / 2>{});
+            wave_lds_sync();
+        }
+        // ---- keys of tile i have landed; its values may still be on their way
+        asm volatile("s_waitcnt vmcnt(%0)" :: "i"(NLD) : "memory");
+        u32x4 kv[KS];
+        if (counts) {
+            const int x = xkey(col);
+            const int sw = D == 128 ? x & 15 : (x & 3) | ((x >> 1) & 4);
+            uint32_t krow = (uint32_t)((RPI * (x % NLD) + x / NLD) * ROWB + ((hh ^ sw) << 4)) + kt_m0;
+            asm volatile("" : "+v"(krow));   // (one register and exclusive-ors instead of a register per read)
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) kv[kk] = *(lds_u32x4_ptr)(uintptr_t)(krow ^ (uint32_t)(kk << 5));
+        }
+        rows_t R1;
+        if (more) read_rows(i + 1, R1);
+        // the key operands are in registers (and this lane's rows of the next tile are known): the key buffer may be refilled
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (more) issue_rows(R1, false);
+        // outstanding now: values of tile i [, keys of tile i+1]
+
+        f32x16 sacc;
+        bf16x8 pb[2];
+        if (counts) {
+            // ---- S^T = K Q^T: A = key rows (lane: key xkey(col)), B = queries
 #pragma unroll
             for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
-            uint4 kv[KS];
-#pragma unroll
-            for (int kk = 0; kk < KS; ++kk)
-                kv[kk] = *(const uint4 *)(kt + col * ROWB + (((kk * 2 + hh) ^ (col & (CPR - 1))) << 4));
-            __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_setprio(2);
 #pragma unroll
             for (int kk = 0; kk < KS; ++kk)
                 sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kv[kk]), qf[kk], sacc, 0, 0, 0);
-            __builtin_amdgcn_s_setprio(0);
 
             // ---- online softmax for query `col` (both half-waves hold the same query)
             float s[16], mx = -INFINITY;
-            if (flags & 2) {
+            if (mask & bit) {
                 // positions of the 16 keys this lane holds scores for: rows 8g + 4hh + {0..3};
                 // admissible range [lo, hi) of key positions for this lane's query
+                const bool window = (SPLIT ? wave + WPI * i : i) >= tiles_sel + tiles_sink;
                 const int visq = min(pos0 + col + 1, kv_len);
                 const int w0q = max(visq - p.n_window, 0);
-                const int lo = (flags & 4) ? w0q : 0, hi = (flags & 4) ? visq : w0q;
+                const int lo = window ? w0q : 0, hi = window ? visq : w0q;
+                const int *tk = list + (i % kListTiles) * 32;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const int4 tq = *(const int4 *)(tk + 8 * g + 4 * hh);
-                    const int tkey[4] = {tq.x, tq.y, tq.z, tq.w};
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const bool ok = tkey[e] >= lo && tkey[e] < hi;
-                        s[4 * g + e] = ok ? sacc[4 * g + e] : -INFINITY;
+                        const int tkey = tk[xkey(8 * g + e) + (D == 128 ? 4 : 2) * hh];
+                        s[4 * g + e] = tkey >= lo && tkey < hi ? sacc[4 * g + e] : -INFINITY;
                     }
+                    asm volatile("" ::: "memory");   // (four positions in registers at a time)
                 }
             } else {
 #pragma unroll
@@ -290,11 +369,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c, -m_safe));
-            // P^T as B operand of the two 16-key steps (registers 8*st .. 8*st+7), rounded to bf16.  The row sum l
-            // is taken over the ROUNDED probabilities (v_dot2_f32_bf16 against ones, fp32 accumulation), so that
-            // numerator and denominator of the output carry the same weights: the rounding of P then perturbs the
-            // weights of a weighted mean by 2^-9 relative instead of adding an error of that size to the output.
-            bf16x8 pb[2];
+            // P^T as B operand of the two 16-key steps (registers 8*st .. 8*st+7), rounded to bf16; the row sum runs
+            // over the rounded values (v_dot2_f32_bf16 against ones, fp32 accumulation)
             float lsum = 0.f;
             {
                 const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
@@ -317,77 +393,105 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
                     for (int r = 0; r < 16; ++r) oacc[ct][r] *= alpha;
             }
+        }
 
-            // ---- O^T += V^T P^T: value tile read back channel-major with the LDS transpose read.
-            // ds_read_b64_tr_b16 works on blocks of 16 lanes: lanes 4e .. 4e+3 of a block point at 16
-            // consecutive bf16 of source row e (e = 0..3), and lane i of the block receives element i
-            // of each of the four rows.  Block = (channel half cb, key half hh): rows are 4 consecutive
-            // keys, so a lane ends up with 4 keys of its channel - half an A operand per read.
-            {
-                const int i16 = lane & 15, cb = (lane >> 4) & 1;
-                const bf16_t *src0 = vt + (4 * hh + (i16 >> 2)) * PITCH + cb * 16 + (i16 & 3) * 4;
+        // ---- the values of tile i have landed
+        if (more) asm volatile("s_waitcnt vmcnt(%0)" :: "i"(NLD) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        bf16x8 va[2][CT];
+        if (counts) {
+            // Value tile read back channel-major with the LDS transpose read.  ds_read_b64_tr_b16 works on blocks of
+            // 16 lanes: lanes 4e .. 4e+3 of a block point at 16 consecutive bf16 of source row e (e = 0..3), and lane
+            // i of the block receives element i of each of the four rows.  Block = (channel half cb, key half hh):
+            // rows are score rows 16 st [+ 8] + 4 hh + e, so a lane ends up with 4 keys of its channel - half an A operand
+            // per read - in the order in which P^T holds them.
+            const int i16 = lane & 15, cb = (lane >> 4) & 1, e = i16 >> 2;
+            const int x0 = xkey(4 * hh + e);   // (adding 8 or 16 to the row adds 8 or 16 to the key: NLD divides both)
+            const int vsw = D == 128 ? 2 * e + hh : (x0 & 1) << 1;   // (x0 % 8 rotated left by one bit)
+            uint32_t vrow = (uint32_t)((RPI * (x0 % NLD) + x0 / NLD) * ROWB + ((cb ^ vsw) << 5) + (i16 & 3) * 8) + vt_m0;
+            asm volatile("" : "+v"(vrow));
 #pragma unroll
-                for (int st = 0; st < 2; ++st) {
-                    bf16x8 va[CT];
+            for (int st = 0; st < 2; ++st)
 #pragma unroll
-                    for (int ct = 0; ct < CT; ++ct) {
-                        // keys 16st + 4hh + {0..3} and 16st + 8 + 4hh + {0..3}, channel ct*32 + col
-                        const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(src0 + (16 * st) * PITCH + ct * 32));
-                        const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(src0 + (16 * st + 8) * PITCH + ct * 32));
-                        const uint2 a = __builtin_bit_cast(uint2, lo4), c2 = __builtin_bit_cast(uint2, hi4);
-                        va[ct] = __builtin_bit_cast(bf16x8, make_uint4(a.x, a.y, c2.x, c2.y));
-                    }
-                    // the CT accumulators are independent: interleave them so that no multiply waits
-                    // for the one before it
-                    __builtin_amdgcn_s_setprio(2);
+                for (int ct = 0; ct < CT; ++ct) {
+                    const uint32_t place = vrow ^ (uint32_t)(ct << 6);
+                    const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)(place + (16 * st / NLD) * ROWB));
+                    const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)(place + ((16 * st + 8) / NLD) * ROWB));
+                    const uint2 a = __builtin_bit_cast(uint2, lo4), c2 = __builtin_bit_cast(uint2, hi4);
+                    va[st][ct] = __builtin_bit_cast(bf16x8, make_uint4(a.x, a.y, c2.x, c2.y));
+                }
+        }
+        // the value operands are in registers: the value buffer may be refilled
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (more) issue_rows(R1, true);
+        if (counts) {
+            // ---- O^T += V^T P^T (the CT accumulators are independent)
 #pragma unroll
-                    for (int ct = 0; ct < CT; ++ct) oacc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[ct], pb[st], oacc[ct], 0, 0, 0);
-                    __builtin_amdgcn_s_setprio(0);
+            for (int st = 0; st < 2; ++st)
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) oacc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[st][ct], pb[st], oacc[ct], 0, 0, 0);
+        }
+    }
+
+    bf16_t *Ob = (bf16_t *)p.O + (int64_t)b * p.os_b + (int64_t)h * p.os_h + (int64_t)row0 * p.os_r;
+    if constexpr (SPLIT) {
+        // Every wave leaves its state (running reference, partial sum, accumulators) in its own buffers, lane-contiguous, and
+        // merges a share of the channels: with m = max of the references, every state is rescaled by 2^(m_w - m) before it
+        // is added (the usual merge of online-softmax states).  Nothing of a list is read any more.
+        constexpr int OWN = WPI < CT ? CT / WPI : 1;   // 32-channel tiles per merging wave
+        float *st = (float *)kt, *ml = (float *)list;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+            if (ct / OWN != wave) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) st[(ct * 16 + r) * 64 + lane] = oacc[ct][r];
+            }
+        const float l_own = l_run + __shfl_xor(l_run, 32, 64);
+        ml[lane] = m_run;
+        ml[64 + lane] = l_own;
+        __syncthreads();
+        if (wave * OWN >= CT) return;
+        float m = m_run, f[WPI], l = 0.f;
+#pragma unroll
+        for (int w = 0; w < WPI; ++w) m = fmaxf(m, ((const float *)(lds + kOffList))[w * LIST + lane]);
+        const float m_safe = m == -INFINITY ? 0.f : m;
+#pragma unroll
+        for (int w = 0; w < WPI; ++w) {
+            const float *mlw = (const float *)(lds + kOffList) + w * LIST;
+            f[w] = __builtin_amdgcn_exp2f(mlw[lane] - m_safe);
+            l = fmaf(mlw[64 + lane], f[w], l);
+        }
+        const float inv = l > 0.f ? 1.f / l : 0.f;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            if (ct / OWN != wave) continue;
+            float own = 0.f;
+#pragma unroll
+            for (int w = 0; w < WPI; ++w) own = w == wave ? f[w] : own;
+            float out[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) out[r] = oacc[ct][r] * own;
+#pragma unroll
+            for (int w = 0; w < WPI; ++w) {
+                if (w == wave) continue;
+                const float *sw = (const float *)(lds + w * 2 * TILEB) + ct * 16 * 64 + lane;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) out[r] = fmaf(sw[r * 64], f[w], out[r]);
+            }
+            if (col < n_rows) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    uint2 u;
+                    u.x = pack_bf16(out[4 * g + 0] * inv, out[4 * g + 1] * inv);
+                    u.y = pack_bf16(out[4 * g + 2] * inv, out[4 * g + 3] * inv);
+                    *(uint2 *)(Ob + (int64_t)col * p.os_r + ct * 32 + g * 8 + hh * 4) = u;
                 }
             }
         }
-        wave_lds_sync();  // the tiles are consumed before the next iteration overwrites them
+        return;
     }
 
-    if (SPLIT) {
-        // Waves 1-3 leave their state (running reference, partial sum, accumulators) in their own tile
-        // buffers, lane-contiguous; wave 0 folds them into its own: with m = max of the references, every
-        // state is rescaled by 2^(m_w - m) before it is added (the usual merge of online-softmax states).
-        constexpr int HALF = (CT / 2) * 16 * 64;  // floats of the first CT/2 accumulators = the key tile's size
-        float *sk = (float *)kt_s[wave], *sv = (float *)vt_s[wave];
-        if (wave != 0) {
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    float *dst = ct < CT / 2 ? sk + (ct * 16 + r) * 64 : sv + ((ct - CT / 2) * 16 + r) * 64;
-                    dst[lane] = oacc[ct][r];
-                }
-            sv[HALF + lane] = m_run;
-            sv[HALF + 64 + lane] = l_run;
-        }
-        __syncthreads();
-        if (wave != 0) return;
-#pragma unroll
-        for (int w = 1; w < 4; ++w) {
-            const float *ok = (const float *)kt_s[w], *ov = (const float *)vt_s[w];
-            const float m_w = ov[HALF + lane], l_w = ov[HALF + 64 + lane];
-            const float m_new = fmaxf(m_run, m_w);
-            const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-            const float a = __builtin_amdgcn_exp2f(m_run - m_safe), bw = __builtin_amdgcn_exp2f(m_w - m_safe);
-            l_run = l_run * a + l_w * bw;
-            m_run = m_new;
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float *src = ct < CT / 2 ? ok + (ct * 16 + r) * 64 : ov + ((ct - CT / 2) * 16 + r) * 64;
-                    oacc[ct][r] = oacc[ct][r] * a + src[lane] * bw;
-                }
-        }
-    }
-
-    // ---- normalise, transpose through LDS, coalesced store
+    // ---- normalise, transpose through LDS (16-byte chunk c of row r at place c ^ (r % CPR)), coalesced store
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
 #pragma unroll
@@ -397,22 +501,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             uint2 u;
             u.x = pack_bf16(oacc[ct][4 * g + 0] * inv, oacc[ct][4 * g + 1] * inv);
             u.y = pack_bf16(oacc[ct][4 * g + 2] * inv, oacc[ct][4 * g + 3] * inv);
-            *(uint2 *)(vt + col * PITCH + ct * 32 + g * 8 + hh * 4) = u;
+            *(uint2 *)(vt + col * ROWB + (((ct * 4 + g) ^ (col & (CPR - 1))) << 4) + hh * 8) = u;
         }
     wave_lds_sync();
-    bf16_t *Ob = (bf16_t *)p.O + (int64_t)b * p.os_b + (int64_t)h * p.os_h + (int64_t)row0 * p.os_r;
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
-        const int row = lane / CPR + i * RPI;
-        if (row < n_rows) *(uint4 *)(Ob + (int64_t)row * p.os_r + (lane % CPR) * 8) = *(const uint4 *)(vt + row * PITCH + (lane % CPR) * 8);
+        const int row = lg + i * RPI;
+        if (row < n_rows) *(uint4 *)(Ob + (int64_t)row * p.os_r + lc * 8) = *(const uint4 *)(vt + row * ROWB + ((lc ^ (row & (CPR - 1))) << 4));
     }
 }
 
 bool attn_mfma_supported(const KParams &p, bool bf16)
 {
-    // contiguous variant: a row's offset inside its (sequence, kv head) slice is kept in 32 bits of 16-byte units
-    const bool fits = p.page_table || (int64_t)p.max_kv_len * p.ks_r < (1LL << 35);
-    return bf16 && p.q_len > 1 && p.bk <= 16 && (p.bk & (p.bk - 1)) == 0 && p.bq <= 64 && fits;
+    return bf16 && p.q_len > 1 && p.bk <= 16 && (p.bk & (p.bk - 1)) == 0 && p.bq <= 64;
 }
 
 hipError_t launch_attn_mfma(const KParams &p, hipStream_t st)
@@ -424,29 +525,22 @@ hipError_t launch_attn_mfma(const KParams &p, hipStream_t st)
     const int64_t per_group = (int64_t)p.g * p.nqb * mtn;
     const int64_t waves = groups * per_group;
     if (waves == 0) return hipSuccess;
-    // few work items (a quarter of the GPU's wave slots or less): a workgroup per work item, four waves share its key tiles
-    const bool split = waves <= 512;
+    // Few work items: a workgroup of four or two waves each.  Measured, d = 128, k = 512, one / two / four waves per item, us: 64
+    // items - / 13.8 / 11.5; 512 - / 19.3 / 19.5; 1024 26.5 / 26.3 / 35.1, over pages 42.9 / 35.6 / 39.4; 1504 30.3 / 34.1 / 35.3;
+    // 2048 36.8 / 54.0 / 62.6.
+    const int wpi = waves <= 512 ? 4 : waves <= 1024 ? 2 : 1;
     // groups worked on at a time (measured: all eight up to 128k tokens at head dim 128, four at 256k, one at a million)
-    const int xcd_map = (groups % 8 == 0 && (split || per_group % 4 == 0)) ? groups_at_a_time((int64_t)p.max_kv_len * p.d * 4, 768LL << 20) : 0;
-    dim3 grid((unsigned)placed_workgroups(xcd_map, split ? 1 : 4, per_group, groups)), block(kThreads);
-    const int mode = p.page_table ? 1 : ((int64_t)p.max_kv_len * p.ks_r * 2 < (1LL << 32) ? 0 : 2);
-#define HIPATTN_LAUNCH(DV, SP)                                                                                  \
-    do {                                                                                                        \
-        if (mode == 1) hipLaunchKernelGGL((attn_mfma_kernel<DV, 1, SP>), grid, block, 0, st, p, log_bk, mtn, xcd_map);      \
-        else if (mode == 0) hipLaunchKernelGGL((attn_mfma_kernel<DV, 0, SP>), grid, block, 0, st, p, log_bk, mtn, xcd_map); \
-        else hipLaunchKernelGGL((attn_mfma_kernel<DV, 2, SP>), grid, block, 0, st, p, log_bk, mtn, xcd_map);                \
-    } while (0)
-    if (p.d == 128 && p.kb <= 1024) {
-        // head dim 128: the variant that loads the gathered rows straight into LDS (attn_mfma_direct.hip)
-        return launch_attn_mfma_direct(p, grid, log_bk, mtn, xcd_map, mode, split, st);
-    }
-    if (p.d == 64) {
-        if (split) HIPATTN_LAUNCH(64, true); else HIPATTN_LAUNCH(64, false);
-    } else {
-        if (split) HIPATTN_LAUNCH(128, true); else HIPATTN_LAUNCH(128, false);
-    }
-#undef HIPATTN_LAUNCH
-    return hipGetLastError();
+    const int xcd_map = (groups % 8 == 0 && (wpi > 1 || per_group % 4 == 0)) ? groups_at_a_time((int64_t)p.max_kv_len * p.d * 4, 768LL << 20) : 0;
+    const dim3 grid((unsigned)placed_workgroups(xcd_map, wpi > 1 ? 1 : 4, per_group, groups)), block(wpi == 2 ? 128 : kThreads);
+    const int mode = p.page_table ? 1 : ((int64_t)p.max_kv_len * p.ks_r * 2 < (1LL << 32) && p.ks_r * 2 < (1 << 24) && p.max_kv_len < (1 << 24) ? 0 : 2);
+    const auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, st, p, log_bk, mtn, xcd_map);
+        return hipGetLastError();
+    };
+#define HIPATTN_MODE(DV, WV) (mode == 0 ? launch(attn_mfma_kernel<DV, 0, WV>) : mode == 1 ? launch(attn_mfma_kernel<DV, 1, WV>) : launch(attn_mfma_kernel<DV, 2, WV>))
+    if (p.d == 64) return wpi == 4 ? HIPATTN_MODE(64, 4) : wpi == 2 ? HIPATTN_MODE(64, 2) : HIPATTN_MODE(64, 1);
+    return wpi == 4 ? HIPATTN_MODE(128, 4) : wpi == 2 ? HIPATTN_MODE(128, 2) : HIPATTN_MODE(128, 1);
+#undef HIPATTN_MODE
 }
 
 }  // namespace hipattn

@@ -41,3 +41,27 @@ def test_launch_shapes_of_long_contexts(pitch, hq, bq, bk):
         b = hipattn.hip_mask_estimate(x["Q"], wide, 256 * bk, q_rows, bk, b_sq=b_sq)
         torch.cuda.synchronize()
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("d,bq,bk,k,n_sink,n_window", [
+    (128, 32, 2, 512, 0, 0),      # the list of keys is full and never refilled
+    (64, 32, 1, 545, 3, 0),       # one key in the eighteenth tile, then a sink tile
+    (128, 16, 4, 1024, 40, 300),  # refills among selected, sink and window tiles
+    (64, 64, 8, 2048, 0, 70),
+    (128, 48, 16, 768, 16, 1),
+])
+def test_key_lists_and_waves_per_item(d, bq, bk, k, n_sink, n_window, page):
+    # four, two and one wave per (head, query tile): up to 512 of them, up to 1024, more
+    tiles = (bq + 31) // 32
+    for items in (60, 513, 1032):
+        hq = 8
+        q_len = -(-items // (hq * tiles)) * bq - 3
+        T = max(q_len, 3 * k) + 17
+        w = synth.Workload("lists", 1, hq, 2, d, q_len, T, k, bq, bk, "bf16", rho=0.9, page_size=page, integer=False, seed=320 + bk)
+        nqb = w.n_query_blocks
+        units = [(0, h, qb) for h in (0, 5) for qb in sorted({0, nqb // 2, nqb - 1})]
+        U.run_case(w, 0, units=units, n_sink=n_sink, n_window=n_window)
+    # a prefix shorter than k: the list ends early
+    w = synth.Workload("short", 1, 8, 2, d, k, k, k, bq, bk, "bf16", rho=0.9, page_size=page, integer=True, seed=330)
+    U.run_case(w, 0, units=[(0, 0, 0), (0, 7, 1), (0, 3, w.n_query_blocks - 1)], n_sink=n_sink, n_window=n_window)
