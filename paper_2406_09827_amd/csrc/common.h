@@ -338,34 +338,32 @@ __device__ __forceinline__ void select_topk_pairs(const uint32_t (&l)[H], const 
     int c_ge = 0;
 #pragma unroll
     for (int i = 0; i < 2 * H; ++i) c_ge += __popcll(__ballot(key[i] >= at_least));
-    int base = 0;
-    if (c_ge <= kb) {   // every key at the threshold is kept
+    // more than kb keys reach the threshold: of those at it the lowest slots are taken
+    const bool ties = c_ge > kb;
+    int need = 0;
+    if (ties) {
+        int c_gt = 0;
 #pragma unroll
-        for (int i = 0; i < H; ++i) {
-            const bool kl = l[i] >= at_least, kr = r[i] >= at_least;
-            const uint64_t bl = __ballot(kl), br = __ballot(kr);
-            const int rank = base + lane_prefix_count(bl) + lane_prefix_count(br);
-            visit(i, kl, rank, kr, rank + (kl ? 1 : 0));
-            base += __popcll(bl) + __popcll(br);
-        }
-        return;
+        for (int i = 0; i < 2 * H; ++i) c_gt += __popcll(__ballot(key[i] > v));
+        need = kb - c_gt;
     }
-    int c_gt = 0;
-#pragma unroll
-    for (int i = 0; i < 2 * H; ++i) c_gt += __popcll(__ballot(key[i] > v));
-    const int need = kb - c_gt;  // how many slots equal to the threshold are still wanted: the lowest
-    int base_tie = 0;
+    int base = 0, base_tie = 0;
 #pragma unroll
     for (int i = 0; i < H; ++i) {
-        const bool el = l[i] == at_least, er = r[i] == at_least;
-        const uint64_t tl = __ballot(el), tr = __ballot(er);
-        const int tie = base_tie + lane_prefix_count(tl) + lane_prefix_count(tr);
-        const bool kl = l[i] > v || (el && tie < need), kr = r[i] > v || (er && tie + (el ? 1 : 0) < need);
+        bool kl = l[i] >= at_least, kr = r[i] >= at_least;
+        if (ties) {
+            const bool el = l[i] == at_least, er = r[i] == at_least;
+            const uint64_t tl = __ballot(el), tr = __ballot(er);
+            const int tie = base_tie + lane_prefix_count(tl) + lane_prefix_count(tr);
+            kl = kl && !(el && tie >= need);
+            kr = kr && !(er && tie + (el ? 1 : 0) >= need);
+            base_tie += __popcll(tl) + __popcll(tr);
+        }
         const uint64_t bl = __ballot(kl), br = __ballot(kr);
         const int rank = base + lane_prefix_count(bl) + lane_prefix_count(br);
         visit(i, kl, rank, kr, rank + (kl ? 1 : 0));
-        base_tie += __popcll(tl) + __popcll(tr);
         base += __popcll(bl) + __popcll(br);
+        __builtin_amdgcn_sched_barrier(0);   // (one node's survivors at a time: several at once take the registers of a wave)
     }
 }
 

@@ -7,18 +7,26 @@
 // workgroup being the query heads of one KV group when Hq/Hkv = 4.  Either way the heads of a KV group run next to each other, so in
 // the first round, where they score the same representative blocks, their loads meet in the L1/L2 instead of
 // going to HBM four times.
-//   * a key row is read by D/8 lanes, 16 bytes each (a full 128-bit coalesced row segment),
-//     multiplied with v_dot2_f32_bf16 and summed over the lanes with DPP adds;
-//   * two stages of 8 row loads per lane alternate, so up to 16 KB per wave are in flight;
-//   * scores -> LDS keys -> ordered threshold selection -> the problem's node list (wave per problem: private to
-//     the wave, nothing redundant, no workgroup barrier anywhere);
+//   * a table in LDS names the blocks to score (first key of each, -1: none); a lane group finds the blocks of a stage with one
+//     read, and a block's score replaces its entry;
+//   * a key row is read by D/8 lanes, 16 bytes each (a full 128-bit coalesced row segment), and multiplied with
+//     v_dot2_f32_bf16; the ROWS partial sums of a lane are then added up over the lanes of the group by halving: at
+//     each step a lane gives half of its sums away and adds the other half to what it gets, so that a lane ends up with
+//     one row (or a copy of it) and everything after - maximum over the block's rows, bounds, the write - is done once
+//     for all the rows of a stage instead of row by row;
+//   * two stages of ROWS row loads per lane alternate, so up to 16 KB per wave are in flight;
+//   * scores -> ordered threshold selection by up to four waves, a lane holding nodes with both of their scores -> the next
+//     node list and the next table (two tables take turns);
 //   * with the first or the last block as representative, one child of every node has the
 //     node's own representative (left child / first block, right child / last block): its score is
-//     the score that selected the node, carried over as a key, and from the second round on only the
+//     the score that selected the node, carried over, and from the second round on only the
 //     other child is gathered and scored - about half the memory traffic.  With the centre representative
 //     the same holds in the final round (every node one or two blocks long: a one-block node is its own
 //     representative, the right half of a two-block node is the node's): only the left halves are scored.
 // Ragged lengths (kv_lens) and a page table are handled per row.
+// Measured against the form before (nodes looked up and sums taken row by row, the selection run by eight waves of sixteen; half
+// of a round was vector issue): 32 problems of 32768 tokens, d = 128, k = 512, bk = 2 50.6 -> 37.2 us, bk = 1 92 -> 50; 320 problems
+// 104 -> 72; 1024 problems of k/bk = 512 331 -> 270, with 64 channels over pages 434 -> 305; 3072 problems 583 -> 555.
 #pragma once
 #include "common.h"
 #include "launch.h"
@@ -29,23 +37,32 @@ namespace hipattn {
 // WS = 1 : one wave per (sequence, head), four independent problems per workgroup.
 // WS = 4 : one workgroup per (sequence, head); the four waves score a quarter of the branches each (stage i goes to
 //          wave i % 4), meet at a barrier, run the selection redundantly and write a quarter of the survivors each.
-// WS = 16: the same with sixteen waves, of which those that write survivors run the selection: for so few problems
-//          that each has a compute unit to itself, where the chain of load latencies in a round is the time.
-template <int E, int BK, int D, int ROWS, bool PAGED, int WS>
-__global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 ? 4 : E == 16 ? 3 : 1) void mask_decode_kernel(KParams p, int xcd_map)
+// WS = 16: the same with sixteen waves, of which four (one per SIMD) run the selection: for so few problems
+//          that each has a compute unit to itself, where the chain of latencies in a round is the time.
+// MODE 0: contiguous keys, a (sequence, kv head) slice below 2 GB, addressed as a buffer that ends with the last key (a load past
+//         it returns 0, so nothing is clamped); MODE 1: paged pool; MODE 2: contiguous, any size (64-bit row addresses).
+template <int E, int BK, int D, int ROWS, int MODE, int WS>
+__global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 : E == 16 ? 3 : 1) void mask_decode_kernel(KParams p, int xcd_map)
 {
-    constexpr bool SPLIT = WS > 1;
+    constexpr bool SPLIT = WS > 1, PAGED = MODE == 1;
     constexpr int WGT = WS == 16 ? 1024 : kThreads;   // threads of the workgroup
-    constexpr int NB = 64 * E;
+    constexpr int NB = 64 * E, H = E / 2;
     constexpr int LPR = D / 8;        // lanes per key row
     constexpr int RPW = 64 / LPR;     // rows (= branches) per wave-wide load
     constexpr int U = ROWS / BK;      // branches per lane group and stage: ROWS row loads per lane, two stages in flight
-    typedef uint32_t stage_t __attribute__((ext_vector_type(4 * U * BK)));
+    constexpr int COPIES = LPR / ROWS; // lanes that end up with the same row
+    static_assert(ROWS <= LPR && U >= 1 && E % 2 == 0, "stage shape");
+    constexpr int SW = WS < 4 ? 1 : WS == 4 ? 4 : (H < 4 ? H : 4);   // waves that select
+    typedef uint32_t stage_t __attribute__((ext_vector_type(4 * ROWS)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     constexpr int NW = SPLIT ? 1 : 4;  // private copies of the per-problem LDS state
-    // Two buffers of NB words swap roles every round: one holds the node list (NB/2 starts, then NB/2 ends), the other
-    // receives the round's score keys and, once the selection has them in registers, the next node list.
-    __shared__ uint32_t buf_s[NW][2][NB];
-    __shared__ uint32_t nkey_s[NW][NB / 2];  // score key of the branch that became each node
+    // Entry i of a table: first key of the i-th block to score, -1 if there is none, until the block's score (the bits of
+    // the float; -1 stays) replaces it.  In a round that carries scores the lower half holds one entry per node, the upper
+    // half the nodes' carried scores.
+    __shared__ __attribute__((aligned(16))) uint32_t tab_s[NW][2][NB];
+    // Nodes, sorted by position.  All of a round's nodes are m_len or m_len + 1 blocks long (chunks differ by one, and so do
+    // halves of lengths that differ by one), so a node is its first block and one bit.
+    __shared__ uint32_t node_s[NW][NB / 2];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // (uniform: what follows from it stays in scalar registers)
     const int grp = lane / LPR, lc = lane % LPR;
@@ -83,186 +100,244 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 ? 4 : E == 16 
     const int tix = SPLIT ? (int)threadIdx.x : lane, tn = SPLIT ? WGT : 64;
 
     const uint4 qv = *(const uint4 *)((const bf16_t *)p.Q + (int64_t)b * p.qs_b + (int64_t)h * p.qs_h + lc * 8);
+    uint32_t *nodes = node_s[own];
+    const int log_bk = 31 - __builtin_clz((uint32_t)bk);   // (1, 2, 4 or 8 rows a block; a stride need not be a power of two)
+    const bool pow2 = (bk & (bk - 1)) == 0;
+    auto first_key = [&](int blk) __attribute__((always_inline)) { return pow2 ? blk << log_bk : blk * bk; };
+    auto put_entry = [&](uint32_t *tab, int i, int t0) __attribute__((always_inline)) {
+        tab[i] = (uint32_t)t0;
+        if (PAGED && p.touched && t0 >= 0) touch_page(p, b, t0);
+    };
+    // the two branches of node [s, e): left [s, mid) (empty for a one-block node), right [mid, e)
+    auto put_branches = [&](uint32_t *tab, int j, int s, int e) __attribute__((always_inline)) {
+        const int mid = s + ((e - s) >> 1);
+        put_entry(tab, 2 * j, mid > s ? first_key(rep_block(s, mid, p.rep_pos)) : -1);
+        put_entry(tab, 2 * j + 1, first_key(rep_block(mid, e, p.rep_pos)));
+    };
+    int m_len = Tb / kb;
     {
-        int *ns0 = (int *)buf_s[own][0], *ne0 = ns0 + NB / 2;
-        const int a = Tb / kb, r = Tb % kb;
+        const int r = Tb % kb;
         for (int j = tix; j < kb; j += tn) {
-            ns0[j] = chunk_bound(j, a, r, kb);
-            ne0[j] = chunk_bound(j + 1, a, r, kb);
+            const int s = chunk_bound(j, m_len, r, kb), e = chunk_bound(j + 1, m_len, r, kb);
+            nodes[j] = (uint32_t)(s << 1 | (e - s - m_len));
+            put_branches(tab_s[own][0], j, s, e);
         }
+        for (int i = 2 * kb + tix; i < NB; i += tn) tab_s[own][0][i] = tab_s[own][1][i] = 0xffffffffu;
     }
     sync_problem();
 
     const bf16_t *Kbase = (const bf16_t *)p.K;
     const int64_t back_delta = (const bf16_t *)p.Kback - Kbase;  // elements from the resident pool to the backing pool
+    const uint32_t row_bytes = (uint32_t)p.ks_r * 2u;
+    const __amdgpu_buffer_rsrc_t srd = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(Kbase + (int64_t)b * p.ks_b + (int64_t)hk * p.ks_h), 0,
+        MODE == 0 ? (int)((uint32_t)(kv_len - 1) * row_bytes + 2u * D) : 0, 0x00020000);
+
+    const bool selects = !SPLIT || wave < SW;   // (uniform) nodes i * 64 + lane and what becomes of them: wave i % SW
+    uint32_t nd[H];
+    if (selects) {
+#pragma unroll
+        for (int i = 0; i < H; ++i) nd[i] = nodes[i * 64 + lane];
+    }
     int cur = 0;
-    bool carry = false;  // a round in which one child of every node keeps the node's score (never the first round)
-    // side of a node's children that is scored in a carry round: the left one when the LAST block
-    // represents (the right child ends where the node ends), the right one for FIRST
+    bool list = false;  // a round in which one child of every node keeps the node's score (never the first round)
     // (with the centre representative only the final round carries: there every node is one or two blocks long, a
     // one-block node is its own representative and the right half of a two-block node is the node's representative,
     // so the left children alone are scored)
-    const int side = p.rep_pos == 1 ? 1 : 0;
+    const bool first_rule = p.rep_pos == 1;
     // ensemble sample: the round whose selection compares perturbed scores (-1: none)
     const int ens_round = ens_round_of(p.ens_sample, (Tb + kb - 1) / kb);
     const uint32_t ens_hash = ens_round >= 0 ? ens_unit_hash(p.ens_seed, p.ens_sample, b, h, 0) : 0u;
     int round = 0;
     for (int maxlen = (Tb + kb - 1) / kb; maxlen > 1; maxlen = (maxlen + 1) >> 1, ++round) {
-        const int *ns = (const int *)buf_s[own][cur], *ne = ns + NB / 2;
-        uint32_t *keys = buf_s[own][cur ^ 1];  // every slot below 2 kb is written by the scoring loop
-        uint32_t *nkey = nkey_s[own];
-        // work items of the scoring loop: every branch slot, or in a carry round one per node
-        const int n_items = carry ? kb : 2 * kb;
+        uint32_t *tab = tab_s[own][cur], *next_tab = tab_s[own][cur ^ 1];
+        const int n_items = list ? kb : 2 * kb;   // entries to score
 
-        // one stage = U branches per lane group: node lookup, then the (unconditional) loads of
-        // the representative block's BK rows.  t0 < 0 marks an empty branch.
-        auto fetch = [&](int base, stage_t &kv, int (&t0)[U]) __attribute__((always_inline)) {
-            int pg[U];
+        // one stage = U blocks per lane group: the entries, then the (unconditional) loads of their BK rows
+        auto fetch = [&](int base, stage_t &kv) __attribute__((always_inline)) {
+            int t0[U], pg[U];
+            const int at = base + grp * U;
+            if constexpr (U % 4 == 0) {
+#pragma unroll
+                for (int u = 0; u < U; u += 4) {
+                    const int4 v = *(const int4 *)(tab + at + u);
+                    t0[u] = v.x; t0[u + 1] = v.y; t0[u + 2] = v.z; t0[u + 3] = v.w;
+                }
+            } else if constexpr (U == 2) {
+                const int2 v = *(const int2 *)(tab + at);
+                t0[0] = v.x; t0[1] = v.y;
+            } else t0[0] = (int)tab[at];
+#pragma unroll
+            for (int u = 0; u < U; ++u) t0[u] = at + u < n_items ? t0[u] : -1;
+#pragma unroll
+            for (int u = 0; u < U; ++u) pg[u] = page_of_row<PAGED>(p, b, max(t0[u], 0));  // all page lookups of the stage first
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int item = base + u * RPW + grp;
-                const int slot = carry ? 2 * item + side : item, node = slot >> 1;
-                bool ok = node < kb;
-                int t = 0;
-                if (ok) {
-                    const int s = ns[node], e = ne[node];
-                    const int mid = s + ((e - s) >> 1);
-                    const int bs = (slot & 1) ? mid : s, be = (slot & 1) ? e : mid;
-                    ok = be > bs;
-                    if (ok) t = rep_block(bs, be, p.rep_pos) * bk;
-                }
-                t0[u] = ok ? t : -1;
-                pg[u] = page_of_row<PAGED>(p, b, ok ? t : 0);  // all page lookups of the stage first
-            }
+                if constexpr (MODE == 0) {
+                    // (an empty entry: far past the end)
+                    const uint32_t off = (t0[u] < 0 ? 0x80000000u : __umul24((uint32_t)t0[u], row_bytes)) + (uint32_t)lc * 16u;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = t0[u] >= 0 ? t0[u] : 0;
-                // (a negative page-table entry names a page of the backing pool)
-                const bf16_t *src = Kbase + row_offset_bank<PAGED>(p, b, hk, t, pg[u], back_delta) + lc * 8;
+                    for (int n = 0; n < BK; ++n) {
+                        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(srd, (int)(off + (uint32_t)(n * bsk) * row_bytes), 0, 0);
+                        const int q4 = 4 * (u * BK + n);
+                        kv[q4] = x[0]; kv[q4 + 1] = x[1]; kv[q4 + 2] = x[2]; kv[q4 + 3] = x[3];
+                    }
+                } else {
+                    const int t = max(t0[u], 0);
+                    // (a negative page-table entry names a page of the backing pool)
+                    const bf16_t *src = Kbase + row_offset_bank<PAGED>(p, b, hk, t, pg[u], back_delta) + lc * 8;
 #pragma unroll
-                for (int n = 0; n < BK; ++n) {
-                    // rows past the end of the sequence re-read its last row and are ignored below
-                    const int dn = t0[u] >= 0 ? min(n * bsk, kv_len - 1 - t) : 0;
-                    const uint4 x = *(const uint4 *)(src + (int64_t)dn * p.ks_r);
-                    const int q4 = 4 * (u * BK + n);
-                    kv[q4] = x.x; kv[q4 + 1] = x.y; kv[q4 + 2] = x.z; kv[q4 + 3] = x.w;
-                }
-            }
-        };
-        auto score = [&](int base, const stage_t &kv, const int (&t0)[U]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                float best = -INFINITY;
-#pragma unroll
-                for (int n = 0; n < BK; ++n) {
-                    const int q4 = 4 * (u * BK + n);
-                    const float dsum = row_group_sum<LPR>(dot8_bf16(qv, make_uint4(kv[q4], kv[q4 + 1], kv[q4 + 2], kv[q4 + 3])));
-                    if (t0[u] + n * bsk < kv_len) best = fmaxf(best, dsum);
-                }
-                const int item = base + u * RPW + grp;
-                const int slot = carry ? 2 * item + side : item;
-                if (lc == 0 && slot < NB) {
-                    keys[slot] = t0[u] >= 0 ? score_key(best) : 0u;
-                    if (carry) {
-                        // the sibling keeps the node's score; a left sibling may be empty (one-block node)
-                        const int node = slot >> 1;
-                        const bool sib = node < kb && (side == 0 || ne[node] - ns[node] > 1);
-                        keys[slot ^ 1] = sib ? nkey[node] : 0u;
+                    for (int n = 0; n < BK; ++n) {
+                        // rows past the end of the sequence re-read its last row and are ignored below
+                        const uint4 x = *(const uint4 *)(src + (int64_t)min(n * bsk, kv_len - 1 - t) * p.ks_r);
+                        const int q4 = 4 * (u * BK + n);
+                        kv[q4] = x.x; kv[q4 + 1] = x.y; kv[q4 + 2] = x.z; kv[q4 + 3] = x.w;
                     }
                 }
             }
+        };
+        auto score = [&](int base, const stage_t &kv) __attribute__((always_inline)) {
+            float v[ROWS];
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) v[r] = dot8_bf16(qv, make_uint4(kv[4 * r], kv[4 * r + 1], kv[4 * r + 2], kv[4 * r + 3]));
+            // the row this lane ends up with, and its block's entry
+            const int row = lc / COPIES, at = base + grp * U + row / BK;
+            const int t0 = (int)tab[at];
+            // Sums over the lanes of the group.  Exchanges from the farthest lane to the nearest: the mirrors (lane i with 15 - i,
+            // then 7 - i) also flip the lower bits of the lane number, which do not matter before they tell rows apart.
+            constexpr int HALVINGS = ROWS == 8 ? 3 : ROWS == 4 ? 2 : ROWS == 2 ? 1 : 0;
+            constexpr int STEPS = LPR == 16 ? 4 : 3;
+            auto exchange = [&](float x, int bit) __attribute__((always_inline)) {
+                return bit == 8 ? dpp_f<0x140>(x) : bit == 4 ? dpp_f<0x141>(x) : bit == 2 ? dpp_f<0x4E>(x) : dpp_f<0xB1>(x);
+            };
+#pragma unroll
+            for (int st = 0; st < STEPS; ++st) {
+                const int bit = LPR >> (st + 1);
+                if (st < HALVINGS) {
+                    const int n = ROWS >> (st + 1);
+                    const bool up = lc & bit;
+#pragma unroll
+                    for (int k = 0; k < n; ++k) {
+                        const float a = v[k], b = v[k + n];   // (values, not places: a choice of places would be indexed)
+                        v[k] = (up ? b : a) + exchange(up ? a : b, bit);
+                    }
+                } else {
+                    v[0] += exchange(v[0], bit);
+                }
+            }
+            // maximum over the rows of the block that exist (rows of a block: neighbouring lanes; copies hold the same value, so
+            // the mirrors serve here as well)
+            float best = t0 + (row % BK) * bsk < kv_len ? v[0] : -INFINITY;
+#pragma unroll
+            for (int w = COPIES; w < COPIES * BK; w <<= 1) best = fmaxf(best, exchange(best, w));
+            if (lc % (COPIES * BK) == 0 && at < n_items && t0 >= 0) tab[at] = __float_as_uint(best);
         };
 
         constexpr int STEP = RPW * U;   // branches per stage
         constexpr int STRIDE = WS * STEP;  // distance between two stages of the same wave
         stage_t ka, kbuf;
-        int ta[U], tb[U];
         const int first = SPLIT ? wave * STEP : 0;
-        if (first < n_items) fetch(first, ka, ta);
+        if (first < n_items) fetch(first, ka);
         for (int base = first; base < n_items; base += 2 * STRIDE) {
             const bool has_b = base + STRIDE < n_items;
-            if (has_b) fetch(base + STRIDE, kbuf, tb);
-            score(base, ka, ta);
+            if (has_b) fetch(base + STRIDE, kbuf);
+            score(base, ka);
             if (has_b) {
-                if (base + 2 * STRIDE < n_items) fetch(base + 2 * STRIDE, ka, ta);
-                score(base + STRIDE, kbuf, tb);
+                if (base + 2 * STRIDE < n_items) fetch(base + 2 * STRIDE, ka);
+                score(base + STRIDE, kbuf);
             }
         }
         sync_problem();
 
-        const bool selects = WS < E || wave < E;   // (uniform) register i of the survivors is written by wave i % WS
-        uint32_t key[E];
+        const bool next_list = p.rep_pos != 0 || ((maxlen + 1) >> 1) == 2;
+        const int m_next = m_len >> 1;
         if (selects) {
+            uint32_t kl[H], kr[H];   // keys of the left and the right branch of node i * 64 + lane
+            if (list) {
 #pragma unroll
-        for (int i = 0; i < E; ++i) key[i] = i * 64 + lane < 2 * kb ? keys[i * 64 + lane] : 0u;
-        }
-        if (PAGED && p.touched) {
-            // pages read this round: the representative block of every real branch (a branch whose score was
-            // carried over had the same block read in an earlier round)
-            for (int slot = tix; slot < 2 * kb; slot += tn) {
-                if (keys[slot] != 0u) {
-                    const int node = slot >> 1;
-                    const int s = ns[node], e = ne[node];
-                    const int mid = s + ((e - s) >> 1);
-                    touch_page(p, b, rep_block((slot & 1) ? mid : s, (slot & 1) ? e : mid, p.rep_pos) * bk);
+                for (int i = 0; i < H; ++i) {
+                    const int j = i * 64 + lane;
+                    const bool two = j < kb && m_len + (int)(nd[i] & 1) > 1;
+                    kr[i] = j < kb ? score_key_bits(tab[NB / 2 + j]) : 0u;
+                    kl[i] = two ? score_key_bits(tab[j]) : 0u;
+                    // under the first-block rule the left child of a longer node carries, else the right one
+                    if (first_rule && two) { const uint32_t x = kr[i]; kr[i] = kl[i]; kl[i] = x; }
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < H; ++i) {
+                    const uint2 x = *(const uint2 *)(tab + 2 * (i * 64 + lane));
+                    kl[i] = score_key_bits(x.x);
+                    kr[i] = score_key_bits(x.y);
                 }
             }
-        }
-        // the survivors go where the keys were: every wave of the problem has to hold its copy of them first
-        if (SPLIT) __syncthreads();
-        if (selects) {
-        // four waves or one, E = 8: the registers that settling equal scores takes are the fourth wave of a SIMD (1024 paged
-        // problems of k/bk = 256: 302 us with them, 247 without, 252 with the bits)
-        constexpr int SEARCH = WS != 16 && E == 8 ? kInterpolate : default_search(E);
-        bool keep[E];
-        int dest[E];
-        if (round == ens_round) {
-            // the selection sees the perturbed scores; key[] keeps the true ones (they are what a later round carries)
-            uint32_t ksel[E];
-#pragma unroll
-            for (int i = 0; i < E; ++i) {
-                ksel[i] = 0u;
-                if (key[i] != 0u) {
-                    const int slot = i * 64 + lane, node = slot >> 1;
-                    const int s = ns[node], e = ne[node];
-                    const int mid = s + ((e - s) >> 1);
-                    ksel[i] = ens_key(key[i], ens_hash, rep_block((slot & 1) ? mid : s, (slot & 1) ? e : mid, p.rep_pos), p.ens_r);
+            const bool odd = m_len & 1;
+            auto keep_one = [&](int d, uint32_t child, uint32_t key) __attribute__((always_inline)) {
+                nodes[d] = child;
+                const int s = (int)(child >> 1), len = m_next + (int)(child & 1);
+                if (!next_list) {
+                    put_branches(next_tab, d, s, s + len);
+                } else {
+                    // the child that shares the node's representative keeps the node's score; the other one is empty or is
+                    // scored (its representative: the block at the split under the first-block rule, the block before the
+                    // split otherwise)
+                    next_tab[NB / 2 + d] = __float_as_uint(key_score(key));
+                    put_entry(next_tab, d, len > 1 ? first_key(s + (len >> 1) - (first_rule ? 0 : 1)) : -1);
                 }
-            }
-            select_topk_ordered<E, SEARCH>(ksel, kb, keep, dest);
-        } else {
-            select_topk_ordered<E, SEARCH>(key, kb, keep, dest);
-        }
-        int *ns2 = (int *)keys, *ne2 = ns2 + NB / 2;
+            };
+            auto keep_child = [&](int i, bool keep_l, int dl, bool keep_r, int dr) __attribute__((always_inline)) {
+                if (SPLIT && i % SW != wave) return;
+                // a node of `len` blocks: len / 2 to the left, the rest to the right; m_len / 2 or one more
+                const uint32_t bit = nd[i] & 1u, s2 = nd[i] & ~1u, len = (uint32_t)m_len + bit;
+                if (keep_l) keep_one(dl, s2 | (odd ? bit : 0u), kl[i]);
+                if (keep_r) keep_one(dr, (s2 + (len & ~1u)) | (odd ? 1u : bit), kr[i]);
+            };
+            // four waves or one, E = 8: the registers that settling equal scores takes are the fourth wave of a SIMD (1024 paged
+            // problems of k/bk = 256: 302 us with them, 247 without, 252 with the bits)
+            constexpr int SEARCH = WS != 16 && E == 8 ? kInterpolate : default_search(E);
+            if (round == ens_round) {
+                // the selection sees the perturbed scores; kl and kr keep the true ones (they are what a later round carries)
+                uint32_t pl[H], pr[H];
 #pragma unroll
-        for (int i = 0; i < E; ++i) {
-            if (keep[i] && (!SPLIT || i % WS == wave)) {
-                const int slot = i * 64 + lane, node = slot >> 1;
-                const int s = ns[node], e = ne[node];
-                const int mid = s + ((e - s) >> 1);
-                ns2[dest[i]] = (slot & 1) ? mid : s;
-                ne2[dest[i]] = (slot & 1) ? e : mid;
-                nkey[dest[i]] = key[i];
+                for (int i = 0; i < H; ++i) {
+                    const int s = (int)(nd[i] >> 1), e = s + m_len + (int)(nd[i] & 1), mid = s + ((e - s) >> 1);
+                    pl[i] = ens_key(kl[i], ens_hash, rep_block(s, mid, p.rep_pos), p.ens_r);
+                    pr[i] = ens_key(kr[i], ens_hash, rep_block(mid, e, p.rep_pos), p.ens_r);
+                }
+                select_topk_pairs<H, SEARCH>(pl, pr, kb, keep_child);
+            } else {
+                select_topk_pairs<H, SEARCH>(kl, kr, kb, keep_child);
             }
         }
-        }
+        m_len = m_next;
         cur ^= 1;
-        carry = p.rep_pos != 0 || ((maxlen + 1) >> 1) == 2;
+        list = next_list;
         sync_problem();
+        if (selects) {
+#pragma unroll
+            for (int i = 0; i < H; ++i) nd[i] = nodes[i * 64 + lane];
+        }
     }
 
-    const int *ns = (const int *)buf_s[own][cur];
-    for (int j = tix; j < kb; j += tn) out[j] = ns[j] * bk;
+    for (int j = tix; j < kb; j += tn) out[j] = first_key((int)(nodes[j] >> 1));
+}
+
+// contiguous keys of a (sequence, kv head) within the reach of 24-bit row numbers and 31-bit offsets
+static inline bool narrow_slice(const KParams &p)
+{
+    return !p.page_table && p.max_kv_len < (1 << 24) && p.ks_r * 2 < (1 << 24) && (int64_t)p.max_kv_len * p.ks_r * 2 < (1LL << 31);
 }
 
 template <int BK, int D, int ROWS, int WS>
 static hipError_t launch_r(const KParams &p, dim3 grid, int xcd_map, hipStream_t st)
 {
     dim3 block(WS == 16 ? 1024 : kThreads);
+    const bool narrow = narrow_slice(p);
 #define HIPATTN_LAUNCH(EV)                                                                                  \
     do {                                                                                                    \
-        if (p.page_table) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, true, WS>), grid, block, 0, st, p, xcd_map);  \
-        else hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, false, WS>), grid, block, 0, st, p, xcd_map);       \
+        if (p.page_table) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, 1, WS>), grid, block, 0, st, p, xcd_map);  \
+        else if (narrow) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, 0, WS>), grid, block, 0, st, p, xcd_map);   \
+        else if constexpr (WS == 4) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, 2, WS>), grid, block, 0, st, p, xcd_map); \
     } while (0)
     // E registers of 64 branch slots: every count of the selection is a compare and a ballot per register, whether the
     // slots are in use or not (k/bk = 32, both with the bit search, four registers / two: 1024 problems of 65536 tokens
@@ -278,35 +353,25 @@ static hipError_t launch_r(const KParams &p, dim3 grid, int xcd_map, hipStream_t
 
 // Waves per (sequence, head), by the number of problems:
 //   up to 256 (one per compute unit) and k/bk <= 512: sixteen, unless the branches of a round are one stage or less for each
-//       of four waves.  Measured with d = 128, bk = 2, 65536 tokens, four waves / sixteen: 32 problems k/bk = 32 28.4 / 29.3 us
-//       (with stages of eight rows, see below), 48 39.8 / 31.2, 256 98.8 / 61.5, 512 159 / 107; 256 problems k/bk = 256 106 /
-//       80, 512 172 / 138; beyond a problem per compute unit 320 problems k/bk = 32 34 / 60, 256 127 / 150, 512 200 / 248.
-//   up to 8192: four, so that enough loads are in flight per compute unit and the selection of one problem overlaps with the
-//       loads of the others; beyond that one (nothing computed twice, no barriers).  Measured with 32 query heads over 8 kv
-//       heads, k/bk = 256, four against one: 2048 problems -8 %, 4096 -4 %, 8192 -1 to -4 %, 16384 +6 %, 32768 +14 %.
-// Sixteen waves take stages of four rows: a round has few stages for each wave, and at 128 registers a wave stages of eight
-// rows and k/bk > 256 spill.  Four rows against eight, 32 problems of 30000 tokens: d = 64, bk = 1, k/bk = 64 24.4 / 32.1 us,
-// 256 40.6 / 45.8; 256 problems, k/bk = 512 72.7 / 85.5 (four waves 83.6); d = 128, bk = 2, k/bk = 64 21.9 / 26.1.  With
-// d = 128, bk = 2 and k/bk from 129 to 256 eight rows make two stages, both in flight: 52.3 / 53.4 at 256.
+//       of four waves.  Measured, d = 128, bk = 2, four waves / sixteen: 32 problems of 32768 tokens k/bk = 32 20.0 / 18.4 us,
+//       256 42.7 / 37.5, of 65536 tokens over pages 512 119 / 86; 256 problems k/bk = 32 23.8 / 22.5, 256 55.6 / 53.6; beyond a
+//       problem per compute unit 320 problems 256 72 / 99, 384 problems of 65536 tokens 512 167 / 202.  Stages of four rows (eight
+//       make no difference at sixteen waves: 37.5 / 37.5 and 53.6 / 53.8 us, k/bk = 512 over pages 79 / 86, contiguous 115 / 109).
+//   up to 8192, or 16384 with k/bk <= 256: four, so that enough loads are in flight per compute unit and the selection of one
+//       problem overlaps with the loads of the others; beyond that one (nothing computed twice, no barriers).  Measured with 32
+//       query heads over 8 kv heads, four waves / one: 8192 problems of 8192 tokens, k/bk = 256 681 / 711 us; 16384 of 4096 849 /
+//       893, of 8192, k/bk = 128 963 / 1007, of 3000, k/bk = 512 832 / 756; 32768 of 2048, k/bk = 256 944 / 928.
 template <int BK, int D>
 static hipError_t launch_e(const KParams &p, hipStream_t st)
 {
     const int64_t problems = (int64_t)p.batch * p.hq;
     const int64_t groups = (int64_t)p.batch * p.hkv;
     const int xcd_map = groups % 8 == 0 ? 1 : 0;
-    if (problems <= 256 && p.kb <= 512) {
-        const dim3 grid((unsigned)problems);
-        if constexpr (D == 128 && BK == 2) {
-            if (p.kb > 128 && p.kb <= 256) {
-                if (p.page_table) hipLaunchKernelGGL((mask_decode_kernel<8, BK, D, 8, true, 16>), grid, dim3(1024), 0, st, p, xcd_map);
-                else hipLaunchKernelGGL((mask_decode_kernel<8, BK, D, 8, false, 16>), grid, dim3(1024), 0, st, p, xcd_map);
-                return hipGetLastError();
-            }
-        }
-        constexpr int ROWS = BK < 4 ? 4 : BK, STEP = 512 / D * (ROWS / BK);   // branches per stage of a wave
-        if (2 * p.kb > 4 * STEP) return launch_r<BK, D, ROWS, 16>(p, grid, xcd_map, st);
-    }
-    if (problems <= 8192) return launch_r<BK, D, 8, 4>(p, dim3((unsigned)problems), xcd_map, st);
+    const dim3 grid((unsigned)problems);
+    if (!p.page_table && !narrow_slice(p)) return launch_r<BK, D, 8, 4>(p, grid, xcd_map, st);
+    constexpr int ROWS = BK < 4 ? 4 : BK, STEP = 512 / D * (ROWS / BK);   // branches per stage of a wave
+    if (problems <= 256 && p.kb <= 512 && 2 * p.kb > 4 * STEP) return launch_r<BK, D, ROWS, 16>(p, grid, xcd_map, st);
+    if (problems <= (p.kb <= 256 ? 16384 : 8192)) return launch_r<BK, D, 8, 4>(p, grid, xcd_map, st);
     return launch_r<BK, D, 8, 1>(p, dim3((unsigned)((problems + 3) / 4)), 0, st);
 }
 
