@@ -1,36 +1,28 @@
 // Block-sparse attention over the selected key blocks for any shape (paper Eq. 2-3): fp32, and the bf16 shapes the
-// tuned kernels (attn_mfma*.hip, attn_decode.hip) leave out.  Arithmetic in fp32 throughout: scores, exponentials,
-// probabilities and their products with the values; bf16 rows are widened.
+// tuned kernels (attn_mfma.hip, attn_decode.hip) leave out.  Scores, exponentials, probabilities and their products with the
+// values are fp32 throughout: fp32 factors enter the matrix cores as three bf16 planes (mfma_generic.h), bf16 ones as they are.
 //
 // One workgroup (4 waves) per (sequence, query head, query block, 16 or 32 query rows); the waves take every fourth
 // tile of 16 gathered keys, each with its own online softmax, and their states are merged through LDS at the end.
-// Both products run on the matrix cores (fp32: v_mfma_f32_16x16x4_f32, the busiest unit: 58 % of the clocks by counter at 4096 tokens):
-//   * S^T = K Q^T: A = key rows (lane l: row l % 16, 16-byte chunk l / 16 of each 64 bytes), B = the query rows, which
-//     stay in registers.  A lane then holds 4 consecutive keys of one query, so the softmax runs along lanes l ^ 16 and
-//     l ^ 32 only and register r of the result IS the B operand (key 4 (l / 16) + r) of step r of the next product;
-//   * O^T += V^T P^T: the A operand of step r takes from key 4 (l / 16) + r four consecutive channels per lane, i.e. a
-//     plain coalesced row load; nothing of K or V passes through LDS.
-// The values of a tile are loaded before its scores are multiplied and the next tile's keys before its values are, so a
-// load has a few thousand matrix clocks to arrive.  The selected blocks' positions and row offsets (page table included)
-// are worked out once per workgroup, in LDS.
-// Measured, fp32, 32 query heads over 8 kv heads, T = 4096, k = 512, bq = 32, bk = 2, d = 128: 6.02 ms with
-// one key per lane and a serial loop over the values before, 0.345 ms now = 100 TFLOP/s of the 152 a large fp32 matrix
-// product reaches; T = 1024, one head, k = 128, bq = 16, d = 64: 109 -> 7.4 us (64 workgroups: latency; 8.5 us
-// each with a pause between launches).
+//   * S^T = K Q^T: A = key rows (lane l: row l % 16, 16-byte chunk l / 16 of each 64 bytes), B = the query rows (bf16: in
+//     registers; fp32: planes in LDS, which their registers would take).  A lane then holds 4 consecutive keys of one query, so the
+//     softmax runs along lanes l ^ 16 and l ^ 32 only;
+//   * O^T += V^T P^T over the 16 keys of a tile: register r of S^T is key 4 (l / 16) + r, and a lane loads four consecutive channels
+//     of its four keys, a plain coalesced row load; nothing of K or V passes through LDS.  A 16x16x32 step takes a lane's four
+//     keys twice, in two planes each: three steps make the six products (bf16 values: two steps for the three).
+// The values of a tile are loaded before its scores are multiplied and the next tile's keys before its values are.  The selected
+// blocks' positions and row offsets (page table included) are worked out once per workgroup, in LDS.
+// What bounds it: the vector units and the address unit (keys as operands are 64 cache accesses an instruction), 65 and 80 % of the
+// clocks, the matrix pipe 31 % (4096 tokens, by counter).  Loading keys coalesced and through LDS is slower (281 us at 4096 tokens, 254 so).
+// Measured, fp32, 32 query heads over 8 kv heads, T = 4096, k = 512, bq = 32, bk = 2, d = 128: 342 us with
+// v_mfma_f32_16x16x4_f32, 254 us with planes; T = 1024, one head, k = 128, bq = 16, d = 64: 10.8 -> 10.8 us (64 workgroups: latency);
+// bf16, 8 heads, 64-row blocks, k = 512: 65 -> 43 us.  Error against 64 bits (T = 4096): 3.3e-7 -> 1.7e-7 in norm.
 #pragma once
 #include "mfma_generic.h"
 #include "launch.h"
 
 namespace hipattn {
 
-// four consecutive channels of a value row, widened
-__device__ __forceinline__ float4 load4(const float *p) { return *(const float4 *)p; }
-__device__ __forceinline__ float4 load4(const bf16_t *p)
-{
-    const uint2 u = *(const uint2 *)p;
-    return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
-                       __uint_as_float(u.y & 0xffff0000u));
-}
 __device__ __forceinline__ void store4(float *p, float4 v) { *(float4 *)p = v; }
 __device__ __forceinline__ void store4(bf16_t *p, float4 v)
 {
@@ -47,14 +39,6 @@ __device__ __forceinline__ float exp_neg(float x)
     const float v = __builtin_amdgcn_exp2f(y);
     return fmaf(v, e * 0.693147181f, v);
 }
-// (by bits that the compiler knows nothing of: it may assume that no float is a NaN)
-__device__ __forceinline__ bool not_finite(float x)
-{
-    uint32_t u = __float_as_uint(x);
-    asm volatile("" : "+v"(u));
-    return (u & 0x7f800000u) == 0x7f800000u;
-}
-
 constexpr int kGenMaxKb = 1024;
 
 // One query row by one wave, one key per lane and its value by all lanes: reads of K and V, and multiplies into the row,
@@ -125,9 +109,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 {
     constexpr int CS = D * (int)sizeof(T) / 64;  // 64-byte steps of a row in S^T = K Q^T
     constexpr int CQ = D / 64;                   // 64-channel groups of O^T
+    constexpr bool F32 = sizeof(T) == 4;
+    constexpr int VW = F32 ? 4 : 2;              // words of four channels of a value row
     constexpr int PITCH = D + 4;                 // floats per row of a merged state
-    // block list while the tiles are walked, then the four waves' states
-    constexpr int kLds = (kGenMaxKb * 12 > 4 * MT * 16 * PITCH * 4) ? kGenMaxKb * 12 : 4 * MT * 16 * PITCH * 4;
+    // block list and query planes while the tiles are walked, then the four waves' states
+    constexpr int kWalk = kGenMaxKb * 12 + (F32 ? MT * (D / 32) * 3 * 1024 : 0), kMerge = 4 * MT * 16 * PITCH * 4;
+    constexpr int kLds = kWalk > kMerge ? kWalk : kMerge;
     __shared__ __attribute__((aligned(16))) char lds[kLds];
     __shared__ float ml_s[4][2][MT * 16];
     __shared__ int n_blk_s;                      // list entries up to the last block; kCut: a block goes on in another page
@@ -168,14 +155,26 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         blk_off[j] = off | (miss ? 1 : 0);
     }
 
-    uint4 qf[MT][CS];
+    // query rows as B operands: bf16 in registers, fp32 as planes in LDS, behind the block list (wave w splits every fourth)
+    uint4 qf[F32 ? 1 : MT][F32 ? 1 : CS];
+    uint4 *qp = (uint4 *)(lds + kGenMaxKb * 12) + lane;   // [mt][step][plane][lane]
     {
         const T *Qb = (const T *)p.Q + (int64_t)b * p.qs_b + (int64_t)h * p.qs_h + (int64_t)row0 * p.qs_r;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const char *src = (const char *)(Qb + (int64_t)min(mt * 16 + r16, n_rows - 1) * p.qs_r) + lg * 16;
+            if constexpr (F32) {
 #pragma unroll
-            for (int cs = 0; cs < CS; ++cs) qf[mt][cs] = *(const uint4 *)(src + cs * 64);
+                for (int cs = 0; cs < CS; cs += 2) {
+                    if (((mt * CS + cs) >> 1 & 3) != wave) continue;
+                    const Planes8 x = split_planes8(*(const uint4 *)(src + cs * 64), *(const uint4 *)(src + cs * 64 + 64));
+                    uint4 *to = qp + (mt * CS + cs) / 2 * 192;
+                    to[0] = x.h; to[64] = x.m; to[128] = x.l;
+                }
+            } else {
+#pragma unroll
+                for (int cs = 0; cs < CS; ++cs) qf[mt][cs] = *(const uint4 *)(src + cs * 64);
+            }
         }
     }
     __syncthreads();
@@ -194,7 +193,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     const int w0_last = max(vis_last - p.n_window, 0);
 
     typedef uint32_t keys_t __attribute__((ext_vector_type(4 * CS)));
-    typedef float vals_t __attribute__((ext_vector_type(16 * CQ)));
+    typedef uint32_t vals_t __attribute__((ext_vector_type(4 * VW * CQ)));
     auto load_keys = [&](int64_t off) __attribute__((always_inline)) {
         const char *src = (const char *)(Kbase + off + (-(off & 1) & k_back)) + lg * 16;
         keys_t kf;
@@ -236,19 +235,44 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                 const T *src = Vbase + off + (-(off & 1) & v_back) + r16 * 4;
 #pragma unroll
                 for (int cq = 0; cq < CQ; ++cq) {
-                    const float4 x = load4(src + cq * 64);
-                    const int at = 4 * (r * CQ + cq);
-                    vf[at] = x.x; vf[at + 1] = x.y; vf[at + 2] = x.z; vf[at + 3] = x.w;
+                    const int at = VW * (r * CQ + cq);
+                    if constexpr (F32) {
+                        const uint4 x = *(const uint4 *)(src + cq * 64);
+                        vf[at] = x.x; vf[at + 1] = x.y; vf[at + 2] = x.z; vf[at + 3] = x.w;
+                    } else {
+                        const uint2 x = *(const uint2 *)(src + cq * 64);
+                        vf[at] = x.x; vf[at + 1] = x.y;
+                    }
                 }
             }
             __builtin_amdgcn_sched_barrier(0);  // (the loads go out before the multiplies)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) s[mt] = gen_f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (F32) {
+                gen_f32x4 low[MT];
 #pragma unroll
-            for (int cs = 0; cs < CS; ++cs)
+                for (int mt = 0; mt < MT; ++mt) low[mt] = gen_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    s[mt] = mfma_chunk<T>(make_uint4(kf[4 * cs], kf[4 * cs + 1], kf[4 * cs + 2], kf[4 * cs + 3]), qf[mt][cs], s[mt]);
+                for (int cs = 0; cs < CS; cs += 2) {
+                    const Planes8 kp = split_planes8(make_uint4(kf[4 * cs], kf[4 * cs + 1], kf[4 * cs + 2], kf[4 * cs + 3]),
+                                                     make_uint4(kf[4 * cs + 4], kf[4 * cs + 5], kf[4 * cs + 6], kf[4 * cs + 7]));
+                    Planes8 q[MT];
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        const uint4 *from = qp + (mt * CS + cs) / 2 * 192;
+                        q[mt] = Planes8{from[0], from[64], from[128]};
+                    }
+                    mfma_planes<true>(kp, q, s, low);
+                }
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) s[mt] += low[mt];
+            } else {
+#pragma unroll
+                for (int cs = 0; cs < CS; ++cs)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        s[mt] = mfma_chunk<T>(make_uint4(kf[4 * cs], kf[4 * cs + 1], kf[4 * cs + 2], kf[4 * cs + 3]), qf[mt][cs], s[mt]);
+            }
             // (unconditional, the last tile again at the end: a load on one path only would make the waits below wait for all)
             key_of(min(tile + 4, to - 1), t_cur, off_cur);
             kf = load_keys(off_cur);
@@ -266,7 +290,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                 mx = fmaxf(__uint_as_float(s16[0]), __uint_as_float(s16[1]));
                 auto s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
                 mx = fmaxf(__uint_as_float(s32[0]), __uint_as_float(s32[1]));
-                const float m_new = fmaxf(m_run[mt], mx), m_safe = m_new == -INFINITY ? 0.f : m_new;
+                // the reference moves when a logit passes it by 8 or more: probabilities then reach e^8, which costs no bits,
+                // and the sums are multiplied on the first tile only as a rule
+                const float m_new = mx > m_run[mt] + 8.f ? mx : m_run[mt], m_safe = m_new == -INFINITY ? 0.f : m_new;
                 const float alpha = exp_neg(m_run[mt] - m_safe);  // 0 on the first tile that counts
                 float sum = 0.f;
 #pragma unroll
@@ -284,15 +310,43 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                         for (int e = 0; e < 4; ++e) acc[mt][cq][e] *= alpha;
                 }
             }
+            // a 16x16x32 step takes a lane's four keys twice, in two planes each
+            Planes p01[MT], p23[MT];
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
+            for (int mt = 0; mt < MT; ++mt) {
+                p01[mt] = split_planes(s[mt][0], s[mt][1]);
+                p23[mt] = split_planes(s[mt][2], s[mt][3]);
+            }
 #pragma unroll
-                for (int cq = 0; cq < CQ; ++cq)
+            for (int cq = 0; cq < CQ; ++cq)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (F32) {
+                        const auto v = [&](int r) __attribute__((always_inline)) { return __uint_as_float(vf[4 * (r * CQ + cq) + e]); };
+                        const Planes a = split_planes(v(0), v(1)), b2 = split_planes(v(2), v(3));
+                        const uint4 hm = make_uint4(a.h, b2.h, a.m, b2.m), hl = make_uint4(a.h, b2.h, a.l, b2.l);
 #pragma unroll
                         for (int mt = 0; mt < MT; ++mt)
-                            acc[mt][cq][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[4 * (r * CQ + cq) + e], s[mt][r], acc[mt][cq][e], 0, 0, 0);
+                            acc[mt][cq][e] = mfma_chunk<bf16_t>(hl, make_uint4(p01[mt].l, p23[mt].l, p01[mt].h, p23[mt].h), acc[mt][cq][e]);
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt)
+                            acc[mt][cq][e] = mfma_chunk<bf16_t>(hm, make_uint4(p01[mt].m, p23[mt].m, p01[mt].m, p23[mt].m), acc[mt][cq][e]);
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt)
+                            acc[mt][cq][e] = mfma_chunk<bf16_t>(hm, make_uint4(p01[mt].h, p23[mt].h, p01[mt].h, p23[mt].h), acc[mt][cq][e]);
+                    } else {
+                        const auto v = [&](int r) __attribute__((always_inline)) { return vf[2 * (r * CQ + cq) + (e >> 1)]; };
+                        const uint32_t half = e & 1 ? 0x07060302u : 0x05040100u;
+                        const uint32_t a = __builtin_amdgcn_perm(v(1), v(0), half), b2 = __builtin_amdgcn_perm(v(3), v(2), half);
+                        const uint4 vv = make_uint4(a, b2, a, b2);
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt)
+                            acc[mt][cq][e] = mfma_chunk<bf16_t>(make_uint4(a, b2, 0u, 0u), make_uint4(p01[mt].l, p23[mt].l, 0u, 0u), acc[mt][cq][e]);
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt)
+                            acc[mt][cq][e] = mfma_chunk<bf16_t>(vv, make_uint4(p01[mt].m, p23[mt].m, p01[mt].h, p23[mt].h), acc[mt][cq][e]);
+                    }
+                }
         }
     };
     if (vis_last > 0) {
@@ -335,7 +389,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     }
     __syncthreads();
     T *Ob = (T *)p.O + (int64_t)b * p.os_b + (int64_t)h * p.os_h + (int64_t)row0 * p.os_r;
-    bool odd = false;  // a result of this lane is not finite
+    bool odd = false;  // a result of this lane is not finite, or so small that its values' planes may have left the range
     for (int i = tid; i < n_rows * (D / 4); i += kThreads) {
         const int row = i / (D / 4), c4 = (i % (D / 4)) * 4;
         float m = -INFINITY;
@@ -352,7 +406,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             sum.x = fmaf(x.x, a, sum.x); sum.y = fmaf(x.y, a, sum.y); sum.z = fmaf(x.z, a, sum.z); sum.w = fmaf(x.w, a, sum.w);
         }
         const float inv = l > 0.f ? 1.f / l : 0.f;
-        odd |= not_finite(fabsf(sum.x) + fabsf(sum.y) + fabsf(sum.z) + fabsf(sum.w) + l);
+        const float mag = fabsf(sum.x) + fabsf(sum.y) + fabsf(sum.z) + fabsf(sum.w);
+        odd |= not_finite(mag + l) || (F32 && mag < 0x1p-100f * l && mag != 0.f);
         store4(Ob + (int64_t)row * p.os_r + c4, make_float4(sum.x * inv, sum.y * inv, sum.z * inv, sum.w * inv));
     }
     if (__ballot(odd) != 0 || n_blk == kCut) {  // the rows that this wave stored, again

@@ -2,54 +2,66 @@
 // tuned kernels (mask_mfma_impl.h, mask_decode_impl.h) leave out.  Any bq <= 64, bk <= 16, k/bk <= 1024, sampling
 // stride and representative, contiguous or paged K with any page size, prefill or decode.
 //
-// One workgroup (4 waves) per (sequence, query head, query block).  The block score is a contraction in fp32 as well,
-// so it runs on the matrix cores: v_mfma_f32_16x16x4_f32 multiplies full fp32 operands into fp32 sums (bf16:
-// v_mfma_f32_16x16x32_bf16).  In fp32 the matrix pipe (64 flop per clock and SIMD, twice the vector unit's
-// rate without packed instructions) is the busiest unit, 52 % of the clocks by counter at 4096 tokens; a wave waits 80 % of its
-// time, for it and for the gathered rows, which three waves per SIMD do not cover.  Everything else keeps off its way:
-//   * The sampled query rows sit in registers as MT operand tiles of 16 rows (small query blocks do not pay for 32).
+// One workgroup (4 waves) per (sequence, query head, query block).  The block score is a contraction, so it runs on the
+// matrix cores (v_mfma_f32_16x16x32_bf16); fp32 operands go in as three bf16 planes (mfma_generic.h): six products at
+// 16 times the rate of the fp32 instruction, and a third of its error.  What bounds the kernel then are the gathered rows: the
+// wide tiles load them straight as operands, 64 cache accesses an instruction, and the address unit is busy 86 % of the
+// clocks (4096 tokens, by counter), the matrix pipe 33 %.
+//   * The sampled query rows are MT operand tiles of 16 rows (small query blocks do not pay for 32), in registers, or their
+//     planes in LDS where two tiles of them would leave two waves per SIMD instead of three (4096 tokens: 398 us with the
+//     planes in registers, 389 so).  fp32 blocks of more than 32 rows: two waves share a tile, each with half of the rows.
 //   * The branches that need a score are put on a list (LDS: block position, row offset, branch slot); a child whose
-//     representative is its node's own representative has the node's score and is not listed.  The key rows of the list
-//     are gathered in tiles of 8 KB per wave: loaded coalesced one tile ahead into registers, written to the wave's LDS
-//     tile with an XOR swizzle and read back as matrix operands (lane l: row l % 16, 16-byte chunk l / 16 of each
-//     64 bytes; the order of the channels inside the contraction is free, so a chunk feeds four fp32 steps).
+//     representative is its node's own representative has the node's score and is not listed.  The key rows of the list are
+//     gathered in tiles of 8 KB per wave, one tile ahead (the order of the channels inside the contraction is free).  Coalesced
+//     and through the wave's LDS tile (XOR swizzle; lane l: row l % 16, chunk l / 16 of each 64 bytes) for bf16 and for one fp32
+//     query tile, whose matrix work is too short to hide the accesses (16-row blocks, 4096 tokens of 32 heads 580 us, straight
+//     735); straight for two query tiles (389 us, through LDS 435) and for k/bk above 512, where the LDS tiles cost a
+//     workgroup per compute unit (8000 tokens, 8 heads, d = 64, k/bk = 1024 258 us, through LDS 478).
 //   * A row's maximum over the admissible query rows goes to its branch's key with an LDS atomic maximum, which takes
 //     any number of rows per block.
 //   * Selection: the ordered threshold selection of common.h, run redundantly by the four waves.
-// Measured, fp32, 32 query heads over 8 kv heads, T = 4096, k = 512, bq = 32, bk = 2, d = 128: 11.77 ms with
-// vector-unit dot products and a shuffle per (row, key) before, 0.58 ms now = 99 TFLOP/s of the 152 a large fp32 matrix
-// product reaches; T = 1024, one head, k = 128, bq = 16, d = 64: 187 -> 18 us (64 workgroups: latency; 20 us each with a
-// pause between launches).
+// Measured, fp32, 32 query heads over 8 kv heads, T = 4096, k = 512, bq = 32, bk = 2, d = 128: 576 us with the fp32 instruction
+// (half of the clocks on the matrix pipe), 389 us with planes; d = 64 337 -> 225; one sequence of 1024 tokens, one head, k = 128, bq = 16, d = 64: 18.0
+// -> 17.1 (64 workgroups: latency).
 #pragma once
 #include "mfma_generic.h"
 #include "launch.h"
 
 namespace hipattn {
 
-// (waves per SIMD: two query tiles of 128 fp32 channels and k/bk <= 256 spill 4 to 8 registers at three waves; at two, with
-// none spilled, 4096 tokens of 32 heads, k/bk = 256 take 636 us instead of 582, k/bk = 64 404 instead of 360)
+// (waves per SIMD: two query tiles of 64 fp32 channels and k/bk <= 256 spill 8 registers at three waves; at two, with none
+// spilled, 4096 tokens of 32 heads, k/bk = 256 take 258 us instead of 225)
 template <typename T, int D, int E, int MT>
 __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) void mask_generic_kernel(KParams p, int xcd_map, uint32_t rows_magic)
 {
+    constexpr bool F32 = sizeof(T) == 4;
+    // fp32, more than 32 rows: two waves share a tile, each scores half of the rows.  Planes of two operand tiles are in LDS.
+    constexpr int HALVES = F32 && MT > 2 ? 2 : 1, MW = MT / HALVES;
+    constexpr bool QLDS = F32 && MW > 1;
+    constexpr bool STAGED = !F32 || (MW == 1 && E <= 16);  // key rows pass through LDS, see above
     constexpr int NB = 64 * E;             // branch slots (two per node)
     constexpr int ROWB = D * (int)sizeof(T);
     constexpr int CPR = ROWB / 16;         // 16-byte chunks per key row = lanes per row of a coalesced load
     constexpr int RPW = 64 / CPR;          // rows per wave-wide load
     constexpr int TILE = 8192 / ROWB;      // key rows per tile
+    constexpr int SW = (CPR < 16 ? CPR : 16) - 1;
     constexpr int KT = TILE / 16, CS = CPR / 4;
     typedef uint32_t stage_t __attribute__((ext_vector_type(32)));
-    constexpr int SW = (CPR < 16 ? CPR : 16) - 1;
-    __shared__ __attribute__((aligned(16))) uint4 tile_s[4][512];
+    __shared__ __attribute__((aligned(16))) uint4 tile_s[STAGED ? 4 : 1][STAGED ? 512 : 1];
     __shared__ int64_t loff[NB];           // list entry: element offset of its block's first row in K
     __shared__ int lt0[NB];                // ... position of that row
     __shared__ int lslot[NB];              // ... branch slot
     __shared__ uint32_t keys[NB];
     __shared__ int nds_s[2][NB / 2], nde_s[2][NB / 2];  // nodes [s, e) of this round and of the next
     __shared__ uint32_t ndk_s[2][NB / 2];  // ... score key of the branch that became the node
+    __shared__ __attribute__((aligned(16))) uint4 qp_s[QLDS ? MT * (CS / 2) * 192 : 1];  // [half][step][operand tile][plane][lane]
+    __shared__ float tiny_s[4];
     __shared__ int n_list_s;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, lg = lane >> 4;
+    const int half = wave & (HALVES - 1), first_tile = wave / HALVES;
+    constexpr int tile_step = 4 / HALVES;
     const uint32_t groups = (uint32_t)p.batch * (uint32_t)p.hkv, per_group = (uint32_t)p.g * (uint32_t)p.nqb;
     uint32_t group, o;
     if (!place_item(xcd_map, blockIdx.x, 1, 0, per_group, groups, group, o)) return;
@@ -75,15 +87,40 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
     }
 
     // sampled query rows as A operands; rows past the last one repeat it (that cannot change a maximum)
-    uint4 qf[MT][CS];
-    {
-        const T *Qb = (const T *)p.Q + (int64_t)b * p.qs_b + (int64_t)h * p.qs_h + (int64_t)row0 * p.qs_r;
+    const auto q_row = [&](int mt) __attribute__((always_inline)) {
+        const int i = min(mt * 16 + r16, n_eff - 1) * bsq;
+        return (const char *)((const T *)p.Q + (int64_t)b * p.qs_b + (int64_t)h * p.qs_h + (int64_t)(row0 + i) * p.qs_r) + lg * 16;
+    };
+    uint4 qf[F32 ? 1 : MT][F32 ? 1 : CS];
+    Planes8 qp[F32 && !QLDS ? CS / 2 : 1][F32 && !QLDS ? MW : 1];
+    float tiny = 0.f;  // scores this close to 0 may have lost more to the planes' range than fp32 products lose
+    const uint4 *q_own = qp_s + half * (CS / 2 * MW * 192) + lane;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const char *src = (const char *)(Qb + (int64_t)(min(mt * 16 + r16, n_eff - 1) * bsq) * p.qs_r) + lg * 16;
+    for (int mt = 0; mt < MT; ++mt) {
+        const char *src = q_row(mt);
+        if constexpr (F32) {
+#pragma unroll
+            for (int cs = 0; cs < CS; cs += 2) {
+                if (QLDS && ((mt * CS + cs) >> 1 & 3) != wave) continue;
+                const uint4 x = *(const uint4 *)(src + cs * 64), y = *(const uint4 *)(src + cs * 64 + 64);
+                const Planes8 pl = split_planes8(x, y);
+                if constexpr (QLDS) {
+                    uint4 *to = qp_s + ((mt / MW * (CS / 2) + cs / 2) * MW + mt % MW) * 192 + lane;
+                    to[0] = pl.h; to[64] = pl.m; to[128] = pl.l;
+                } else {
+                    qp[cs / 2][mt] = pl;
+                }
+                const auto mag = [](uint32_t u, uint32_t v) __attribute__((always_inline)) { return fmaxf(fabsf(__uint_as_float(u)), fabsf(__uint_as_float(v))); };
+                tiny = fmaxf(tiny, fmaxf(fmaxf(mag(x.x, x.y), mag(x.z, x.w)), fmaxf(mag(y.x, y.y), mag(y.z, y.w))));
+            }
+        } else {
 #pragma unroll
             for (int cs = 0; cs < CS; ++cs) qf[mt][cs] = *(const uint4 *)(src + cs * 64);
         }
+    }
+    if constexpr (F32) {  // (whole numbers order magnitudes)
+        tiny = __uint_as_float(wave_max_u32(__float_as_uint(tiny)));
+        if (lane == 0) tiny_s[wave] = tiny;
     }
 
     // initial nodes: kb chunks of [0, Tb) with rounded bounds; all non-empty because Tb > kb
@@ -95,10 +132,19 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
     if (tid == 0) n_list_s = 0;
     for (int i = 2 * kb + tid; i < NB; i += kThreads) keys[i] = 0u;
     __syncthreads();
+    if constexpr (F32) {
+        tiny = fmaxf(fmaxf(tiny_s[0], tiny_s[1]), fmaxf(tiny_s[2], tiny_s[3]));
+        tiny = tiny < 0x1p-76f ? INFINITY : tiny * D * 0x1p-100f;
+    }
 
     const T *Kbase = (const T *)p.K;
     const int64_t back_delta = (const T *)p.Kback - Kbase;  // elements from the resident pool to the backing pool
-    char *tile = (char *)tile_s[wave];
+
+    // this lane's part of a coalesced load and of a tile in LDS (chunk c of row r is at place c ^ (r & SW) of the row), and
+    // where its operands are: the steps of 4 chunks and the rows of a load only flip bits of these
+    const char *kchunk = (const char *)Kbase + (lane % CPR) * 16;
+    char *const tile = (char *)tile_s[STAGED ? wave : 0];
+    const int put = lane / CPR * ROWB + (((lane % CPR) ^ (lane / CPR)) << 4), get = r16 * ROWB + ((lg ^ (r16 & SW)) << 4);
 
     // ensemble sample: the round whose selection compares perturbed scores (-1: none)
     const int ens_round = ens_round_of(p.ens_sample, a + (r ? 1 : 0));
@@ -143,62 +189,164 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
         const int n_list = __builtin_amdgcn_readfirstlane(n_list_s);
         const int n_tiles = (n_list * rpb + TILE - 1) / TILE;
 
-        stage_t stage;  // one vector value, so that it stays in registers
-        auto load_tile = [&](int t) __attribute__((always_inline)) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int rr = t * TILE + j * RPW + lane / CPR;
-                const int li0 = div_small(rr, rows_magic), li = min(li0, n_list - 1), n = li0 < n_list ? rr - li0 * rpb : 0;
-                const int dn = min(n * bsk, kv_len - 1 - lt0[li]);  // rows past the end re-read the last one and are dropped
-                const uint4 x = *(const uint4 *)((const char *)(Kbase + loff[li] + (int64_t)dn * p.ks_r) + (lane % CPR) * 16);
-                stage[4 * j] = x.x; stage[4 * j + 1] = x.y; stage[4 * j + 2] = x.z; stage[4 * j + 3] = x.w;
-            }
-        };
-        if (wave < n_tiles) load_tile(wave);
-        for (int t = wave; t < n_tiles; t += 4) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int row = j * RPW + lane / CPR;
-                *(uint4 *)(tile + row * ROWB + (((lane % CPR) ^ (row & SW)) << 4)) =
-                    make_uint4(stage[4 * j], stage[4 * j + 1], stage[4 * j + 2], stage[4 * j + 3]);
-            }
-            load_tile(min(t + 4, n_tiles - 1));
-            wave_lds_sync();
-            gen_f32x4 acc[KT][MT];
-#pragma unroll
-            for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) acc[kt][mt] = gen_f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int cs = 0; cs < CS; ++cs)
-#pragma unroll
-                for (int kt = 0; kt < KT; ++kt) {
-                    const uint4 kv = *(const uint4 *)(tile + (kt * 16 + r16) * ROWB + (((cs * 4 + lg) ^ (r16 & SW)) << 4));
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) acc[kt][mt] = mfma_chunk<T>(qf[mt][cs], kv, acc[kt][mt]);
-                }
-            wave_lds_sync();  // the operands are read: the tile may be overwritten
-            // lane: key row kt*16 + r16 of the tile, query rows mt*16 + 4*lg + {0..3}
+        struct Rows { int64_t off[KT]; int tk[KT], slot[KT]; };  // rows l % 16 of a tile, lane l: place in bytes, position, branch slot
+        auto rows_of = [&](int t) __attribute__((always_inline)) {
+            Rows r;
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt) {
                 const int rr = t * TILE + kt * 16 + r16;
-                const int li = div_small(rr, rows_magic);
-                const bool listed = li < n_list;
-                const int tk = listed ? lt0[li] + (rr - li * rpb) * bsk : kv_len;
-                const int lo = tk - pos0;  // block rows below lo would look into the future
-                float v = -INFINITY;
+                const int li0 = div_small(rr, rows_magic), li = min(li0, n_list - 1), dn = li0 < n_list ? (rr - li0 * rpb) * bsk : 0;
+                const int t0 = lt0[li];
+                // rows past the end re-read the last one and are dropped
+                r.off[kt] = (loff[li] + (int64_t)min(dn, kv_len - 1 - t0) * p.ks_r) * (int)sizeof(T);
+                r.tk[kt] = li0 < n_list ? t0 + dn : kv_len;
+                r.slot[kt] = lslot[li];
+            }
+            return r;
+        };
+        auto score_tile = [&](const Rows &rows, auto key_chunk) __attribute__((always_inline)) {
+            gen_f32x4 acc[KT][MW];
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
+            for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int i = min(mt * 16 + lg * 4 + e, n_eff - 1);  // (a repeated row counts as the row it repeats)
-                        if (i * bsq >= lo) v = fmaxf(v, acc[kt][mt][e]);
+                for (int mt = 0; mt < MW; ++mt) acc[kt][mt] = gen_f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (F32) {
+                gen_f32x4 low[KT][MW];
+#pragma unroll
+                for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                    for (int mt = 0; mt < MW; ++mt) low[kt][mt] = gen_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int cs = 0; cs < CS; cs += 2)
+#pragma unroll
+                    for (int kt = 0; kt < KT; ++kt) {
+                        const Planes8 kp = split_planes8(key_chunk(kt, cs), key_chunk(kt, cs + 1));
+                        if constexpr (QLDS) {
+                            Planes8 q[MW];
+#pragma unroll
+                            for (int mt = 0; mt < MW; ++mt) {
+                                const uint4 *from = q_own + (cs / 2 * MW + mt) * 192;
+                                q[mt] = Planes8{from[0], from[64], from[128]};
+                            }
+                            mfma_planes<false>(kp, q, acc[kt], low[kt]);
+                        } else {
+                            mfma_planes<false>(kp, qp[cs / 2], acc[kt], low[kt]);
+                        }
                     }
+                bool again = false;
+#pragma unroll
+                for (int kt = 0; kt < KT; ++kt) {
+                    float all = 0.f;
+#pragma unroll
+                    for (int mt = 0; mt < MW; ++mt)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            acc[kt][mt][e] += low[kt][mt][e];
+                            all += fabsf(acc[kt][mt][e]);
+                        }
+                    again |= not_finite(all) || (all < tiny && all != 0.f);
+                }
+                if (__builtin_expect(__ballot(again) != 0, 0)) {  // infinities, or magnitudes at the end of the range: once more, in fp32
+#pragma unroll
+                    for (int mt = 0; mt < MW; ++mt) {
+                        const char *src = q_row(half * MW + mt);
+#pragma unroll
+                        for (int kt = 0; kt < KT; ++kt) acc[kt][mt] = gen_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int cs = 0; cs < CS; ++cs) {
+                            const uint4 qv = *(const uint4 *)(src + cs * 64);
+#pragma unroll
+                            for (int kt = 0; kt < KT; ++kt) acc[kt][mt] = mfma_chunk<float>(qv, key_chunk(kt, cs), acc[kt][mt]);
+                        }
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int cs = 0; cs < CS; ++cs)
+#pragma unroll
+                    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                        for (int mt = 0; mt < MW; ++mt) acc[kt][mt] = mfma_chunk<T>(qf[mt][cs], key_chunk(kt, cs), acc[kt][mt]);
+            }
+            // lane: key row kt*16 + r16 of the tile, query rows mt*16 + 4*lg + {0..3}
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt) {
+                const int tk = rows.tk[kt];
+                float v = -INFINITY;
+                if (__ballot(tk > pos0 && tk < kv_len) == 0) {  // no row has these keys in its future
+#pragma unroll
+                    for (int mt = 0; mt < MW; ++mt)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v = fmaxf(v, acc[kt][mt][e]);
+                } else {
+                    const int lo = tk - pos0;  // block rows below lo would look into the future
+#pragma unroll
+                    for (int mt = 0; mt < MW; ++mt)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int i = min((half * MW + mt) * 16 + lg * 4 + e, n_eff - 1);  // (a repeated row counts as the row it repeats)
+                            if (i * bsq >= lo) v = fmaxf(v, acc[kt][mt][e]);
+                        }
+                }
                 auto s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
                 v = fmaxf(__uint_as_float(s16[0]), __uint_as_float(s16[1]));
                 auto s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
                 v = fmaxf(__uint_as_float(s32[0]), __uint_as_float(s32[1]));
-                if (lg == 0 && tk < kv_len && v > -INFINITY) atomicMax(&keys[lslot[li]], score_key(v));
+                if (lg == 0 && tk < kv_len && v > -INFINITY) atomicMax(&keys[rows.slot[kt]], score_key(v));
+            }
+        };
+        // the loads of a tile are in flight while another one is multiplied (the last tile's once more at the end: a load on one
+        // path only would make the waits of the other wait for all)
+        if constexpr (STAGED) {
+            stage_t stage;  // one vector value, so that it stays in registers
+            Rows next;
+            auto load_tile = [&](int t) __attribute__((always_inline)) {
+                next = rows_of(t);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int64_t off = __shfl((long long)next.off[j * RPW / 16], j * RPW % 16 + lane / CPR, 64);
+                    const uint4 x = *(const uint4 *)(kchunk + off);
+                    stage[4 * j] = x.x; stage[4 * j + 1] = x.y; stage[4 * j + 2] = x.z; stage[4 * j + 3] = x.w;
+                }
+            };
+            if (first_tile < n_tiles) load_tile(first_tile);
+            for (int t = first_tile; t < n_tiles; t += tile_step) {
+                const Rows rows = next;
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    *(uint4 *)(tile + ((put ^ ((j * RPW & SW) << 4)) + j * RPW * ROWB)) =
+                        make_uint4(stage[4 * j], stage[4 * j + 1], stage[4 * j + 2], stage[4 * j + 3]);
+                load_tile(min(t + tile_step, n_tiles - 1));
+                wave_lds_sync();
+                score_tile(rows, [&](int kt, int cs) __attribute__((always_inline)) { return *(const uint4 *)(tile + ((get ^ (cs << 6)) + kt * 16 * ROWB)); });
+                wave_lds_sync();  // the operands are read: the tile may be overwritten
+            }
+        } else if (first_tile < n_tiles) {
+            stage_t xa, xb;
+            Rows ra, rb;
+            auto load_tile = [&](int t, stage_t &x, Rows &r) __attribute__((always_inline)) {
+                r = rows_of(t);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const uint4 v = *(const uint4 *)((const char *)Kbase + r.off[i / CS] + lg * 16 + i % CS * 64);
+                    x[4 * i] = v.x; x[4 * i + 1] = v.y; x[4 * i + 2] = v.z; x[4 * i + 3] = v.w;
+                }
+                __builtin_amdgcn_sched_barrier(0);  // (the loads go out before the multiplies)
+            };
+            const auto chunks = [](const stage_t &x) __attribute__((always_inline)) {
+                return [&x](int kt, int cs) __attribute__((always_inline)) {
+                    const int at = 4 * (kt * CS + cs);
+                    return make_uint4(x[at], x[at + 1], x[at + 2], x[at + 3]);
+                };
+            };
+            load_tile(first_tile, xa, ra);
+            for (int t = first_tile;;) {
+                load_tile(min(t + tile_step, n_tiles - 1), xb, rb);
+                score_tile(ra, chunks(xa));
+                if ((t += tile_step) >= n_tiles) break;
+                load_tile(min(t + tile_step, n_tiles - 1), xa, ra);
+                score_tile(rb, chunks(xb));
+                if ((t += tile_step) >= n_tiles) break;
             }
         }
         __syncthreads();

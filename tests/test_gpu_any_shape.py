@@ -139,3 +139,40 @@ def test_fp32_attention_keeps_fp32_precision(T, k, bq, bk, d):
         got[u, :n] = out[b, h, qb * bq:qb * bq + n]
         ref[u, n:] = 0
     assert float((got - ref).norm() / ref.norm()) <= 5e-6
+
+
+@pytest.mark.parametrize("bq,d", [(16, 64), (16, 128), (32, 64), (32, 128), (64, 64), (64, 128)])
+@pytest.mark.parametrize("scale,best", [(1.0, 1 + 2.0 ** -20), (2.0 ** -118, 1 + 2.0 ** -20), (1.0, float("inf"))], ids=["one", "smallest", "infinite"])
+def test_fp32_scores_keep_fp32_range(bq, d, scale, best):
+    # 100 keys, 64 kept in one round, so exactly the 64 largest scores: 63 of 4, one of `best`, 36 of 1 (before and behind it),
+    # times a power of two: the scores are exact in fp32, and 1 + 2^-20 is above 1 at any scale.
+    T, k, dev = 100, 64, "cuda"
+    score = torch.ones(T)
+    score[torch.arange(T) % 3 != 0] = 4.0  # 66 of them
+    score[[1, 50, 97]] = 1.0
+    score[33] = best
+    K = torch.zeros(1, 1, T, d)
+    K[0, 0, :, 5] = score * scale
+    Q = torch.zeros(1, 1, bq, d)
+    Q[..., 5] = 1.0
+    idx = U.hipattn.hip_mask_estimate(Q.to(dev), K.to(dev), k, bq, 1).cpu().flatten()
+    want = torch.nonzero(score > 1.0).flatten()
+    assert len(want) == k and torch.equal(idx.sort().values.long(), want)
+
+
+@pytest.mark.parametrize("bq,bk,d", [(16, 2, 64), (32, 4, 128)])
+@pytest.mark.parametrize("scale", [2.0 ** -118, 2.0 ** 120])
+def test_fp32_attention_keeps_fp32_range(bq, bk, d, scale):
+    # the smallest and the largest values: the same bound as test_fp32_attention_keeps_fp32_precision
+    T, kb, dev = 130, 6, "cuda"
+    gen = torch.Generator().manual_seed(bq + d)
+    Q, K, V = (torch.randn(1, n, T, d, generator=gen) for n in (2, 1, 1))
+    V *= scale
+    nqb = -(-T // bq)
+    idx = torch.full((1, 2, nqb, kb), U.hipattn.SENTINEL, dtype=torch.int32)
+    for qb in range(nqb):
+        seen = -(-min((qb + 1) * bq, T) // bk)
+        idx[0, :, qb, :min(kb, seen)] = torch.randperm(seen, generator=gen)[:kb].sort().values.int() * bk
+    out = U.hipattn.hip_sparse_attn(Q.to(dev), K.to(dev), V.to(dev), idx.to(dev), kb * bk, bq, bk)[0].double().cpu()
+    ref = _attention_by_rows(Q[0].double(), K[0].double(), V[0].double(), idx[0], bq, bk, d ** -0.5, 0, 0, 3.4e38)
+    assert float((out - ref).norm() / ref.norm()) <= 5e-6
