@@ -5,8 +5,8 @@
 // One workgroup (4 waves) per (sequence, query head, query block).  The block score is a contraction, so it runs on the
 // matrix cores (v_mfma_f32_16x16x32_bf16); fp32 operands go in as three bf16 planes (mfma_generic.h): six products at
 // 16 times the rate of the fp32 instruction, and a third of its error.  What bounds the kernel then are the gathered rows: the
-// wide tiles load them straight as operands, 64 cache accesses an instruction, and the address unit is busy 86 % of the
-// clocks (4096 tokens, by counter), the matrix pipe 33 %.
+// wide tiles load them straight as operands, 64 cache accesses an instruction: the address unit is busy 82 % of the
+// clocks, the return path 93 %, vector issue 51 %, the matrix pipe 32 % (4096 tokens, by counter).
 //   * The sampled query rows are MT operand tiles of 16 rows (small query blocks do not pay for 32), in registers, or their
 //     planes in LDS where two tiles of them would leave two waves per SIMD instead of three (4096 tokens: 398 us with the
 //     planes in registers, 389 so).  fp32 blocks of more than 32 rows: two waves share a tile, each with half of the rows.
