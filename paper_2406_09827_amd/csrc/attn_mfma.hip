@@ -62,8 +62,8 @@ constexpr int kListTiles = 16;   // tiles whose keys are listed; refilled by hal
 
 }  // namespace
 
-// MODE 0: contiguous K/V, a (sequence, kv head) slice below 4 GB: rows are addressed by a scalar slice base plus a
-//         32-bit lane offset; MODE 1: paged pool; MODE 2: contiguous, any size (64-bit row addresses).
+// MODE 0: contiguous K/V, rows within reach of a 32-bit lane offset (rows_by_lane_offset): addressed by that and a scalar
+//         slice base; MODE 1: paged pool; MODE 2: contiguous, any size (64-bit row addresses).
 // WPI: waves per work item.  With 2 or 4 the workgroup takes ONE work item; wave w walks key tiles w, w + WPI, ... with its own
 //      softmax state and the states are merged through LDS at the end.
 template <int D, int MODE, int WPI>
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_wa
     // compiler warns that it does not track the clobber.  It is written and consumed inside one asm statement, and nothing else
     // in this kernel uses M0.)
     // An instruction offset moves both the global and the LDS address, so one M0 serves four loads; what it adds to the global
-    // address is taken off the lane's part (3072 bytes stand before it so that nothing gets negative).
+    // address is taken off the lane's part (kRowBias bytes stand before it so that nothing gets negative).
     const uint32_t kchunk = (uint32_t)((D == 128 ? lc ^ ((lg & 1) << 3) : lc ^ ((lg & 2) << 1)) << 4), vchunk = (uint32_t)(lc << 4);
     auto issue_rows = [&](const rows_t &R, bool val) __attribute__((always_inline)) {
 #pragma unroll
@@ -250,8 +250,8 @@ __global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_wa
             const uint32_t dst = __builtin_amdgcn_readfirstlane((val ? vt_m0 : kt_m0) + (j & ~3) * 1024);
             const int back = (j & 3) * 1024;
             if constexpr (MODE == 0) {
-                const uint32_t vo = R.off[j] + chunk + (uint32_t)(3072 - back);
-                const char *base = (val ? Vseq : Kseq) - 3072;
+                const uint32_t vo = R.off[j] + chunk + (uint32_t)(kRowBias - back);
+                const char *base = (val ? Vseq : Kseq) - kRowBias;
                 if (j & 3) asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" :: "v"(vo), "s"(base), "i"(back) : "memory");
                 else asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                                   :: "v"(vo), "s"(base), "s"(dst) : "memory", "m0");
@@ -532,7 +532,7 @@ hipError_t launch_attn_mfma(const KParams &p, hipStream_t st)
     // groups worked on at a time (measured: all eight up to 128k tokens at head dim 128, four at 256k, one at a million)
     const int xcd_map = (groups % 8 == 0 && (wpi > 1 || per_group % 4 == 0)) ? groups_at_a_time((int64_t)p.max_kv_len * p.d * 4, 768LL << 20) : 0;
     const dim3 grid((unsigned)placed_workgroups(xcd_map, wpi > 1 ? 1 : 4, per_group, groups)), block(wpi == 2 ? 128 : kThreads);
-    const int mode = p.page_table ? 1 : ((int64_t)p.max_kv_len * p.ks_r * 2 < (1LL << 32) && p.ks_r * 2 < (1 << 24) && p.max_kv_len < (1 << 24) ? 0 : 2);
+    const int mode = p.page_table ? 1 : rows_by_lane_offset(p.max_kv_len, p.ks_r * 2, p.d) ? 0 : 2;
     const auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, block, 0, st, p, log_bk, mtn, xcd_map);
         return hipGetLastError();

@@ -1,6 +1,7 @@
 // Host-side launchers of the kernel families (one translation unit each).
 #pragma once
 #include "common.h"
+#include "launch_rules.h"
 
 namespace hipattn {
 

@@ -65,3 +65,25 @@ def test_key_lists_and_waves_per_item(d, bq, bk, k, n_sink, n_window, page):
     # a prefix shorter than k: the list ends early
     w = synth.Workload("short", 1, 8, 2, d, k, k, k, bq, bk, "bf16", rho=0.9, page_size=page, integer=True, seed=330)
     U.run_case(w, 0, units=[(0, 0, 0), (0, 7, 1), (0, 3, w.n_query_blocks - 1)], n_sink=n_sink, n_window=n_window)
+
+
+@pytest.mark.parametrize("T", [4194301, 4194303])
+def test_last_keys_of_a_slice_of_four_gigabytes(T):
+    # rows 1024 bytes apart: the longest slice whose rows 32-bit lane offsets reach, and one that takes 64-bit addresses.  Rows
+    # that attend to the last keys, from blocks at the front and the back of the context, against plain attention.
+    d, bq, bk, kb, pitch = 128, 32, 2, 24, 512
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    blocks = torch.cat([torch.arange(4), torch.tensor([1000, 2 ** 20]), torch.arange(kb - 6) + (T - 1) // bk - (kb - 7)]) * bk
+    rows = (blocks[:, None] + torch.arange(bk)).flatten()
+    rows = rows[rows < T].cuda()
+    K, V = (torch.empty(T * pitch, dtype=torch.bfloat16, device="cuda").as_strided((1, 1, T, d), (T * pitch, T * pitch, pitch, 1)) for _ in range(2))
+    for x in (K, V):
+        x[0, 0, 0] = 0
+        x[0, 0, rows] = torch.randn(len(rows), d, device="cuda", generator=gen).bfloat16()
+    Q = torch.randn(1, 4, bq, d, device="cuda", generator=gen).bfloat16()
+    idx = blocks.int().cuda().expand(1, 4, 1, kb).contiguous()
+    out = hipattn.hip_sparse_attn(Q, K, V, idx, kb * bk, bq, bk)[0].double()
+    x = Q[0].double() @ K[0, 0, rows].double().T * d ** -0.5
+    x = x.masked_fill(rows[None, :] > torch.arange(T - bq, T, device="cuda")[:, None], float("-inf"))
+    ref = torch.softmax(x, -1) @ V[0, 0, rows].double()
+    assert float((out - ref).abs().max()) <= 2e-2   # (outputs below 4: see gpu_util)

@@ -1,0 +1,41 @@
+"""Host-side check of the launchers' rules (csrc/launch_rules.h), compiled with the host compiler as they stand."""
+import subprocess
+from pathlib import Path
+
+CSRC = Path(__file__).resolve().parents[1] / "paper_2406_09827_amd" / "csrc"
+
+
+def run(tmp_path, body: str) -> str:
+    src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
+    src.write_text('#include "launch_rules.h"\n#include <cstdio>\n#include <initializer_list>\nusing namespace hipattn;\nint main() {\n' + body + "\nreturn 0; }\n")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I", str(CSRC), "-o", str(exe), str(src)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
+
+
+def test_row_offsets_of_the_prefill_attention_stay_within_32_bits(tmp_path):
+    # the largest offset a lane forms (last row, last 16-byte chunk, load without an instruction offset) for lengths on either
+    # side of the bound, and that a slice well below 4 GB is still taken
+    out = run(tmp_path, r"""
+    for (int d : {64, 128})
+        for (int64_t row : {2LL * d, 512LL, 1024LL, 2048LL, 4096LL, 8192LL, 65536LL}) {
+            const int64_t edge = (1LL << 32) / row;
+            for (int64_t T = edge - 40 > 2 ? edge - 40 : 2; T <= edge + 2; ++T) {
+                const int64_t largest = (T - 1) * row + (2 * d - 16) + kRowBias;
+                if (rows_by_lane_offset(T, row, d) && (largest >= 1LL << 32 || T >= 1 << 24)) { std::printf("wraps: d %d row %lld T %lld\n", d, (long long)row, (long long)T); return 1; }
+            }
+            if (!rows_by_lane_offset(edge * 9 / 10 < (1 << 24) ? edge * 9 / 10 : (1 << 24) - 1, row, d)) { std::printf("refused: d %d row %lld\n", d, (long long)row); return 1; }
+        }
+    // lengths that the sum without the bias would let through
+    const int64_t past[][2] = {{16777205, 256}, {16777215, 256}, {8388603, 512}, {8388607, 512}, {4194302, 1024}, {4194303, 1024}};
+    for (auto &c : past) if (rows_by_lane_offset(c[0], c[1], 128)) { std::printf("taken: %lld\n", (long long)c[0]); return 1; }
+    std::printf("ok %d\n", (int)rows_by_lane_offset(4194301, 1024, 128));
+    """)
+    assert out.strip() == "ok 1"
+
+
+def test_the_prefill_attention_uses_the_rule_it_is_tested_with():
+    src = (CSRC / "attn_mfma.hip").read_text()
+    assert "rows_by_lane_offset(p.max_kv_len, p.ks_r * 2, p.d)" in src
+    assert src.count("kRowBias - back") == 1 and src.count(": Kseq) - kRowBias") == 1 and "3072" not in src
