@@ -63,7 +63,16 @@ __device__ __forceinline__ uint32_t score_key(float f)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// The same from the float's bits, in whole numbers (all ones, no float that a score can be, give key 0)
+// The bits of a score as the tables hold it: a NaN with the sign bit set counts as -inf.  (Its key would lie below that of -inf,
+// where the selection does not look: it would keep fewer than kb branches and leave the places of the others as they were.  A
+// NaN without the sign bit lies above +inf, which does no harm.)  Scores are NaN where inputs are not finite; which branches are
+// kept is then open, but they are kb branches of the sequence.
+__device__ __forceinline__ uint32_t score_bits(float f)
+{
+    return min(__float_as_uint(f), 0xff800000u);
+}
+
+// score_key from those bits, in whole numbers (all ones, an empty entry, give key 0)
 __device__ __forceinline__ uint32_t score_key_bits(uint32_t u)
 {
     if ((u << 1) == 0u) u = 0u;
@@ -172,7 +181,7 @@ __device__ __forceinline__ uint32_t ens_key(uint32_t key, uint32_t unit_hash, in
     const uint32_t x = fmix32(unit_hash ^ (uint32_t)rep_blk);
     const float u = (float)((int)(x >> 8) - (1 << 23)) * (1.0f / 8388608.0f);   // exact
     const float moved = __fadd_rn(__uint_as_float(bits), __fmul_rn(r_e, u));    // no fused multiply-add
-    return score_key(moved);
+    return score_key_bits(score_bits(moved));
 }
 
 constexpr uint32_t kKeyNegInf = 0x007fffffu;  // score_key(-inf): a real branch without admissible pair

@@ -230,7 +230,7 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 
             float best = t0 + (row % BK) * bsk < kv_len ? v[0] : -INFINITY;
 #pragma unroll
             for (int w = COPIES; w < COPIES * BK; w <<= 1) best = fmaxf(best, exchange(best, w));
-            if (lc % (COPIES * BK) == 0 && at < n_items && t0 >= 0) tab[at] = __float_as_uint(best);
+            if (lc % (COPIES * BK) == 0 && at < n_items && t0 >= 0) tab[at] = score_bits(best);
         };
 
         constexpr int STEP = RPW * U;   // branches per stage

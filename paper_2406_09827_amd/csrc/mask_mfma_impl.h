@@ -280,7 +280,7 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map, in
         if (LB >= 1) v = fmaxf(v, dpp_f<0xB1>(v));  // lane ^ 1
         if (LB >= 2) v = fmaxf(v, dpp_f<0x4E>(v));  // lane ^ 2
         if (LB >= 3) v = fmaxf(v, dpp_f<0x141>(v)); // lane i <-> 7 - i of each 8 lanes: the other quad (quads are uniform by now)
-        if (writes) *at = masked && t0 < 0 ? 0xffffffffu : __float_as_uint(v);
+        if (writes) *at = masked && t0 < 0 ? 0xffffffffu : score_bits(v);
     };
 
     static_assert(NLD == KS, "one load per k-step");
