@@ -40,12 +40,17 @@ __device__ __forceinline__ float exp_neg(float x)
     return fmaf(v, e * 0.693147181f, v);
 }
 constexpr int kGenMaxKb = 1024;
+// fp32: probabilities of the walk are 2^23 times e^(logit - reference), so that their planes hold all the bits of the smallest,
+// 2^-126.  (Sums that overflow for it, of values beyond 2^90, are not finite and done again by rows.)
+template <typename T> constexpr float kProbScale = sizeof(T) == 4 ? 0x1p23f : 1.f;
 
 // One query row by one wave, one key per lane and its value by all lanes: reads of K and V, and multiplies into the row,
 // only what counts for it.  The matrix-core walk gives a key that does not count for a row (one in the row's future, or of
 // another of the three ranges) probability 0, and 0 * inf = NaN: a row that is not finite is done again here, so that an
 // infinite or NaN value reaches the rows that attend to it and no others.  So are the rows of a query block with a block that
-// does not lie in one page; here every key's page is looked up.
+// does not lie in one page (here every key's page is looked up), and fp32 rows that the planes' range would show in: a channel
+// that comes out small beside its weights, queries with lost bits, queries so large that those lost of a key would show.
+// (A channel whose values are all below 2^-134, where nothing of them is left in the planes, comes out as 0.)
 template <typename T, int D>
 __device__ __forceinline__ void attend_row(const KParams &p, int b, int h, int hk, int kv_len, int row, const int32_t *idx, int lane)
 {
@@ -117,7 +122,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     constexpr int kLds = kWalk > kMerge ? kWalk : kMerge;
     __shared__ __attribute__((aligned(16))) char lds[kLds];
     __shared__ float ml_s[4][2][MT * 16];
-    __shared__ int n_blk_s;                      // list entries up to the last block; kCut: a block goes on in another page
+    __shared__ int n_blk_s;                      // list entries up to the last block; kCut: no walk, the rows are done one by one
     constexpr int kCut = kGenMaxKb + 1;
     int64_t *blk_off = (int64_t *)lds;           // element offset of a selected block's first row, bit 0: in the backing pools
     int *blk_pos = (int *)(lds + kGenMaxKb * 8); // its position, -1: no block
@@ -159,6 +164,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     uint4 qf[F32 ? 1 : MT][F32 ? 1 : CS];
     uint4 *qp = (uint4 *)(lds + kGenMaxKb * 12) + lane;   // [mt][step][plane][lane]
     {
+        QueryReach reach;
         const T *Qb = (const T *)p.Q + (int64_t)b * p.qs_b + (int64_t)h * p.qs_h + (int64_t)row0 * p.qs_r;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
@@ -167,7 +173,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
                 for (int cs = 0; cs < CS; cs += 2) {
                     if (((mt * CS + cs) >> 1 & 3) != wave) continue;
-                    const Planes8 x = split_planes8(*(const uint4 *)(src + cs * 64), *(const uint4 *)(src + cs * 64 + 64));
+                    const uint4 q0 = *(const uint4 *)(src + cs * 64), q1 = *(const uint4 *)(src + cs * 64 + 64);
+                    reach.add(q0);
+                    reach.add(q1);
+                    const Planes8 x = split_planes8(q0, q1);
                     uint4 *to = qp + (mt * CS + cs) / 2 * 192;
                     to[0] = x.h; to[64] = x.m; to[128] = x.l;
                 }
@@ -176,6 +185,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                 for (int cs = 0; cs < CS; ++cs) qf[mt][cs] = *(const uint4 *)(src + cs * 64);
             }
         }
+        // (a logit has an error of 2^-133 times the sum of the magnitudes of its queries from the keys' lost bits)
+        if (F32 && __ballot(reach.loses_bits() || reach.largest >= __float_as_uint(0x1p90f)) != 0 && lane == 0) atomicMax(&n_blk_s, kCut);
     }
     __syncthreads();
 
@@ -297,7 +308,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                 float sum = 0.f;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    x[r] = exp_neg(x[r] - m_safe);
+                    x[r] = exp_neg(x[r] - m_safe) * kProbScale<T>;
                     sum += x[r];
                 }
                 s[mt] = gen_f32x4{x[0], x[1], x[2], x[3]};
@@ -406,8 +417,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             sum.x = fmaf(x.x, a, sum.x); sum.y = fmaf(x.y, a, sum.y); sum.z = fmaf(x.z, a, sum.z); sum.w = fmaf(x.w, a, sum.w);
         }
         const float inv = l > 0.f ? 1.f / l : 0.f;
-        const float mag = fabsf(sum.x) + fabsf(sum.y) + fabsf(sum.z) + fabsf(sum.w);
-        odd |= not_finite(mag + l) || (F32 && mag < 0x1p-100f * l && mag != 0.f);
+        const auto small = [&](float s) __attribute__((always_inline)) { return fabsf(s) < 0x1p-100f * l && s != 0.f; };
+        odd |= not_finite(fabsf(sum.x) + fabsf(sum.y) + fabsf(sum.z) + fabsf(sum.w) + l) ||
+               (F32 && (small(sum.x) || small(sum.y) || small(sum.z) || small(sum.w)));
         store4(Ob + (int64_t)row * p.os_r + c4, make_float4(sum.x * inv, sum.y * inv, sum.z * inv, sum.w * inv));
     }
     if (__ballot(odd) != 0 || n_blk == kCut) {  // the rows that this wave stored, again

@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
     };
     uint4 qf[F32 ? 1 : MT][F32 ? 1 : CS];
     Planes8 qp[F32 && !QLDS ? CS / 2 : 1][F32 && !QLDS ? MW : 1];
-    float tiny = 0.f;  // scores this close to 0 may have lost more to the planes' range than fp32 products lose
+    QueryReach reach;
     const uint4 *q_own = qp_s + half * (CS / 2 * MW * 192) + lane;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
@@ -110,16 +110,17 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
                 } else {
                     qp[cs / 2][mt] = pl;
                 }
-                const auto mag = [](uint32_t u, uint32_t v) __attribute__((always_inline)) { return fmaxf(fabsf(__uint_as_float(u)), fabsf(__uint_as_float(v))); };
-                tiny = fmaxf(tiny, fmaxf(fmaxf(mag(x.x, x.y), mag(x.z, x.w)), fmaxf(mag(y.x, y.y), mag(y.z, y.w))));
+                reach.add(x);
+                reach.add(y);
             }
         } else {
 #pragma unroll
             for (int cs = 0; cs < CS; ++cs) qf[mt][cs] = *(const uint4 *)(src + cs * 64);
         }
     }
+    float tiny = 0.f;  // scores this close to 0 may have lost more to the planes' range than fp32 products lose
     if constexpr (F32) {  // (whole numbers order magnitudes)
-        tiny = __uint_as_float(wave_max_u32(__float_as_uint(tiny)));
+        tiny = __uint_as_float(wave_max_u32(__ballot(reach.loses_bits()) != 0 ? 0x7f800000u : reach.largest));
         if (lane == 0) tiny_s[wave] = tiny;
     }
 
@@ -134,7 +135,7 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
     __syncthreads();
     if constexpr (F32) {
         tiny = fmaxf(fmaxf(tiny_s[0], tiny_s[1]), fmaxf(tiny_s[2], tiny_s[3]));
-        tiny = tiny < 0x1p-76f ? INFINITY : tiny * D * 0x1p-100f;
+        tiny = tiny < 0x1p-76f && tiny > 0.f ? INFINITY : tiny * D * 0x1p-100f;   // (queries of 0: scores of 0)
     }
 
     const T *Kbase = (const T *)p.K;
@@ -244,7 +245,7 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
                             acc[kt][mt][e] += low[kt][mt][e];
                             all += fabsf(acc[kt][mt][e]);
                         }
-                    again |= not_finite(all) || (all < tiny && all != 0.f);
+                    again |= not_finite(all) || all < tiny;
                 }
                 if (__builtin_expect(__ballot(again) != 0, 0)) {  // infinities, or magnitudes at the end of the range: once more, in fp32
 #pragma unroll

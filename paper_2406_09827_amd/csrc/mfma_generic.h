@@ -22,8 +22,8 @@ template <> __device__ __forceinline__ gen_f32x4 mfma_chunk<bf16_t>(const uint4 
 }
 
 // fp32 operands as three bf16 planes (high, middle, low: 8 significand bits each, every remainder rounded to nearest), so
-// that a product runs at the bf16 rate, 16 times the fp32 one.  x = h + m + l exactly unless a part falls below 2^-126 and is
-// lost: the kernels do in fp32 what comes out small enough for that to show.  Six of the nine products are formed; the ones
+// that a product runs at the bf16 rate, 16 times the fp32 one.  x = h + m + l exactly down to 2^-110; below, bits under 2^-133 are
+// lost: the kernels do in fp32 what comes out small enough for that to show, and query rows that reach further (QueryReach).  Six of the nine products are formed; the ones
 // left out (m l, l m, l l) are below 2^-25 of the product, half an ulp of fp32 being 2^-24.  A part of an infinite value, or
 // of one that rounds up to infinity, is NaN: so is what it is multiplied into, and the kernels do that again too.
 // Error of 128-channel products against 64 bits, over the sum of the products' magnitudes, rms / largest: fp32 instruction 2.8e-8 /
@@ -64,6 +64,17 @@ __device__ __forceinline__ Planes8 split_planes8(const uint4 &a, const uint4 &b)
     const Planes z = split_planes(__uint_as_float(b.x), __uint_as_float(b.y)), w = split_planes(__uint_as_float(b.z), __uint_as_float(b.w));
     return Planes8{make_uint4(x.h, y.h, z.h, w.h), make_uint4(x.m, y.m, z.m, w.m), make_uint4(x.l, y.l, z.l, w.l)};
 }
+// How far the values of a query row reach: their largest magnitude, and whether one that is not 0 has lost bits to the planes' range
+// (what such a value is multiplied with may be large enough for that to show, whatever the product's size).
+struct QueryReach {
+    uint32_t largest = 0u, smallest = ~0u;  // bits of the magnitude; twice those less one, which takes 0 out
+    __device__ __forceinline__ void add(const uint4 &x)
+    {
+        largest = max(max(largest, max(x.x & 0x7fffffffu, x.y & 0x7fffffffu)), max(x.z & 0x7fffffffu, x.w & 0x7fffffffu));
+        smallest = min(min(smallest, min((x.x << 1) - 1u, (x.y << 1) - 1u)), min((x.z << 1) - 1u, (x.w << 1) - 1u));
+    }
+    __device__ __forceinline__ bool loses_bits() const { return smallest < ((127u - 110u) << 24) - 1u; }
+};
 // hi += the products of the high planes, lo += the five smaller ones: kept apart, so that adding a small one does not round
 // the large sum.  One operand against N, so that 2 N sums take turns on the matrix pipe; ONE_IS_A: it is the rows of the result.
 template <bool ONE_IS_A, int N>

@@ -176,3 +176,52 @@ def test_fp32_attention_keeps_fp32_range(bq, bk, d, scale):
     out = U.hipattn.hip_sparse_attn(Q.to(dev), K.to(dev), V.to(dev), idx.to(dev), kb * bk, bq, bk)[0].double().cpu()
     ref = _attention_by_rows(Q[0].double(), K[0].double(), V[0].double(), idx[0], bq, bk, d ** -0.5, 0, 0, 3.4e38)
     assert float((out - ref).norm() / ref.norm()) <= 5e-6
+
+
+@pytest.mark.parametrize("bq,d", [(16, 64), (32, 128), (64, 128)])
+@pytest.mark.parametrize("lost", ["all", "bits", "to zero"])
+def test_fp32_scores_of_queries_at_the_end_of_the_range(bq, d, lost):
+    # as above, with a score that only the low bits of a query of 2^-120 beside one of 1 set apart (keys of 2^120), with nothing but
+    # such queries, and with subnormal queries, whose planes are 0
+    T, k, dev, e = 100, 64, "cuda", -140 if lost == "to zero" else -120
+    score = torch.ones(T)
+    score[torch.arange(T) % 3 != 0] = 4.0  # 66 of them
+    score[[1, 50, 97]] = 1.0
+    K, Q = torch.zeros(1, 1, T, d), torch.zeros(1, 1, bq, d)
+    K[0, 0, :, 6] = score * 2.0 ** 120
+    Q[..., 5], Q[..., 6] = (1 + 2.0 ** -20 if lost != "to zero" else 2.0) * 2.0 ** e, 2.0 ** e
+    K[0, 0, 33, 5:7] = torch.tensor([2.0 ** 120, 0.0])
+    if lost == "bits":
+        Q[..., 9] = 1.0
+    idx = U.hipattn.hip_mask_estimate(Q.to(dev), K.to(dev), k, bq, 1).cpu().flatten()
+    want = torch.nonzero((score > 1.0) | (torch.arange(T) == 33)).flatten()
+    assert len(want) == k and torch.equal(idx.sort().values.long(), want)
+
+
+@pytest.mark.parametrize("bq,bk,d", [(16, 2, 64), (32, 4, 128)])
+@pytest.mark.parametrize("case", ["small channel", "smallest channel", "far behind", "large queries", "small queries"])
+def test_fp32_attention_of_mixed_magnitudes(case, bq, bk, d):
+    # All keys selected, every channel against 64 bits by itself.  The bound is that of test_fp32_attention_keeps_fp32_precision for
+    # logits below 10; "far behind": a first key with values of 0 whose logit is ahead by 86, i.e. logits with errors of a few
+    # 2^-24 * 86.
+    T, dev = 130, "cuda"
+    gen = torch.Generator().manual_seed(bq + d)
+    Q, K, V = (torch.randn(1, n, T, d, generator=gen) for n in (2, 1, 1))
+    V = V.abs() + 0.5
+    bound = 5e-6
+    if case in ("small channel", "smallest channel"):
+        V[..., 5] *= 2.0 ** (-118 if case == "small channel" else -124)
+    elif case == "far behind":
+        K *= 0.1
+        K[..., 7], K[0, 0, 0], V[0, 0, 0], Q[..., 7] = 0, 0, 0, d ** 0.5
+        K[0, 0, 0, 7] = 86.0
+        V *= 2.0 ** 30
+        bound = 8 * 2.0 ** -24 * 86
+    else:
+        e = 120 if case == "large queries" else -120
+        Q, K = Q * 2.0 ** e, K * 2.0 ** -e
+    nqb, kb = -(-T // bq), -(-T // bk)
+    idx = (torch.arange(kb, dtype=torch.int32) * bk).expand(1, 2, nqb, kb).contiguous()
+    out = U.hipattn.hip_sparse_attn(Q.to(dev), K.to(dev), V.to(dev), idx.to(dev), kb * bk, bq, bk)[0].double().cpu()
+    ref = _attention_by_rows(Q[0].double(), K[0].double(), V[0].double(), idx[0], bq, bk, d ** -0.5, 0, 0, 3.4e38)
+    assert bool(((out - ref)[:, 1:].norm(dim=(0, 1)) <= bound * ref[:, 1:].norm(dim=(0, 1))).all())
