@@ -52,7 +52,7 @@ __device__ __forceinline__ float max_half_swap(float v)
 // the first round they all score the same representative blocks (the initial nodes depend on the lengths only), so they
 // go through that round in step: every tile is loaded once, a quarter of it by each wave, and read by all of them.
 template <int MT, int E, int D, bool PAGED, int LB, int WPI, bool SHARE>
-__device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map, int in_step)
+__device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
 {
     static_assert(WPI == 1 || (WPI == 4 && !SHARE), "a wave or a workgroup per work item");
     static_assert(!(SHARE && PAGED), "shared first round: contiguous keys");
@@ -389,8 +389,10 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map, in
                 };
                 int tile = first_tile;
                 for (; tile + STEP < n_tiles; tile += STEP) {
-                    // (the four heads stay together, so that their rows meet in the L2; see the launcher)
-                    if (SHARE && in_step && (tile & 7) == 0 && !list) asm volatile("s_barrier" ::: "memory");
+                    // The four heads stay together, so that their rows meet in the L2: they still share half of the nodes in
+                    // the second round.  (32 heads, without / with the barrier: 4k tokens 78.1 / 77.8 us, 32k 1582 / 1581, 48k 2883 /
+                    // 2852, 64k 4705 / 4533, 128k 15.0 / 14.3 ms; 64 channels, 128k 5935 / 5888)
+                    if (SHARE && (tile & 7) == 0 && !list) asm volatile("s_barrier" ::: "memory");
                     step(tile, true);
                 }
                 step(tile, false);
@@ -507,9 +509,9 @@ constexpr int mask_waves(int MT, int E, int D, bool PAGED, bool SPLIT)
     return by_lds < by_regs ? by_lds : by_regs;
 }
 template <int MT, int E, int D, bool PAGED, int LB, int WPI, bool SHARE>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(mask_waves(MT, E, D, PAGED, WPI > 1)))) void mask_mfma_kernel(KParams p, int xcd_map, int in_step)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(mask_waves(MT, E, D, PAGED, WPI > 1)))) void mask_mfma_kernel(KParams p, int xcd_map)
 {
-    mask_mfma_body<MT, E, D, PAGED, LB, WPI, SHARE>(p, xcd_map, in_step);
+    mask_mfma_body<MT, E, D, PAGED, LB, WPI, SHARE>(p, xcd_map);
 }
 
 template <int MT, int E, int D, int LB>
@@ -517,22 +519,11 @@ static hipError_t launch_mask_mfma_e(const KParams &p, int xcd_map, dim3 grid, b
 {
     // (the four work items of a workgroup are then four heads of one query block: they share the first round's tiles)
     const bool share = one_sequence_per_workgroup && p.g % 4 == 0 && !p.page_table && !(p.flags & 2);
-    // Where the keys of a kv head do not stay in the caches the kernel waits for the memory side, and what counts is how often
-    // the waves of an XCD meet in its L2.  Two things bring them closer: the four heads of a workgroup stay in step in the
-    // later rounds too (a barrier every eight tiles; they still share half of the nodes in the second round), and fewer
-    // workgroups share a compute unit (the launch asks for LDS that it does not use).  Measured, 32 query heads over 8 kv
-    // heads, in ms, as many workgroups as fit / the same in step / in step and three / two / one to a compute unit:
-    //   bq = 32, bk = 2, k = 512:  64k tokens (16 MB of keys per kv head) 4.69 / 4.52 / 4.54 / 4.96 / 7.42;
-    //     128k (32 MB) 15.01 / 14.34 / 14.20 / 14.05 / 18.45;  256k (64 MB) 43.3 / - / 40.6 / 39.4 / 45.1
-    //   bq = 64, bk = 4, k = 2048:  1M (256 MB) 413.9 / - / - / 387.4 / 376.7;  k = 1024, 200k (50 MB): - / 23.4 / - / - / 27.0
-    const int64_t key_bytes = (int64_t)p.max_kv_len * p.ks_r * 2;
-    const int in_step = key_bytes > (12 << 20);
-    // (a tile of 64 channels is half the bytes: twice as many)
-    const int per_cu = (key_bytes > (128 << 20) ? 1 : key_bytes > (24 << 20) ? 2 : 4) * (128 / D);
+    const int per_cu = mask_workgroups_per_cu(p.max_kv_len, D, p.kv_lens == nullptr);
     const auto launch = [&](auto kernel, bool paged, bool split_) {
         const int lds = (split_ ? 1 : 4) * 256 * E * (paged ? 2 : 1) + 4 * 64 * D + (split_ ? 128 * E : 0);
-        const int pad = per_cu < 4 && !split_ ? (160 << 10) / per_cu - lds : 0;
-        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), (unsigned)(pad > 0 ? pad & ~1023 : 0), st, p, xcd_map, in_step);
+        const int pad = per_cu && !split_ ? (160 << 10) / per_cu - lds : 0;
+        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), (unsigned)(pad > 0 ? pad & ~1023 : 0), st, p, xcd_map);
         return hipGetLastError();
     };
     // the page-table variant is a separate instantiation: a table read in the row-offset code

@@ -27,20 +27,26 @@ def test_table_sizes(k, bk, d, bq, rep_pos, heads, page):
         U.run_case(synth.scaled(w, integer=False), 0, units=units[:3], rep_pos=rep_pos)
 
 
-@pytest.mark.parametrize("hq,bq,bk", [(4, 32, 2), (3, 32, 2), (4, 64, 4)])
-@pytest.mark.parametrize("pitch", [2048, 8192, 32768])
-def test_launch_shapes_of_long_contexts(pitch, hq, bq, bk):
-    # how many workgroups share a compute unit, and whether four heads stay in step, follows the bytes that a kv head's keys
-    # span: rows 4, 16 and 64 KB apart span 16, 67 and 268 MB.  Same indices as from the packed keys.
-    T = 4100
-    x = synth.make_inputs(synth.Workload("pitch", 1, hq, 1, 128, T, T, 256 * bk, bq // 4, bk, "bf16", rho=0.95, seed=311), device="cuda", threads=4)
-    wide = torch.empty(T * pitch, dtype=torch.bfloat16, device="cuda").as_strided((1, 1, T, 128), (T * pitch, T * pitch, pitch, 1))
-    wide.copy_(x["K"])
-    for b_sq, q_rows in ((1, bq), (1, bq // 4)):
-        a = hipattn.hip_mask_estimate(x["Q"], x["K"], 256 * bk, q_rows, bk, b_sq=b_sq)
-        b = hipattn.hip_mask_estimate(x["Q"], wide, 256 * bk, q_rows, bk, b_sq=b_sq)
-        torch.cuda.synchronize()
-        assert torch.equal(a, b)
+@pytest.mark.parametrize("T,d,hq,bq,bk", [
+    (100_000, 128, 4, 32, 2), (100_000, 128, 3, 32, 2), (100_000, 128, 4, 64, 4),   # over 24 MB of keys: two workgroups to a compute unit
+    (530_000, 128, 4, 32, 2), (530_000, 128, 3, 64, 4), (1_050_000, 64, 4, 32, 2),  # over 128 MB: one, with 64 channels two
+])
+def test_launch_shapes_of_long_contexts(T, d, hq, bq, bk):
+    # How many workgroups share a compute unit follows the bytes of a kv head's keys, not how far apart they are stored, where the
+    # host knows the lengths.  Same indices as with the lengths on the device, and as from keys stored among another head's.
+    nqb = -(-1540 // hq)
+    assert hq * nqb > 1536   # a wave per work item
+    gen = torch.Generator(device="cuda").manual_seed(bk + d)
+    K = torch.randn(1, 1, T, d, device="cuda", generator=gen).bfloat16()
+    Q = torch.randn(1, hq, nqb * bq - 3, d, device="cuda", generator=gen).bfloat16()
+    lens = torch.tensor([T], dtype=torch.int32, device="cuda")
+    apart = torch.empty(1, T, 2, d, dtype=torch.bfloat16, device="cuda").permute(0, 2, 1, 3)[:, 1:]
+    apart.copy_(K)
+    for rep_pos in (0, 2):
+        a = hipattn.hip_mask_estimate(Q, K, 256 * bk, bq, bk, rep_pos=rep_pos)
+        b = hipattn.hip_mask_estimate(Q, K, 256 * bk, bq, bk, rep_pos=rep_pos, kv_lens=lens)
+        c = hipattn.hip_mask_estimate(Q, apart, 256 * bk, bq, bk, rep_pos=rep_pos)
+        assert torch.equal(a, b) and torch.equal(a, c)
 
 
 @pytest.mark.parametrize("page", [0, 16])

@@ -35,6 +35,22 @@ def test_row_offsets_of_the_prefill_attention_stay_within_32_bits(tmp_path):
     assert out.strip() == "ok 1"
 
 
+def test_workgroups_per_compute_unit_follow_the_bytes_of_keys(tmp_path):
+    # 128 channels: 24 MB are 98304 tokens, 128 MB 524288; what a paged table or a cache with lengths on the device could hold cuts
+    # nothing, and the pitch of the rows does not come into it
+    out = run(tmp_path, r"""
+    struct { int64_t T; int d; bool known; int want; } c[] = {
+        {32768, 128, true, 0}, {65536, 128, true, 0}, {98304, 128, true, 0}, {98305, 128, true, 2}, {524288, 128, true, 2}, {524289, 128, true, 1},
+        {1 << 20, 128, true, 1}, {131072, 64, true, 0}, {1 << 20, 64, true, 0}, {(1 << 20) + 1, 64, true, 2},
+        {131072, 128, false, 0}, {1 << 20, 128, false, 0}, {1 << 23, 64, false, 0}};
+    for (auto &x : c) if (mask_workgroups_per_cu(x.T, x.d, x.known) != x.want) { std::printf("%lld %d\n", (long long)x.T, x.d); return 1; }
+    std::printf("ok\n");
+    """)
+    assert out.strip() == "ok"
+    src = (CSRC / "mask_mfma_impl.h").read_text()
+    assert "mask_workgroups_per_cu(p.max_kv_len, D, p.kv_lens == nullptr)" in src and "p.max_kv_len * p.ks_r" not in src
+
+
 def test_the_prefill_attention_uses_the_rule_it_is_tested_with():
     src = (CSRC / "attn_mfma.hip").read_text()
     assert "rows_by_lane_offset(p.max_kv_len, p.ks_r * 2, p.d)" in src
