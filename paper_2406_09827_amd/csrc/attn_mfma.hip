@@ -16,7 +16,8 @@
 //   * The keys of a work item - selected blocks, sink, window - are worked out before the loop, 16 tiles of them, into a list
 //     in LDS (position of every key; over a paged pool its page as well), with two bits per tile that say whether any key
 //     counts and whether any needs masking.  Longer lists are refilled 8 tiles at a time.  The loop itself then only reads
-//     its rows' positions.  (Any k in 72 KB of LDS: two workgroups to a compute unit where an index row of 1024 entries in LDS left one.)
+//     its rows' positions.  (Any k in 72 KB of LDS, over pages 80: two workgroups to a compute unit where an index row of 1024
+//     entries in LDS left one.)
 //   * global_load_lds_dwordx4 delivers lane l's 16 bytes at M0 + 16 l without passing through registers or the LDS
 //     instruction pipe.  Load j of a tile fills LDS rows RPI j .. RPI j + RPI - 1 (RPI = 4 rows of 256 bytes or 8 of 128); lane
 //     group lg supplies gathered key NLD lg + j (a lane's rows are consecutive keys: one or two 16-byte reads of the list tell
@@ -66,8 +67,12 @@ constexpr int kListTiles = 16;   // tiles whose keys are listed; refilled by hal
 //         slice base; MODE 1: paged pool; MODE 2: contiguous, any size (64-bit row addresses).
 // WPI: waves per work item.  With 2 or 4 the workgroup takes ONE work item; wave w walks key tiles w, w + WPI, ... with its own
 //      softmax state and the states are merged through LDS at the end.
+// Waves per SIMD: two with 128 channels; with 64 four (1 to 3 registers spilled; three waves without: 16k tokens, 32 heads 131 us, so
+// 125), over pages three, which is what their LDS leaves room for.  Over pages a row's address takes 64-bit multiplies: once for its
+// key and value (page sizes 16 and 64 alike; for each of them: 181 us with 64 channels, now 160; 383 with 128, now 328; as many
+// waves as a target of four left, two: 229).
 template <int D, int MODE, int WPI>
-__global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2))) void attn_mfma_kernel(KParams p, int log_bk, int mtn, int xcd_map)
+__global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_waves_per_eu(D == 64 ? (MODE == 1 ? 3 : 4) : 2))) void attn_mfma_kernel(KParams p, int log_bk, int mtn, int xcd_map)
 {
     constexpr bool PAGED = MODE == 1, SPLIT = WPI > 1;
     constexpr int W = SPLIT ? WPI : 4;   // waves of the workgroup
@@ -212,20 +217,22 @@ __global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_wa
         any = (uint32_t)__builtin_amdgcn_readfirstlane((int)any);
         mask = (uint32_t)__builtin_amdgcn_readfirstlane((int)mask);
     };
-    // Where this lane's rows of a listed tile are.
-    struct rows_t { uint32_t off[NLD]; int pg[PAGED ? NLD : 1]; };
+    // Where this lane's rows of a listed tile are.  Paged: bytes from the start of the pool, once for the key and the value; bit 0: of
+    // the backing pool (a negative page-table entry).
+    struct rows_t { uint32_t off[PAGED ? 1 : NLD]; int64_t at[PAGED ? NLD : 1]; };
     auto read_rows = [&](int i, rows_t &R) __attribute__((always_inline)) {
         const int x = (i % kListTiles) * 32 + lg * NLD;
 #pragma unroll
         for (int j = 0; j < NLD; j += 4) {
             const int4 t4 = *(const int4 *)(list + x + j);
-            R.off[j] = (uint32_t)t4.x; R.off[j + 1] = (uint32_t)t4.y; R.off[j + 2] = (uint32_t)t4.z; R.off[j + 3] = (uint32_t)t4.w;
-        }
-        if constexpr (PAGED) {
-#pragma unroll
-            for (int j = 0; j < NLD; j += 4) {
+            if constexpr (PAGED) {
                 const int4 p4 = *(const int4 *)(pages + x + j);
-                R.pg[j] = p4.x; R.pg[j + 1] = p4.y; R.pg[j + 2] = p4.z; R.pg[j + 3] = p4.w;
+                const int tk[4] = {t4.x, t4.y, t4.z, t4.w}, pg[4] = {p4.x, p4.y, p4.z, p4.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    R.at[j + e] = row_offset_in<true>(p, b, hk, max(tk[e], 0), page_in_pool(pg[e])) * 2 + (pg[e] < 0 ? 1 : 0);
+            } else {
+                R.off[j] = (uint32_t)t4.x; R.off[j + 1] = (uint32_t)t4.y; R.off[j + 2] = (uint32_t)t4.z; R.off[j + 3] = (uint32_t)t4.w;
             }
         }
         if constexpr (MODE == 0) {
@@ -257,14 +264,11 @@ __global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_wa
                                   :: "v"(vo), "s"(base), "s"(dst) : "memory", "m0");
             } else {
                 const char *src;
-                const int tr = max((int)R.off[j], 0);
                 if constexpr (PAGED) {
-                    // (a negative page-table entry names a page of the backing pools)
-                    const int e = R.pg[j];
-                    const bf16_t *pool = (const bf16_t *)(val ? pool_of(e, Vbase, p.Vback) : pool_of(e, Kbase, p.Kback));
-                    src = (const char *)(pool + row_offset_in<true>(p, b, hk, tr, page_in_pool(e))) + chunk;
+                    const char *pool = (const char *)(val ? p.V : p.K), *backing = (const char *)(val ? p.Vback : p.Kback) - 1;
+                    src = (R.at[j] & 1 ? backing : pool) + R.at[j] + chunk;
                 } else {
-                    src = (const char *)((val ? Vbase : Kbase) + seq_off + (int64_t)tr * p.ks_r) + chunk;
+                    src = (const char *)((val ? Vbase : Kbase) + seq_off + (int64_t)max((int)R.off[j], 0) * p.ks_r) + chunk;
                 }
                 src -= back;
                 if (j & 3) asm volatile("global_load_lds_dwordx4 %0, off offset:%1" :: "v"(src), "i"(back) : "memory");

@@ -2,6 +2,8 @@
 import subprocess
 from pathlib import Path
 
+from paper_2406_09827_amd import build
+
 CSRC = Path(__file__).resolve().parents[1] / "paper_2406_09827_amd" / "csrc"
 
 
@@ -55,3 +57,15 @@ def test_the_prefill_attention_uses_the_rule_it_is_tested_with():
     src = (CSRC / "attn_mfma.hip").read_text()
     assert "rows_by_lane_offset(p.max_kv_len, p.ks_r * 2, p.d)" in src
     assert src.count("kRowBias - back") == 1 and src.count(": Kseq) - kRowBias") == 1 and "3072" not in src
+
+
+def occupancy_failures(source: str) -> list:
+    """The kernels of a source that the compiler could not give the waves per SIMD they ask for (it then gives up on a target)."""
+    r = subprocess.run([build.HIPCC, *build.FLAGS, "-Rpass-analysis=kernel-resource-usage", "--cuda-device-only", "-c", str(CSRC / source),
+                        "-o", "/dev/null"], capture_output=True, text=True)
+    assert r.returncode == 0 and "Occupancy [waves/SIMD]" in r.stderr, r.stderr
+    return [line for line in r.stderr.splitlines() if "failed to meet occupancy target" in line]
+
+
+def test_attention_kernels_get_the_waves_they_ask_for():
+    assert occupancy_failures("attn_mfma.hip") == []
