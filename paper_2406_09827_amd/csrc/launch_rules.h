@@ -34,4 +34,26 @@ inline int mask_workgroups_per_cu(int64_t max_kv_len, int d, bool lengths_known)
     return key_bytes > (128 << 20) ? 1 : 2;
 }
 
+// Decode mask estimation: waves per (sequence, head), by the number of problems (`step`: branches per stage of a wave):
+//   up to 256 (one per compute unit) and k/bk <= 512: sixteen, unless the branches of a round are one stage or less for each
+//       of four waves.  Measured, d = 128, bk = 2, four waves / sixteen: 32 problems of 32768 tokens k/bk = 32 20.0 / 18.4 us,
+//       256 42.7 / 37.5, of 65536 tokens over pages 512 119 / 86; 256 problems k/bk = 32 23.8 / 22.5, 256 55.6 / 53.6; beyond a
+//       problem per compute unit 320 problems 256 72 / 99, 384 problems of 65536 tokens 512 167 / 202.  Stages of four rows (eight
+//       make no difference at sixteen waves: 37.5 / 37.5 and 53.6 / 53.8 us, k/bk = 512 over pages 79 / 86, contiguous 115 / 109).
+//       With eight scored rows a block and k/bk above 256 the sixteen-wave kernels spill (24 registers over pages, 6 contiguous)
+//       and are mostly the better ones all the same: k/bk = 512, 32768 tokens, four / sixteen: 32
+//       problems 86.9 / 67.8 us, over pages 151 / 79.6, 64 channels 48.4 / 41.8; 256 problems 140 / 159, over pages 225 / 159.
+//       A contiguous slice of 2 GB or more, a million tokens stored token by token with 8 kv heads: 32 problems k/bk = 256 91.9 /
+//       78.6, 128 problems 512 195 / 188.
+//   up to 8192, or 16384 with k/bk <= 256: four, so that enough loads are in flight per compute unit and the selection of one
+//       problem overlaps with the loads of the others; beyond that one (nothing computed twice, no barriers).  Measured with 32
+//       query heads over 8 kv heads, four waves / one: 8192 problems of 8192 tokens, k/bk = 256 681 / 711 us; 16384 of 4096 849 /
+//       893, of 8192, k/bk = 128 963 / 1007, of 3000, k/bk = 512 832 / 756; 32768 of 2048, k/bk = 256 944 / 928.  (So many
+//       problems over slices of 2 GB or more do not fit the memory: there is no such kernel, they take four.)
+inline int decode_mask_waves(int64_t problems, int kb, int step, bool wide_slice)
+{
+    if (problems <= 256 && kb <= 512 && 2 * kb > 4 * step) return 16;
+    return problems <= (kb <= 256 ? 16384 : 8192) || wide_slice ? 4 : 1;
+}
+
 }  // namespace hipattn

@@ -337,7 +337,8 @@ static hipError_t launch_r(const KParams &p, dim3 grid, int xcd_map, hipStream_t
     do {                                                                                                    \
         if (p.page_table) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, 1, WS>), grid, block, 0, st, p, xcd_map);  \
         else if (narrow) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, 0, WS>), grid, block, 0, st, p, xcd_map);   \
-        else if constexpr (WS == 4) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, 2, WS>), grid, block, 0, st, p, xcd_map); \
+        else if constexpr (WS > 1) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, 2, WS>), grid, block, 0, st, p, xcd_map); \
+        else return hipErrorInvalidValue;   /* (decode_mask_waves takes such a slice to four waves) */                \
     } while (0)
     // E registers of 64 branch slots: every count of the selection is a compare and a ballot per register, whether the
     // slots are in use or not (k/bk = 32, both with the bit search, four registers / two: 1024 problems of 65536 tokens
@@ -351,16 +352,6 @@ static hipError_t launch_r(const KParams &p, dim3 grid, int xcd_map, hipStream_t
     return hipGetLastError();
 }
 
-// Waves per (sequence, head), by the number of problems:
-//   up to 256 (one per compute unit) and k/bk <= 512: sixteen, unless the branches of a round are one stage or less for each
-//       of four waves.  Measured, d = 128, bk = 2, four waves / sixteen: 32 problems of 32768 tokens k/bk = 32 20.0 / 18.4 us,
-//       256 42.7 / 37.5, of 65536 tokens over pages 512 119 / 86; 256 problems k/bk = 32 23.8 / 22.5, 256 55.6 / 53.6; beyond a
-//       problem per compute unit 320 problems 256 72 / 99, 384 problems of 65536 tokens 512 167 / 202.  Stages of four rows (eight
-//       make no difference at sixteen waves: 37.5 / 37.5 and 53.6 / 53.8 us, k/bk = 512 over pages 79 / 86, contiguous 115 / 109).
-//   up to 8192, or 16384 with k/bk <= 256: four, so that enough loads are in flight per compute unit and the selection of one
-//       problem overlaps with the loads of the others; beyond that one (nothing computed twice, no barriers).  Measured with 32
-//       query heads over 8 kv heads, four waves / one: 8192 problems of 8192 tokens, k/bk = 256 681 / 711 us; 16384 of 4096 849 /
-//       893, of 8192, k/bk = 128 963 / 1007, of 3000, k/bk = 512 832 / 756; 32768 of 2048, k/bk = 256 944 / 928.
 template <int BK, int D>
 static hipError_t launch_e(const KParams &p, hipStream_t st)
 {
@@ -368,10 +359,10 @@ static hipError_t launch_e(const KParams &p, hipStream_t st)
     const int64_t groups = (int64_t)p.batch * p.hkv;
     const int xcd_map = groups % 8 == 0 ? 1 : 0;
     const dim3 grid((unsigned)problems);
-    if (!p.page_table && !narrow_slice(p)) return launch_r<BK, D, 8, 4>(p, grid, xcd_map, st);
     constexpr int ROWS = BK < 4 ? 4 : BK, STEP = 512 / D * (ROWS / BK);   // branches per stage of a wave
-    if (problems <= 256 && p.kb <= 512 && 2 * p.kb > 4 * STEP) return launch_r<BK, D, ROWS, 16>(p, grid, xcd_map, st);
-    if (problems <= (p.kb <= 256 ? 16384 : 8192)) return launch_r<BK, D, 8, 4>(p, grid, xcd_map, st);
+    const int waves = decode_mask_waves(problems, p.kb, STEP, !p.page_table && !narrow_slice(p));
+    if (waves == 16) return launch_r<BK, D, ROWS, 16>(p, grid, xcd_map, st);
+    if (waves == 4) return launch_r<BK, D, 8, 4>(p, grid, xcd_map, st);
     return launch_r<BK, D, 8, 1>(p, dim3((unsigned)((problems + 3) / 4)), 0, st);
 }
 

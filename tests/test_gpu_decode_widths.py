@@ -1,7 +1,9 @@
 """Decode on either side of the line between sixteen and four waves per (sequence, head): 256 and 264 problems, block lists
 from less than a stage of one wave to several stages of every wave, at every block width and head dim."""
 import pytest
+import torch
 
+import paper_2406_09827_amd as hipattn
 from paper_2406_09827_amd import synth
 from tests import gpu_util as U
 
@@ -42,3 +44,20 @@ def test_short_block_lists(bk, d, k, page):
         T = 6 * k + 41
         w = synth.Workload("decode_short", 9, 8, 2, d, 1, T, k, 1, bk, "bf16", rho=0.9, ragged=(k, T), page_size=page, integer=True, seed=821 + bk)
         U.run_case(w, 0, n_sink=n_sink, n_window=n_window, b_sk=b_sk)
+
+
+@pytest.mark.parametrize("bk,d,k", [(1, 64, 20), (2, 128, 256), (4, 64, 900), (8, 128, 4096), (2, 64, 1200)])
+def test_slices_beyond_32_bit_offsets(bk, d, k):
+    # rows 512 KB apart: a slice of over 2 GB, on the sixteen-wave (12 problems) and the four-wave kernels.  Same indices as from
+    # the packed keys.
+    T, pitch, hq = max(4100, 4 * k // 3), 1 << 18, 4
+    w = synth.Workload("wide_slice", 1, hq, 1, d, 1, T, k, 1, bk, "bf16", rho=0.9, integer=True, seed=831)
+    K = synth.make_inputs(w, device="cuda", threads=4)["K"]
+    far = torch.empty(T * pitch, dtype=torch.bfloat16, device="cuda").as_strided((1, 1, T, d), (T * pitch, T * pitch, pitch, 1))
+    far.copy_(K)
+    for batch in (3, 66):
+        Q = torch.randn(batch, hq, 1, d, device="cuda", generator=torch.Generator(device="cuda").manual_seed(batch)).bfloat16()
+        lens = torch.tensor([T - 7 * (i % 5) for i in range(batch)], dtype=torch.int32, device="cuda")
+        for rep_pos in (0, 1):
+            a, b = (hipattn.hip_mask_estimate(Q, x.expand(batch, 1, T, d), k, 1, bk, kv_lens=lens, rep_pos=rep_pos) for x in (K, far))
+            assert torch.equal(a, b)

@@ -53,6 +53,23 @@ def test_workgroups_per_compute_unit_follow_the_bytes_of_keys(tmp_path):
     assert "mask_workgroups_per_cu(p.max_kv_len, D, p.kv_lens == nullptr)" in src and "p.max_kv_len * p.ks_r" not in src
 
 
+def test_waves_of_the_decode_mask(tmp_path):
+    # the lines between sixteen, four and one wave per problem; a slice beyond 32-bit offsets changes nothing below the last one
+    out = run(tmp_path, r"""
+    struct { int64_t problems; int kb, step; int want, want_wide; } c[] = {
+        {1, 256, 4, 16, 16}, {256, 256, 4, 16, 16}, {257, 256, 4, 4, 4}, {32, 8, 4, 4, 4}, {32, 9, 4, 16, 16}, {32, 512, 4, 16, 16}, {32, 513, 4, 4, 4},
+        {16384, 256, 4, 4, 4}, {16385, 256, 4, 1, 4}, {8192, 257, 4, 4, 4}, {8193, 257, 4, 1, 4}};
+    for (auto &x : c)
+        if (decode_mask_waves(x.problems, x.kb, x.step, false) != x.want || decode_mask_waves(x.problems, x.kb, x.step, true) != x.want_wide) {
+            std::printf("%lld %d\n", (long long)x.problems, x.kb);
+            return 1;
+        }
+    std::printf("ok\n");
+    """)
+    assert out.strip() == "ok"
+    assert "decode_mask_waves(problems, p.kb, STEP, !p.page_table && !narrow_slice(p))" in (CSRC / "mask_decode_impl.h").read_text()
+
+
 def test_the_prefill_attention_uses_the_rule_it_is_tested_with():
     src = (CSRC / "attn_mfma.hip").read_text()
     assert "rows_by_lane_offset(p.max_kv_len, p.ks_r * 2, p.d)" in src
