@@ -501,11 +501,19 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
 }
 
 // Waves per SIMD that LDS and registers are laid out for: 10 KB of LDS per wave with up to 512 branch slots (8 KB of it the
-// tile at head dim 128), which makes four; 1024 slots or a table of pages three, 2048 slots two.
+// tile at head dim 128), which makes four; 1024 slots or a table of pages three, 2048 slots or 1024 with a table two, 2048
+// with a table one.
+// Two query tiles at head dim 128 and three waves spill: over pages 1 to 6 registers with 256 slots, 3 to 13 with 512, 10 to 24 with
+// 1024 (a workgroup per item), contiguous 2 to 10 with 1024.  Measured, 64-row blocks over 16384 tokens, three waves / two without
+// spills: a workgroup per item over pages, the last 256 rows of 32 heads, bk = 4, k/bk = 512 124 / 74 us (2048 rows 309 / 211),
+// bk = 1 74 / 63, bk = 2 71 / 67, k/bk = 128 38.5 / 37.7: two there.  A wave per item, whole prompts over pages, bk = 2, k/bk = 128
+// 340 / 360, 256 511 / 528, 512 level (two fit); contiguous, k/bk = 512, bk = 1 470 / 483, bk = 2 628 / 665, bk = 4 809 / 832,
+// bk = 8 860 / 887 (8 heads 151 / 145, 200 / 197 and level): three.
+// One tile, bk = 1 and 512 slots over pages, a workgroup per item spills 2 at four waves: 1024 rows 70 us, at three waves 89.
 constexpr int mask_waves(int MT, int E, int D, bool PAGED, bool SPLIT)
 {
     const int lds_wave = 32 * D * 2 + (SPLIT ? 64 * E : 256 * E) * (PAGED ? 2 : 1) + (SPLIT ? 32 * E : 0);
-    const int by_lds = (160 << 10) / (4 * lds_wave), by_regs = MT == 2 && D == 128 ? 3 : E >= 32 ? 2 : E >= 16 ? 3 : 4;
+    const int by_lds = (160 << 10) / (4 * lds_wave), by_regs = MT == 2 && D == 128 ? (PAGED && SPLIT ? 2 : 3) : E >= 32 ? 2 : E >= 16 ? 3 : 4;
     return by_lds < by_regs ? by_lds : by_regs;
 }
 template <int MT, int E, int D, bool PAGED, int LB, int WPI, bool SHARE>
