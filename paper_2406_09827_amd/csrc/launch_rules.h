@@ -34,7 +34,8 @@ inline int mask_workgroups_per_cu(int64_t max_kv_len, int d, bool lengths_known)
     return key_bytes > (128 << 20) ? 1 : 2;
 }
 
-// Decode mask estimation: waves per (sequence, head), by the number of problems (`step`: branches per stage of a wave):
+// Decode mask estimation: waves per (sequence, head), by the number of problems (`step`: branches per stage of a wave,
+// `step8`: with eight rows a stage, as four waves and one take them):
 //   up to 256 (one per compute unit) and k/bk <= 512: sixteen, unless the branches of a round are one stage or less for each
 //       of four waves.  Measured, d = 128, bk = 2, four waves / sixteen: 32 problems of 32768 tokens k/bk = 32 20.0 / 18.4 us,
 //       256 42.7 / 37.5, of 65536 tokens over pages 512 119 / 86; 256 problems k/bk = 32 23.8 / 22.5, 256 55.6 / 53.6; beyond a
@@ -45,15 +46,20 @@ inline int mask_workgroups_per_cu(int64_t max_kv_len, int d, bool lengths_known)
 //       problems 86.9 / 67.8 us, over pages 151 / 79.6, 64 channels 48.4 / 41.8; 256 problems 140 / 159, over pages 225 / 159.
 //       A contiguous slice of 2 GB or more, a million tokens stored token by token with 8 kv heads: 32 problems k/bk = 256 91.9 /
 //       78.6, 128 problems 512 195 / 188.
-//   up to 8192, or 16384 with k/bk <= 256: four, so that enough loads are in flight per compute unit and the selection of one
-//       problem overlaps with the loads of the others; beyond that one (nothing computed twice, no barriers).  Measured with 32
-//       query heads over 8 kv heads, four waves / one: 8192 problems of 8192 tokens, k/bk = 256 681 / 711 us; 16384 of 4096 849 /
-//       893, of 8192, k/bk = 128 963 / 1007, of 3000, k/bk = 512 832 / 756; 32768 of 2048, k/bk = 256 944 / 928.  (So many
-//       problems over slices of 2 GB or more do not fit the memory: there is no such kernel, they take four.)
-inline int decode_mask_waves(int64_t problems, int kb, int step, bool wide_slice)
+//   up to 8192, or 16384 of 128 channels over contiguous keys with k/bk <= 256 and eight stages or more: four, so that enough loads
+//       are in flight per compute unit and the selection of one problem overlaps with the loads of the others; beyond that one
+//       (nothing computed twice, no barriers).  Measured with 32 query heads over 8 kv heads, four waves / one: 8192 problems of
+//       8192 tokens, k/bk = 256 681 / 711 us; 16384 of 4096 849 / 893, of 8192, k/bk = 128 963 / 1007, of 3000, k/bk = 512 832 /
+//       756; 32768 of 2048, k/bk = 256 944 / 928.  12288 of 4096 tokens, bk = 2: k/bk = 16 240 / 166, 32 (four stages) 263 / 248,
+//       64 350 / 369, 256 642 / 673; over pages 32 322 / 255, 64 420 / 391, 256 759 / 727; with 64 channels 16 219 / 81, 64 220 /
+//       184, 256 355 / 342, over pages 64 264 / 189, 256 418 / 369.  (So many problems over slices of 2 GB or more do not fit the
+//       memory: there is no such kernel, they take four.)
+enum class Slice { paged, narrow, wide };   // contiguous: within 32-bit offsets or not
+inline int decode_mask_waves(int64_t problems, int kb, int d, int step, int step8, Slice slice)
 {
     if (problems <= 256 && kb <= 512 && 2 * kb > 4 * step) return 16;
-    return problems <= (kb <= 256 ? 16384 : 8192) || wide_slice ? 4 : 1;
+    if (problems <= 8192 || slice == Slice::wide) return 4;
+    return problems <= 16384 && slice == Slice::narrow && d == 128 && kb <= 256 && 2 * kb >= 8 * step8 ? 4 : 1;
 }
 
 }  // namespace hipattn

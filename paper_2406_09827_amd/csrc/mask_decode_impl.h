@@ -360,7 +360,8 @@ static hipError_t launch_e(const KParams &p, hipStream_t st)
     const int xcd_map = groups % 8 == 0 ? 1 : 0;
     const dim3 grid((unsigned)problems);
     constexpr int ROWS = BK < 4 ? 4 : BK, STEP = 512 / D * (ROWS / BK);   // branches per stage of a wave
-    const int waves = decode_mask_waves(problems, p.kb, STEP, !p.page_table && !narrow_slice(p));
+    const Slice slice = p.page_table ? Slice::paged : narrow_slice(p) ? Slice::narrow : Slice::wide;
+    const int waves = decode_mask_waves(problems, p.kb, D, STEP, 512 / D * (8 / BK), slice);
     if (waves == 16) return launch_r<BK, D, ROWS, 16>(p, grid, xcd_map, st);
     if (waves == 4) return launch_r<BK, D, 8, 4>(p, grid, xcd_map, st);
     return launch_r<BK, D, 8, 1>(p, dim3((unsigned)((problems + 3) / 4)), 0, st);

@@ -54,20 +54,21 @@ def test_workgroups_per_compute_unit_follow_the_bytes_of_keys(tmp_path):
 
 
 def test_waves_of_the_decode_mask(tmp_path):
-    # the lines between sixteen, four and one wave per problem; a slice beyond 32-bit offsets changes nothing below the last one
+    # the lines between sixteen, four and one wave per problem
     out = run(tmp_path, r"""
-    struct { int64_t problems; int kb, step; int want, want_wide; } c[] = {
-        {1, 256, 4, 16, 16}, {256, 256, 4, 16, 16}, {257, 256, 4, 4, 4}, {32, 8, 4, 4, 4}, {32, 9, 4, 16, 16}, {32, 512, 4, 16, 16}, {32, 513, 4, 4, 4},
-        {16384, 256, 4, 4, 4}, {16385, 256, 4, 1, 4}, {8192, 257, 4, 4, 4}, {8193, 257, 4, 1, 4}};
-    for (auto &x : c)
-        if (decode_mask_waves(x.problems, x.kb, x.step, false) != x.want || decode_mask_waves(x.problems, x.kb, x.step, true) != x.want_wide) {
-            std::printf("%lld %d\n", (long long)x.problems, x.kb);
-            return 1;
-        }
+    const Slice N = Slice::narrow, W = Slice::wide, P = Slice::paged;
+    struct { int64_t problems; int kb, d; Slice slice; int want; } c[] = {
+        {1, 256, 128, N, 16}, {256, 256, 128, W, 16}, {256, 256, 64, P, 16}, {257, 256, 128, N, 4}, {257, 256, 128, W, 4}, {32, 16, 128, N, 4}, {32, 17, 128, N, 16},
+        {32, 512, 128, P, 16}, {32, 513, 128, P, 4}, {8192, 16, 64, P, 4}, {8193, 256, 128, N, 4}, {8193, 256, 128, P, 1}, {8193, 256, 64, N, 1}, {8193, 257, 128, N, 1},
+        {16384, 64, 128, N, 4}, {16384, 63, 128, N, 1}, {16384, 16, 64, P, 1}, {16385, 256, 128, N, 1}, {16385, 256, 128, W, 4}};
+    for (auto &x : c) {   // bk = 2: stages of four and of eight rows
+        const int rpw = 512 / x.d, got = decode_mask_waves(x.problems, x.kb, x.d, rpw * 2, rpw * 4, x.slice);
+        if (got != x.want) { std::printf("%lld problems, k/bk %d, d %d: %d\n", (long long)x.problems, x.kb, x.d, got); return 1; }
+    }
     std::printf("ok\n");
     """)
     assert out.strip() == "ok"
-    assert "decode_mask_waves(problems, p.kb, STEP, !p.page_table && !narrow_slice(p))" in (CSRC / "mask_decode_impl.h").read_text()
+    assert "decode_mask_waves(problems, p.kb, D, STEP, 512 / D * (8 / BK), slice)" in (CSRC / "mask_decode_impl.h").read_text()
 
 
 def test_the_prefill_attention_uses_the_rule_it_is_tested_with():
