@@ -14,6 +14,29 @@ inline bool rows_by_lane_offset(int64_t max_kv_len, int64_t row_bytes, int d)
     return max_kv_len < (1 << 24) && row_bytes < (1 << 24) && (max_kv_len - 1) * row_bytes + 2 * d + kRowBias <= (1LL << 32);
 }
 
+// Prefill mask: a workgroup per work item (its waves share the tiles and select redundantly) or a wave, by the number of work items.
+// The fewer blocks a round has, the less there is to share.  Measured, 16384 tokens, 32 heads over 8 kv heads, a wave / a workgroup
+// per item, us; 128 channels and bk = 2 if not said otherwise:
+//   k/bk      512 items      768         1024          1504
+//   32        35 / 29        36 / 34     36 / 38       41 / 58     64-row blocks, bk = 4: 52 / 37, 52 / 42, 52 / 65, 61 / 74
+//   64        45 / 32        44 / 36     44 / 41       52 / 65     bk = 1: 37 / 31, 38 / 36, 37 / 40, 43 / 62
+//   128       60 / 36        59 / 42     58 / 49       72 / 75     64 channels 45 / 29, 46 / 33, 46 / 37, 52 / 47
+//   256       90 / 49        89 / 58     89 / 72      108 / 106    64-row blocks, bk = 4, over pages 153 / 81, 154 / 123, 157 / 149, 220 / 213
+//   512      128 / 68       127 / 86    127 / 105     161 / 150    bk = 1: 105 / 61, 105 / 71, 104 / 111, 124 / 129
+//   1024     172 / 91          -        174 / 163     208 / 233    16 items 205 / 66; 64-row blocks, bk = 4: 16 items 223 / 66, 512 220 / 106,
+//                                                                  1024 225 / 195; 64 channels, bk = 1 132 / 73, -, 135 / 134, 146 / 191
+// 2048 items, k/bk = 256, over 32k tokens 157 / 182.
+// Over pages with 128 channels and k/bk above 512 a wave per item would leave one wave a SIMD, a workgroup two: a workgroup whatever
+// the number (k/bk = 1024, 1024 items 210 / 184, 2048 413 / 349, 16384 2426 / 1933; 64-row blocks, bk = 4, 8192 items 1608 / 1212;
+// bk = 8, 16384 items 2885 / 1982; k/bk = 600, bk = 1, 16384 items 2039 / 2059).
+// (The line at 1024 is at 768 for two query tiles of 128 channels: so many workgroups run at a time.)
+inline bool mask_item_per_workgroup(int64_t units, int kb, int d, bool two_tiles, bool paged)
+{
+    if (units <= 512) return true;
+    if (kb > 512) return units <= 1024 || (paged && d == 128);   // (the kernel of the other form is not built)
+    return units <= (two_tiles && d == 128 ? 768 : 1024) ? kb > 32 : units <= 1536 && kb > 128;
+}
+
 // Workgroups of the prefill mask kernel that may share a compute unit (0: as many as fit), by the bytes of a kv head's keys.  Where
 // these do not stay in the caches the kernel waits for the memory side, and what counts is how often the waves of an XCD meet in
 // its L2: fewer workgroups at a time (the launch asks for LDS that it does not use) meet more often.  Measured, in ms, as many as

@@ -501,8 +501,7 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
 }
 
 // Waves per SIMD that LDS and registers are laid out for: 10 KB of LDS per wave with up to 512 branch slots (8 KB of it the
-// tile at head dim 128), which makes four; 1024 slots or a table of pages three, 2048 slots or 1024 with a table two, 2048
-// with a table one.
+// tile at head dim 128), which makes four; 1024 slots or a table of pages three, 2048 slots or 1024 with a table two.
 // Two query tiles at head dim 128 and three waves spill: over pages 1 to 6 registers with 256 slots, 3 to 13 with 512, 10 to 24 with
 // 1024 (a workgroup per item), contiguous 2 to 10 with 1024.  Measured, 64-row blocks over 16384 tokens, three waves / two without
 // spills: a workgroup per item over pages, the last 256 rows of 32 heads, bk = 4, k/bk = 512 124 / 74 us (2048 rows 309 / 211),
@@ -513,7 +512,7 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
 constexpr int mask_waves(int MT, int E, int D, bool PAGED, bool SPLIT)
 {
     const int lds_wave = 32 * D * 2 + (SPLIT ? 64 * E : 256 * E) * (PAGED ? 2 : 1) + (SPLIT ? 32 * E : 0);
-    const int by_lds = (160 << 10) / (4 * lds_wave), by_regs = MT == 2 && D == 128 ? (PAGED && SPLIT ? 2 : 3) : E >= 32 ? 2 : E >= 16 ? 3 : 4;
+    const int by_lds = (160 << 10) / (4 * lds_wave), by_regs = MT == 2 && D == 128 ? (E >= 32 || (PAGED && SPLIT) ? 2 : 3) : E >= 32 ? 2 : E >= 16 ? 3 : 4;
     return by_lds < by_regs ? by_lds : by_regs;
 }
 template <int MT, int E, int D, bool PAGED, int LB, int WPI, bool SHARE>
@@ -536,11 +535,12 @@ static hipError_t launch_mask_mfma_e(const KParams &p, int xcd_map, dim3 grid, b
     };
     // the page-table variant is a separate instantiation: a table read in the row-offset code
     // would otherwise put a full memory wait into the contiguous path's load pipeline
-    if constexpr (E <= 16) {
-        if (split) return p.page_table ? launch(mask_mfma_kernel<MT, E, D, true, LB, 4, false>, true, true)
-                                       : launch(mask_mfma_kernel<MT, E, D, false, LB, 4, false>, false, true);
+    if (split) return p.page_table ? launch(mask_mfma_kernel<MT, E, D, true, LB, 4, false>, true, true)
+                                   : launch(mask_mfma_kernel<MT, E, D, false, LB, 4, false>, false, true);
+    if (p.page_table) {
+        if constexpr (E < 32 || D == 64) return launch(mask_mfma_kernel<MT, E, D, true, LB, 1, false>, true, false);
+        return hipErrorInvalidValue;
     }
-    if (p.page_table) return launch(mask_mfma_kernel<MT, E, D, true, LB, 1, false>, true, false);
     return share ? launch(mask_mfma_kernel<MT, E, D, false, LB, 1, true>, false, false)
                  : launch(mask_mfma_kernel<MT, E, D, false, LB, 1, false>, false, false);
 }
@@ -560,14 +560,11 @@ template <int LB> hipError_t launch_mask_mfma_lb(const KParams &p, hipStream_t s
     const int64_t per_group = (int64_t)p.g * p.nqb;
     const int64_t units = groups * per_group;
     if (units == 0) return hipSuccess;
-    // Few work items: a workgroup each.  Measured, 32 heads over 8 kv heads, k/bk = 256, a wave / a workgroup per work item:
-    // 1024 items over 32k tokens 121 / 97 us, four ragged sequences in pages 160 / 103; 1504 items over 32k tokens 158 / 153, a
-    // prompt of 1500 tokens 31.4 / 27.1; 2048 items over 32k tokens 157 / 182, a prompt of 2000 (2016 items) 36 / 43.
-    const bool split = units <= 1536 && p.kb <= 512;
+    const bool one_tile = (p.bq + p.b_sq - 1) / p.b_sq <= 32;
+    const bool split = mask_item_per_workgroup(units, p.kb, p.d, !one_tile, p.page_table != nullptr);
     // groups worked on at a time: as many as keep the key rows in flight inside the memory-side cache
     const int xcd_map = (groups % 8 == 0 && (split || per_group % 4 == 0)) ? groups_at_a_time((int64_t)p.max_kv_len * p.d * 2, 160LL << 20) : 0;
     dim3 grid((unsigned)placed_workgroups(xcd_map, split ? 1 : 4, per_group, groups));
-    const bool one_tile = (p.bq + p.b_sq - 1) / p.b_sq <= 32;
     // the four work items of a workgroup are consecutive items of one (sequence, kv head) group
     const bool one_seq = !split && per_group % 4 == 0;
     if constexpr (LB <= 2) {

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("heads", [(4, 1), (6, 2)], ids=["g4", "g3"])
 @pytest.mark.parametrize("k,bk,d,bq,rep_pos", [
     (128, 1, 128, 32, 0), (258, 2, 128, 64, 1), (256, 1, 64, 64, 2), (1028, 4, 64, 32, 0), (1024, 2, 128, 32, 2),
-    (514, 1, 128, 64, 0), (64, 2, 64, 16, 0), (1032, 8, 128, 48, 1),
+    (514, 1, 128, 64, 0), (64, 2, 64, 16, 0), (1032, 8, 128, 48, 1), (2048, 2, 128, 32, 0), (1030, 2, 64, 32, 1),
 ])
 def test_table_sizes(k, bk, d, bq, rep_pos, heads, page):
     hq, hkv = heads

@@ -53,6 +53,19 @@ def test_workgroups_per_compute_unit_follow_the_bytes_of_keys(tmp_path):
     assert "mask_workgroups_per_cu(p.max_kv_len, D, p.kv_lens == nullptr)" in src and "p.max_kv_len * p.ks_r" not in src
 
 
+def test_workgroup_or_wave_per_item_of_the_prefill_mask(tmp_path):
+    out = run(tmp_path, r"""
+    struct { int64_t units; int kb, d; bool two_tiles, paged, want; } c[] = {
+        {1, 1024, 128, 0, 0, 1}, {512, 16, 64, 1, 1, 1}, {513, 32, 128, 0, 0, 0}, {513, 33, 128, 1, 1, 1}, {768, 100, 128, 1, 0, 1}, {769, 128, 128, 1, 0, 0},
+        {769, 129, 128, 1, 0, 1}, {1024, 33, 64, 1, 0, 1}, {1024, 33, 128, 0, 1, 1}, {1025, 128, 128, 0, 1, 0}, {1025, 129, 128, 0, 1, 1}, {1536, 512, 64, 0, 0, 1},
+        {1537, 256, 128, 0, 1, 0}, {1024, 1024, 64, 0, 1, 1}, {1025, 1024, 64, 0, 1, 0}, {1025, 1024, 128, 0, 0, 0}, {100000, 513, 128, 1, 1, 1}, {100000, 512, 128, 1, 1, 0}};
+    for (auto &x : c) if (mask_item_per_workgroup(x.units, x.kb, x.d, x.two_tiles, x.paged) != x.want) { std::printf("%lld %d\n", (long long)x.units, x.kb); return 1; }
+    std::printf("ok\n");
+    """)
+    assert out.strip() == "ok"
+    assert "split = mask_item_per_workgroup(units, p.kb, p.d, !one_tile, p.page_table != nullptr);" in (CSRC / "mask_mfma_impl.h").read_text()
+
+
 def test_waves_of_the_decode_mask(tmp_path):
     # the lines between sixteen, four and one wave per problem
     out = run(tmp_path, r"""
