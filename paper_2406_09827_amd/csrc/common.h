@@ -407,13 +407,13 @@ __device__ __forceinline__ bool place_item(int xcd_map, uint32_t bid, int upw, i
     }
     // gc = xcd_map is 1, 2, 4 or 8; upw is 1 or 4
     const uint32_t lgc = (uint32_t)__builtin_ctz((uint32_t)xcd_map), ls = 3u - lgc, x = bid & 7u, q = bid >> 3;
-    const uint32_t wpg = upw == 4 ? per_group >> 2 : per_group;   // workgroups per group
+    const uint32_t wpg = upw == 4 ? (per_group + 3u) >> 2 : per_group;   // workgroups per group (items of the last one may be missing)
     const uint32_t wpp = (wpg + (1u << ls) - 1u) >> ls;            // per XCD and group
     const uint32_t qd = q / wpp, qm = q - qd * wpp;
     const uint32_t w_g = (qm << ls) + (x >> lgc);
     group = (qd << lgc) + (x & ((1u << lgc) - 1u));
     o = w_g * (uint32_t)upw + (uint32_t)unit;
-    return group < groups && w_g < wpg;
+    return group < groups && w_g < wpg && o < per_group;
 }
 
 // Host side: the launch size that goes with place_item, and how many groups to work on at a time: the largest
@@ -424,13 +424,21 @@ inline int64_t placed_workgroups(int xcd_map, int upw, int64_t per_group, int64_
 {
     if (!xcd_map) return (groups * per_group + upw - 1) / upw;
     const int gc = xcd_map, s = 8 / gc;
-    const int64_t wpg = per_group / upw, wpp = (wpg + s - 1) / s;
+    const int64_t wpg = (per_group + upw - 1) / upw, wpp = (wpg + s - 1) / s;
     return 8 * (groups / gc) * wpp;
 }
 inline int groups_at_a_time(int64_t bytes_per_group, int64_t budget_bytes)
 {
     int gc = 8;
     while (gc > 1 && gc * bytes_per_group > budget_bytes) gc >>= 1;
+    return gc;
+}
+// The same for any number of groups: as many at a time as divide it; an odd number is taken in linear order.
+inline int groups_at_a_time_of(int64_t groups, int64_t bytes_per_group, int64_t budget_bytes)
+{
+    if (groups % 2) return 0;
+    int gc = groups_at_a_time(bytes_per_group, budget_bytes);
+    while (groups % gc) gc >>= 1;
     return gc;
 }
 

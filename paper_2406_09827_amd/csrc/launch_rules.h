@@ -29,12 +29,25 @@ inline bool rows_by_lane_offset(int64_t max_kv_len, int64_t row_bytes, int d)
 // Over pages with 128 channels and k/bk above 512 a wave per item would leave one wave a SIMD, a workgroup two: a workgroup whatever
 // the number (k/bk = 1024, 1024 items 210 / 184, 2048 413 / 349, 16384 2426 / 1933; 64-row blocks, bk = 4, 8192 items 1608 / 1212;
 // bk = 8, 16384 items 2885 / 1982; k/bk = 600, bk = 1, 16384 items 2039 / 2059).
+// What is shared inside a workgroup that holds four heads of a query block has to be found in the L2 by workgroups of a head each, so
+// beyond 768 items (512 where the groups, of a sequence and kv head each, go in linear order) the keys that an XCD reads at a time must
+// not be too many.  `gc` of place_item, 0 in linear order; k/bk = 256, bk = 2, a wave / a workgroup per item:
+//   eight groups (gc = 8): 64k tokens 768 items 147 / 112, 1024 148 / 140, 1472 187 / 198; 128k 182 / 178, 203 / 228, 270 / 318
+//   twelve (4): 16k about 900 items 104 / 87, 1400 121 / 111; 32k 128 / 130, 152 / 173; four, 64k 1024 items 149 / 156, 1472 186 / 219
+//   six (2): 16k 103 / 92, 119 / 113; 32k 128 / 146, 150 / 187
+//   one, three, five (0): 16k 89 / 68, 103 / 93, 105 / 111; 32k 124 / 98, 128 / 147, 132 / 159
+//   over pages, where four heads of a workgroup share nothing: eight groups 128k 215 / 178, 232 / 231, 303 / 314; twelve 32k 153 /
+//   130, 183 / 180; six 154 / 148, 182 / 193; three and five in linear order 153 / 148, 183 / 195, 157 / 161, 192 / 211
 // (The line at 1024 is at 768 for two query tiles of 128 channels: so many workgroups run at a time.)
-inline bool mask_item_per_workgroup(int64_t units, int kb, int d, bool two_tiles, bool paged)
+inline bool mask_item_per_workgroup(int64_t units, int kb, int d, bool two_tiles, bool paged, int64_t groups, int gc, int64_t max_kv_len)
 {
     if (units <= 512) return true;
-    if (kb > 512) return units <= 1024 || (paged && d == 128);   // (the kernel of the other form is not built)
-    return units <= (two_tiles && d == 128 ? 768 : 1024) ? kb > 32 : units <= 1536 && kb > 128;
+    if (paged && d == 128 && kb > 512) return true;   // (the kernel of the other form is not built)
+    const int64_t mb = 1 << 20, key_bytes = max_kv_len * d * 2;
+    const bool few = units <= (two_tiles && d == 128 ? 768 : 1024);
+    if (few ? kb <= 32 : units > 1536 || kb <= 128 || kb > 512) return false;
+    if (gc == 0) return key_bytes * groups <= 12 * mb;
+    return paged || units <= 768 || key_bytes <= (few ? 2 : 1) * mb * gc;
 }
 
 // Workgroups of the prefill mask kernel that may share a compute unit (0: as many as fit), by the bytes of a kv head's keys.  Where

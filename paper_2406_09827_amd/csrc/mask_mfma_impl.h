@@ -561,9 +561,13 @@ template <int LB> hipError_t launch_mask_mfma_lb(const KParams &p, hipStream_t s
     const int64_t units = groups * per_group;
     if (units == 0) return hipSuccess;
     const bool one_tile = (p.bq + p.b_sq - 1) / p.b_sq <= 32;
-    const bool split = mask_item_per_workgroup(units, p.kb, p.d, !one_tile, p.page_table != nullptr);
     // groups worked on at a time: as many as keep the key rows in flight inside the memory-side cache
-    const int xcd_map = (groups % 8 == 0 && (split || per_group % 4 == 0)) ? groups_at_a_time((int64_t)p.max_kv_len * p.d * 2, 160LL << 20) : 0;
+    const int gc = groups_at_a_time_of(groups, (int64_t)p.max_kv_len * p.d * 2, 160LL << 20);
+    const bool split = mask_item_per_workgroup(units, p.kb, p.d, !one_tile, p.page_table != nullptr, groups, gc, p.max_kv_len);
+    // Measured, 32 heads' worth of rows over 32k tokens, in linear order / so many groups at a time: three sequences of 2 kv heads (two at a
+    // time) 383 / 316 us, six (four) 454 / 318, 12 heads in threes over 24 groups 956 / 574, over pages 915 / 613; but a wave per item
+    // over pages, two of six at a time 294 / 318 (16k tokens): linear.
+    const int xcd_map = !split && p.page_table && gc == 2 && groups > 2 ? 0 : gc;
     dim3 grid((unsigned)placed_workgroups(xcd_map, split ? 1 : 4, per_group, groups));
     // the four work items of a workgroup are consecutive items of one (sequence, kv head) group
     const bool one_seq = !split && per_group % 4 == 0;

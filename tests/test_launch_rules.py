@@ -55,15 +55,27 @@ def test_workgroups_per_compute_unit_follow_the_bytes_of_keys(tmp_path):
 
 def test_workgroup_or_wave_per_item_of_the_prefill_mask(tmp_path):
     out = run(tmp_path, r"""
-    struct { int64_t units; int kb, d; bool two_tiles, paged, want; } c[] = {
-        {1, 1024, 128, 0, 0, 1}, {512, 16, 64, 1, 1, 1}, {513, 32, 128, 0, 0, 0}, {513, 33, 128, 1, 1, 1}, {768, 100, 128, 1, 0, 1}, {769, 128, 128, 1, 0, 0},
-        {769, 129, 128, 1, 0, 1}, {1024, 33, 64, 1, 0, 1}, {1024, 33, 128, 0, 1, 1}, {1025, 128, 128, 0, 1, 0}, {1025, 129, 128, 0, 1, 1}, {1536, 512, 64, 0, 0, 1},
-        {1537, 256, 128, 0, 1, 0}, {1024, 1024, 64, 0, 1, 1}, {1025, 1024, 64, 0, 1, 0}, {1025, 1024, 128, 0, 0, 0}, {100000, 513, 128, 1, 1, 1}, {100000, 512, 128, 1, 1, 0}};
-    for (auto &x : c) if (mask_item_per_workgroup(x.units, x.kb, x.d, x.two_tiles, x.paged) != x.want) { std::printf("%lld %d\n", (long long)x.units, x.kb); return 1; }
+    struct { int64_t units; int kb, d; bool two_tiles, paged; int groups, gc; int64_t T; bool want; } c[] = {
+        // blocks of a round, query tiles
+        {1, 1024, 128, 0, 0, 8, 8, 1 << 20, 1}, {512, 16, 64, 1, 1, 5, 0, 1 << 20, 1}, {513, 32, 128, 0, 0, 8, 8, 16384, 0}, {513, 33, 128, 1, 1, 8, 8, 16384, 1},
+        {768, 100, 128, 1, 0, 8, 8, 16384, 1}, {769, 128, 128, 1, 0, 8, 8, 16384, 0}, {769, 129, 128, 1, 0, 8, 8, 16384, 1}, {1024, 33, 64, 1, 0, 8, 8, 16384, 1},
+        {1024, 33, 128, 0, 1, 8, 8, 16384, 1}, {1025, 128, 128, 0, 1, 8, 8, 16384, 0}, {1025, 129, 128, 0, 1, 8, 8, 16384, 1}, {1536, 512, 64, 0, 0, 8, 8, 16384, 1},
+        {1537, 256, 128, 0, 1, 8, 8, 16384, 0}, {1024, 1024, 64, 0, 1, 8, 8, 16384, 1}, {1025, 1024, 64, 0, 1, 8, 8, 16384, 0}, {1025, 1024, 128, 0, 0, 8, 8, 16384, 0},
+        {100000, 513, 128, 1, 1, 3, 0, 1 << 20, 1}, {100000, 512, 128, 1, 1, 8, 8, 16384, 0},
+        // keys that an XCD reads at a time
+        {768, 256, 128, 0, 0, 8, 8, 1 << 20, 1}, {769, 256, 128, 0, 0, 8, 8, 65536, 1}, {769, 256, 128, 0, 0, 8, 8, 65537, 0}, {1025, 256, 128, 0, 0, 8, 8, 32768, 1},
+        {1025, 256, 128, 0, 0, 8, 8, 32769, 0}, {1025, 256, 64, 0, 0, 8, 8, 65536, 1}, {900, 256, 128, 0, 0, 12, 4, 32768, 1}, {900, 256, 128, 0, 0, 12, 4, 32769, 0},
+        {900, 256, 128, 0, 0, 6, 2, 16384, 1}, {900, 256, 128, 0, 0, 6, 2, 32768, 0}, {1400, 256, 128, 0, 1, 6, 2, 1 << 20, 1}, {513, 256, 128, 0, 0, 1, 0, 49152, 1},
+        {513, 256, 128, 0, 0, 1, 0, 49153, 0}, {513, 256, 128, 0, 1, 5, 0, 16384, 0}, {1400, 256, 128, 0, 0, 3, 0, 16384, 1}};
+    for (auto &x : c)
+        if (mask_item_per_workgroup(x.units, x.kb, x.d, x.two_tiles, x.paged, x.groups, x.gc, x.T) != x.want) {
+            std::printf("%lld items, k/bk %d, %d groups, %lld tokens\n", (long long)x.units, x.kb, x.groups, (long long)x.T);
+            return 1;
+        }
     std::printf("ok\n");
     """)
     assert out.strip() == "ok"
-    assert "split = mask_item_per_workgroup(units, p.kb, p.d, !one_tile, p.page_table != nullptr);" in (CSRC / "mask_mfma_impl.h").read_text()
+    assert "mask_item_per_workgroup(units, p.kb, p.d, !one_tile, p.page_table != nullptr, groups, gc, p.max_kv_len)" in (CSRC / "mask_mfma_impl.h").read_text()
 
 
 def test_waves_of_the_decode_mask(tmp_path):

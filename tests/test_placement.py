@@ -24,9 +24,10 @@ int main()
     const int maps[] = {0, 1, 2, 4, 8};
     for (int xcd_map : maps)
         for (int upw : {1, 4})
-            for (uint32_t per_group = upw; per_group <= 200; per_group += upw)   // the launchers require per_group % upw == 0 with a map
-                for (uint32_t groups : {8u, 16u, 24u, 40u}) {
-                    if (xcd_map && per_group > 64 && per_group % 12) continue;   // thin out the large ones
+            for (uint32_t per_group = 1; per_group <= 200; ++per_group)
+                for (uint32_t groups : {8u, 16u, 24u, 40u, 2u, 4u, 12u, 6u, 3u}) {
+                    if (xcd_map && groups % xcd_map) continue;   // (groups_at_a_time_of)
+                    if (per_group > 64 && per_group % 12 && per_group % 13) continue;   // thin out the large ones
                     const int64_t wgs = placed_workgroups(xcd_map, upw, per_group, groups);
                     std::vector<int> seen((size_t)groups * per_group, 0);
                     for (int64_t bid = 0; bid < wgs; ++bid)
@@ -58,6 +59,13 @@ int main()
         groups_at_a_time(256 * mb, 160 * mb) != 1 || groups_at_a_time(128 * mb, 768 * mb) != 4 || groups_at_a_time(512 * mb, 768 * mb) != 1 ||
         groups_at_a_time(96 * mb, 768 * mb) != 8) {
         std::printf("groups_at_a_time\n");
+        return 1;
+    }
+    // ... and that divides the number of groups; odd numbers go in linear order
+    if (groups_at_a_time_of(16, 8 * mb, 160 * mb) != 8 || groups_at_a_time_of(12, 8 * mb, 160 * mb) != 4 || groups_at_a_time_of(6, 8 * mb, 160 * mb) != 2 ||
+        groups_at_a_time_of(12, 64 * mb, 160 * mb) != 2 || groups_at_a_time_of(2, 256 * mb, 160 * mb) != 1 || groups_at_a_time_of(1, mb, 160 * mb) != 0 ||
+        groups_at_a_time_of(15, mb, 160 * mb) != 0) {
+        std::printf("groups_at_a_time_of\n");
         return 1;
     }
     std::printf("ok %ld\n", cases);
