@@ -165,7 +165,7 @@ __global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_wa
     // this wave's tiles: all of them, or every WPI-th one
     int nt = SPLIT ? (n_tiles > wave ? (n_tiles - wave + WPI - 1) / WPI : 0) : n_tiles;
 
-    // Lists the keys of the wave's tiles i0 .. i0 + N - 1 (N = 8 or 16; i0 a multiple of 8).  Keys that do not count load
+    // Lists the keys of the wave's tiles i0 .. i0 + N - 1 (N = 4, 8 or 16; i0 a multiple of 8).  Keys that do not count load
     // row 0 of the sequence (always mapped, finite) and get probability 0.  Bit i % 16 of `any`: some key of tile i may count
     // for some row; of `mask`: some (key, row) pair needs masking.
     uint32_t any = 0, mask = 0;
@@ -279,7 +279,14 @@ __global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_wa
     // row r of the score tile is gathered key xkey(r)
     auto xkey = [](int r) __attribute__((always_inline)) { return D == 128 ? r : (r & 25) | ((r & 2) << 1) | ((r & 4) >> 1); };
 
-    list_tiles(0, std::integral_constant<int, kListTiles>{});
+    // (no more tiles than there are, by fours: 64 to 256 keys of 4096 query tiles, all sixteen listed / so many: 25.0 / 23.3 us, 29.4 / 27.4,
+    // 39.5 / 38.1)
+    // (64 channels over contiguous rows at a wave an item: the choice spills two more of the loop's registers, 36.5 -> 37.5 us at 4096
+    // tiles of k = 512, and gives 0.3 us at k = 64)
+    constexpr bool kChoose = D == 128 || PAGED || SPLIT;
+    if (kChoose && nt <= 4) list_tiles(0, std::integral_constant<int, 4>{});
+    else if (kChoose && nt <= 8) list_tiles(0, std::integral_constant<int, 8>{});
+    else list_tiles(0, std::integral_constant<int, kListTiles>{});
     // (the tail of a list that ends early: a prefix with fewer keys than k)
     if (nt <= kListTiles) nt = any ? 32 - __builtin_clz(any) : 0;
     // The query loads end here, where the compiler can see it: it does not count the loads that the loop issues from
@@ -529,16 +536,15 @@ hipError_t launch_attn_mfma(const KParams &p, hipStream_t st)
     const int64_t per_group = (int64_t)p.g * p.nqb * mtn;
     const int64_t waves = groups * per_group;
     if (waves == 0) return hipSuccess;
-    // Few work items: a workgroup of four or two waves each.  Measured, d = 128, k = 512, one / two / four waves per item, us: 64
-    // items - / 13.8 / 11.5; 512 - / 19.3 / 19.5; 1024 26.5 / 26.3 / 35.1, over pages 42.9 / 35.6 / 39.4; 1504 30.3 / 34.1 / 35.3;
-    // 2048 36.8 / 54.0 / 62.6.
-    const int wpi = waves <= 512 ? 4 : waves <= 1024 ? 2 : 1;
-    // groups worked on at a time (measured: all eight up to 128k tokens at head dim 128, four at 256k, one at a million)
-    const int xcd_map = (groups % 8 == 0 && (wpi > 1 || per_group % 4 == 0)) ? groups_at_a_time((int64_t)p.max_kv_len * p.d * 4, 768LL << 20) : 0;
-    const dim3 grid((unsigned)placed_workgroups(xcd_map, wpi > 1 ? 1 : 4, per_group, groups)), block(wpi == 2 ? 128 : kThreads);
+    // groups worked on at a time (measured: all eight up to 128k tokens at head dim 128, four at 256k, one at a million; as many as
+    // divide their number against linear order: twelve of four heads, 32k tokens, the last 2656 rows 115.6 / 89.2 us, over pages 125.6 / 96.0;
+    // 36 of three 273 / 206)
+    const int gc = groups_at_a_time_of(groups, (int64_t)p.max_kv_len * p.d * 4, 768LL << 20);
+    const int wpi = attn_waves_per_item(waves, p.kb * p.bk, p.d, p.page_table != nullptr, groups, gc, p.max_kv_len);
+    const dim3 grid((unsigned)placed_workgroups(gc, wpi > 1 ? 1 : 4, per_group, groups)), block(wpi == 2 ? 128 : kThreads);
     const int mode = p.page_table ? 1 : rows_by_lane_offset(p.max_kv_len, p.ks_r * 2, p.d) ? 0 : 2;
     const auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, st, p, log_bk, mtn, xcd_map);
+        hipLaunchKernelGGL(kernel, grid, block, 0, st, p, log_bk, mtn, gc);
         return hipGetLastError();
     };
 #define HIPATTN_MODE(DV, WV) (mode == 0 ? launch(attn_mfma_kernel<DV, 0, WV>) : mode == 1 ? launch(attn_mfma_kernel<DV, 1, WV>) : launch(attn_mfma_kernel<DV, 2, WV>))

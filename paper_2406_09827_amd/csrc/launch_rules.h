@@ -98,4 +98,21 @@ inline int decode_mask_waves(int64_t problems, int kb, int d, int step, int step
     return problems <= 16384 && slice == Slice::narrow && d == 128 && kb <= 256 && 2 * kb >= 8 * step8 ? 4 : 1;
 }
 
+// Prefill sparse attention: waves per work item (query tile), by the number of items and of selected keys (32 a tile).  Measured, 16384
+// tokens, one / two / four waves per item, us (11 us is what a launch takes):
+//   128 channels   64 items k = 512 21.6 / 12.7 / 11.0;  512 k = 256 14.5 / 11.5 / 11.6, 512 22.4 / 16.6 / 15.4;  1024 k = 128 12.0 / 12.9 / 17.0,
+//                  256 15.8 / 16.3 / 20.6, 512 23.5 / 20.9 / 27.3;  1536 512 29.9 / 34.4 / 37.6
+//   over pages     64 512 31.1 / 17.9 / 12.1;  512 512 31.8 / 22.8 / 17.1;  1024 128 13.9 / 13.9 / 18.0, 256 20.1 / 18.0 / 22.2, 512 33.1 / 26.3 / 30.6;
+//                  1536 512 42.9 / 45.6 / 43.2
+//   64 channels    512 512 16.6 / 12.0 / 11.2;  1024 256 11.3 / 11.1 / 10.9, 512 17.3 / 13.6 / 13.3;  1536 256 13.7 / 12.5 / 15.0, 512 20.8 / 18.6 / 19.4;  4096 512
+//                  34.7 / 36.7 / 40.6;  over pages 1536 512 27.5 / 21.1 / 22.5, 4096 512 48.2 / 48.1 / 50.9
+// Where the groups go in linear order (an odd number: `gc` 0) the heads that share rows are on different XCDs with two waves an item: five
+// groups of 16384 tokens, 900 items, one / two 28.5 / 31.7 (the keys and values of one or three fit the caches).
+inline int attn_waves_per_item(int64_t items, int n_keys, int d, bool paged, int64_t groups, int gc, int64_t max_kv_len)
+{
+    if (items <= 512) return 4;
+    if (items > 1024 || n_keys <= (d == 128 && !paged ? 256 : 128)) return 1;
+    return gc == 0 && !paged && groups * max_kv_len * d * 4 > (24 << 20) ? 1 : 2;
+}
+
 }  // namespace hipattn

@@ -78,6 +78,19 @@ def test_workgroup_or_wave_per_item_of_the_prefill_mask(tmp_path):
     assert "mask_item_per_workgroup(units, p.kb, p.d, !one_tile, p.page_table != nullptr, groups, gc, p.max_kv_len)" in (CSRC / "mask_mfma_impl.h").read_text()
 
 
+def test_waves_per_item_of_the_prefill_attention(tmp_path):
+    out = run(tmp_path, r"""
+    struct { int64_t items; int n_keys, d; bool paged; int groups, gc, T, want; } c[] = {
+        {1, 64, 128, 0, 8, 8, 16384, 4}, {512, 2048, 64, 1, 5, 0, 16384, 4}, {513, 256, 128, 0, 8, 8, 16384, 1}, {513, 257, 128, 0, 8, 8, 16384, 2},
+        {1024, 128, 128, 1, 8, 8, 16384, 1}, {1024, 129, 128, 1, 8, 8, 16384, 2}, {1024, 128, 64, 0, 8, 8, 16384, 1}, {1024, 256, 64, 0, 8, 8, 16384, 2},
+        {1025, 512, 128, 1, 8, 8, 16384, 1}, {900, 512, 128, 0, 3, 0, 16384, 2}, {900, 512, 128, 0, 5, 0, 16384, 1}, {900, 512, 128, 1, 5, 0, 16384, 2}};
+    for (auto &x : c) if (attn_waves_per_item(x.items, x.n_keys, x.d, x.paged, x.groups, x.gc, x.T) != x.want) { std::printf("%lld %d\n", (long long)x.items, x.n_keys); return 1; }
+    std::printf("ok\n");
+    """)
+    assert out.strip() == "ok"
+    assert "attn_waves_per_item(waves, p.kb * p.bk, p.d, p.page_table != nullptr, groups, gc, p.max_kv_len)" in (CSRC / "attn_mfma.hip").read_text()
+
+
 def test_waves_of_the_decode_mask(tmp_path):
     # the lines between sixteen, four and one wave per problem
     out = run(tmp_path, r"""
