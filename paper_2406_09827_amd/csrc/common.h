@@ -327,11 +327,6 @@ __device__ __forceinline__ void select_topk_visit(const uint32_t (&key)[E], int 
         base_keep += __popcll(bkp);
     }
 }
-template <int E, int SEARCH = default_search(E)>
-__device__ __forceinline__ void select_topk_ordered(const uint32_t (&key)[E], int kb, bool (&keep)[E], int (&dest)[E])
-{
-    select_topk_visit<E, SEARCH>(key, kb, [&](int i, bool kp, int d) __attribute__((always_inline)) { keep[i] = kp; dest[i] = d; });
-}
 
 /*
  * The same for slots in pairs: lane `lane` holds slots 2 (i*64 + lane) and 2 (i*64 + lane) + 1 in registers l[i] and r[i], so a

@@ -55,7 +55,8 @@ def _samples_match(w, n_e, seed, r_e, flags=0, units=None, **opts):
 
 @pytest.mark.parametrize("integer", [True, False], ids=["int", "normal"])
 def test_ensemble_samples_prefill_tuned(integer):
-    # 32-row blocks on the direct-to-LDS kernel (k/bk = 128 and 256), a 64-row shape, a paged pool, list rounds
+    # 32-row blocks (k/bk = 128 and 256; 752 items, a workgroup each), 15-row ones (1600, a wave each), a 64-row shape, a paged pool, list
+    # rounds
     w = synth.Workload("ens_pre", 1, 4, 2, 128, 6000, 6000, 256, 32, 2, "bf16", rho=0.95, spike_every=1024, integer=integer, seed=701)
     nqb = w.n_query_blocks
     units = [(0, h, qb) for h in range(4) for qb in (3, 9, 17, 40, 77, nqb // 2, nqb - 2, nqb - 1)]
@@ -65,6 +66,9 @@ def test_ensemble_samples_prefill_tuned(integer):
     _samples_match(w64, 2, 13, 5.0, units=[(0, h, qb) for h in range(2) for qb in (5, 20, 77, 140)])
     wp = synth.scaled(w, page_size=64, seed=704)
     _samples_match(wp, 2, 14, 5.0, units=units, rep_pos=1)
+    for v in (w, wp):
+        _samples_match(synth.scaled(v, bq=15), 2, 15, 5.0, units=[(0, h, qb) for h in range(4) for qb in (20, 85, 164, 200, 398, 399)], rep_pos=1)
+    _samples_match(synth.scaled(w64, bq=48, n_q_heads=12, n_kv_heads=3), 2, 16, 5.0, units=[(0, h, qb) for h in (0, 5, 11) for qb in (7, 27, 103, 187)])
 
 
 @pytest.mark.parametrize("integer", [True, False], ids=["int", "normal"])

@@ -478,10 +478,9 @@ def test_k_over_bk_up_to_1024(integer):
 
 @pytest.mark.parametrize("integer", [True, False], ids=["int", "normal"])
 def test_paged_prefill_variants(integer):
-    # prefill over a paged pool on every tuned mask kernel: k/bk = 256 (page ids kept per branch slot), 512 with 32-row
-    # (packed list rounds) and 64-row query blocks, 1024 (page look-ups issued from the tile loop), list rounds with the
-    # first / last representative, a chunk of rows at the end of a long context (one work item per workgroup), and a
-    # page size that is not a power of two (generic kernel)
+    # prefill over a paged pool on every tuned mask kernel: k/bk = 256, 512 with 32-row and 64-row query blocks, 1024, list
+    # rounds with the first / last representative, a chunk of rows at the end of a long context (a workgroup per work item),
+    # and a page size that is not a power of two (generic kernel)
     w = synth.Workload("paged_pf", 2, 4, 2, 128, 9000 + 30, 9000 + 30, 512, 32, 2, "bf16", rho=0.95, spike_every=2048,
                        page_size=64, integer=integer, seed=111)
     nqb = w.n_query_blocks
@@ -495,8 +494,7 @@ def test_paged_prefill_variants(integer):
     U.run_case(synth.scaled(w, q_len=64, page_size=8), 0)
     U.run_case(synth.scaled(w, q_len=64, k=1024, page_size=8), 0, rep_pos=2)
     U.run_case(synth.scaled(w, q_len=96, k=1024, bq=64, page_size=8, head_dim=64), 0, rep_pos=1)
-    # four query heads per kv head: the four work items of a workgroup share a sequence, which the variant with the page
-    # table cached in LDS needs; with 8-key pages the table (1129 pages) is too long for it
+    # four query heads per kv head (the four work items of a workgroup share a sequence); a table of 1129 pages
     w4 = synth.scaled(w, n_q_heads=8, n_kv_heads=2)
     units4 = [(b, h, qb) for b in range(2) for h in (0, 3, 4, 7) for qb in (0, 15, 16, 70, nqb // 2, nqb - 1)]
     for rep_pos in (0, 2):
@@ -566,23 +564,23 @@ def test_token_bank_in_host_memory():
 
 @pytest.mark.parametrize("integer", [True, False], ids=["int", "normal"])
 def test_direct_to_lds_variant_limits(integer):
-    # the mask kernel with direct-to-LDS loads serves contiguous K of up to 32 MB per kv head (128k keys at head dim
-    # 128): the largest context it takes, the first one it leaves to the register-staged kernel, 64k keys, a short last
-    # key block, list rounds (first / last representative), key sampling and a ragged batch
+    # contiguous K of 16 to 32 MB per kv head (64k to 128k keys at head dim 128) with a workgroup and with a wave per work item
+    # (2048 items, two workgroups to a compute unit), a short last key block, list rounds (first / last representative), key
+    # sampling and a ragged batch
     w = synth.Workload("direct_128k", 1, 4, 1, 128, 8192, 131072, 512, 32, 2, "bf16", rho=0.95, spike_every=8192,
                        integer=integer, seed=131)
     nqb = w.n_query_blocks
     units = [(0, h, qb) for h in range(4) for qb in (0, 1, 77, nqb // 2, nqb - 2, nqb - 1)]
-    U.run_case(w, 0, units=units)
-    U.run_case(synth.scaled(w, kv_len=131072 + 64), 0, units=units)
+    U.run_case(w, 0, units=units)   # 1024 items, a workgroup each
+    U.run_case(synth.scaled(w, kv_len=131072 + 64, bq=16), 0, units=units)
     U.run_case(synth.scaled(w, kv_len=65536 + 64), 0, units=units)
     U.run_case(synth.scaled(w, kv_len=40001, q_len=9001), 0, units=[(0, h, qb) for h in range(4) for qb in (0, 100, 281)], rep_pos=2)
     U.run_case(synth.scaled(w, kv_len=30000, q_len=30000, bk=4, k=1024), 0,
                units=[(0, h, qb) for h in range(4) for qb in (0, 31, 32, 33, 500, 937)], rep_pos=1, b_sk=2, n_window=17)
-    wr = synth.Workload("direct_ragged", 3, 4, 2, 128, 3000, 9000, 256, 32, 2, "bf16", rho=0.9, ragged=(3500, 9000),
+    wr = synth.Workload("direct_ragged", 3, 4, 2, 128, 3000, 9000, 256, 16, 2, "bf16", rho=0.9, ragged=(3500, 9000),
                         integer=integer, seed=132)
     nqb = wr.n_query_blocks
-    U.run_case(wr, 0, units=[(b, h, qb) for b in range(3) for h in range(4) for qb in (0, 40, nqb - 1)])
+    U.run_case(wr, 0, units=[(b, h, qb) for b in range(3) for h in range(4) for qb in (0, 80, nqb - 1)])   # 2256 items
 
 
 @pytest.mark.parametrize("integer", [True, False], ids=["int", "normal"])
@@ -594,6 +592,7 @@ def test_blocks_of_8_and_16_keys(integer):
     nqb = w.n_query_blocks
     units = [(0, h, qb) for h in range(4) for qb in (0, 31, 32, 33, 70, nqb // 2, nqb - 2, nqb - 1)]
     U.run_case(w, 0, units=units)
+    U.run_case(synth.scaled(w, bq=15), 0, units=units)   # 1616 items: a wave each
     U.run_case(synth.scaled(w, bk=16, k=2048, bq=64), 0, units=[(0, h, qb) for h in range(4) for qb in (0, 15, 16, 40, nqb // 2 - 1)],
                b_sk=2, rep_pos=2, n_sink=8, n_window=40)
     wd = synth.Workload("bk8_dec", 4, 4, 2, 128, 1, 30000, 2048, 1, 8, "bf16", rho=0.9, ragged=(3000, 30000),
@@ -606,17 +605,18 @@ def test_blocks_of_8_and_16_keys(integer):
 @pytest.mark.parametrize("bk,b_sk,g,rep_pos,b_sq", [(1, 1, 4, 0, 1), (2, 2, 4, 0, 1), (2, 1, 4, 2, 2), (4, 1, 8, 0, 1), (8, 1, 4, 1, 1),
                                                     (2, 1, 8, 0, 1)])
 def test_first_round_shared_by_the_heads_of_a_kv_group(bk, b_sk, g, rep_pos, b_sq):
-    # more than 512 work items with g a multiple of 4: the four waves of a workgroup are four heads of one query block and
+    # more than 1536 work items (and k/bk of at most 512) with g a multiple of 4: the four waves of a workgroup are four heads of one query block and
     # go through the first round in step, each tile loaded once (1, 2, 4 and 8 scored rows per block; a ragged last query
     # block; the ensemble's perturbed round, which is the first one for short prefixes).  Against the oracle, and bit for
     # bit against the same call with every head gathering for itself.
     import paper_2406_09827_amd as hipattn
+    bq = 8 if g == 4 else 16   # (the sampling stride divides it)
     T = 4500 + 13
     for integer in (True, False):
-        w = synth.Workload("shared_round", 1, g, 1, 128, T, T, 96 * bk, 32, bk, "bf16", rho=0.95, spike_every=1024, integer=integer, seed=120 + bk)
+        w = synth.Workload("shared_round", 1, g, 1, 128, T, T, 96 * bk, bq, bk, "bf16", rho=0.95, spike_every=1024, integer=integer, seed=120 + bk)
         nqb = w.n_query_blocks
-        assert g * nqb > 512
-        units = [(0, h, qb) for h in range(g) for qb in (3, 4, 7, 12, 40, nqb // 2, nqb - 2, nqb - 1)]
+        assert g * nqb > 1536
+        units = [(0, h, qb) for h in range(g) for qb in (12, 16, 28, 48, 160, nqb // 2, nqb - 2, nqb - 1)]
         U.run_case(w, 0, units=units, rep_pos=rep_pos, b_sq=b_sq, b_sk=b_sk)
         x = synth.make_inputs(w, device="cuda", threads=4)
         for ens in (0, 2):

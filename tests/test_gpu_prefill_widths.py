@@ -18,10 +18,11 @@ pytestmark = pytest.mark.gpu
 ])
 def test_table_sizes(k, bk, d, bq, rep_pos, heads, page):
     hq, hkv = heads
-    for q_len in (3 * bq + 5, bq * (1540 // hq)):   # below and above the line between a workgroup and a wave per work item
+    for q_len in (3 * bq + 5, bq * -(-1540 // hq)):   # below and above the line between a workgroup and a wave per work item
         T = max(q_len, 7 * k + 3)
         w = synth.Workload("widths", 1, hq, hkv, d, q_len, T, k, bq, bk, "bf16", rho=0.9, page_size=page, integer=True, seed=300 + k)
         nqb = w.n_query_blocks
+        assert hq * nqb <= 512 or hq * nqb > 1536
         units = [(0, h, qb) for h in (0, hq - 1) for qb in sorted({0, 1, nqb // 2, nqb - 1})]
         U.run_case(w, 0, units=units, rep_pos=rep_pos, b_sk=2 if bk == 8 else 1)
         U.run_case(synth.scaled(w, integer=False), 0, units=units[:3], rep_pos=rep_pos)
