@@ -15,7 +15,7 @@
 // What bounds it: the cache's return path (keys as operands are 64 accesses an instruction), busy 75 % of the clocks, and vector
 // issue (planes, softmax), 59 %; the matrix pipe is busy 30 % (4096 tokens, by counter).  Loading keys coalesced and through LDS is slower (281 us at 4096 tokens, 254 so).
 // Measured, fp32, 32 query heads over 8 kv heads, T = 4096, k = 512, bq = 32, bk = 2, d = 128: 342 us with
-// v_mfma_f32_16x16x4_f32, 254 us with planes; T = 1024, one head, k = 128, bq = 16, d = 64: 10.8 -> 10.8 us (64 workgroups: latency);
+// v_mfma_f32_16x16x4_f32, 257 us with planes; T = 1024, one head, k = 128, bq = 16, d = 64: 10.8 -> 10.8 us (64 workgroups: latency);
 // bf16, 8 heads, 64-row blocks, k = 512: 65 -> 43 us.  Error against 64 bits (T = 4096): 3.3e-7 -> 1.7e-7 in norm.
 #pragma once
 #include "mfma_generic.h"

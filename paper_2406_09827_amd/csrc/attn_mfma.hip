@@ -33,9 +33,9 @@
 //     after the transpose reads.  The direct loads are inline assembly with hand-placed waits (the compiler neither knows
 //     that they write LDS nor counts them) and, but for a refill of the list, the only vector memory instructions of the loop.
 // Measured, 32 query heads over 8 kv heads, d = 128, k = 512, bq = 32, against the form before (metadata in the loop, the whole
-// index row in LDS; 64 channels staged through registers at two waves a SIMD, now four): 3k tokens 59.2 -> 54.3 us, 32k 553 ->
-// 544, over pages 852 -> 763, d = 64 298 -> 265; k = 2048 2903 -> 1771.  At 32k two waves a SIMD, each a chain of about 4000
-// clocks per tile (a third of it waiting for loads), keep vector issue 44 %, the matrix pipe 23 %, the vector L1 53 % busy.
+// index row in LDS; 64 channels staged through registers at three waves a SIMD, now four, over pages three): 3k tokens 59.2 -> 54.3 us, 32k 553 ->
+// 544, over pages 852 -> 763, d = 64 298 -> 265; k = 2048 2903 -> 1771.  At 32k the cache's data return path is 93 % busy, the
+// address unit 78 %, cache accesses 58 %, vector issue 48 %, the matrix pipe 25 %.
 #include "common.h"
 #include "launch.h"
 #include <type_traits>

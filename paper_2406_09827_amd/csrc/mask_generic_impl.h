@@ -21,7 +21,7 @@
 //     any number of rows per block.
 //   * Selection: the ordered threshold selection of common.h, run redundantly by the four waves.
 // Measured, fp32, 32 query heads over 8 kv heads, T = 4096, k = 512, bq = 32, bk = 2, d = 128: 576 us with the fp32 instruction
-// (half of the clocks on the matrix pipe), 389 us with planes; d = 64 337 -> 225; one sequence of 1024 tokens, one head, k = 128, bq = 16, d = 64: 18.0
+// (half of the clocks on the matrix pipe), 378 us with planes; d = 64 337 -> 224; one sequence of 1024 tokens, one head, k = 128, bq = 16, d = 64: 18.0
 // -> 17.1 (64 workgroups: latency).
 #pragma once
 #include "mfma_generic.h"
