@@ -62,7 +62,7 @@ int prepare(const hip_problem *hp, KParams &kp)
     kp = KParams{};
     kp.batch = p.batch; kp.hq = p.n_q_heads; kp.hkv = p.n_kv_heads; kp.g = p.n_q_heads / p.n_kv_heads;
     kp.d = d; kp.q_len = p.q_len; kp.max_kv_len = p.max_kv_len;
-    kp.kb = p.k / p.bk; kp.bq = p.bq; kp.bk = p.bk; kp.nqb = nqb;
+    kp.kb = p.k / p.bk; kp.kb_magic = chunk_magic(kp.kb); kp.bq = p.bq; kp.bk = p.bk; kp.nqb = nqb;
     // a single query row is a one-row query block whatever bq says: the decode kernels then serve it
     if (p.q_len == 1) kp.bq = 1;
     kp.kv_lens = p.kv_lens; kp.page_table = p.page_table;

@@ -22,6 +22,7 @@ struct KParams {
     int64_t ks_b, ks_h, ks_r;
     int64_t os_b, os_h, os_r;
     int32_t batch, hq, hkv, g, d, q_len, max_kv_len, kb, bq, bk, nqb, page_size, max_pages;
+    uint32_t kb_magic;         // chunk_magic(kb)
     int32_t page_shift;        // log2(page_size) when it is a power of two, else -1
     int32_t n_sink, n_window;  // sparse attention: always-attended first / most recent keys
     int32_t b_sq, b_sk;        // mask estimation: row / key sampling strides of the block score (>= 1)
@@ -139,11 +140,42 @@ __device__ __forceinline__ int lane_prefix_count(uint64_t mask)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
 }
 
-// Representative block of the branch [bs, be) (be > bs).
-__device__ __forceinline__ int rep_block(int bs, int be, int rep_pos)
+// The representative rule (rep_pos: 0 centre, 1 first, 2 last block) as numbers, so that no code branches on it: a uniform branch
+// costs a wave 20 to 40 clocks, and the survivors of a round met dozens (decode, 32 problems of 32k tokens: 37.8 us with the branches, 36.7).
+struct RepRule {
+    int shift, less, keep;       // offset of the representative block in a branch of n blocks: ((n >> shift) - less) & keep
+    uint32_t own_left;           // all ones: a left half has its node's representative
+    int own_right, beg_left;     // right halves of nodes up to this long have it; left halves of nodes up to this long begin with theirs
+};
+__device__ __forceinline__ RepRule rep_rule(int rep_pos)
 {
-    return rep_pos == 1 ? bs : rep_pos == 2 ? be - 1 : bs + ((be - bs) >> 1);
+    return RepRule{rep_pos == 0 ? 1 : 0, rep_pos == 2 ? 1 : 0, rep_pos == 1 ? 0 : -1, rep_pos == 1 ? ~0u : 0u,
+                   rep_pos == 0 ? 2 : rep_pos == 1 ? 1 : 0x7fffffff, rep_pos == 0 ? 3 : 0};
 }
+// Representative block of the branch [bs, be) (be > bs).
+__device__ __forceinline__ int rep_block(int bs, int be, const RepRule &rule)
+{
+    return bs + ((((be - bs) >> rule.shift) - rule.less) & rule.keep);
+}
+
+// What a round knows without scoring about the two branches of a node of `len` blocks (0: no node): `left` and `right` are their
+// keys, or 0 where the branch is empty or has to be scored (need_l, need_r).  `own` is the key of the node's representative block,
+// scored when the node was a branch, and `beg` that of its first block, where that block has been an ancestor's
+// representative, else 0.  (The centre of a node is the first block of its right half, and a left half begins where its node
+// begins: only a node that left halves alone lead to from an initial node, which is not scored, does not know its first block.)
+// With the first (last) block as representative the left (right) child has its parent's in every round after the first.  With
+// the centre it is a block alone, the right half of a node of two, and the left half of a node of two or three if `beg` is known.
+__device__ __forceinline__ void known_branches(const RepRule &rule, int len, uint32_t own, uint32_t beg, uint32_t &left, uint32_t &right,
+                                               bool &need_l, bool &need_r)
+{
+    left = (own & rule.own_left) | (len <= rule.beg_left ? beg : 0u);
+    if (len <= 1) left = 0u;
+    right = len > 0 && len <= rule.own_right ? own : 0u;
+    need_l = len > 1 && left == 0u;
+    need_r = len > 0 && right == 0u;
+}
+// Does a round profit from that: one whose nodes are m or m + 1 blocks long.
+__device__ __forceinline__ bool round_knows_scores(int rep_pos, int m) { return rep_pos != 0 || m <= 3; }
 
 // ---- ensemble samples (paper appendix "Ensemble Hierarchical Top-k Approximation") ------------------
 // A sample e > 0 differs from the plain mask in ONE round of the search, the middle one (round R / 2 of the
@@ -187,10 +219,13 @@ __device__ __forceinline__ uint32_t ens_key(uint32_t key, uint32_t unit_hash, in
 constexpr uint32_t kKeyNegInf = 0x007fffffu;  // score_key(-inf): a real branch without admissible pair
 
 // rounded chunk bound round(j*Tb/kb), halves up, with Tb = a*kb + r split so that
-// everything fits 32-bit arithmetic (j, r <= 1024).
-__device__ __forceinline__ int chunk_bound(int j, int a, int r, int kb)
+// everything fits 32-bit arithmetic (j, r <= 1024).  The division by 2 kb is a multiplication by
+// m = ceil(2^32 / 2 kb): the dividend is at most 2 kb (kb - 1) + kb < 2^21 and m 2 kb exceeds 2^32 by less than 2 kb <= 2^11, so the
+// quotient is exact.
+inline uint32_t chunk_magic(int kb) { return (uint32_t)(((1ull << 32) + 2u * (uint32_t)kb - 1u) / (2u * (uint32_t)kb)); }
+__device__ __forceinline__ int chunk_bound(int j, int a, int r, int kb, uint32_t m)
 {
-    return j * a + (2 * j * r + kb) / (2 * kb);
+    return j * a + (int)__umulhi((uint32_t)(2 * j * r + kb), m);
 }
 
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)

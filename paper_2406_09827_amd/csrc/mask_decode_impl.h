@@ -17,12 +17,11 @@
 //   * two stages of ROWS row loads per lane alternate, so up to 16 KB per wave are in flight;
 //   * scores -> ordered threshold selection by up to four waves, a lane holding nodes with both of their scores -> the next
 //     node list and the next table (two tables take turns);
-//   * with the first or the last block as representative, one child of every node has the
-//     node's own representative (left child / first block, right child / last block): its score is
-//     the score that selected the node, carried over, and from the second round on only the
-//     other child is gathered and scored - about half the memory traffic.  With the centre representative
-//     the same holds in the final round (every node one or two blocks long: a one-block node is its own
-//     representative, the right half of a two-block node is the node's): only the left halves are scored.
+//   * a branch whose representative block was scored in an earlier round keeps that score (known_branches in common.h): with
+//     the first or the last block as representative one child of every node, from the second round on; with the centre
+//     most branches of the last two rounds.  Such a branch has no entry in the table, and where a node has at most one branch to
+//     score the table has one entry a node.  (Before, only the right halves of two-block nodes in the last round: 1024 problems of
+//     128k tokens 264 -> 252 us, 4096 of 20k 583 -> 510, 8960 of 12k over pages 752 -> 653; 32 problems level.)
 // Ragged lengths (kv_lens) and a page table are handled per row.
 // Measured against the form before (nodes looked up and sums taken row by row, the selection run by eight waves of sixteen; half
 // of a round was vector issue): 32 problems of 32768 tokens, d = 128, k = 512, bk = 2 50.6 -> 37.2 us, bk = 1 92 -> 50; 320 problems
@@ -30,6 +29,7 @@
 #pragma once
 #include "common.h"
 #include "launch.h"
+#include <type_traits>
 
 namespace hipattn {
 
@@ -42,7 +42,7 @@ namespace hipattn {
 // MODE 0: contiguous keys, a (sequence, kv head) slice below 2 GB, addressed as a buffer that ends with the last key (a load past
 //         it returns 0, so nothing is clamped); MODE 1: paged pool; MODE 2: contiguous, any size (64-bit row addresses).
 template <int E, int BK, int D, int ROWS, int MODE, int WS>
-__global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 : E == 16 ? 3 : 1) void mask_decode_kernel(KParams p, int xcd_map)
+__global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 : E == 16 ? 3 : 2) void mask_decode_kernel(KParams p, int xcd_map)
 {
     constexpr bool SPLIT = WS > 1, PAGED = MODE == 1;
     constexpr int WGT = WS == 16 ? 1024 : kThreads;   // threads of the workgroup
@@ -57,12 +57,14 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     constexpr int NW = SPLIT ? 1 : 4;  // private copies of the per-problem LDS state
     // Entry i of a table: first key of the i-th block to score, -1 if there is none, until the block's score (the bits of
-    // the float; -1 stays) replaces it.  In a round that carries scores the lower half holds one entry per node, the upper
-    // half the nodes' carried scores.
+    // the float; -1 stays) replaces it.
     __shared__ __attribute__((aligned(16))) uint32_t tab_s[NW][2][NB];
     // Nodes, sorted by position.  All of a round's nodes are m_len or m_len + 1 blocks long (chunks differ by one, and so do
     // halves of lengths that differ by one), so a node is its first block and one bit.
     __shared__ uint32_t node_s[NW][NB / 2];
+    // What each node knows: the keys of its own score (entry j) and of its first block's (entry kb + j), for this round and the
+    // next.  A wave with a problem of its own keeps them in the table that is not being scored.
+    __shared__ uint32_t known_s[2][SPLIT ? NB : 1];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // (uniform: what follows from it stays in scalar registers)
     const int grp = lane / LPR, lc = lane % LPR;
@@ -101,26 +103,28 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 
 
     const uint4 qv = *(const uint4 *)((const bf16_t *)p.Q + (int64_t)b * p.qs_b + (int64_t)h * p.qs_h + lc * 8);
     uint32_t *nodes = node_s[own];
-    const int log_bk = 31 - __builtin_clz((uint32_t)bk);   // (1, 2, 4 or 8 rows a block; a stride need not be a power of two)
-    const bool pow2 = (bk & (bk - 1)) == 0;
-    auto first_key = [&](int blk) __attribute__((always_inline)) { return pow2 ? blk << log_bk : blk * bk; };
-    auto put_entry = [&](uint32_t *tab, int i, int t0) __attribute__((always_inline)) {
-        tab[i] = (uint32_t)t0;
-        if (PAGED && p.touched && t0 >= 0) touch_page(p, b, t0);
+    const RepRule rule = rep_rule(p.rep_pos);
+    auto first_key = [&](int blk) __attribute__((always_inline)) { return MODE == 0 ? (int)__umul24((uint32_t)blk, (uint32_t)bk) : blk * bk; };
+    auto touch = [&](int t0) __attribute__((always_inline)) { if (PAGED && p.touched && t0 >= 0) touch_page(p, b, t0); };
+    auto put_pair = [&](uint32_t *tab, int j, int tl, int tr) __attribute__((always_inline)) {
+        *(uint2 *)(tab + 2 * j) = make_uint2((uint32_t)tl, (uint32_t)tr);
+        touch(tl);
+        touch(tr);
     };
     // the two branches of node [s, e): left [s, mid) (empty for a one-block node), right [mid, e)
     auto put_branches = [&](uint32_t *tab, int j, int s, int e) __attribute__((always_inline)) {
         const int mid = s + ((e - s) >> 1);
-        put_entry(tab, 2 * j, mid > s ? first_key(rep_block(s, mid, p.rep_pos)) : -1);
-        put_entry(tab, 2 * j + 1, first_key(rep_block(mid, e, p.rep_pos)));
+        put_pair(tab, j, mid > s ? first_key(rep_block(s, mid, rule)) : -1, first_key(rep_block(mid, e, rule)));
     };
     int m_len = Tb / kb;
     {
         const int r = Tb % kb;
         for (int j = tix; j < kb; j += tn) {
-            const int s = chunk_bound(j, m_len, r, kb), e = chunk_bound(j + 1, m_len, r, kb);
+            const int s = chunk_bound(j, m_len, r, kb, p.kb_magic), e = chunk_bound(j + 1, m_len, r, kb, p.kb_magic);
             nodes[j] = (uint32_t)(s << 1 | (e - s - m_len));
             put_branches(tab_s[own][0], j, s, e);
+            uint32_t *known = SPLIT ? known_s[0] : tab_s[own][1];
+            known[j] = known[kb + j] = 0u;
         }
         for (int i = 2 * kb + tix; i < NB; i += tn) tab_s[own][0][i] = tab_s[own][1][i] = 0xffffffffu;
     }
@@ -140,18 +144,14 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 
         for (int i = 0; i < H; ++i) nd[i] = nodes[i * 64 + lane];
     }
     int cur = 0;
-    bool list = false;  // a round in which one child of every node keeps the node's score (never the first round)
-    // (with the centre representative only the final round carries: there every node is one or two blocks long, a
-    // one-block node is its own representative and the right half of a two-block node is the node's representative,
-    // so the left children alone are scored)
-    const bool first_rule = p.rep_pos == 1;
+    bool knows = false, one_each = false;  // a round that knows scores (never the first), with one entry a node
     // ensemble sample: the round whose selection compares perturbed scores (-1: none)
     const int ens_round = ens_round_of(p.ens_sample, (Tb + kb - 1) / kb);
     const uint32_t ens_hash = ens_round >= 0 ? ens_unit_hash(p.ens_seed, p.ens_sample, b, h, 0) : 0u;
     int round = 0;
     for (int maxlen = (Tb + kb - 1) / kb; maxlen > 1; maxlen = (maxlen + 1) >> 1, ++round) {
+        const int n_items = one_each ? kb : 2 * kb;   // entries to score
         uint32_t *tab = tab_s[own][cur], *next_tab = tab_s[own][cur ^ 1];
-        const int n_items = list ? kb : 2 * kb;   // entries to score
 
         // one stage = U blocks per lane group: the entries, then the (unconditional) loads of their BK rows
         auto fetch = [&](int base, stage_t &kv) __attribute__((always_inline)) {
@@ -247,22 +247,28 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 
                 score(base + STRIDE, kbuf);
             }
         }
+        // What the nodes know.  (A wave with a problem of its own: in registers, the selection overwrites them.)
+        const uint32_t *known = SPLIT ? known_s[cur] : next_tab;
+        uint32_t own_key[SPLIT ? 1 : H], beg_key[SPLIT ? 1 : H];
+        if constexpr (!SPLIT) {
+#pragma unroll
+            for (int i = 0; i < H; ++i) {
+                own_key[i] = known[i * 64 + lane];
+                beg_key[i] = known[kb + i * 64 + lane];
+            }
+        }
+        auto own_of = [&](int i) __attribute__((always_inline)) { return SPLIT ? known[i * 64 + lane] : own_key[SPLIT ? 0 : i]; };
+        auto beg_of = [&](int i) __attribute__((always_inline)) { return SPLIT ? known[kb + i * 64 + lane] : beg_key[SPLIT ? 0 : i]; };
         sync_problem();
 
-        const bool next_list = p.rep_pos != 0 || ((maxlen + 1) >> 1) == 2;
         const int m_next = m_len >> 1;
+        // (with the first or last block every node has one branch at most to score, with the centre nodes of one or two blocks)
+        const bool last = maxlen <= 2, next_one = p.rep_pos != 0 || ((maxlen + 1) >> 1) == 2, next_knows = round_knows_scores(p.rep_pos, m_next);
         if (selects) {
             uint32_t kl[H], kr[H];   // keys of the left and the right branch of node i * 64 + lane
-            if (list) {
+            if (one_each) {
 #pragma unroll
-                for (int i = 0; i < H; ++i) {
-                    const int j = i * 64 + lane;
-                    const bool two = j < kb && m_len + (int)(nd[i] & 1) > 1;
-                    kr[i] = j < kb ? score_key_bits(tab[NB / 2 + j]) : 0u;
-                    kl[i] = two ? score_key_bits(tab[j]) : 0u;
-                    // under the first-block rule the left child of a longer node carries, else the right one
-                    if (first_rule && two) { const uint32_t x = kr[i]; kr[i] = kl[i]; kl[i] = x; }
-                }
+                for (int i = 0; i < H; ++i) kl[i] = kr[i] = score_key_bits(tab[i * 64 + lane]);
             } else {
 #pragma unroll
                 for (int i = 0; i < H; ++i) {
@@ -271,27 +277,50 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 
                     kr[i] = score_key_bits(x.y);
                 }
             }
+            if (knows) {
+#pragma unroll
+                for (int i = 0; i < H; ++i) {
+                    uint32_t left, right;
+                    bool need_l, need_r;
+                    known_branches(rule, i * 64 + lane < kb ? m_len + (int)(nd[i] & 1) : 0, own_of(i), beg_of(i), left, right, need_l, need_r);
+                    if (!need_l) kl[i] = left;
+                    if (!need_r) kr[i] = right;
+                }
+            }
             const bool odd = m_len & 1;
-            auto keep_one = [&](int d, uint32_t child, uint32_t key) __attribute__((always_inline)) {
+            uint32_t *next_known = SPLIT ? known_s[cur ^ 1] : tab;
+            // (two forms, so that the survivors' code has few branches: with a round to come that scores every branch, and any other)
+            auto keep_one = [&](auto any, int d, uint32_t child, uint32_t own, uint32_t beg) __attribute__((always_inline)) {
                 nodes[d] = child;
-                const int s = (int)(child >> 1), len = m_next + (int)(child & 1);
-                if (!next_list) {
+                if (any && last) return;
+                next_known[d] = own;
+                if (!any || rule.beg_left) next_known[kb + d] = beg;
+                const int s = (int)(child >> 1), len = m_next + (int)(child & 1), mid = s + (len >> 1);
+                if (!any || !next_knows) {
                     put_branches(next_tab, d, s, s + len);
+                    return;
+                }
+                uint32_t left, right;
+                bool need_l, need_r;
+                known_branches(rule, len, own, beg, left, right, need_l, need_r);
+                const int tl = need_l ? first_key(rep_block(s, mid, rule)) : -1, tr = need_r ? first_key(rep_block(mid, s + len, rule)) : -1;
+                if (next_one) {
+                    next_tab[d] = (uint32_t)max(tl, tr);
+                    touch(max(tl, tr));
                 } else {
-                    // the child that shares the node's representative keeps the node's score; the other one is empty or is
-                    // scored (its representative: the block at the split under the first-block rule, the block before the
-                    // split otherwise)
-                    next_tab[NB / 2 + d] = __float_as_uint(key_score(key));
-                    put_entry(next_tab, d, len > 1 ? first_key(s + (len >> 1) - (first_rule ? 0 : 1)) : -1);
+                    put_pair(next_tab, d, tl, tr);
                 }
             };
-            auto keep_child = [&](int i, bool keep_l, int dl, bool keep_r, int dr) __attribute__((always_inline)) {
+            auto keep_child = [&](auto any, int i, bool keep_l, int dl, bool keep_r, int dr) __attribute__((always_inline)) {
                 if (SPLIT && i % SW != wave) return;
                 // a node of `len` blocks: len / 2 to the left, the rest to the right; m_len / 2 or one more
                 const uint32_t bit = nd[i] & 1u, s2 = nd[i] & ~1u, len = (uint32_t)m_len + bit;
-                if (keep_l) keep_one(dl, s2 | (odd ? bit : 0u), kl[i]);
-                if (keep_r) keep_one(dr, (s2 + (len & ~1u)) | (odd ? 1u : bit), kr[i]);
+                const uint32_t own = own_of(i), beg = beg_of(i);
+                if (keep_l) keep_one(any, dl, s2 | (odd ? bit : 0u), kl[i], beg);
+                if (keep_r) keep_one(any, dr, (s2 + (len & ~1u)) | (odd ? 1u : bit), kr[i], own);
             };
+            auto keep_any = [&](int i, bool keep_l, int dl, bool keep_r, int dr) __attribute__((always_inline)) { keep_child(std::true_type{}, i, keep_l, dl, keep_r, dr); };
+            auto keep_all = [&](int i, bool keep_l, int dl, bool keep_r, int dr) __attribute__((always_inline)) { keep_child(std::false_type{}, i, keep_l, dl, keep_r, dr); };
             // four waves or one, E = 8: the registers that settling equal scores takes are the fourth wave of a SIMD (1024 paged
             // problems of k/bk = 256: 302 us with them, 247 without, 252 with the bits)
             constexpr int SEARCH = WS != 16 && E == 8 ? kInterpolate : default_search(E);
@@ -301,17 +330,20 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 
 #pragma unroll
                 for (int i = 0; i < H; ++i) {
                     const int s = (int)(nd[i] >> 1), e = s + m_len + (int)(nd[i] & 1), mid = s + ((e - s) >> 1);
-                    pl[i] = ens_key(kl[i], ens_hash, rep_block(s, mid, p.rep_pos), p.ens_r);
-                    pr[i] = ens_key(kr[i], ens_hash, rep_block(mid, e, p.rep_pos), p.ens_r);
+                    pl[i] = ens_key(kl[i], ens_hash, rep_block(s, mid, rule), p.ens_r);
+                    pr[i] = ens_key(kr[i], ens_hash, rep_block(mid, e, rule), p.ens_r);
                 }
-                select_topk_pairs<H, SEARCH>(pl, pr, kb, keep_child);
+                select_topk_pairs<H, SEARCH>(pl, pr, kb, keep_any);
+            } else if (next_knows) {   // (also after the last round)
+                select_topk_pairs<H, SEARCH>(kl, kr, kb, keep_any);
             } else {
-                select_topk_pairs<H, SEARCH>(kl, kr, kb, keep_child);
+                select_topk_pairs<H, SEARCH>(kl, kr, kb, keep_all);
             }
         }
         m_len = m_next;
         cur ^= 1;
-        list = next_list;
+        knows = next_knows;
+        one_each = next_one;
         sync_problem();
         if (selects) {
 #pragma unroll

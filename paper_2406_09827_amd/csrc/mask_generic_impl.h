@@ -10,8 +10,9 @@
 //   * The sampled query rows are MT operand tiles of 16 rows (small query blocks do not pay for 32), in registers, or their
 //     planes in LDS where two tiles of them would leave two waves per SIMD instead of three (4096 tokens: 398 us with the
 //     planes in registers, 389 so).  fp32 blocks of more than 32 rows: two waves share a tile, each with half of the rows.
-//   * The branches that need a score are put on a list (LDS: block position, row offset, branch slot); a child whose
-//     representative is its node's own representative has the node's score and is not listed.  The key rows of the list are
+//   * The branches that need a score are put on a list (LDS: block position, row offset, branch slot); a branch whose
+//     representative block was scored in an earlier round has that score and is not listed (known_branches in common.h; fp32, 4096 tokens
+//     of 32 heads 389 -> 367 us against right halves in the last round alone).  The key rows of the list are
 //     gathered in tiles of 8 KB per wave, one tile ahead (the order of the channels inside the contraction is free).  Coalesced
 //     and through the wave's LDS tile (XOR swizzle; lane l: row l % 16, chunk l / 16 of each 64 bytes) for bf16 and for one fp32
 //     query tile, whose matrix work is too short to hide the accesses (16-row blocks, 4096 tokens of 32 heads 580 us, straight
@@ -52,8 +53,10 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
     __shared__ int lt0[NB];                // ... position of that row
     __shared__ int lslot[NB];              // ... branch slot
     __shared__ uint32_t keys[NB];
-    __shared__ int nds_s[2][NB / 2], nde_s[2][NB / 2];  // nodes [s, e) of this round and of the next
-    __shared__ uint32_t ndk_s[2][NB / 2];  // ... score key of the branch that became the node
+    // Nodes of this round and of the next: first block and one bit (all of a round's nodes are m_len or m_len + 1 blocks long:
+    // chunks differ by one, and so do halves of lengths that differ by one)
+    __shared__ uint32_t nd_s[2][NB / 2];
+    __shared__ uint32_t ndk_s[2][NB / 2], ndb_s[2][NB / 2];  // ... keys of its own and its first block's score, 0: not known (known_branches)
     __shared__ __attribute__((aligned(16))) uint4 qp_s[QLDS ? MT * (CS / 2) * 192 : 1];  // [half][step][operand tile][plane][lane]
     __shared__ float tiny_s[4];
     __shared__ int n_list_s;
@@ -127,8 +130,9 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
     // initial nodes: kb chunks of [0, Tb) with rounded bounds; all non-empty because Tb > kb
     const int a = Tb / kb, r = Tb % kb;
     for (int j = tid; j < kb; j += kThreads) {
-        nds_s[0][j] = chunk_bound(j, a, r, kb);
-        nde_s[0][j] = chunk_bound(j + 1, a, r, kb);
+        const int s = chunk_bound(j, a, r, kb, p.kb_magic);
+        nd_s[0][j] = (uint32_t)(s << 1 | (chunk_bound(j + 1, a, r, kb, p.kb_magic) - s - a));
+        ndk_s[0][j] = ndb_s[0][j] = 0u;
     }
     if (tid == 0) n_list_s = 0;
     for (int i = 2 * kb + tid; i < NB; i += kThreads) keys[i] = 0u;
@@ -150,27 +154,25 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
     // ensemble sample: the round whose selection compares perturbed scores (-1: none)
     const int ens_round = ens_round_of(p.ens_sample, a + (r ? 1 : 0));
     const uint32_t ens_hash = ens_round >= 0 ? ens_unit_hash(p.ens_seed, p.ens_sample, b, h, qb) : 0u;
-    int round = 0;
+    const RepRule rule = rep_rule(p.rep_pos);
+    int round = 0, m_len = a;
     // maxlen bounds the longest node
-    for (int maxlen = a + (r ? 1 : 0); maxlen > 1; maxlen = (maxlen + 1) >> 1, ++round) {
-        const int *nd_s = nds_s[round & 1], *nd_e = nde_s[round & 1];
-        const uint32_t *nd_key = ndk_s[round & 1];
+    for (int maxlen = a + (r ? 1 : 0); maxlen > 1; maxlen = (maxlen + 1) >> 1, ++round, m_len >>= 1) {
+        const uint32_t *nd = nd_s[round & 1], *nd_own = ndk_s[round & 1], *nd_beg = ndb_s[round & 1];
         // split every node into its left and right branch (slots 2j, 2j+1; left may be empty) and list the blocks to score
         for (int base = wave * 64; base < 2 * kb; base += kThreads) {
             const int slot = base + lane;
             bool todo = false;
             int blk = 0;
             if (slot < 2 * kb) {
-                const int s = nd_s[slot >> 1], e = nd_e[slot >> 1], mid = s + ((e - s) >> 1);
-                const int bs = (slot & 1) ? mid : s, be = (slot & 1) ? e : mid;
-                uint32_t k0 = 0u;  // an empty branch
-                if (be > bs) {
-                    blk = rep_block(bs, be, p.rep_pos);
-                    todo = round == 0 || blk != rep_block(s, e, p.rep_pos);
-                    // a real branch starts at "-inf" (it may end up without an admissible pair)
-                    k0 = todo ? kKeyNegInf : nd_key[slot >> 1];
-                }
-                keys[slot] = k0;
+                const int j = slot >> 1, s = (int)(nd[j] >> 1), len = m_len + (int)(nd[j] & 1), mid = s + (len >> 1);
+                uint32_t left, right;
+                bool need_l, need_r;
+                known_branches(rule, len, nd_own[j], nd_beg[j], left, right, need_l, need_r);
+                todo = (slot & 1) ? need_r : need_l;
+                blk = (slot & 1) ? rep_block(mid, s + len, rule) : rep_block(s, mid, rule);
+                // a branch to score starts at "-inf" (it may end up without an admissible pair)
+                keys[slot] = todo ? kKeyNegInf : (slot & 1) ? right : left;
             }
             const uint64_t m = __ballot(todo);
             int at = 0;
@@ -357,7 +359,7 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
 #pragma unroll
         for (int i = 0; i < E; ++i) ksel[i] = keys[i * 64 + lane];
         auto branch_of = [&](int slot, int &s, int &e) __attribute__((always_inline)) {
-            s = nd_s[slot >> 1], e = nd_e[slot >> 1];
+            s = (int)(nd[slot >> 1] >> 1), e = s + m_len + (int)(nd[slot >> 1] & 1);
             const int mid = s + ((e - s) >> 1);
             if (slot & 1) s = mid; else e = mid;
         };
@@ -367,24 +369,24 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
                 if (ksel[i] == 0u) continue;
                 int s, e;
                 branch_of(i * 64 + lane, s, e);
-                ksel[i] = ens_key(ksel[i], ens_hash, rep_block(s, e, p.rep_pos), p.ens_r);
+                ksel[i] = ens_key(ksel[i], ens_hash, rep_block(s, e, rule), p.ens_r);
             }
         }
-        int *ns2 = nds_s[(round & 1) ^ 1], *ne2 = nde_s[(round & 1) ^ 1];
-        uint32_t *nk2 = ndk_s[(round & 1) ^ 1];
+        uint32_t *nd2 = nd_s[(round & 1) ^ 1], *nk2 = ndk_s[(round & 1) ^ 1], *nb2 = ndb_s[(round & 1) ^ 1];
         select_topk_visit<E>(ksel, kb, [&](int i, bool kept, int dest) __attribute__((always_inline)) {
             if ((i & 3) != wave || !kept) return;
             int s, e;
-            branch_of(i * 64 + lane, s, e);
-            ns2[dest] = s;
-            ne2[dest] = e;
-            nk2[dest] = keys[i * 64 + lane];
+            const int slot = i * 64 + lane;
+            branch_of(slot, s, e);
+            nd2[dest] = (uint32_t)(s << 1 | (e - s - (m_len >> 1)));
+            nk2[dest] = keys[slot];
+            nb2[dest] = ((slot & 1) ? nd_own : nd_beg)[slot >> 1];   // (a right half begins with its node's centre)
         });
         if (tid == 0) n_list_s = 0;
         __syncthreads();
     }
 
-    for (int j = tid; j < kb; j += kThreads) out[j] = nds_s[round & 1][j] * bk;
+    for (int j = tid; j < kb; j += kThreads) out[j] = (int)(nd_s[round & 1][j] >> 1) * bk;
 }
 
 template <typename T, int D, int MT>

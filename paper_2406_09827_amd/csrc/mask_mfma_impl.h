@@ -18,6 +18,10 @@
 //   * A block's score replaces its table entry, so a wave's whole state is the table (2 KB for 512 branches) and a tile.
 //     With that and 128 registers four waves fit a SIMD, which is what the loop lives on: a wave has one tile in flight,
 //     and its own chain (operands from LDS, multiplies one after the other, reduction) is long.
+//   * A branch whose representative block was scored in an earlier round keeps that score (known_branches in common.h): most
+//     branches of the last two or three rounds, which score what is left from a compact list.  (Before, only the right halves
+//     of two-block nodes in the last round did: 32k tokens 1.57 -> 1.36 ms, 128k 14.05 -> 12.2, a million 376 -> 343, 32 draft
+//     rows over 12k tokens 96 times 0.59 -> 0.51.)
 //   * A lane holds nodes and their two scores each; the wave runs the ordered threshold selection, writes the surviving
 //     nodes compacted to LDS and, per surviving node, the representative blocks of its two branches into the table.
 // Nodes are ranges of block indices; the list stays sorted by position throughout, which
@@ -70,9 +74,10 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
     constexpr int NS = SPLIT ? 1 : 4;  // copies of the per-work-item state
     // LDS, carved by hand: the tile buffers come first (the LDS address of a direct load travels in M0 and stays below
     // 64 KB), then per work item the table and, over a paged pool, the page of every entry's block.  The nodes lie over
-    // the wave's tile buffer between two rounds and in registers during one (SPLIT: in an array of their own).
+    // the wave's tile buffer between two rounds and in registers during one (SPLIT: in an array of their own, with two more for
+    // what they know).
     constexpr int kOffTab = 4 * TILEB, kOffPg = kOffTab + NS * NB * 4, kOffNode = kOffPg + (PAGED ? NS * NB * 4 : 0);
-    __shared__ __attribute__((aligned(1024))) char lds[kOffNode + (SPLIT ? NB * 2 : 0)];
+    __shared__ __attribute__((aligned(1024))) char lds[kOffNode + (SPLIT ? NB * 6 : 0)];
     static_assert(4 * TILEB <= 65536 && NB * 2 <= TILEB, "LDS layout");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -150,18 +155,20 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
         if (SPLIT) __syncthreads(); else wave_lds_sync();
     };
     // the two branches of node [s, e): left [s, mid) (empty for a one-block node), right [mid, e)
+    const RepRule rule = rep_rule(p.rep_pos);
     auto put_branches = [&](int j, int s, int e) __attribute__((always_inline)) {
         const int mid = s + ((e - s) >> 1);
-        set_entry(2 * j, mid > s ? rep_block(s, mid, p.rep_pos) << lbk : -1);
-        set_entry(2 * j + 1, rep_block(mid, e, p.rep_pos) << lbk);
+        set_entry(2 * j, mid > s ? rep_block(s, mid, rule) << lbk : -1);
+        set_entry(2 * j + 1, rep_block(mid, e, rule) << lbk);
     };
     int m_len = Tb / kb;
     {
         const int r = Tb % kb;
         for (int j = tix; j < kb; j += TN) {
-            const int s = chunk_bound(j, m_len, r, kb), e = chunk_bound(j + 1, m_len, r, kb);
+            const int s = chunk_bound(j, m_len, r, kb, p.kb_magic), e = chunk_bound(j + 1, m_len, r, kb, p.kb_magic);
             nodes[j] = (uint32_t)(s << 1 | (e - s - m_len));
             put_branches(j, s, e);
+            if constexpr (SPLIT) nodes[NB / 2 + j] = nodes[NB + j] = 0u;   // (own_s, beg_s)
         }
         for (int i = 2 * kb + tix; i < NB; i += TN) set_entry(i, -1);
     }
@@ -292,24 +299,31 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) asm volatile("" :: "v"(qf[mt][kk]));
 
-    // Rounds that run from a compact list.  A child that has its parent's representative block has the
-    // parent's score, which is carried over from the round that kept the parent, and only the other
-    // child is gathered and scored: with the first (last) block as representative that is the left
-    // (right) child in every round after the first; with the centre representative it happens in the
-    // final round, where every node is one or two blocks long, a one-block node IS its representative
-    // and the right half of a two-block node is the node's representative.  In such a round the lower half of the table
-    // is the list of the blocks to score, one for every node of two blocks or more in their order, and the upper half
-    // holds the nodes' carried scores.
+    // Scores of earlier rounds: with a node go the keys of its own and its first block's score (known_branches).  A round that
+    // profits from them runs from a compact list of what is left to score, node by node, left before right.  (Survivors take the
+    // two along through the table, which is free while they are written; SPLIT: in arrays of their own.)
+    uint32_t *own_s = SPLIT ? nodes + NB / 2 : tab, *beg_s = SPLIT ? own_s + NB / 2 : tab + kb;
     bool list = false;
-    const bool first_rule = p.rep_pos == 1;
     int n_entries = 2 * kb;
     // ensemble sample: the round whose selection compares perturbed scores (-1: none)
     const int ens_round = ens_round_of(p.ens_sample, (Tb + kb - 1) / kb);
     const uint32_t ens_hash = ens_round >= 0 ? ens_unit_hash(p.ens_seed, p.ens_sample, b, h, qb) : 0u;
     int round = 0;
     uint32_t nd[E / 2];  // the nodes, in registers while the tiles pass through the buffers
+    uint32_t own[SPLIT ? 1 : E / 2], beg[SPLIT ? 1 : E / 2];
 #pragma unroll
     for (int i = 0; i < E / 2; ++i) nd[i] = nodes[i * 64 + lane];
+    if constexpr (!SPLIT) {
+#pragma unroll
+        for (int i = 0; i < E / 2; ++i) own[i] = beg[i] = 0u;
+    }
+    auto own_of = [&](int i) __attribute__((always_inline)) { return SPLIT ? own_s[i * 64 + lane] : own[SPLIT ? 0 : i]; };
+    auto beg_of = [&](int i) __attribute__((always_inline)) { return SPLIT ? beg_s[i * 64 + lane] : beg[SPLIT ? 0 : i]; };
+    auto known = [&](int i, uint32_t &left, uint32_t &right, bool &need_l, bool &need_r) __attribute__((always_inline)) {
+        const int len = i * 64 + lane < kb ? m_len + (int)(nd[i] & 1) : 0;
+        known_branches(rule, len, own_of(i), beg_of(i), left, right, need_l, need_r);
+        return len;
+    };
     for (int maxlen = (Tb + kb - 1) / kb; maxlen > 1; maxlen = (maxlen + 1) >> 1, ++round) {
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         const int n_tiles = __builtin_amdgcn_readfirstlane((n_entries + EPT - 1) / EPT);
@@ -413,14 +427,13 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
             int n_before = 0;
 #pragma unroll
             for (int i = 0; i < E / 2; ++i) {
-                const int j = i * 64 + lane;
-                const bool two = j < kb && m_len + (int)(nd[i] & 1) > 1;
-                const uint64_t b2 = __ballot(two);
-                kr[i] = j < kb ? score_key_bits(tab[NB / 2 + j]) : 0u;
-                kl[i] = two ? score_key_bits(tab[n_before + lane_prefix_count(b2)]) : 0u;
-                // under the first-block rule the left child of a longer node carries, else the right one
-                if (first_rule && two) { const uint32_t x = kr[i]; kr[i] = kl[i]; kl[i] = x; }
-                n_before += __popcll(b2);
+                bool need_l, need_r;
+                known(i, kl[i], kr[i], need_l, need_r);
+                const uint64_t bl = __ballot(need_l), br = __ballot(need_r);
+                const int at = n_before + lane_prefix_count(bl) + lane_prefix_count(br);
+                if (need_l) kl[i] = score_key_bits(tab[at]);
+                if (need_r) kr[i] = score_key_bits(tab[at + (need_l ? 1 : 0)]);
+                n_before += __popcll(bl) + __popcll(br);
             }
         } else {
 #pragma unroll
@@ -430,20 +443,27 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
                 kr[i] = score_key_bits(x.y);
             }
         }
-        // Next round as a compact list: always once the first or last block represents a branch (one
-        // child of every node then has the node's own representative and keeps its score), and for the
-        // centre representative in the final round (see above).
-        const bool next_list = p.rep_pos != 0 || ((maxlen + 1) >> 1) == 2;
+        // SPLIT: what the nodes know whose survivors this wave writes, before they are overwritten
+        uint32_t own_w[(E / 2 + 3) / 4], beg_w[(E / 2 + 3) / 4];
+        if constexpr (SPLIT) {
+#pragma unroll
+            for (int i = 0; i < (E / 2 + 3) / 4; ++i) {
+                const int j = min((i * 4 + wave) * 64 + lane, NB / 2 - 1);
+                own_w[i] = own_s[j];
+                beg_w[i] = beg_s[j];
+            }
+        }
+        const bool next_list = round_knows_scores(p.rep_pos, m_len >> 1);
         sync_unit();   // (every wave has the scores)
-        // Ordered top-kb selection; survivors go to their places in the node array, their scores to the upper half of the
-        // table if the next round is a list.
+        // Ordered top-kb selection; survivors go to their places in the node array, with the keys they know.
         auto keep_child = [&](int i, bool kl_, int dl, bool kr_, int dr) __attribute__((always_inline)) {
             if (SPLIT && i % WPI != wave) return;
             int len;
             uint32_t left, right;
             child_of(nd[i], len, left, right);
-            if (kl_) { nodes[dl] = left; if (next_list) tab[NB / 2 + dl] = __float_as_uint(key_score(kl[i])); }
-            if (kr_) { nodes[dr] = right; if (next_list) tab[NB / 2 + dr] = __float_as_uint(key_score(kr[i])); }
+            const uint32_t o = SPLIT ? own_w[i / 4] : own[SPLIT ? 0 : i], f = SPLIT ? beg_w[i / 4] : beg[SPLIT ? 0 : i];
+            if (kl_) { nodes[dl] = left; own_s[dl] = kl[i]; beg_s[dl] = f; }
+            if (kr_) { nodes[dr] = right; own_s[dr] = kr[i]; beg_s[dr] = o; }
         };
         if (round == ens_round) {
             // the selection sees the perturbed scores; kl and kr keep the true ones (they are what a later round carries)
@@ -451,8 +471,8 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
 #pragma unroll
             for (int i = 0; i < E / 2; ++i) {
                 const int s = (int)(nd[i] >> 1), e = s + m_len + (int)(nd[i] & 1), mid = s + ((e - s) >> 1);
-                pl[i] = ens_key(kl[i], ens_hash, rep_block(s, mid, p.rep_pos), p.ens_r);
-                pr[i] = ens_key(kr[i], ens_hash, rep_block(mid, e, p.rep_pos), p.ens_r);
+                pl[i] = ens_key(kl[i], ens_hash, rep_block(s, mid, rule), p.ens_r);
+                pr[i] = ens_key(kr[i], ens_hash, rep_block(mid, e, rule), p.ens_r);
             }
             select_topk_pairs<E / 2>(pl, pr, kb, keep_child);
         } else {
@@ -461,7 +481,12 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
         m_len >>= 1;
         sync_unit();
 #pragma unroll
-        for (int i = 0; i < E / 2; ++i) nd[i] = nodes[i * 64 + lane];
+        for (int i = 0; i < E / 2; ++i) {
+            nd[i] = nodes[i * 64 + lane];
+            if constexpr (!SPLIT) { own[i] = own_s[i * 64 + lane]; beg[i] = beg_s[i * 64 + lane]; }
+        }
+        if (maxlen <= 2) break;   // every node is one block
+        wave_lds_sync();   // (they are in registers: the table's entries may be written)
         // the blocks that the next round scores
         if (!next_list) {
 #pragma unroll
@@ -474,14 +499,17 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
             int n_todo = 0;
 #pragma unroll
             for (int i = 0; i < E / 2; ++i) {
-                // the child that shares the node's representative keeps the node's score; the other one is empty or goes on
-                // the list (its representative: the block at the split under the first-block rule, the block before the
-                // split otherwise)
-                const int s = (int)(nd[i] >> 1), len = m_len + (int)(nd[i] & 1);
-                const bool two = i * 64 + lane < kb && len > 1;  // both children exist
-                const uint64_t b2 = __ballot(two);
-                if (two && (!SPLIT || i % WPI == wave)) set_entry(n_todo + lane_prefix_count(b2), (s + (len >> 1) - (first_rule ? 0 : 1)) << lbk);
-                n_todo += __popcll(b2);
+                uint32_t left, right;
+                bool need_l, need_r;
+                const int len = known(i, left, right, need_l, need_r);
+                const uint64_t bl = __ballot(need_l), br = __ballot(need_r);
+                const int at = n_todo + lane_prefix_count(bl) + lane_prefix_count(br);
+                const int s = (int)(nd[i] >> 1), mid = s + (len >> 1);
+                if (!SPLIT || i % WPI == wave) {
+                    if (need_l) set_entry(at, rep_block(s, mid, rule) << lbk);
+                    if (need_r) set_entry(at + (need_l ? 1 : 0), rep_block(mid, s + len, rule) << lbk);
+                }
+                n_todo += __popcll(bl) + __popcll(br);
             }
             // the rest of the last tile
             n_todo = __builtin_amdgcn_readfirstlane(n_todo);
@@ -511,7 +539,7 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
 // One tile, bk = 1 and 512 slots over pages, a workgroup per item spills 2 at four waves: 1024 rows 70 us, at three waves 89.
 constexpr int mask_waves(int MT, int E, int D, bool PAGED, bool SPLIT)
 {
-    const int lds_wave = 32 * D * 2 + (SPLIT ? 64 * E : 256 * E) * (PAGED ? 2 : 1) + (SPLIT ? 32 * E : 0);
+    const int lds_wave = 32 * D * 2 + (SPLIT ? 64 * E : 256 * E) * (PAGED ? 2 : 1) + (SPLIT ? 96 * E : 0);
     const int by_lds = (160 << 10) / (4 * lds_wave), by_regs = MT == 2 && D == 128 ? (E >= 32 || (PAGED && SPLIT) ? 2 : 3) : E >= 32 ? 2 : E >= 16 ? 3 : 4;
     return by_lds < by_regs ? by_lds : by_regs;
 }
@@ -528,7 +556,7 @@ static hipError_t launch_mask_mfma_e(const KParams &p, int xcd_map, dim3 grid, b
     const bool share = one_sequence_per_workgroup && p.g % 4 == 0 && !p.page_table && !(p.flags & 2);
     const int per_cu = mask_workgroups_per_cu(p.max_kv_len, D, p.kv_lens == nullptr);
     const auto launch = [&](auto kernel, bool paged, bool split_) {
-        const int lds = (split_ ? 1 : 4) * 256 * E * (paged ? 2 : 1) + 4 * 64 * D + (split_ ? 128 * E : 0);
+        const int lds = (split_ ? 1 : 4) * 256 * E * (paged ? 2 : 1) + 4 * 64 * D + (split_ ? 384 * E : 0);
         const int pad = per_cu && !split_ ? (160 << 10) / per_cu - lds : 0;
         hipLaunchKernelGGL(kernel, grid, dim3(kThreads), (unsigned)(pad > 0 ? pad & ~1023 : 0), st, p, xcd_map);
         return hipGetLastError();
