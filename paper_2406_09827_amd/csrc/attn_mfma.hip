@@ -123,18 +123,6 @@ __global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_wa
     const int w0_first = wlo;                                             // smallest w0 over the rows
     const int w0_last = max(vis_last - p.n_window, 0);                    // largest w0 over the rows
 
-    // ---- query tile as B operand (lane: query col, channels kk*16 + hh*8 ..)
-    bf16x8 qf[KS];
-    {
-        const bf16_t *Qb = (const bf16_t *)p.Q + (int64_t)b * p.qs_b + (int64_t)h * p.qs_h + (int64_t)row0 * p.qs_r;
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (col < n_rows) v = *(const uint4 *)(Qb + (int64_t)col * p.qs_r + kk * 16 + hh * 8);
-            qf[kk] = __builtin_bit_cast(bf16x8, v);
-        }
-    }
-
     auto uniform64 = [](int64_t v) __attribute__((always_inline)) {
         return ((int64_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
     };
@@ -170,18 +158,16 @@ __global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_wa
     // for some row; of `mask`: some (key, row) pair needs masking.
     uint32_t any = 0, mask = 0;
     const uint32_t plain = (uint32_t)max(w0_first - p.n_sink, 0);   // (w0_first <= kv_len)
-    auto list_tiles = [&](int i0, auto count) __attribute__((always_inline)) {
+    // (All index entries are read first, then all page entries: two latencies, not one per tile.)
+    auto index_entry = [&](int i0, int u) __attribute__((always_inline)) {
+        const int tile = SPLIT ? wave + WPI * (i0 + 2 * u + hh) : i0 + 2 * u + hh;
+        return idx[min(tile * 32 + col, n_keys - 1) >> log_bk];
+    };
+    auto list_tiles = [&](int i0, auto count, int (&t)[kListTiles / 2]) __attribute__((always_inline)) {
         constexpr int N = decltype(count)::value;
         const uint32_t at = (uint32_t)i0 % kListTiles, bits = ((1u << N) - 1u) << at;
         any &= ~bits;
         mask &= ~bits;
-        // all index entries first, then all page entries: two latencies, not one per tile
-        int t[N / 2];
-#pragma unroll
-        for (int u = 0; u < N / 2; ++u) {
-            const int tile = SPLIT ? wave + WPI * (i0 + 2 * u + hh) : i0 + 2 * u + hh;
-            t[u] = idx[min(tile * 32 + col, n_keys - 1) >> log_bk];
-        }
 #pragma unroll
         for (int u = 0; u < N / 2; ++u) {
             const int tile = SPLIT ? wave + WPI * (i0 + 2 * u + hh) : i0 + 2 * u + hh;
@@ -284,16 +270,37 @@ __global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_wa
     // (64 channels over contiguous rows at a wave an item: the choice spills two more of the loop's registers, 36.5 -> 37.5 us at 4096
     // tiles of k = 512, and gives 0.3 us at k = 64)
     constexpr bool kChoose = D == 128 || PAGED || SPLIT;
-    if (kChoose && nt <= 4) list_tiles(0, std::integral_constant<int, 4>{});
-    else if (kChoose && nt <= 8) list_tiles(0, std::integral_constant<int, 8>{});
-    else list_tiles(0, std::integral_constant<int, kListTiles>{});
+    int entry[kListTiles / 2];
+#pragma unroll
+    for (int u = 0; u < kListTiles / 2; ++u) entry[u] = index_entry(0, u);
+    // The query tile travels like a key tile, through the key buffer and with its swizzle: eight coalesced loads, which land while
+    // the keys are listed, after the index entries that these need first.  (Straight into registers, a row a lane, each of the eight
+    // was 64 cache accesses, and the entries waited behind them: 11800 of an item's 61000 clocks until its first tile was there
+    // at 32k tokens, now 10100; 64 channels 11600 of 64500, now 9600 of 59300.)  Rows past the last one repeat it and are not stored.
+    {
+        const char *Qb = (const char *)((const bf16_t *)p.Q + (int64_t)b * p.qs_b + (int64_t)h * p.qs_h + (int64_t)row0 * p.qs_r);
+#pragma unroll
+        for (int j = 0; j < NLD; ++j) {
+            const char *src = Qb + (int64_t)min(lg * NLD + j, n_rows - 1) * p.qs_r * 2 + (kchunk ^ (uint32_t)(j << 4));
+            const uint32_t dst = __builtin_amdgcn_readfirstlane(kt_m0 + j * 1024);
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(src), "s"(dst) : "memory", "m0");
+        }
+    }
+    if (kChoose && nt <= 4) list_tiles(0, std::integral_constant<int, 4>{}, entry);
+    else if (kChoose && nt <= 8) list_tiles(0, std::integral_constant<int, 8>{}, entry);
+    else list_tiles(0, std::integral_constant<int, kListTiles>{}, entry);
     // (the tail of a list that ends early: a prefix with fewer keys than k)
     if (nt <= kListTiles) nt = any ? 32 - __builtin_clz(any) : 0;
-    // The query loads end here, where the compiler can see it: it does not count the loads that the loop issues from
-    // inline assembly, and a wait for a query fragment left inside that loop would wait for them.
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) asm volatile("" :: "v"(qf[kk]));
     wave_lds_sync();
+    // query tile as B operand (lane: query col, channels kk*16 + hh*8 ..)
+    bf16x8 qf[KS];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    {
+        const int sw = D == 128 ? col & 15 : (col & 3) | ((col >> 1) & 4);
+        const uint32_t qrow = (uint32_t)((RPI * (col % NLD) + col / NLD) * ROWB + ((hh ^ sw) << 4)) + kt_m0;
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *(lds_u32x4_ptr)(uintptr_t)(qrow ^ (uint32_t)(kk << 5)));
+    }
     if (nt > 0) {
         rows_t R0;
         read_rows(0, R0);
@@ -309,7 +316,10 @@ __global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_wa
         const bool counts = any & bit;
         if (more && i + 1 >= kListTiles && (i + 1) % (kListTiles / 2) == 0) {
             // tiles i + 1 .. i + 8 go where tiles i - 15 .. i - 8 were (this tile's keys are in the other half)
-            list_tiles(i + 1, std::integral_constant<int, kListTiles / 2>{});
+            int entry[kListTiles / 2];
+#pragma unroll
+            for (int u = 0; u < kListTiles / 4; ++u) entry[u] = index_entry(i + 1, u);
+            list_tiles(i + 1, std::integral_constant<int, kListTiles / 2>{}, entry);
             wave_lds_sync();
         }
         // ---- keys of tile i have landed; its values may still be on their way
