@@ -258,7 +258,8 @@ __device__ __forceinline__ float key_score(uint32_t key)   // inverse of score_k
  *                     maxima over 32 or 64 rows 16 to 20.
  *   kInterpolate      [lo, hi] brackets the key and the candidate is the linear interpolation of the scores at its ends by
  *                     their counts: 6 to 8 counts for the scores of a round, but a step costs about twice a step of the
- *                     bits.  After 8 of them the bracket is halved.  Modelled for kb = 256 and 1024: one score far out,
+ *                     bits (a search over 512 keys takes 3400 to 4000 clocks of a wave alone, 3800 to 4500 with the ends kept as
+ *                     keys; starting from the mean took fewer steps of these scores and made decode of k/bk = 1024 9 % slower).  After 8 of them the bracket is halved.  Modelled for kb = 256 and 1024: one score far out,
  *                     heavy tails or two clusters take 8 steps and 10 to 12 halvings, many equal scores 8 and up to 30.
  *                     -inf is never inside the bracket.
  *   kInterpolateTies  the same with the bracket's ends moved to the nearest keys before every 8th halving, which settles
@@ -300,18 +301,22 @@ __device__ __forceinline__ uint32_t select_threshold(const uint32_t (&key)[E], i
     uint32_t hi = wave_max_u32(mx), lo = ~wave_max_u32(mn);
     int c_lo = count_ge(lo), c_hi = 0;   // keys >= lo, keys > hi
     if (c_lo <= kb) return kKeyNegInf;   // all of them, and the first ones of -inf
+    // (a, b: the scores of the bracket's ends, in scalar registers; a step's chain of dependent instructions is its time)
+    float a = key_score(lo), b = key_score(hi);
 #pragma unroll 1
     for (int it = 0; it < 8 && lo < hi; ++it) {
-        const float a = key_score(lo), t = (float)(c_lo - kb) * __builtin_amdgcn_rcpf((float)(c_lo - c_hi));
-        uint32_t cand = (uint32_t)__builtin_amdgcn_readfirstlane((int)score_key(fmaf(key_score(hi) - a, t, a)));
-        cand = min(max(cand, lo + 1), hi);   // (whatever the interpolation gave: always inside the bracket)
+        const float t = (float)(c_lo - kb) * __builtin_amdgcn_rcpf((float)(c_lo - c_hi));
+        const uint32_t u = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_int(fmaf(b - a, t, a)));
+        const uint32_t cand = min(max((u & 0x80000000u) ? ~u : u | 0x80000000u, lo + 1), hi);   // (whatever the interpolation gave: always inside the bracket)
         const int c = count_ge(cand);
         if (c >= kb) {
             lo = cand;
+            a = __uint_as_float(u);
             c_lo = c;
             if (c == kb) return lo;
         } else {
             hi = cand - 1;
+            b = __uint_as_float(u);
             c_hi = c;
         }
     }
