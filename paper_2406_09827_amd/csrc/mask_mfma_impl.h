@@ -116,21 +116,33 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
         return;
     }
 
-    // query block as MFMA A operand: lane holds row (lane % 32) [+32], 8 channels per k-step
+    // query block as MFMA A operand: lane holds row (lane % 32) [+32], 8 channels per k-step.  Operand rows past the sampled rows of the
+    // block repeat the last one: a repeated row cannot change a maximum, so tiles that need no causal masking take the short
+    // reduction whatever the number of rows.  One tile travels like a key tile, through the wave's tile buffer, and lands while
+    // the initial nodes are laid out (straight into registers, a row a lane, each of its
+    // loads is 64 cache accesses: 256 rows of 4 sequences over pages 135.7 -> 133.8 us with the attention, 3k tokens 98.9 -> 97.2).
+    constexpr bool QLDS = MT == 1;
+    const int lg = lane / CPR, lc = lane % CPR;  // loading role: tile rows lg*NLD .. +NLD-1, chunk lc
+    const uint32_t chunk0 = (uint32_t)((lc ^ ((lg * NLD) & (CPR - 1))) << 4);
+    const uint32_t ring0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds, ring = ring0 + wave * TILEB;
     bf16x8 qf[MT][KS];
     {
         const bf16_t *Qb = (const bf16_t *)p.Q + (int64_t)b * p.qs_b + (int64_t)h * p.qs_h + (int64_t)row0 * p.qs_r;
+        if constexpr (QLDS) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const int i = mt * 32 + col;
-#pragma unroll
-            for (int kk = 0; kk < KS; ++kk) {
-                // operand rows past the sampled rows of the block repeat the last one: a repeated row cannot
-                // change a maximum, so tiles that need no causal masking take the short reduction whatever
-                // the number of rows
-                const uint4 v = *(const uint4 *)(Qb + (int64_t)(min(i, n_eff - 1) << qs) * p.qs_r + kk * 16 + hh * 8);
-                qf[mt][kk] = __builtin_bit_cast(bf16x8, v);
+            for (int j = 0; j < NLD; ++j) {
+                const char *src = (const char *)(Qb + (int64_t)(min(lg * NLD + j, n_eff - 1) << qs) * p.qs_r) + (chunk0 ^ (uint32_t)(j << 4));
+                const uint32_t dst = __builtin_amdgcn_readfirstlane(ring + j * 1024);
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(src), "s"(dst) : "memory", "m0");
             }
+        } else {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int kk = 0; kk < KS; ++kk) {
+                    const uint4 v = *(const uint4 *)(Qb + (int64_t)(min(mt * 32 + col, n_eff - 1) << qs) * p.qs_r + kk * 16 + hh * 8);
+                    qf[mt][kk] = __builtin_bit_cast(bf16x8, v);
+                }
         }
     }
 
@@ -162,19 +174,27 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
         set_entry(2 * j + 1, rep_block(mid, e, rule) << lbk);
     };
     int m_len = Tb / kb;
+    uint32_t nd[E / 2];  // the nodes, in registers while the tiles pass through the buffers
     {
         const int r = Tb % kb;
-        for (int j = tix; j < kb; j += TN) {
+        auto first_node = [&](int j) __attribute__((always_inline)) {
             const int s = chunk_bound(j, m_len, r, kb, p.kb_magic), e = chunk_bound(j + 1, m_len, r, kb, p.kb_magic);
-            nodes[j] = (uint32_t)(s << 1 | (e - s - m_len));
             put_branches(j, s, e);
-            if constexpr (SPLIT) nodes[NB / 2 + j] = nodes[NB + j] = 0u;   // (own_s, beg_s)
+            return (uint32_t)(s << 1 | (e - s - m_len));
+        };
+        if constexpr (SPLIT) {
+            for (int j = tix; j < kb; j += TN) {
+                nodes[j] = first_node(j);
+                nodes[NB / 2 + j] = nodes[NB + j] = 0u;   // (own_s, beg_s)
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < E / 2; ++i) nd[i] = i * 64 + lane < kb ? first_node(i * 64 + lane) : 0u;
         }
         for (int i = 2 * kb + tix; i < NB; i += TN) set_entry(i, -1);
     }
     sync_unit();
 
-    const int lg = lane / CPR, lc = lane % CPR;  // loading role: tile rows lg*NLD .. +NLD-1, chunk lc
     // Contiguous keys: row 0 of this sequence / kv head as a buffer whose size ends with the last key.  A load past it (an
     // empty entry, a row past the end in the last block) is dropped by the address unit, so the loop has no clamps.
     // The slice address is the same in every lane; saying so (readfirstlane) makes it scalar (the launcher checks that
@@ -218,7 +238,6 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
     // memory instruction is issued inside a tile loop.  (M0 is a reserved register: the compiler warns that it does not
     // track the clobber.  It is written and consumed inside one asm statement, and nothing else in these kernels uses M0.)
     const int last = kv_len - 1;
-    const uint32_t chunk0 = (uint32_t)((lc ^ ((lg * NLD) & (CPR - 1))) << 4);
     auto issue_row = [&](const meta_t &mt_, uint32_t buf, int j) __attribute__((always_inline)) {
         const int i = SPL == 1 ? 0 : j >> LB;
         const int rho = lg * NLD + j, n = rho & (BK - 1);
@@ -242,7 +261,6 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
                          :: "v"(voff), "s"(srd), "s"(dst) : "memory", "m0");
         }
     };
-    const uint32_t ring0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds, ring = ring0 + wave * TILEB;
     // operands of the tile in `buf` (aligned to ROWB): tile row `col` sits in LDS row RPI (col % NLD) + col / NLD
     typedef __attribute__((address_space(3))) const u32x4 *lds_u32x4_ptr;
     const uint32_t op0 = (uint32_t)((RPI * (col % NLD) + col / NLD) * ROWB + ((hh ^ (col & (CPR - 1))) << 4));
@@ -292,6 +310,13 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
 
     static_assert(NLD == KS, "one load per k-step");
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if constexpr (QLDS) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        u32x4 qv[KS];
+        read_operands(ring, qv);
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) qf[0][kk] = __builtin_bit_cast(bf16x8, qv[kk]);
+    }
     // The query loads end here, where the compiler can see it: it does not count the loads that the tile loop
     // issues from inline assembly, and a wait for a query fragment left inside that loop would wait for them.
 #pragma unroll
@@ -309,13 +334,11 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
     const int ens_round = ens_round_of(p.ens_sample, (Tb + kb - 1) / kb);
     const uint32_t ens_hash = ens_round >= 0 ? ens_unit_hash(p.ens_seed, p.ens_sample, b, h, qb) : 0u;
     int round = 0;
-    uint32_t nd[E / 2];  // the nodes, in registers while the tiles pass through the buffers
     uint32_t own[SPLIT ? 1 : E / 2], beg[SPLIT ? 1 : E / 2];
 #pragma unroll
-    for (int i = 0; i < E / 2; ++i) nd[i] = nodes[i * 64 + lane];
-    if constexpr (!SPLIT) {
-#pragma unroll
-        for (int i = 0; i < E / 2; ++i) own[i] = beg[i] = 0u;
+    for (int i = 0; i < E / 2; ++i) {
+        if constexpr (SPLIT) nd[i] = nodes[i * 64 + lane];
+        else own[i] = beg[i] = 0u;
     }
     auto own_of = [&](int i) __attribute__((always_inline)) { return SPLIT ? own_s[i * 64 + lane] : own[SPLIT ? 0 : i]; };
     auto beg_of = [&](int i) __attribute__((always_inline)) { return SPLIT ? beg_s[i * 64 + lane] : beg[SPLIT ? 0 : i]; };
