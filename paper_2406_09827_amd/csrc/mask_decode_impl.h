@@ -52,6 +52,10 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 
     constexpr int U = ROWS / BK;      // branches per lane group and stage: ROWS row loads per lane, two stages in flight
     constexpr int COPIES = LPR / ROWS; // lanes that end up with the same row
     static_assert(ROWS <= LPR && U >= 1 && E % 2 == 0, "stage shape");
+    // Up to 64 nodes hand on their own keys alone, and only to a round with one entry a node: their rounds are so short that first
+    // blocks' keys cost what they save (64 channels, k/bk = 32, the first block as representative: 1920 problems 48.0 us handing both on,
+    // 45.4 so; 6 problems 16.1 / 15.0).
+    constexpr bool HAND_ON = E > 2;
     constexpr int SW = WS < 4 ? 1 : WS == 4 ? 4 : (H < 4 ? H : 4);   // waves that select
     typedef uint32_t stage_t __attribute__((ext_vector_type(4 * ROWS)));
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -254,16 +258,16 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 
 #pragma unroll
             for (int i = 0; i < H; ++i) {
                 own_key[i] = known[i * 64 + lane];
-                beg_key[i] = known[kb + i * 64 + lane];
+                beg_key[i] = HAND_ON ? known[kb + i * 64 + lane] : 0u;
             }
         }
         auto own_of = [&](int i) __attribute__((always_inline)) { return SPLIT ? known[i * 64 + lane] : own_key[SPLIT ? 0 : i]; };
-        auto beg_of = [&](int i) __attribute__((always_inline)) { return SPLIT ? known[kb + i * 64 + lane] : beg_key[SPLIT ? 0 : i]; };
+        auto beg_of = [&](int i) __attribute__((always_inline)) { return !HAND_ON ? 0u : SPLIT ? known[kb + i * 64 + lane] : beg_key[SPLIT ? 0 : i]; };
         sync_problem();
 
         const int m_next = m_len >> 1;
         // (with the first or last block every node has one branch at most to score, with the centre nodes of one or two blocks)
-        const bool last = maxlen <= 2, next_one = p.rep_pos != 0 || ((maxlen + 1) >> 1) == 2, next_knows = round_knows_scores(p.rep_pos, m_next);
+        const bool last = maxlen <= 2, next_one = p.rep_pos != 0 || ((maxlen + 1) >> 1) == 2, next_knows = HAND_ON ? round_knows_scores(p.rep_pos, m_next) : next_one;
         if (selects) {
             uint32_t kl[H], kr[H];   // keys of the left and the right branch of node i * 64 + lane
             if (one_each) {
@@ -293,8 +297,8 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 
             auto keep_one = [&](auto any, int d, uint32_t child, uint32_t own, uint32_t beg) __attribute__((always_inline)) {
                 nodes[d] = child;
                 if (any && last) return;
-                next_known[d] = own;
-                if (!any || rule.beg_left) next_known[kb + d] = beg;
+                if (any || HAND_ON) next_known[d] = own;
+                if (HAND_ON && (!any || rule.beg_left)) next_known[kb + d] = beg;
                 const int s = (int)(child >> 1), len = m_next + (int)(child & 1), mid = s + (len >> 1);
                 if (!any || !next_knows) {
                     put_branches(next_tab, d, s, s + len);
@@ -315,7 +319,7 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 
                 if (SPLIT && i % SW != wave) return;
                 // a node of `len` blocks: len / 2 to the left, the rest to the right; m_len / 2 or one more
                 const uint32_t bit = nd[i] & 1u, s2 = nd[i] & ~1u, len = (uint32_t)m_len + bit;
-                const uint32_t own = own_of(i), beg = beg_of(i);
+                const uint32_t own = HAND_ON ? own_of(i) : 0u, beg = beg_of(i);   // (own: what a right half begins with)
                 if (keep_l) keep_one(any, dl, s2 | (odd ? bit : 0u), kl[i], beg);
                 if (keep_r) keep_one(any, dr, (s2 + (len & ~1u)) | (odd ? 1u : bit), kr[i], own);
             };

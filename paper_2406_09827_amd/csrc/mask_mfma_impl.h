@@ -28,8 +28,9 @@
 // is why the result needs no sort.
 // Measured, 32 query heads over 8 kv heads, d = 128, k = 512, bq = 32, bk = 2, against the form before (registers and
 // ds_write, or straight into LDS with three waves a SIMD): 8k tokens 245 -> 217 us, 32k 1742 -> 1568; k = 2048 5929 -> 3864; bq = 64
-// 1701 -> 1076; 16 heads of 64 channels, 16k tokens, bq = 64, bk = 4 159 -> 106.  At 32k the cache's data return path is 89 %
-// busy, the address unit 75 %, cache accesses 65 %, vector issue 50 %, the matrix pipe 38 %.
+// 1701 -> 1076; 16 heads of 64 channels, 16k tokens, bq = 64, bk = 4 159 -> 106.  By the clock, 32k tokens, sixteen waves a
+// compute unit: 60000 clocks for the 32 tiles of a full round (1870 a tile; the multiplies take 256 of a SIMD's for each of its four waves),
+// 45000 for the shared first one, 3000 each for the last two, 8500 for a round's selection and survivors.
 #pragma once
 #include "common.h"
 #include "launch.h"
