@@ -41,8 +41,19 @@ namespace hipattn {
 //          that each has a compute unit to itself, where the chain of latencies in a round is the time.
 // MODE 0: contiguous keys, a (sequence, kv head) slice below 2 GB, addressed as a buffer that ends with the last key (a load past
 //         it returns 0, so nothing is clamped); MODE 1: paged pool; MODE 2: contiguous, any size (64-bit row addresses).
+//
+// Waves per SIMD that the registers are laid out for.  With up to 64 nodes five fit (96 registers), where that spills nothing or one: the
+// keys that nodes hand on took most of these kernels to four (104 registers).  us, four / five waves: 4096 problems of 8192 tokens, k/bk = 64,
+// bk = 1, 64 channels 83.6 / 76.6, first block as representative 80.5 / 73.8; 128 channels 114.7 / 109.6, 94.2 / 87.2; 9600 problems of 4096
+// tokens over pages, 64 channels 115 / 110.  Four stay for four waves a problem over pages (2 to 5 spilled) and for 128 channels with two
+// or four rows a block (one spilled: 4096 problems, k/bk = 64 174 / 181, 9600 276 / 294).
+constexpr int decode_waves(int E, int BK, int D, int MODE, int WS)
+{
+    const bool five = E == 2 && (WS == 1 || (MODE != 1 && (D == 64 || BK == 1 || BK == 8)));
+    return WS == 16 ? 4 : five ? 5 : E <= 8 ? 4 : E == 16 ? 3 : 2;
+}
 template <int E, int BK, int D, int ROWS, int MODE, int WS>
-__global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 : E == 16 ? 3 : 2) void mask_decode_kernel(KParams p, int xcd_map)
+__global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, MODE, WS)) void mask_decode_kernel(KParams p, int xcd_map)
 {
     constexpr bool SPLIT = WS > 1, PAGED = MODE == 1;
     constexpr int WGT = WS == 16 ? 1024 : kThreads;   // threads of the workgroup
@@ -338,7 +349,7 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, WS == 16 || E <= 8 ? 4 
                     pr[i] = ens_key(kr[i], ens_hash, rep_block(mid, e, rule), p.ens_r);
                 }
                 select_topk_pairs<H, SEARCH>(pl, pr, kb, keep_any);
-            } else if (next_knows) {   // (also after the last round)
+            } else if (next_knows) {   // (E > 2: also after the last round)
                 select_topk_pairs<H, SEARCH>(kl, kr, kb, keep_any);
             } else {
                 select_topk_pairs<H, SEARCH>(kl, kr, kb, keep_all);
