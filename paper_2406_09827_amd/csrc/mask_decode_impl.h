@@ -304,10 +304,12 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, 
             }
             const bool odd = m_len & 1;
             uint32_t *next_known = SPLIT ? known_s[cur ^ 1] : tab;
-            // (two forms, so that the survivors' code has few branches: with a round to come that scores every branch, and any other)
+            // (two forms, so that the survivors' code has few branches: with a round to come that scores every branch, and any other.
+            // After the last round, which up to 64 nodes takes either, no table is written: 32 problems of 8192 tokens over pages, 128
+            // channels, k/bk = 32 16.9 us writing one, 16.7 so)
             auto keep_one = [&](auto any, int d, uint32_t child, uint32_t own, uint32_t beg) __attribute__((always_inline)) {
                 nodes[d] = child;
-                if (any && last) return;
+                if ((any || !HAND_ON) && last) return;
                 if (any || HAND_ON) next_known[d] = own;
                 if (HAND_ON && (!any || rule.beg_left)) next_known[kb + d] = beg;
                 const int s = (int)(child >> 1), len = m_next + (int)(child & 1), mid = s + (len >> 1);
@@ -349,7 +351,7 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, 
                     pr[i] = ens_key(kr[i], ens_hash, rep_block(mid, e, rule), p.ens_r);
                 }
                 select_topk_pairs<H, SEARCH>(pl, pr, kb, keep_any);
-            } else if (next_knows) {   // (E > 2: also after the last round)
+            } else if (next_knows) {   // (more than 64 nodes: also after the last round)
                 select_topk_pairs<H, SEARCH>(kl, kr, kb, keep_any);
             } else {
                 select_topk_pairs<H, SEARCH>(kl, kr, kb, keep_all);
