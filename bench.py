@@ -37,12 +37,46 @@ def rounds_of(Tb: int, kb: int) -> int:
     return (c - 1).bit_length()
 
 
+def least_branches_scored(Tb: int, kb: int, rep_pos: int = 0) -> int:
+    """Branches that a unit with Tb visible key blocks has to score whatever the scores are: those whose representative
+    block no earlier round can have scored.  All of them in the first round; later the nodes are m or m + 1 blocks long
+    (m halves from round to round), and of a node of n blocks at least need(n) branches have no score yet.  Centre block as
+    representative: the right half of two blocks, the left half of two or three and a block alone may be known, so
+    need = 0, 0, 1, 2, 2, ...; first or last block: one child has its parent's representative, need = 0, 1, 1, ..."""
+    if Tb <= kb:
+        return 0
+    m = Tb // kb
+    total = 2 * kb if m > 1 else Tb      # (a node of one block has one branch)
+    for _ in range(rounds_of(Tb, kb) - 1):
+        m >>= 1
+        total += kb * (min(max(m - 2, 0), 2) if rep_pos == 0 else min(m - 1, 1))
+    return total
+
+
+def _units(w, kv_lens):
+    """(rows, visible key blocks) of every query block of every sequence, one head."""
+    for b in range(w.batch):
+        kv_len = int(kv_lens[b]) if kv_lens is not None else w.kv_len
+        for qb in range(w.n_query_blocks):
+            r0 = qb * w.bq
+            n = min(w.bq, w.q_len - r0)
+            L = min(kv_len, kv_len - w.q_len + r0 + n)
+            yield n, -(-L // w.bk) if L > 0 else 0
+
+
+def mask_scored_bytes(w, kv_lens, rep_pos: int = 0, b_sk: int = 1) -> float:
+    """Bytes that mask estimation cannot do without: the key rows of the branches that have to be scored
+    (least_branches_scored; the kernels score a few more, by the nodes that survive), the query block once and the indices."""
+    row = w.head_dim * (2 if w.dtype == "bf16" else 4)
+    total = sum(least_branches_scored(Tb, w.kb, rep_pos) * (w.bk // b_sk) * row + n * row + w.kb * 4 for n, Tb in _units(w, kv_lens))
+    return float(total) * w.n_q_heads
+
+
 def mask_algorithmic_bytes(w, kv_lens, rep_pos: int = 0) -> float:
-    """Key bytes the method has to touch in mask estimation, counted conservatively:
-    every round but a unit's last scores 2*kb branches, the last at least kb (nodes that are
-    already one block long have a single branch); plus the query block once and the indices.
-    With the first or last block as representative, a child that shares its parent's representative
-    needs no new bytes: one round of 2*kb branches, kb per later round."""
+    """Key bytes of the branches that the method's rounds name, whether their scores are known or not: 2*kb branches a
+    round, kb in a unit's last (nodes that are already one block long have a single branch); plus the query block once and the
+    indices.  With the first or last block as representative, a child that shares its parent's representative is left out:
+    one round of 2*kb branches, kb per later round.  The kernels read less (mask_scored_bytes), so no rate is formed of it."""
     size = 2 if w.dtype == "bf16" else 4
     row = w.head_dim * size
     total = 0.0
@@ -81,22 +115,9 @@ def attn_algorithmic(w, kv_lens):
 
 
 def mask_score_flops(w, kv_lens, rep_pos: int = 0, b_sq: int = 1, b_sk: int = 1) -> float:
-    """Multiply-adds of the block scores as flops: 2 * rows * keys * d per scored branch, with the same
-    branch count as mask_algorithmic_bytes."""
-    total = 0.0
-    for b in range(w.batch):
-        kv_len = int(kv_lens[b]) if kv_lens is not None else w.kv_len
-        for qb in range(w.n_query_blocks):
-            r0 = qb * w.bq
-            n = min(w.bq, w.q_len - r0)
-            L = min(kv_len, kv_len - w.q_len + r0 + n)
-            Tb = -(-L // w.bk) if L > 0 else 0
-            R = rounds_of(Tb, w.kb)
-            if rep_pos == 0:
-                branches = (R - 1) * 2 * w.kb + w.kb if R > 0 else 0
-            else:
-                branches = (R + 1) * w.kb if R > 0 else 0
-            total += 2.0 * branches * (w.bk // b_sk) * -(-n // b_sq) * w.head_dim
+    """Multiply-adds of the block scores as flops: 2 * rows * keys * d per branch that has to be scored
+    (least_branches_scored)."""
+    total = sum(2.0 * least_branches_scored(Tb, w.kb, rep_pos) * (w.bk // b_sk) * -(-n // b_sq) * w.head_dim for n, Tb in _units(w, kv_lens))
     return total * w.n_q_heads
 
 
@@ -343,7 +364,7 @@ def measure(args, w, tag, steps, warmup, with_cpu):
     ms_mask, ms_attn = sum(t_mask) / len(t_mask), sum(t_attn) / len(t_attn)
 
     size = 2 if w.dtype == "bf16" else 4
-    mask_bytes = n_e * mask_algorithmic_bytes(w, kv_lens, args.rep_pos)
+    mask_bytes = n_e * mask_scored_bytes(w, kv_lens, args.rep_pos, max(args.b_sk, 1))
     mask_flops = n_e * mask_score_flops(w, kv_lens, args.rep_pos, max(args.b_sq, 1), max(args.b_sk, 1))
     # (ensemble: the merged list is at most k_attn keys long; its real length depends on the data, so the
     # attention's algorithmic figures are upper bounds there)
@@ -368,7 +389,7 @@ def measure(args, w, tag, steps, warmup, with_cpu):
         traffic, tsrc = read_traffic(f"{kernel}_{tag}")
         c = {}
         if kernel == "mask_estimate":
-            # bytes side: every scored key row passes L2 -> compute unit once (algorithmic bytes); whether it also
+            # bytes side: every key row that has to be scored passes L2 -> compute unit once (mask_scored_bytes); whether it also
             # passes HBM -> L2 depends on the working set, so the HBM fraction by algorithmic bytes is a candidate
             # that only binds when it stays a fraction (decode over GBs of keys), and the HBM-side counter bytes of
             # an earlier profile run, when current, give the memory-side rate
