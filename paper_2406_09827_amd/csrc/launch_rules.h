@@ -50,6 +50,19 @@ inline bool mask_item_per_workgroup(int64_t units, int kb, int d, bool two_tiles
     return paged || units <= 768 || key_bytes <= (few ? 2 : 1) * mb * gc;
 }
 
+// Prefill mask, k/bk up to 128: do nodes hand on their first blocks' scores, so that branches of the last two rounds that an earlier round
+// has scored are left out, or their own scores alone (one branch a node from the second round on with the first or last block as
+// representative, in the last round with the centre).  With the first or last block nothing else is known.  With the centre the rows that are
+// not gathered pay for the bookkeeping but where they are 128 bytes each.  Measured, 16 heads over 4 kv heads, bq = 32, own scores alone / all, us:
+//   last block as representative, 16k tokens: 128 channels, bk = 2, k/bk = 32 78.7 / 85.3, 64 100.8 / 103.2; 64 channels, bk = 1, k/bk = 16 65.4 / 72.0
+//   centre, 16k tokens, bk = 1: 64 channels k/bk = 16 59.4 / 62.0 (33k tokens 112 / 120), 64 67.6 / 69.5 (135 / 142), 96 79.6 / 76.9 (159 / 160), 128
+//     85.8 / 82.5; over 64-row blocks, 33k tokens, k/bk = 64 102.9 / 98.5; bk = 2, k/bk = 16 61.0 / 60.4, 48 76.7 / 72.6;
+//     128 channels, bk = 1, k/bk = 16 74.4 / 73.7, 48 91.0 / 87.6; bk = 2, k/bk = 32 97.0 / 92.3, 48 120 / 111
+inline bool mask_hands_on(int kb, int d, int scored_rows, bool two_tiles, int rep_pos)
+{
+    return rep_pos == 0 && (d == 128 || scored_rows > 1 || two_tiles || kb > 64);
+}
+
 // Workgroups of the prefill mask kernel that may share a compute unit (0: as many as fit), by the bytes of a kv head's keys.  Where
 // these do not stay in the caches the kernel waits for the memory side, and what counts is how often the waves of an XCD meet in
 // its L2: fewer workgroups at a time (the launch asks for LDS that it does not use) meet more often.  Measured, in ms, as many as

@@ -18,8 +18,9 @@
 //   * A block's score replaces its table entry, so a wave's whole state is the table (2 KB for 512 branches) and a tile.
 //     With that and 128 registers four waves fit a SIMD, which is what the loop lives on: a wave has one tile in flight,
 //     and its own chain (operands from LDS, multiplies one after the other, reduction) is long.
-//   * A branch whose representative block was scored in an earlier round keeps that score (known_branches in common.h): most
-//     branches of the last two or three rounds, which score what is left from a compact list.  (Before, only the right halves
+//   * A branch whose representative block was scored in an earlier round keeps that score (known_branches in common.h): with the centre as
+//     representative most branches of the last round, and those of two or three blocks in the one before it; with the first or last block
+//     one child of every node in every round after the first.  Such rounds score what is left from a compact list.  (Before, only the right halves
 //     of two-block nodes in the last round did: 32k tokens 1.57 -> 1.36 ms, 128k 14.05 -> 12.2, a million 376 -> 343, 32 draft
 //     rows over 12k tokens 96 times 0.59 -> 0.51.)
 //   * A lane holds nodes and their two scores each; the wave runs the ordered threshold selection, writes the surviving
@@ -56,7 +57,9 @@ __device__ __forceinline__ float max_half_swap(float v)
 // SHARE (with WPI = 1): the four waves of a workgroup are four query heads of ONE (sequence, kv head, query block).  In
 // the first round they all score the same representative blocks (the initial nodes depend on the lengths only), so they
 // go through that round in step: every tile is loaded once, a quarter of it by each wave, and read by all of them.
-template <int MT, int E, int D, bool PAGED, int LB, int WPI, bool SHARE>
+// HAND_ON: nodes hand on what they know of their own and of their first block's score in every round; without it a node's own score alone, and
+// only to a round with one branch a node to score (below).
+template <int MT, int E, int D, bool PAGED, int LB, int WPI, bool SHARE, bool HAND_ON>
 __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
 {
     static_assert(WPI == 1 || (WPI == 4 && !SHARE), "a wave or a workgroup per work item");
@@ -78,7 +81,7 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
     // the wave's tile buffer between two rounds and in registers during one (SPLIT: in an array of their own, with two more for
     // what they know).
     constexpr int kOffTab = 4 * TILEB, kOffPg = kOffTab + NS * NB * 4, kOffNode = kOffPg + (PAGED ? NS * NB * 4 : 0);
-    __shared__ __attribute__((aligned(1024))) char lds[kOffNode + (SPLIT ? NB * 6 : 0)];
+    __shared__ __attribute__((aligned(1024))) char lds[kOffNode + (SPLIT ? NB * (HAND_ON ? 6 : 2) : 0)];
     static_assert(4 * TILEB <= 65536 && NB * 2 <= TILEB, "LDS layout");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -186,7 +189,7 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
         if constexpr (SPLIT) {
             for (int j = tix; j < kb; j += TN) {
                 nodes[j] = first_node(j);
-                nodes[NB / 2 + j] = nodes[NB + j] = 0u;   // (own_s, beg_s)
+                if (HAND_ON) nodes[NB / 2 + j] = nodes[NB + j] = 0u;   // (own_s, beg_s)
             }
         } else {
 #pragma unroll
@@ -328,21 +331,26 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
     // Scores of earlier rounds: with a node go the keys of its own and its first block's score (known_branches).  A round that
     // profits from them runs from a compact list of what is left to score, node by node, left before right.  (Survivors take the
     // two along through the table, which is free while they are written; SPLIT: in arrays of their own.)
-    uint32_t *own_s = SPLIT ? nodes + NB / 2 : tab, *beg_s = SPLIT ? own_s + NB / 2 : tab + kb;
+    // Not HAND_ON: with the first (last) block as representative every round after the first is a list of the right (left) branches of
+    // nodes of two blocks and more, with the centre the last one, of left halves.  What a node knows is the score of its other branch, or of
+    // itself alone; it lies in the upper half of the table, since the list has an entry a node.
+    uint32_t *own_s = !HAND_ON ? tab + NB / 2 : SPLIT ? nodes + NB / 2 : tab, *beg_s = SPLIT ? own_s + NB / 2 : tab + kb;
+    const bool first_rule = p.rep_pos == 1;
     bool list = false;
     int n_entries = 2 * kb;
     // ensemble sample: the round whose selection compares perturbed scores (-1: none)
     const int ens_round = ens_round_of(p.ens_sample, (Tb + kb - 1) / kb);
     const uint32_t ens_hash = ens_round >= 0 ? ens_unit_hash(p.ens_seed, p.ens_sample, b, h, qb) : 0u;
     int round = 0;
-    uint32_t own[SPLIT ? 1 : E / 2], beg[SPLIT ? 1 : E / 2];
+    constexpr bool IN_REGS = HAND_ON && !SPLIT;
+    uint32_t own[IN_REGS ? E / 2 : 1], beg[IN_REGS ? E / 2 : 1];
 #pragma unroll
     for (int i = 0; i < E / 2; ++i) {
         if constexpr (SPLIT) nd[i] = nodes[i * 64 + lane];
-        else own[i] = beg[i] = 0u;
+        if constexpr (IN_REGS) own[i] = beg[i] = 0u;
     }
-    auto own_of = [&](int i) __attribute__((always_inline)) { return SPLIT ? own_s[i * 64 + lane] : own[SPLIT ? 0 : i]; };
-    auto beg_of = [&](int i) __attribute__((always_inline)) { return SPLIT ? beg_s[i * 64 + lane] : beg[SPLIT ? 0 : i]; };
+    auto own_of = [&](int i) __attribute__((always_inline)) { return IN_REGS ? own[IN_REGS ? i : 0] : own_s[i * 64 + lane]; };
+    auto beg_of = [&](int i) __attribute__((always_inline)) { return IN_REGS ? beg[IN_REGS ? i : 0] : beg_s[i * 64 + lane]; };
     auto known = [&](int i, uint32_t &left, uint32_t &right, bool &need_l, bool &need_r) __attribute__((always_inline)) {
         const int len = i * 64 + lane < kb ? m_len + (int)(nd[i] & 1) : 0;
         known_branches(rule, len, own_of(i), beg_of(i), left, right, need_l, need_r);
@@ -356,7 +364,7 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
             // it says that tile t has landed (every wave waited for its share) and that every wave has the operands of
             // tile t - 1 in registers, so that its buffer may be refilled.  (Waves hold equal tables here.)
             constexpr int SH = NLD / 4;
-            asm volatile("s_barrier" ::: "memory");   // every wave holds its nodes in registers
+            asm volatile("s_barrier" ::: "memory");   // every wave has its query tile out of its buffer, which the others now load into
             auto issue_share = [&](int t) __attribute__((always_inline)) {
                 // load j = SH * wave + jj: the lane's row of load j
 #pragma unroll
@@ -451,6 +459,16 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
             int n_before = 0;
 #pragma unroll
             for (int i = 0; i < E / 2; ++i) {
+                if constexpr (!HAND_ON) {
+                    const int j = i * 64 + lane;
+                    const bool two = j < kb && m_len + (int)(nd[i] & 1) > 1;
+                    const uint64_t b2 = __ballot(two);
+                    kr[i] = j < kb ? own_s[j] : 0u;
+                    kl[i] = two ? score_key_bits(tab[n_before + lane_prefix_count(b2)]) : 0u;
+                    if (first_rule && two) { const uint32_t x = kr[i]; kr[i] = kl[i]; kl[i] = x; }
+                    n_before += __popcll(b2);
+                    continue;
+                }
                 bool need_l, need_r;
                 known(i, kl[i], kr[i], need_l, need_r);
                 const uint64_t bl = __ballot(need_l), br = __ballot(need_r);
@@ -469,7 +487,7 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
         }
         // SPLIT: what the nodes know whose survivors this wave writes, before they are overwritten
         uint32_t own_w[(E / 2 + 3) / 4], beg_w[(E / 2 + 3) / 4];
-        if constexpr (SPLIT) {
+        if constexpr (SPLIT && HAND_ON) {
 #pragma unroll
             for (int i = 0; i < (E / 2 + 3) / 4; ++i) {
                 const int j = min((i * 4 + wave) * 64 + lane, NB / 2 - 1);
@@ -477,7 +495,7 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
                 beg_w[i] = beg_s[j];
             }
         }
-        const bool next_list = round_knows_scores(p.rep_pos, m_len >> 1);
+        const bool next_list = HAND_ON ? round_knows_scores(p.rep_pos, m_len >> 1) : p.rep_pos != 0 || ((maxlen + 1) >> 1) == 2;
         sync_unit();   // (every wave has the scores)
         // Ordered top-kb selection; survivors go to their places in the node array, with the keys they know.
         auto keep_child = [&](int i, bool kl_, int dl, bool kr_, int dr) __attribute__((always_inline)) {
@@ -485,7 +503,12 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
             int len;
             uint32_t left, right;
             child_of(nd[i], len, left, right);
-            const uint32_t o = SPLIT ? own_w[i / 4] : own[SPLIT ? 0 : i], f = SPLIT ? beg_w[i / 4] : beg[SPLIT ? 0 : i];
+            if constexpr (!HAND_ON) {
+                if (kl_) { nodes[dl] = left; if (next_list) own_s[dl] = kl[i]; }
+                if (kr_) { nodes[dr] = right; if (next_list) own_s[dr] = kr[i]; }
+                return;
+            }
+            const uint32_t o = SPLIT ? own_w[i / 4] : own[IN_REGS ? i : 0], f = SPLIT ? beg_w[i / 4] : beg[IN_REGS ? i : 0];
             if (kl_) { nodes[dl] = left; own_s[dl] = kl[i]; beg_s[dl] = f; }
             if (kr_) { nodes[dr] = right; own_s[dr] = kr[i]; beg_s[dr] = o; }
         };
@@ -507,10 +530,10 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
 #pragma unroll
         for (int i = 0; i < E / 2; ++i) {
             nd[i] = nodes[i * 64 + lane];
-            if constexpr (!SPLIT) { own[i] = own_s[i * 64 + lane]; beg[i] = beg_s[i * 64 + lane]; }
+            if constexpr (IN_REGS) { own[i] = own_s[i * 64 + lane]; beg[i] = beg_s[i * 64 + lane]; }
         }
         if (maxlen <= 2) break;   // every node is one block
-        wave_lds_sync();   // (they are in registers: the table's entries may be written)
+        if constexpr (HAND_ON) wave_lds_sync();   // (they are in registers: the table's entries may be written)
         // the blocks that the next round scores
         if (!next_list) {
 #pragma unroll
@@ -523,6 +546,14 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
             int n_todo = 0;
 #pragma unroll
             for (int i = 0; i < E / 2; ++i) {
+                if constexpr (!HAND_ON) {
+                    const int s = (int)(nd[i] >> 1), len = m_len + (int)(nd[i] & 1);
+                    const bool two = i * 64 + lane < kb && len > 1;
+                    const uint64_t b2 = __ballot(two);
+                    if (two && (!SPLIT || i % WPI == wave)) set_entry(n_todo + lane_prefix_count(b2), (s + (len >> 1) - (first_rule ? 0 : 1)) << lbk);
+                    n_todo += __popcll(b2);
+                    continue;
+                }
                 uint32_t left, right;
                 bool need_l, need_r;
                 const int len = known(i, left, right, need_l, need_r);
@@ -561,48 +592,49 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
 // 340 / 360, 256 511 / 528, 512 level (two fit); contiguous, k/bk = 512, bk = 1 470 / 483, bk = 2 628 / 665, bk = 4 809 / 832,
 // bk = 8 860 / 887 (8 heads 151 / 145, 200 / 197 and level): three.
 // One tile, bk = 1 and 512 slots over pages, a workgroup per item spills 2 at four waves: 1024 rows 70 us, at three waves 89.
-constexpr int mask_waves(int MT, int E, int D, bool PAGED, bool SPLIT)
+constexpr int mask_waves(int MT, int E, int D, bool PAGED, bool SPLIT, bool HAND_ON)
 {
-    const int lds_wave = 32 * D * 2 + (SPLIT ? 64 * E : 256 * E) * (PAGED ? 2 : 1) + (SPLIT ? 96 * E : 0);
+    const int lds_wave = 32 * D * 2 + (SPLIT ? 64 * E : 256 * E) * (PAGED ? 2 : 1) + (SPLIT ? (HAND_ON ? 96 : 32) * E : 0);
     const int by_lds = (160 << 10) / (4 * lds_wave), by_regs = MT == 2 && D == 128 ? (E >= 32 || (PAGED && SPLIT) ? 2 : 3) : E >= 32 ? 2 : E >= 16 ? 3 : 4;
     return by_lds < by_regs ? by_lds : by_regs;
 }
-template <int MT, int E, int D, bool PAGED, int LB, int WPI, bool SHARE>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(mask_waves(MT, E, D, PAGED, WPI > 1)))) void mask_mfma_kernel(KParams p, int xcd_map)
+template <int MT, int E, int D, bool PAGED, int LB, int WPI, bool SHARE, bool HAND_ON>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(mask_waves(MT, E, D, PAGED, WPI > 1, HAND_ON)))) void mask_mfma_kernel(KParams p, int xcd_map)
 {
-    mask_mfma_body<MT, E, D, PAGED, LB, WPI, SHARE>(p, xcd_map);
+    mask_mfma_body<MT, E, D, PAGED, LB, WPI, SHARE, HAND_ON>(p, xcd_map);
 }
 
-template <int MT, int E, int D, int LB>
+template <int MT, int E, int D, int LB, bool HAND_ON>
 static hipError_t launch_mask_mfma_e(const KParams &p, int xcd_map, dim3 grid, bool split, bool one_sequence_per_workgroup, hipStream_t st)
 {
     // (the four work items of a workgroup are then four heads of one query block: they share the first round's tiles)
     const bool share = one_sequence_per_workgroup && p.g % 4 == 0 && !p.page_table && !(p.flags & 2);
     const int per_cu = mask_workgroups_per_cu(p.max_kv_len, D, p.kv_lens == nullptr);
     const auto launch = [&](auto kernel, bool paged, bool split_) {
-        const int lds = (split_ ? 1 : 4) * 256 * E * (paged ? 2 : 1) + 4 * 64 * D + (split_ ? 384 * E : 0);
+        const int lds = (split_ ? 1 : 4) * 256 * E * (paged ? 2 : 1) + 4 * 64 * D + (split_ ? (HAND_ON ? 384 : 128) * E : 0);
         const int pad = per_cu && !split_ ? (160 << 10) / per_cu - lds : 0;
         hipLaunchKernelGGL(kernel, grid, dim3(kThreads), (unsigned)(pad > 0 ? pad & ~1023 : 0), st, p, xcd_map);
         return hipGetLastError();
     };
     // the page-table variant is a separate instantiation: a table read in the row-offset code
     // would otherwise put a full memory wait into the contiguous path's load pipeline
-    if (split) return p.page_table ? launch(mask_mfma_kernel<MT, E, D, true, LB, 4, false>, true, true)
-                                   : launch(mask_mfma_kernel<MT, E, D, false, LB, 4, false>, false, true);
+    if (split) return p.page_table ? launch(mask_mfma_kernel<MT, E, D, true, LB, 4, false, HAND_ON>, true, true)
+                                   : launch(mask_mfma_kernel<MT, E, D, false, LB, 4, false, HAND_ON>, false, true);
     if (p.page_table) {
-        if constexpr (E < 32 || D == 64) return launch(mask_mfma_kernel<MT, E, D, true, LB, 1, false>, true, false);
+        if constexpr (E < 32 || D == 64) return launch(mask_mfma_kernel<MT, E, D, true, LB, 1, false, HAND_ON>, true, false);
         return hipErrorInvalidValue;
     }
-    return share ? launch(mask_mfma_kernel<MT, E, D, false, LB, 1, true>, false, false)
-                 : launch(mask_mfma_kernel<MT, E, D, false, LB, 1, false>, false, false);
+    return share ? launch(mask_mfma_kernel<MT, E, D, false, LB, 1, true, HAND_ON>, false, false)
+                 : launch(mask_mfma_kernel<MT, E, D, false, LB, 1, false, HAND_ON>, false, false);
 }
 template <int MT, int D, int LB>
 static hipError_t launch_mask_mfma_d(const KParams &p, int xcd_map, dim3 grid, bool split, bool one_seq, hipStream_t st)
 {
-    if (p.kb <= 128) return launch_mask_mfma_e<MT, 4, D, LB>(p, xcd_map, grid, split, one_seq, st);
-    if (p.kb <= 256) return launch_mask_mfma_e<MT, 8, D, LB>(p, xcd_map, grid, split, one_seq, st);
-    if (p.kb <= 512) return launch_mask_mfma_e<MT, 16, D, LB>(p, xcd_map, grid, split, one_seq, st);
-    return launch_mask_mfma_e<MT, 32, D, LB>(p, xcd_map, grid, split, one_seq, st);
+    if (p.kb <= 128) return mask_hands_on(p.kb, D, 1 << LB, MT == 2, p.rep_pos) ? launch_mask_mfma_e<MT, 4, D, LB, true>(p, xcd_map, grid, split, one_seq, st)
+                                                           : launch_mask_mfma_e<MT, 4, D, LB, false>(p, xcd_map, grid, split, one_seq, st);
+    if (p.kb <= 256) return launch_mask_mfma_e<MT, 8, D, LB, true>(p, xcd_map, grid, split, one_seq, st);
+    if (p.kb <= 512) return launch_mask_mfma_e<MT, 16, D, LB, true>(p, xcd_map, grid, split, one_seq, st);
+    return launch_mask_mfma_e<MT, 32, D, LB, true>(p, xcd_map, grid, split, one_seq, st);
 }
 
 // One translation unit per key-block size instantiates this.
