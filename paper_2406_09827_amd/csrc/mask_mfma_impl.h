@@ -123,9 +123,11 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
     // query block as MFMA A operand: lane holds row (lane % 32) [+32], 8 channels per k-step.  Operand rows past the sampled rows of the
     // block repeat the last one: a repeated row cannot change a maximum, so tiles that need no causal masking take the short
     // reduction whatever the number of rows.  One tile travels like a key tile, through the wave's tile buffer, and lands while
-    // the initial nodes are laid out (straight into registers, a row a lane, each of its
-    // loads is 64 cache accesses: 256 rows of 4 sequences over pages 135.7 -> 133.8 us with the attention, 3k tokens 98.9 -> 97.2).
-    constexpr bool QLDS = MT == 1;
+    // the initial nodes are laid out, where that is the faster way (straight into registers, a row a lane, each of its
+    // loads is 64 cache accesses).  Measured, 32 heads, bk = 2, registers / buffer, us: a workgroup per item, the last 256 rows of 4
+    // sequences over pages, k/bk = 256 54.4 / 52.1; a wave per item, 3k tokens: 64 channels, k/bk = 64 25.4 / 24.5 (16-row blocks 37.7 /
+    // 33.5); 128 channels, k/bk = 256 50.1 / 49.0, but 32 27.4 / 28.1, 64 32.1 / 32.7 (16-row blocks 56.8 / 61.4), 512 57.7 / 58.1, 1024 99.5 / 102.2.
+    constexpr bool QLDS = MT == 1 && (SPLIT || PAGED || D == 64 || E == 8);
     const int lg = lane / CPR, lc = lane % CPR;  // loading role: tile rows lg*NLD .. +NLD-1, chunk lc
     const uint32_t chunk0 = (uint32_t)((lc ^ ((lg * NLD) & (CPR - 1))) << 4);
     const uint32_t ring0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds, ring = ring0 + wave * TILEB;
