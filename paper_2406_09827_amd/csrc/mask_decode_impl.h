@@ -42,6 +42,13 @@ namespace hipattn {
 // MODE 0: contiguous keys, a (sequence, kv head) slice below 2 GB, addressed as a buffer that ends with the last key (a load past
 //         it returns 0, so nothing is clamped); MODE 1: paged pool; MODE 2: contiguous, any size (64-bit row addresses).
 //
+// Nodes hand on the keys of their own and of their first block's score in every round (HAND_ON), or their own alone, and only to a round with
+// one entry a node: with up to 64 nodes, whose rounds are so short that first blocks' keys cost what they save (64 channels, k/bk = 32, the
+// first block as representative: 1920 problems 48.0 us handing both on, 45.4 so; 6 problems 16.1 / 15.0), and, as kOwnAlone, for up to 256 nodes
+// of four and sixteen waves with the first or last block as representative, where no round asks for a first block's key (both / own, us, first
+// block: 32 problems of 32k tokens, 128 channels, k/bk = 128 22.7 / 21.8, 64 channels 20.9 / 19.5; 1024 of 12k, 64 channels 31.5 / 30.7).
+constexpr int kOwnAlone = 4;
+
 // Waves per SIMD that the registers are laid out for.  With up to 64 nodes five fit (96 registers), where that spills nothing or one: the
 // keys that nodes hand on took most of these kernels to four (104 registers).  us, four / five waves: 4096 problems of 8192 tokens, k/bk = 64,
 // bk = 1, 64 channels 83.6 / 76.6, first block as representative 80.5 / 73.8; 128 channels 114.7 / 109.6, 94.2 / 87.2; 9600 problems of 4096
@@ -52,10 +59,12 @@ constexpr int decode_waves(int E, int BK, int D, int MODE, int WS)
     const bool five = E == 2 && (WS == 1 || (MODE != 1 && (D == 64 || BK == 1 || BK == 8)));
     return WS == 16 ? 4 : five ? 5 : E <= 8 ? 4 : E == 16 ? 3 : 2;
 }
-template <int E, int BK, int D, int ROWS, int MODE, int WS>
-__global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, MODE, WS)) void mask_decode_kernel(KParams p, int xcd_map)
+// FORM: MODE, or MODE + kOwnAlone.
+template <int E, int BK, int D, int ROWS, int FORM, int WS>
+__global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, FORM, WS)) void mask_decode_kernel(KParams p, int xcd_map)
 {
-    constexpr bool SPLIT = WS > 1, PAGED = MODE == 1;
+    constexpr int MODE = FORM % kOwnAlone;
+    constexpr bool SPLIT = WS > 1, PAGED = MODE == 1, HAND_ON = E > 2 && FORM < kOwnAlone;
     constexpr int WGT = WS == 16 ? 1024 : kThreads;   // threads of the workgroup
     constexpr int NB = 64 * E, H = E / 2;
     constexpr int LPR = D / 8;        // lanes per key row
@@ -63,10 +72,6 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, 
     constexpr int U = ROWS / BK;      // branches per lane group and stage: ROWS row loads per lane, two stages in flight
     constexpr int COPIES = LPR / ROWS; // lanes that end up with the same row
     static_assert(ROWS <= LPR && U >= 1 && E % 2 == 0, "stage shape");
-    // Up to 64 nodes hand on their own keys alone, and only to a round with one entry a node: their rounds are so short that first
-    // blocks' keys cost what they save (64 channels, k/bk = 32, the first block as representative: 1920 problems 48.0 us handing both on,
-    // 45.4 so; 6 problems 16.1 / 15.0).
-    constexpr bool HAND_ON = E > 2;
     constexpr int SW = WS < 4 ? 1 : WS == 4 ? 4 : (H < 4 ? H : 4);   // waves that select
     typedef uint32_t stage_t __attribute__((ext_vector_type(4 * ROWS)));
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -119,6 +124,7 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, 
     const uint4 qv = *(const uint4 *)((const bf16_t *)p.Q + (int64_t)b * p.qs_b + (int64_t)h * p.qs_h + lc * 8);
     uint32_t *nodes = node_s[own];
     const RepRule rule = rep_rule(p.rep_pos);
+    const bool first_rule = p.rep_pos == 1;
     auto first_key = [&](int blk) __attribute__((always_inline)) { return MODE == 0 ? (int)__umul24((uint32_t)blk, (uint32_t)bk) : blk * bk; };
     auto touch = [&](int t0) __attribute__((always_inline)) { if (PAGED && p.touched && t0 >= 0) touch_page(p, b, t0); };
     auto put_pair = [&](uint32_t *tab, int j, int tl, int tr) __attribute__((always_inline)) {
@@ -138,8 +144,10 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, 
             const int s = chunk_bound(j, m_len, r, kb, p.kb_magic), e = chunk_bound(j + 1, m_len, r, kb, p.kb_magic);
             nodes[j] = (uint32_t)(s << 1 | (e - s - m_len));
             put_branches(tab_s[own][0], j, s, e);
-            uint32_t *known = SPLIT ? known_s[0] : tab_s[own][1];
-            known[j] = known[kb + j] = 0u;
+            if (HAND_ON) {
+                uint32_t *known = SPLIT ? known_s[0] : tab_s[own][1];
+                known[j] = known[kb + j] = 0u;
+            }
         }
         for (int i = 2 * kb + tix; i < NB; i += tn) tab_s[own][0][i] = tab_s[own][1][i] = 0xffffffffu;
     }
@@ -283,7 +291,19 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, 
             uint32_t kl[H], kr[H];   // keys of the left and the right branch of node i * 64 + lane
             if (one_each) {
 #pragma unroll
-                for (int i = 0; i < H; ++i) kl[i] = kr[i] = score_key_bits(tab[i * 64 + lane]);
+                for (int i = 0; i < H; ++i) {
+                    if constexpr (HAND_ON) {
+                        kl[i] = kr[i] = score_key_bits(tab[i * 64 + lane]);
+                    } else {
+                        // the branch that was scored, if the node has two, and the one that has the node's own score
+                        int j = i * 64 + lane;
+                        asm volatile("" : "+v"(j));   // (addresses kept through the loads are registers that spill)
+                        const uint32_t own = j < kb ? (SPLIT ? known[j] : own_key[SPLIT ? 0 : i]) : 0u, scored = j < kb ? score_key_bits(tab[j]) : 0u;
+                        const bool left_is_own = first_rule && m_len + (int)(nd[i] & 1) > 1;
+                        kl[i] = left_is_own ? own : scored;
+                        kr[i] = left_is_own ? scored : own;
+                    }
+                }
             } else {
 #pragma unroll
                 for (int i = 0; i < H; ++i) {
@@ -292,7 +312,7 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, 
                     kr[i] = score_key_bits(x.y);
                 }
             }
-            if (knows) {
+            if (HAND_ON && knows) {
 #pragma unroll
                 for (int i = 0; i < H; ++i) {
                     uint32_t left, right;
@@ -304,17 +324,25 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, 
             }
             const bool odd = m_len & 1;
             uint32_t *next_known = SPLIT ? known_s[cur ^ 1] : tab;
-            // (two forms, so that the survivors' code has few branches: with a round to come that scores every branch, and any other.
-            // After the last round, which up to 64 nodes takes either, no table is written: 32 problems of 8192 tokens over pages, 128
-            // channels, k/bk = 32 16.9 us writing one, 16.7 so)
-            auto keep_one = [&](auto any, int d, uint32_t child, uint32_t own, uint32_t beg) __attribute__((always_inline)) {
+            // (three forms, so that the survivors' code has few branches: a round to come scores every branch, it knows some, or any of the two.
+            // After the last round, which without HAND_ON takes the first or the second, no table is written: 32 problems of 8192 tokens over
+            // pages, 128 channels, k/bk = 32 16.9 us writing one, 16.7 so)
+            auto keep_one = [&](auto form, int d, uint32_t child, uint32_t own, uint32_t beg) __attribute__((always_inline)) {
+                constexpr bool all = decltype(form)::value == 0, any = decltype(form)::value == 2;
                 nodes[d] = child;
-                if ((any || !HAND_ON) && last) return;
-                if (any || HAND_ON) next_known[d] = own;
-                if (HAND_ON && (!any || rule.beg_left)) next_known[kb + d] = beg;
+                if ((!all || !HAND_ON) && last) return;
+                if (!all || HAND_ON) next_known[d] = own;
+                if (HAND_ON && (all || rule.beg_left)) next_known[kb + d] = beg;
                 const int s = (int)(child >> 1), len = m_next + (int)(child & 1), mid = s + (len >> 1);
-                if (!any || !next_knows) {
+                if (all || (any && !next_knows)) {
                     put_branches(next_tab, d, s, s + len);
+                    return;
+                }
+                if constexpr (!HAND_ON) {
+                    // (the block at the split with the first one as representative, else the block before it)
+                    const int t0 = len > 1 ? first_key(mid) - (first_rule ? 0 : bk) : -1;
+                    next_tab[d] = (uint32_t)t0;
+                    touch(t0);
                     return;
                 }
                 uint32_t left, right;
@@ -328,16 +356,17 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, 
                     put_pair(next_tab, d, tl, tr);
                 }
             };
-            auto keep_child = [&](auto any, int i, bool keep_l, int dl, bool keep_r, int dr) __attribute__((always_inline)) {
+            auto keep_child = [&](auto form, int i, bool keep_l, int dl, bool keep_r, int dr) __attribute__((always_inline)) {
                 if (SPLIT && i % SW != wave) return;
                 // a node of `len` blocks: len / 2 to the left, the rest to the right; m_len / 2 or one more
                 const uint32_t bit = nd[i] & 1u, s2 = nd[i] & ~1u, len = (uint32_t)m_len + bit;
                 const uint32_t own = HAND_ON ? own_of(i) : 0u, beg = beg_of(i);   // (own: what a right half begins with)
-                if (keep_l) keep_one(any, dl, s2 | (odd ? bit : 0u), kl[i], beg);
-                if (keep_r) keep_one(any, dr, (s2 + (len & ~1u)) | (odd ? 1u : bit), kr[i], own);
+                if (keep_l) keep_one(form, dl, s2 | (odd ? bit : 0u), kl[i], beg);
+                if (keep_r) keep_one(form, dr, (s2 + (len & ~1u)) | (odd ? 1u : bit), kr[i], own);
             };
-            auto keep_any = [&](int i, bool keep_l, int dl, bool keep_r, int dr) __attribute__((always_inline)) { keep_child(std::true_type{}, i, keep_l, dl, keep_r, dr); };
-            auto keep_all = [&](int i, bool keep_l, int dl, bool keep_r, int dr) __attribute__((always_inline)) { keep_child(std::false_type{}, i, keep_l, dl, keep_r, dr); };
+            auto keep_all = [&](int i, bool keep_l, int dl, bool keep_r, int dr) __attribute__((always_inline)) { keep_child(std::integral_constant<int, 0>{}, i, keep_l, dl, keep_r, dr); };
+            auto keep_own = [&](int i, bool keep_l, int dl, bool keep_r, int dr) __attribute__((always_inline)) { keep_child(std::integral_constant<int, 1>{}, i, keep_l, dl, keep_r, dr); };
+            auto keep_any = [&](int i, bool keep_l, int dl, bool keep_r, int dr) __attribute__((always_inline)) { keep_child(std::integral_constant<int, 2>{}, i, keep_l, dl, keep_r, dr); };
             // four waves or one, E = 8: the registers that settling equal scores takes are the fourth wave of a SIMD (1024 paged
             // problems of k/bk = 256: 302 us with them, 247 without, 252 with the bits)
             constexpr int SEARCH = WS != 16 && E == 8 ? kInterpolate : default_search(E);
@@ -351,8 +380,9 @@ __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, 
                     pr[i] = ens_key(kr[i], ens_hash, rep_block(mid, e, rule), p.ens_r);
                 }
                 select_topk_pairs<H, SEARCH>(pl, pr, kb, keep_any);
-            } else if (next_knows) {   // (more than 64 nodes: also after the last round)
-                select_topk_pairs<H, SEARCH>(kl, kr, kb, keep_any);
+            } else if (next_knows) {   // (HAND_ON: also after the last round)
+                if constexpr (HAND_ON) select_topk_pairs<H, SEARCH>(kl, kr, kb, keep_any);
+                else select_topk_pairs<H, SEARCH>(kl, kr, kb, keep_own);
             } else {
                 select_topk_pairs<H, SEARCH>(kl, kr, kb, keep_all);
             }
@@ -382,12 +412,18 @@ static hipError_t launch_r(const KParams &p, dim3 grid, int xcd_map, hipStream_t
 {
     dim3 block(WS == 16 ? 1024 : kThreads);
     const bool narrow = narrow_slice(p);
+#define HIPATTN_LAUNCH_FORM(EV, OWN)                                                                        \
+    do {                                                                                                    \
+        if (p.page_table) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, 1 + OWN, WS>), grid, block, 0, st, p, xcd_map);  \
+        else if (narrow) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, 0 + OWN, WS>), grid, block, 0, st, p, xcd_map);   \
+        else if constexpr (WS > 1) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, 2 + OWN, WS>), grid, block, 0, st, p, xcd_map); \
+        else return hipErrorInvalidValue;   /* (decode_mask_waves takes such a slice to four waves) */                \
+    } while (0)
 #define HIPATTN_LAUNCH(EV)                                                                                  \
     do {                                                                                                    \
-        if (p.page_table) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, 1, WS>), grid, block, 0, st, p, xcd_map);  \
-        else if (narrow) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, 0, WS>), grid, block, 0, st, p, xcd_map);   \
-        else if constexpr (WS > 1) hipLaunchKernelGGL((mask_decode_kernel<EV, BK, D, ROWS, 2, WS>), grid, block, 0, st, p, xcd_map); \
-        else return hipErrorInvalidValue;   /* (decode_mask_waves takes such a slice to four waves) */                \
+        constexpr bool both = WS > 1 && (EV == 4 || EV == 8);                                                \
+        if (both && p.rep_pos != 0) HIPATTN_LAUNCH_FORM(EV, (both ? kOwnAlone : 0));                          \
+        else HIPATTN_LAUNCH_FORM(EV, 0);                                                                     \
     } while (0)
     // E registers of 64 branch slots: every count of the selection is a compare and a ballot per register, whether the
     // slots are in use or not (k/bk = 32, both with the bit search, four registers / two: 1024 problems of 65536 tokens
@@ -398,6 +434,7 @@ static hipError_t launch_r(const KParams &p, dim3 grid, int xcd_map, hipStream_t
     else if (WS == 16 || p.kb <= 512) HIPATTN_LAUNCH(16);   // (sixteen waves: k/bk <= 512, 32 keys a lane do not fit their 128 registers)
     else if constexpr (WS != 16) HIPATTN_LAUNCH(32);
 #undef HIPATTN_LAUNCH
+#undef HIPATTN_LAUNCH_FORM
     return hipGetLastError();
 }
 
