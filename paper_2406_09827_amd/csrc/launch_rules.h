@@ -90,7 +90,7 @@ inline int mask_workgroups_per_cu(int64_t max_kv_len, int d, bool lengths_known)
 //       256 42.7 / 37.5, of 65536 tokens over pages 512 119 / 86; 256 problems k/bk = 32 23.8 / 22.5, 256 55.6 / 53.6; beyond a
 //       problem per compute unit 320 problems 256 72 / 99, 384 problems of 65536 tokens 512 167 / 202.  Stages of four rows (eight
 //       make no difference at sixteen waves: 37.5 / 37.5 and 53.6 / 53.8 us, k/bk = 512 over pages 79 / 86, contiguous 115 / 109).
-//       With eight scored rows a block and k/bk above 256 the sixteen-wave kernels spill (24 registers over pages, 6 contiguous)
+//       With eight scored rows a block and k/bk above 256 the sixteen-wave kernels spill (21 registers over pages, 6 contiguous)
 //       and are mostly the better ones all the same: k/bk = 512, 32768 tokens, four / sixteen: 32
 //       problems 86.9 / 67.8 us, over pages 151 / 79.6, 64 channels 48.4 / 41.8; 256 problems 140 / 159, over pages 225 / 159.
 //       A contiguous slice of 2 GB or more, a million tokens stored token by token with 8 kv heads: 32 problems k/bk = 256 91.9 /

@@ -47,6 +47,10 @@ namespace hipattn {
 // first block as representative: 1920 problems 48.0 us handing both on, 45.4 so; 6 problems 16.1 / 15.0), and, as kOwnAlone, for up to 256 nodes
 // of four and sixteen waves with the first or last block as representative, where no round asks for a first block's key (both / own, us, first
 // block: 32 problems of 32k tokens, 128 channels, k/bk = 128 22.7 / 21.8, 64 channels 20.9 / 19.5; 1024 of 12k, 64 channels 31.5 / 30.7).
+// Their own alone also with sixteen waves, eight rows a block and more than 256 nodes: handing both on spills 33 registers over contiguous keys and
+// 34 over pages instead of 6 and 21.  Both / own, us, bk = 8, 128 channels: k/bk = 300, 32 problems of 32k tokens over pages 74.6 / 73.2, 256 123.5 /
+// 119.7, of 8000 tokens 40.5 / 39.7, contiguous 37.7 / 36.0, k/bk = 512 33.7 / 32.7, 64 channels 24.3 / 22.8; only 256 problems of 32k tokens
+// with k/bk = 512, whose last round scores nothing then, 149.6 / 157.
 constexpr int kOwnAlone = 4;
 
 // Waves per SIMD that the registers are laid out for.  With up to 64 nodes five fit (96 registers), where that spills nothing or one: the
@@ -64,7 +68,7 @@ template <int E, int BK, int D, int ROWS, int FORM, int WS>
 __global__ __launch_bounds__(WS == 16 ? 1024 : kThreads, decode_waves(E, BK, D, FORM, WS)) void mask_decode_kernel(KParams p, int xcd_map)
 {
     constexpr int MODE = FORM % kOwnAlone;
-    constexpr bool SPLIT = WS > 1, PAGED = MODE == 1, HAND_ON = E > 2 && FORM < kOwnAlone;
+    constexpr bool SPLIT = WS > 1, PAGED = MODE == 1, HAND_ON = E > 2 && FORM < kOwnAlone && !(E == 16 && ROWS == 8 && WS == 16);
     constexpr int WGT = WS == 16 ? 1024 : kThreads;   // threads of the workgroup
     constexpr int NB = 64 * E, H = E / 2;
     constexpr int LPR = D / 8;        // lanes per key row
