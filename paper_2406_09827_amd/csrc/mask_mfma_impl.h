@@ -587,21 +587,25 @@ __device__ __forceinline__ void mask_mfma_body(const KParams &p, int xcd_map)
 
 // Waves per SIMD that LDS and registers are laid out for: 10 KB of LDS per wave with up to 512 branch slots (8 KB of it the
 // tile at head dim 128), which makes four; 1024 slots or a table of pages three, 2048 slots or 1024 with a table two.
-// Two query tiles at head dim 128 and three waves spill: over pages 1 to 6 registers with 256 slots, 3 to 13 with 512, 10 to 24 with
-// 1024 (a workgroup per item), contiguous 2 to 10 with 1024.  Measured, 64-row blocks over 16384 tokens, three waves / two without
-// spills: a workgroup per item over pages, the last 256 rows of 32 heads, bk = 4, k/bk = 512 124 / 74 us (2048 rows 309 / 211),
-// bk = 1 74 / 63, bk = 2 71 / 67, k/bk = 128 38.5 / 37.7: two there.  A wave per item, whole prompts over pages, bk = 2, k/bk = 128
-// 340 / 360, 256 511 / 528, 512 level (two fit); contiguous, k/bk = 512, bk = 1 470 / 483, bk = 2 628 / 665, bk = 4 809 / 832,
-// bk = 8 860 / 887 (8 heads 151 / 145, 200 / 197 and level): three.
-// One tile, bk = 1 and 512 slots over pages, a workgroup per item spills 2 at four waves: 1024 rows 70 us, at three waves 89.
-constexpr int mask_waves(int MT, int E, int D, bool PAGED, bool SPLIT, bool HAND_ON)
+// Two query tiles at head dim 128 and three waves spill.  64-row blocks, three waves / two without spills, us:
+//   a workgroup per item over pages (1 to 6 registers with 256 slots, 3 to 13 with 512, 10 to 24 with 1024), the last 256 rows of 32 heads over 16k
+//     tokens, bk = 4, k/bk = 512 124 / 74 (2048 rows 309 / 211), bk = 1 74 / 63, bk = 2 71 / 67, k/bk = 128 38.5 / 37.7: two;
+//   a wave per item over pages (up to 12 with 256 slots, 11 to 22 with 512), the last 4096 rows of 4 sequences of 16k tokens, k/bk = 100 bk = 1
+//     286 / 298, bk = 2 357 / 373, bk = 4 490 / 505, 256 445 / 453, 609 / 614, 858 / 865 (1024 slots: two fit): three;
+//   contiguous, 512 slots (up to 11), 32 heads of 16k tokens in groups of four, k/bk = 256 bk = 1 282 / 291, bk = 2 376 / 391, bk = 4 527 / 553, without
+//     groups 304 / 311, 424 / 425, 574 / 575: three;
+//   contiguous, 1024 slots, k/bk = 512: in groups of four (28 to 40) bk = 1 457 / 424 (40k tokens 1494 / 1453), but bk = 2 557 / 573, bk = 4 721 / 749,
+//     bk = 8 858 / 887: two for bk = 1; without groups (14 to 22) bk = 1 500 / 461, bk = 2 606 / 608, bk = 4 799 / 791, bk = 8 991 / 999, 24 heads of 12k
+//     tokens in groups of three 267 / 238, 318 / 315, 439 / 384, 8 heads of 16k 169 / 134, 187 / 178, 238 / 234, 309 / 311: two.
+// One tile, bk = 1 and 512 slots over pages, a workgroup per item spills 4 at four waves: 1024 rows 70 us, at three waves 89 (2 spilled then).
+constexpr int mask_waves(int MT, int E, int D, bool PAGED, int LB, bool SPLIT, bool SHARE, bool HAND_ON)
 {
     const int lds_wave = 32 * D * 2 + (SPLIT ? 64 * E : 256 * E) * (PAGED ? 2 : 1) + (SPLIT ? (HAND_ON ? 96 : 32) * E : 0);
-    const int by_lds = (160 << 10) / (4 * lds_wave), by_regs = MT == 2 && D == 128 ? (E >= 32 || (PAGED && SPLIT) ? 2 : 3) : E >= 32 ? 2 : E >= 16 ? 3 : 4;
+    const int by_lds = (160 << 10) / (4 * lds_wave), by_regs = MT == 2 && D == 128 ? (E >= 32 || (PAGED && SPLIT) || (E == 16 && !SPLIT && (LB == 0 || !SHARE)) ? 2 : 3) : E >= 32 ? 2 : E >= 16 ? 3 : 4;
     return by_lds < by_regs ? by_lds : by_regs;
 }
 template <int MT, int E, int D, bool PAGED, int LB, int WPI, bool SHARE, bool HAND_ON>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(mask_waves(MT, E, D, PAGED, WPI > 1, HAND_ON)))) void mask_mfma_kernel(KParams p, int xcd_map)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(mask_waves(MT, E, D, PAGED, LB, WPI > 1, SHARE, HAND_ON)))) void mask_mfma_kernel(KParams p, int xcd_map)
 {
     mask_mfma_body<MT, E, D, PAGED, LB, WPI, SHARE, HAND_ON>(p, xcd_map);
 }
