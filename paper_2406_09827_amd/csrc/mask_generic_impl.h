@@ -30,8 +30,8 @@
 
 namespace hipattn {
 
-// (waves per SIMD: two query tiles of 64 fp32 channels and k/bk <= 256 spill 8 registers at three waves; at two, with none
-// spilled, 4096 tokens of 32 heads, k/bk = 256 take 258 us instead of 225)
+// (waves per SIMD: two query tiles of 64 fp32 channels and k/bk <= 256 spill 4 to 7 registers at three waves; at two, with none
+// spilled, 4096 tokens of 32 heads, k/bk = 256 take 245 us instead of 216, k/bk = 64 182 instead of 153)
 template <typename T, int D, int E, int MT>
 __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) void mask_generic_kernel(KParams p, int xcd_map, uint32_t rows_magic)
 {
@@ -154,7 +154,17 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
     // ensemble sample: the round whose selection compares perturbed scores (-1: none)
     const int ens_round = ens_round_of(p.ens_sample, a + (r ? 1 : 0));
     const uint32_t ens_hash = ens_round >= 0 ? ens_unit_hash(p.ens_seed, p.ens_sample, b, h, qb) : 0u;
-    const RepRule rule = rep_rule(p.rep_pos);
+    // Two tiles of 64 fp32 channels work the representative rule and the selection's LDS addresses out where they are needed: kept
+    // through the tiles these are up to 9 spilled registers more (k/bk = 256, 2000 tokens of 32 heads 73.1 / 70.1 us, 4096 216 / 210; k/bk = 64 152 /
+    // 148).  One tile is 2 % slower so.
+    constexpr bool kAnew = F32 && D == 64 && MT == 2;
+    const RepRule rule_kept = rep_rule(p.rep_pos);
+    auto rule_now = [&]() __attribute__((always_inline)) {
+        if constexpr (!kAnew) return rule_kept;
+        int rep_pos = p.rep_pos;
+        asm volatile("" : "+s"(rep_pos));
+        return rep_rule(rep_pos);
+    };
     int round = 0, m_len = a;
     // maxlen bounds the longest node
     for (int maxlen = a + (r ? 1 : 0); maxlen > 1; maxlen = (maxlen + 1) >> 1, ++round, m_len >>= 1) {
@@ -165,6 +175,7 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
             bool todo = false;
             int blk = 0;
             if (slot < 2 * kb) {
+                const RepRule rule = rule_now();
                 const int j = slot >> 1, s = (int)(nd[j] >> 1), len = m_len + (int)(nd[j] & 1), mid = s + (len >> 1);
                 uint32_t left, right;
                 bool need_l, need_r;
@@ -355,9 +366,11 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
         __syncthreads();
 
         // every wave selects redundantly; wave (i % 4) writes the survivors of register i
+        int lane_sel = lane;
+        if constexpr (kAnew) asm volatile("" : "+v"(lane_sel));
         uint32_t ksel[E];
 #pragma unroll
-        for (int i = 0; i < E; ++i) ksel[i] = keys[i * 64 + lane];
+        for (int i = 0; i < E; ++i) ksel[i] = keys[i * 64 + lane_sel];
         auto branch_of = [&](int slot, int &s, int &e) __attribute__((always_inline)) {
             s = (int)(nd[slot >> 1] >> 1), e = s + m_len + (int)(nd[slot >> 1] & 1);
             const int mid = s + ((e - s) >> 1);
@@ -368,15 +381,15 @@ __global__ __launch_bounds__(kThreads, E > 16 ? 1 : (E > 8 || MT > 2) ? 2 : 3) v
             for (int i = 0; i < E; ++i) {
                 if (ksel[i] == 0u) continue;
                 int s, e;
-                branch_of(i * 64 + lane, s, e);
-                ksel[i] = ens_key(ksel[i], ens_hash, rep_block(s, e, rule), p.ens_r);
+                branch_of(i * 64 + lane_sel, s, e);
+                ksel[i] = ens_key(ksel[i], ens_hash, rep_block(s, e, rule_now()), p.ens_r);
             }
         }
         uint32_t *nd2 = nd_s[(round & 1) ^ 1], *nk2 = ndk_s[(round & 1) ^ 1], *nb2 = ndb_s[(round & 1) ^ 1];
         select_topk_visit<E>(ksel, kb, [&](int i, bool kept, int dest) __attribute__((always_inline)) {
             if ((i & 3) != wave || !kept) return;
             int s, e;
-            const int slot = i * 64 + lane;
+            const int slot = i * 64 + lane_sel;
             branch_of(slot, s, e);
             nd2[dest] = (uint32_t)(s << 1 | (e - s - (m_len >> 1)));
             nk2[dest] = keys[slot];
