@@ -57,7 +57,8 @@ constexpr int kOwnAlone = 4;
 // keys that nodes hand on took most of these kernels to four (104 registers).  us, four / five waves: 4096 problems of 8192 tokens, k/bk = 64,
 // bk = 1, 64 channels 83.6 / 76.6, first block as representative 80.5 / 73.8; 128 channels 114.7 / 109.6, 94.2 / 87.2; 9600 problems of 4096
 // tokens over pages, 64 channels 115 / 110.  Four stay for four waves a problem over pages (2 to 5 spilled) and for 128 channels with two
-// or four rows a block (one spilled: 4096 problems, k/bk = 64 174 / 181, 9600 276 / 294).
+// or four rows a block (one spilled: 4096 problems, k/bk = 64 174 / 181, 9600 276 / 294).  More than 512 nodes: two; asked for one, a wave a problem
+// takes 258 registers (16384 problems of 4096 tokens, k/bk = 1024, two / one: 1001 / 1498, over pages 1618 / 2956).
 constexpr int decode_waves(int E, int BK, int D, int MODE, int WS)
 {
     const bool five = E == 2 && (WS == 1 || (MODE != 1 && (D == 64 || BK == 1 || BK == 8)));
