@@ -271,45 +271,40 @@ __global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_wa
     // (64 channels over contiguous rows at a wave an item: the choice spills two more of the loop's registers, 36.5 -> 37.5 us at 4096
     // tiles of k = 512, and gives 0.3 us at k = 64)
     constexpr bool kChoose = D == 128 || PAGED || SPLIT;
-    const int n_listed = kChoose && nt <= 4 ? 4 : kChoose && nt <= 8 ? 8 : kListTiles;
     int entry[kListTiles / 2];
-    entry[0] = index_entry(0, 0);
-    entry[1] = index_entry(0, 1);
-    if (n_listed > 4) {
-        entry[2] = index_entry(0, 2);
-        entry[3] = index_entry(0, 3);
-        if (n_listed > 8) {
 #pragma unroll
-            for (int u = 4; u < kListTiles / 2; ++u) entry[u] = index_entry(0, u);
-        }
-    }
-    // The query tile comes in through the key buffer, row x to LDS row x, by coalesced loads of RPI rows, behind the index entries that
+    for (int u = 0; u < kListTiles / 2; ++u) entry[u] = index_entry(0, u);
+    // The query tile comes in through the key buffer by coalesced loads of RPI rows, behind the index entries that
     // the listing needs first.  (Straight into registers, a row a lane, each of eight loads
     // was 64 cache accesses, and the entries waited behind them: 11800 of an item's 61000 clocks until its first tile was there
     // at 32k tokens, now 10100; 64 channels 11600 of 64500, now 9600 of 59300.  The listing does not run under these loads: the compiler
     // does not count them, so its waits for the entries are waits for the tile too.)
-    // Blocks of up to 8 or 16 rows load so many: with all 32, as copies of the last one, 8-row blocks of 8192 tokens took 4 % more
-    // (two sequences of 16 heads, k = 256: 128 channels 230 us, straight into registers 220, so 220; 64 channels 126 / 122 / 118).
-    const uint32_t qchunk = (uint32_t)((D == 128 ? lc ^ lg : lc ^ (lg >> 1)) << 4);
-    auto issue_query = [&](auto from, auto to) __attribute__((always_inline)) {
+    // Tiles of up to 8 or 16 rows load so many, row x to LDS row x: with all 32, as copies of the last one, 8-row blocks of 8192 tokens took 4 %
+    // more (two sequences of 16 heads, k = 256: 128 channels 230 us, straight into registers 220, so 220; 64 channels 126 / 122 / 118).  Others
+    // go where a key tile goes, rows NLD apart in a load: with neighbouring rows in a load 32k tokens take 1 % more (529 / 535 us).
+    const bool few = n_rows <= 16;
+    auto issue_query = [&](int j, int row, uint32_t chunk) __attribute__((always_inline)) {
         const char *Qb = (const char *)((const bf16_t *)p.Q + (int64_t)b * p.qs_b + (int64_t)h * p.qs_h + (int64_t)row0 * p.qs_r);
-#pragma unroll
-        for (int j = decltype(from)::value / RPI; j < decltype(to)::value / RPI; ++j) {
-            const char *src = Qb + (int64_t)min(RPI * j + lg, n_rows - 1) * p.qs_r * 2 + (qchunk ^ (uint32_t)((D == 128 ? j & 3 : j & 1) << 6));
-            const uint32_t dst = __builtin_amdgcn_readfirstlane(kt_m0 + j * 1024);
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(src), "s"(dst) : "memory", "m0");
-        }
+        const char *src = Qb + (int64_t)min(row, n_rows - 1) * p.qs_r * 2 + chunk;
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(kt_m0 + j * 1024);
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(src), "s"(dst) : "memory", "m0");
     };
-    using std::integral_constant;
-    if (n_rows > 16) {
-        issue_query(integral_constant<int, 0>{}, integral_constant<int, 32>{});
+    if (!few) {
+#pragma unroll
+        for (int j = 0; j < NLD; ++j) issue_query(j, lg * NLD + j, kchunk ^ (uint32_t)(j << 4));
     } else {
-        issue_query(integral_constant<int, 0>{}, integral_constant<int, 8>{});
-        if (n_rows > 8) issue_query(integral_constant<int, 8>{}, integral_constant<int, 16>{});
+        const uint32_t qchunk = (uint32_t)((D == 128 ? lc ^ lg : lc ^ (lg >> 1)) << 4);
+        auto eight_rows = [&](auto from) __attribute__((always_inline)) {
+            constexpr int j0 = decltype(from)::value / RPI;
+#pragma unroll
+            for (int j = j0; j < j0 + 8 / RPI; ++j) issue_query(j, RPI * j + lg, qchunk ^ (uint32_t)((D == 128 ? j & 3 : j & 1) << 6));
+        };
+        eight_rows(std::integral_constant<int, 0>{});
+        if (n_rows > 8) eight_rows(std::integral_constant<int, 8>{});
     }
-    if (n_listed == 4) list_tiles(0, integral_constant<int, 4>{}, entry);
-    else if (n_listed == 8) list_tiles(0, integral_constant<int, 8>{}, entry);
-    else list_tiles(0, integral_constant<int, kListTiles>{}, entry);
+    if (kChoose && nt <= 4) list_tiles(0, std::integral_constant<int, 4>{}, entry);
+    else if (kChoose && nt <= 8) list_tiles(0, std::integral_constant<int, 8>{}, entry);
+    else list_tiles(0, std::integral_constant<int, kListTiles>{}, entry);
     // (the tail of a list that ends early: a prefix with fewer keys than k)
     if (nt <= kListTiles) nt = any ? 32 - __builtin_clz(any) : 0;
     wave_lds_sync();
@@ -317,8 +312,8 @@ __global__ __launch_bounds__(WPI == 2 ? 128 : kThreads) __attribute__((amdgpu_wa
     bf16x8 qf[KS];
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     {
-        const int sw = D == 128 ? col & 15 : (col >> 1) & 7;
-        const uint32_t qrow = (uint32_t)(col * ROWB + ((hh ^ sw) << 4)) + kt_m0;
+        const int sw = D == 128 ? col & 15 : few ? (col >> 1) & 7 : (col & 3) | ((col >> 1) & 4);
+        const uint32_t qrow = (uint32_t)((few ? col : RPI * (col % NLD) + col / NLD) * ROWB + ((hh ^ sw) << 4)) + kt_m0;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *(lds_u32x4_ptr)(uintptr_t)(qrow ^ (uint32_t)(kk << 5)));
         if (n_rows < 32) {   // (rows past the last one need not have been loaded)

@@ -19,7 +19,7 @@
 //     node list and the next table (two tables take turns);
 //   * a branch whose representative block was scored in an earlier round keeps that score (known_branches in common.h): with
 //     the first or the last block as representative one child of every node, from the second round on; with the centre
-//     most branches of the last two rounds.  Such a branch has no entry in the table, and where a node has at most one branch to
+//     most branches of the last two rounds (where nodes hand on their own scores alone, see kOwnAlone: right halves of the last).  Such a branch has no entry in the table, and where a node has at most one branch to
 //     score the table has one entry a node.  (Before, only the right halves of two-block nodes in the last round: 1024 problems of
 //     128k tokens 264 -> 252 us, 4096 of 20k 583 -> 510, 8960 of 12k over pages 752 -> 653; 32 problems level.)
 // Ragged lengths (kv_lens) and a page table are handled per row.
