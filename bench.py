@@ -280,8 +280,11 @@ def build_workload(args, name=None, seq_len=None):
 
 def pick_roof(cands: dict):
     """The roof that binds = the candidate with the largest fraction that is a fraction (<= 1): a rate above a
-    peak means that peak is not what the data passes through (cache hits), so it cannot bound the kernel."""
-    valid = {n: c for n, c in cands.items() if c is not None and c["frac"] <= 1.0}
+    peak means that peak is not what the data passes through (cache hits), so it cannot bound the kernel.  Where
+    counters say what crossed the memory side, they are the HBM candidate: algorithmic bytes count a row once per head,
+    and heads of a KV group share rows in the L2."""
+    counted = cands.get("hbm_counter") is not None
+    valid = {n: c for n, c in cands.items() if c is not None and c["frac"] <= 1.0 and not (counted and n == "hbm_algorithmic")}
     if not valid:
         return None
     return max(valid, key=lambda n: valid[n]["frac"])

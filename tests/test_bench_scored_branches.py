@@ -41,3 +41,10 @@ def test_scored_bytes_are_fewer_than_the_rounds_name():
     for w in (synth.C2, synth.C3, synth.C4):
         least, named = bench.mask_scored_bytes(w, None), bench.mask_algorithmic_bytes(w, None)
         assert 0.6 * named < least < named
+
+
+def test_counted_bytes_take_the_place_of_algorithmic_ones():
+    c = {"hbm_algorithmic": {"frac": 0.92}, "hbm_counter": {"frac": 0.71}, "l2_fill_algorithmic": {"frac": 0.19}}
+    assert bench.pick_roof(c) == "hbm_counter"
+    assert bench.pick_roof({**c, "hbm_counter": None}) == "hbm_algorithmic"
+    assert bench.pick_roof({**c, "l2_fill_algorithmic": {"frac": 0.8}}) == "l2_fill_algorithmic"
